@@ -75,7 +75,7 @@ inline int tile_systems(int mapping, int n) {
     return mapping == MAP_SPL ? spl_tile_systems() : bpl_tile_systems(n);
 }
 
-// ---- launchers (fb_kernels.hip) -------------------------------------------
+// ---- launchers (fb_kernels.hip; the MVS steps in fb_mvs.hip) --------------
 // pad_tail: also initialise slots count..pitch-1 as inert padding (a whole
 // bucket); false for a view of a bucket shared with other owners.
 hipError_t launch_pack(const Bucket &B, const double *mass, const double *pos,

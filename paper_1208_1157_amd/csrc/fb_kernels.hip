@@ -25,7 +25,7 @@
 //   v1 = vp - 1/2 (a0 - ak) h - (5 j0 + jk) h^2 / 12
 // The a0/j0 parts are folded into per-step bases, so each correction costs
 // four FMAs per component and does not need the corrected velocity.
-#include "fb_internal.h"
+#include "fb_device.h"
 
 #include <algorithm>
 #include <climits>
@@ -48,311 +48,6 @@
 
 namespace fb {
 namespace {
-
-// ---------------------------------------------------------------------------
-// small device helpers
-// ---------------------------------------------------------------------------
-
-// LDS exchange among the lanes of one wavefront: order this wave's LDS
-// writes before its subsequent reads (no workgroup barrier needed: every
-// exchange stays inside one wavefront's slice).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// 1/sqrt(x): hardware estimate y (v_rsq_f64, relative error ~6e-8 on
-// gfx950) refined by one third-order step of the series
-// 1/sqrt(x) = y (1 - e)^(-1/2) = y (1 + e/2 + 3e^2/8 + ...), e = 1 - x y^2,
-// whose truncation (~e^3) is far below FP64 rounding.
-__device__ __forceinline__ double rsqrt_nr(double x)
-{
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    const double p = fma(0.375, e, 0.5);
-    return fma(y * e, p, y);
-}
-
-__device__ __forceinline__ bool finite3(const double (&p)[3])
-{
-    return __builtin_isfinite(p[0]) && __builtin_isfinite(p[1]) && __builtin_isfinite(p[2]);
-}
-
-// Wave-uniform copies (scalar registers) of values every lane holds alike:
-// tests on them are scalar branches rather than exec-mask changes.
-__device__ __forceinline__ int uniform_i(const int v)
-{
-    return __builtin_amdgcn_readfirstlane(v);
-}
-
-__device__ __forceinline__ long long uniform_ll(const long long v)
-{
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(v & 0xffffffffll));
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32));
-    return (long long)(((unsigned long long)hi << 32) | lo);
-}
-
-__device__ __forceinline__ double uniform_d(const double v)
-{
-    return __longlong_as_double(uniform_ll(__double_as_longlong(v)));
-}
-
-__device__ __forceinline__ StepParams uniform_params(const StepParams &P)
-{
-    StepParams u;
-    u.adaptive = uniform_i(P.adaptive);
-    u.stop_rules = uniform_i(P.stop_rules);
-    u.eta = uniform_d(P.eta);
-    u.r_eject = uniform_d(P.r_eject);
-    u.max_steps = uniform_ll(P.max_steps);
-    u.quantum = uniform_i(P.quantum);
-    u.pad = 0;
-    return u;
-}
-
-// Step coefficients of the predictor (Eq. 3) and corrector (Eq. 4).
-struct Coef {
-    double h, hh2, hhh6;       // predictor: h, h^2/2, h^3/6
-    double bxa, bxj, bva, bvj; // bases: -3/20 h^2, -7/60 h^3, -h/2, -5/12 h^2
-    double cxa, cxj, cva, cvj; // corrections: 3/20 h^2, -h^3/30, h/2, -h^2/12
-};
-
-__device__ __forceinline__ Coef make_coef(double h)
-{
-    Coef k;
-    const double h2 = h * h, h3 = h2 * h;
-    k.h = h;
-    k.hh2 = 0.5 * h2;
-    k.hhh6 = h3 * (1.0 / 6.0);
-    k.cxa = 0.15 * h2;
-    k.cxj = h3 * (-1.0 / 30.0);
-    k.cva = 0.5 * h;
-    k.cvj = h2 * (-1.0 / 12.0);
-    k.bxa = -k.cxa;
-    k.bxj = h3 * (-7.0 / 60.0);
-    k.bva = -k.cva;
-    k.bvj = h2 * (-5.0 / 12.0);
-    return k;
-}
-
-// Predicted state and the per-step bases of the corrector for one component.
-__device__ __forceinline__ void predict_comp(const Coef &k, double x, double v, double a,
-                                             double j, double &xp, double &vp, double &bx,
-                                             double &bv)
-{
-    xp = fma(k.hhh6, j, fma(k.hh2, a, fma(k.h, v, x)));
-    vp = fma(k.hh2, j, fma(k.h, a, v));
-    bx = fma(k.bxj, j, fma(k.bxa, a, xp));
-    bv = fma(k.bvj, j, fma(k.bva, a, vp));
-}
-
-// One correction of one component from the latest evaluation (ak, jk).
-__device__ __forceinline__ void correct_comp(const Coef &k, double bx, double bv, double ak,
-                                             double jk, double &xc, double &vc)
-{
-    xc = fma(k.cxj, jk, fma(k.cxa, ak, bx));
-    vc = fma(k.cvj, jk, fma(k.cva, ak, bv));
-}
-
-// One wavefront's LDS slice: the current evaluation state of its 64 lanes
-// (as 16-byte pairs so a partner costs three ds_read_b128 and one b64), and
-// per lane its mass beside a reduction scratch value, so every row of a
-// partner sits at the same 16-byte slot offset.
-struct BplLds {
-    double2 xy[64];
-    double2 zvx[64];
-    double2 vyvz[64];
-    double2 mr[64];   // (mass, reduction scratch)
-};
-
-// System-per-lane steps of at least this many bodies park the corrector
-// bases (6 doubles per body, idle during each evaluation) in the wavefront's
-// LDS slice, so the evaluation's working set (12 doubles per body) stays in
-// VGPRs.
-#ifndef FB_SPL_LDS_MIN
-#define FB_SPL_LDS_MIN 6
-#endif
-
-// Rows parked after the bases by the adaptive step loop (n <= kMaxSplAdv):
-// the step size and the system's clock (t, t_end, carried step, run steps,
-// steps, status, last step).
-constexpr int kSplParkClock = 8;
-
-// LDS bytes per wavefront a system-per-lane step of n bodies uses.
-__host__ __device__ constexpr size_t spl_lds_bytes(int n)
-{
-    return n >= FB_SPL_LDS_MIN
-               ? (size_t)(6 * n + (n <= kMaxSplAdv ? kSplParkClock : 0)) * 64 * sizeof(double)
-               : 0;
-}
-
-// Per-wavefront LDS stride of the system-per-lane fused class, whose waves
-// may run either kind of tile side by side in one workgroup: large enough
-// for the body-per-lane slice and for the largest parked bases.
-constexpr size_t kWideLdsStride = 6 * kMaxSplBodies * 64 * sizeof(double);
-static_assert(kWideLdsStride >= sizeof(BplLds), "wide LDS stride too small");
-static_assert(kWideLdsStride >= spl_lds_bytes(kMaxSplAdv) &&
-                  kWideLdsStride >= spl_lds_bytes(kMaxSplBodies), "wide LDS stride too small");
-
-// This wavefront's slice of its workgroup's dynamic LDS, reached through
-// the module-level symbol (not a pointer argument) so separately compiled
-// tile functions still address LDS directly.  PACKED is the slice size when
-// every wave of the launch runs the same kind of tile; WIDE selects the
-// common stride of the system-per-lane fused class.
-template <size_t PACKED, bool WIDE>
-__device__ __forceinline__ char *wave_lds_base()
-{
-    extern __shared__ char fb_dyn_lds[];
-    return fb_dyn_lds + (size_t)(threadIdx.x >> 6) * (WIDE ? kWideLdsStride : PACKED);
-}
-
-// ---------------------------------------------------------------------------
-// per-system clock (Algorithm 1's loop control)
-// ---------------------------------------------------------------------------
-struct Clock {
-    double t, t_end, dt, dtn, t0;
-    long long k, nfull, steps;
-    int status;
-};
-
-__device__ __forceinline__ Clock load_clock(const Bucket &B, int s)
-{
-    Clock c;
-    c.t = B.t[s];
-    c.t_end = B.t_end[s];
-    c.dt = B.dt[s];
-    c.dtn = B.dtn[s];
-    c.t0 = B.t0run[s];
-    c.k = B.krun[s];
-    c.nfull = B.nfull[s];
-    c.steps = B.steps[s];
-    c.status = B.status[s];
-    return c;
-}
-
-__device__ __forceinline__ void store_clock(const Bucket &B, int s, const Clock &c)
-{
-    B.t[s] = c.t;
-    B.dtn[s] = c.dtn;
-    B.krun[s] = c.k;
-    B.steps[s] = c.steps;
-    B.status[s] = c.status;
-}
-
-// Size of the next step, or false (with the status updated) if the system
-// takes no further step.
-__device__ __forceinline__ bool plan_step(Clock &c, const StepParams &P, double &h, bool &last)
-{
-    if (c.status != ST_ACTIVE)
-        return false;
-    if (P.adaptive) {
-        if (!(c.t < c.t_end)) {
-            c.status = ST_DONE;
-            return false;
-        }
-        if (c.steps >= P.max_steps) {
-            c.status = ST_MAXSTEPS;
-            return false;
-        }
-        if (__builtin_isnan(c.dtn)) {
-            c.status = ST_NONFINITE;
-            return false;
-        }
-        if (!(c.dtn >= 1e-12 * fabs(c.t_end))) {
-            c.status = ST_STALLED;
-            return false;
-        }
-        last = c.t + c.dtn >= c.t_end;
-        h = last ? c.t_end - c.t : c.dtn;
-        return true;
-    }
-    if (c.steps >= P.max_steps) {
-        c.status = ST_MAXSTEPS;
-        return false;
-    }
-    if (c.k < c.nfull) {
-        h = c.dt;
-        last = false;
-        return true;
-    }
-    const double rem = c.t_end - c.t;
-    if (rem * c.dt > 1e-9 * c.dt * c.dt) {   // remainder in the direction of dt
-        h = rem;
-        last = true;
-        return true;
-    }
-    c.t = c.t_end;
-    c.status = ST_DONE;
-    return false;
-}
-
-__device__ __forceinline__ void finish_step(Clock &c, const StepParams &P, bool last, double h,
-                                            double dt_prop)
-{
-    c.steps += 1;
-    if (P.adaptive) {
-        c.t = last ? c.t_end : c.t + h;
-        c.dtn = dt_prop;
-        if (last)
-            c.status = ST_DONE;
-        return;
-    }
-    if (last) {
-        c.t = c.t_end;
-        c.status = ST_DONE;
-        return;
-    }
-    c.k += 1;
-    c.t = fma((double)c.k, c.dt, c.t0);
-    if (c.k >= c.nfull) {
-        const double rem = c.t_end - c.t;
-        if (!(rem * c.dt > 1e-9 * c.dt * c.dt)) {
-            c.t = c.t_end;
-            c.status = ST_DONE;
-        }
-    }
-}
-
-__device__ __forceinline__ int status_of_flags(int fl)
-{
-    return (fl & 1) ? ST_NONFINITE : (fl & 2) ? ST_ENCOUNTER : (fl & 4) ? ST_EJECTED : ST_ACTIVE;
-}
-
-// Adaptive-step forms of plan_step and finish_step (the same tests in the
-// same order) as selects rather than branches, for a wave that runs alone on
-// its SIMD, where every branch and exec-mask change is latency on the step's
-// critical path.  A lane whose system is not active keeps its clock.
-__device__ __forceinline__ bool plan_step_adaptive(Clock &c, const StepParams &P, double &h,
-                                                   bool &last)
-{
-    const bool running = c.status == ST_ACTIVE;
-    // every test evaluated, then the first that holds wins
-    const bool done = !(c.t < c.t_end);
-    const bool maxed = c.steps >= P.max_steps;
-    const bool nonfinite = __builtin_isnan(c.dtn);
-    const bool stalled = !(c.dtn >= 1e-12 * fabs(c.t_end));
-    int ns = stalled ? ST_STALLED : ST_ACTIVE;
-    ns = nonfinite ? ST_NONFINITE : ns;
-    ns = maxed ? ST_MAXSTEPS : ns;
-    ns = done ? ST_DONE : ns;
-    c.status = running ? ns : c.status;
-    last = c.t + c.dtn >= c.t_end;
-    h = last ? c.t_end - c.t : c.dtn;
-    return running && ns == ST_ACTIVE;
-}
-
-__device__ __forceinline__ void finish_step_adaptive(Clock &c, const bool act, const bool last,
-                                                     const double h, const double dt_prop,
-                                                     const int fl)
-{
-    c.steps += act ? 1 : 0;
-    c.t = act ? (last ? c.t_end : c.t + h) : c.t;
-    c.dtn = act ? dt_prop : c.dtn;
-    const int st = fl ? status_of_flags(fl) : (last ? ST_DONE : c.status);
-    c.status = act ? st : c.status;
-}
 
 // ---------------------------------------------------------------------------
 // system-per-lane (SPL)
@@ -718,7 +413,6 @@ __device__ __forceinline__ void spl_run(const Bucket &B, const int slot, const S
 // body-per-lane (BPL)
 // ---------------------------------------------------------------------------
 
-
 // LDS slot of the k-th planet partner (0 <= k < N-2, the other planets in
 // ascending order) of body b of system s, with own = b S (the star lane
 // passes 64, past every body): (k + 1) S + s, moved one body up from b on.
@@ -817,56 +511,6 @@ __device__ __forceinline__ void bpl_eval(BplLds &L, const int lane, const int b,
     }
     bpl_interact<TS>(L, (b == 0 ? N - 1 : 0) * S + s, xi, vi, a, jk, wmax);
     wave_sync();
-}
-
-template <int N>
-__device__ __forceinline__ double sys_max(BplLds &L, int lane, int s, double v)
-{
-    constexpr int S = 64 / N;
-    L.mr[lane].y = v;
-    wave_sync();
-    double r = L.mr[s].y;
-#pragma unroll
-    for (int k = 1; k < N; ++k)
-        r = fmax(r, L.mr[k * S + s].y);
-    wave_sync();
-    return r;
-}
-
-// Sum over the system's lanes in body order (deterministic).
-template <int N>
-__device__ __forceinline__ double sys_sum(BplLds &L, int lane, int s, double v)
-{
-    constexpr int S = 64 / N;
-    L.mr[lane].y = v;
-    wave_sync();
-    double r = L.mr[s].y;
-#pragma unroll
-    for (int k = 1; k < N; ++k)
-        r += L.mr[k * S + s].y;
-    wave_sync();
-    return r;
-}
-
-// OR of the stop-flag bits (1, 2, 4) over the system's lanes (s, s + S, ...)
-// from three wave ballots: no LDS round trip.
-template <int N>
-__device__ __forceinline__ int sys_or_flags(int s, int v)
-{
-    constexpr int S = 64 / N;
-    constexpr unsigned long long kBase = [] {
-        unsigned long long m = 0;
-        for (int k = 0; k < N; ++k)
-            m |= 1ull << (k * S);
-        return m;
-    }();
-    const unsigned long long sm = kBase << s;
-    int r = 0;
-#pragma unroll
-    for (int bit = 1; bit <= 4; bit <<= 1)
-        if (__ballot((v & bit) != 0) & sm)
-            r |= bit;
-    return r;
 }
 
 template <int N, bool ILP = false>
@@ -1570,7 +1214,6 @@ __global__ void k_begin_run(Bucket B, int fixed_steps, long long n_steps, double
     }
 }
 
-
 // bucket SoA -> AoS rows in caller order (any output may be null).
 __global__ void k_unpack(Bucket B, const long long *__restrict__ orig_off, double *pos,
                          double *vel, double *acc, double *jerk, double *t, int *status,
@@ -1731,183 +1374,6 @@ __global__ void k_count_active(Bucket B, int *count)
 // planet-planet accelerations at Q, which the next step's first kick reuses:
 // the drifts move all Q_i together, so the separations do not change.
 
-// (r, v) advanced by dt on its Kepler orbit about mu.  The change x of the
-// eccentric anomaly solves Kepler's equation in difference form,
-//   n dt = x - (1 - r0/a) sin x + (r.v / sqrt(mu a)) (1 - cos x),
-// by Newton iteration from x = n dt; Lagrange's f and g functions give the
-// new state.  The caller has checked 1/a > 0.  Returns false if the
-// iteration does not converge in kMvsNewtonMax steps.
-constexpr int kMvsNewtonMax = 50;
-
-__device__ __forceinline__ bool kepler_drift(const double mu, double (&r)[3], double (&v)[3],
-                                             const double dt)
-{
-    const double r2 = fma(r[2], r[2], fma(r[1], r[1], r[0] * r[0]));
-    const double v2 = fma(v[2], v[2], fma(v[1], v[1], v[0] * v[0]));
-    const double rv = fma(r[2], v[2], fma(r[1], v[1], r[0] * v[0]));
-    const double r0 = sqrt(r2);
-    const double alpha = 2.0 / r0 - v2 / mu;
-    const double a = 1.0 / alpha;
-    const double sqmua = sqrt(mu * a);
-    const double nmot = sqmua * alpha * alpha;   // sqrt(mu / a^3)
-    const double ec = 1.0 - r0 * alpha;
-    const double es = rv / sqmua;
-    const double M = nmot * dt;
-    double x = M, s = 0.0, c = 1.0;
-    bool ok = false;
-    for (int it = 0; it < kMvsNewtonMax; ++it) {
-        sincos(x, &s, &c);
-        const double F = fma(-ec, s, x) + fma(es, 1.0 - c, -M);
-        const double dF = fma(es, s, fma(-ec, c, 1.0));
-        const double dx = F / dF;
-        x -= dx;
-        if (fabs(dx) <= 1e-15 * (1.0 + fabs(x))) {
-            ok = true;
-            break;
-        }
-    }
-    if (!ok)
-        return false;
-    sincos(x, &s, &c);
-    const double omc = 1.0 - c;
-    const double f = fma(-a / r0, omc, 1.0);
-    const double g = dt - (x - s) / nmot;
-    const double rn = a * fma(es, s, fma(-ec, c, 1.0));
-    const double fd = -sqmua * s / (rn * r0);
-    const double gd = fma(-a / rn, omc, 1.0);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double rk = r[k], vk = v[k];
-        r[k] = fma(f, rk, g * vk);
-        v[k] = fma(fd, rk, gd * vk);
-    }
-    return true;
-}
-
-// Planet-planet accelerations at heliocentric positions Q[1..N-1].
-template <int N>
-__device__ __forceinline__ void mvs_acc(const double (&m)[N], const double (&Q)[N][3],
-                                        double (&acc)[N][3])
-{
-#pragma unroll
-    for (int i = 1; i < N; ++i)
-        acc[i][0] = acc[i][1] = acc[i][2] = 0.0;
-#pragma unroll
-    for (int i = 1; i < N; ++i)
-#pragma unroll
-        for (int j = i + 1; j < N; ++j) {
-            const double d0 = Q[j][0] - Q[i][0], d1 = Q[j][1] - Q[i][1], d2 = Q[j][2] - Q[i][2];
-            const double s = rsqrt_nr(fma(d2, d2, fma(d1, d1, d0 * d0)));
-            const double s3 = s * s * s;
-            const double mj = m[j] * s3, mi = m[i] * s3;
-            acc[i][0] = fma(mj, d0, acc[i][0]);
-            acc[i][1] = fma(mj, d1, acc[i][1]);
-            acc[i][2] = fma(mj, d2, acc[i][2]);
-            acc[j][0] = fma(-mi, d0, acc[j][0]);
-            acc[j][1] = fma(-mi, d1, acc[j][1]);
-            acc[j][2] = fma(-mi, d2, acc[j][2]);
-        }
-}
-
-// Drift of every Q_i by h sum_j m_j V_j / m0 and of X by h Vc (body 0's rows).
-template <int N>
-__device__ __forceinline__ void mvs_drift(const double (&m)[N], double (&Q)[N][3],
-                                          const double (&V)[N][3], const double inv_m0,
-                                          const double h)
-{
-    double P[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int i = 1; i < N; ++i)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            P[c] = fma(m[i], V[i][c], P[c]);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double dq = h * P[c] * inv_m0;
-#pragma unroll
-        for (int i = 1; i < N; ++i)
-            Q[i][c] += dq;
-        Q[0][c] = fma(h, V[0][c], Q[0][c]);
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void mvs_kick(double (&V)[N][3], const double (&acc)[N][3], const double h)
-{
-#pragma unroll
-    for (int i = 1; i < N; ++i)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            V[i][c] = fma(h, acc[i][c], V[i][c]);
-}
-
-// One MVS step of h.  Returns ST_ACTIVE, or ST_UNBOUND when a planet's
-// heliocentric orbit is not bound (the half drift and kick are undone, so
-// the state is the step's start up to rounding) or Kepler's equation does not
-// converge (state of the planets drifted so far).
-template <int N>
-__device__ __forceinline__ int mvs_step(const double (&m)[N], double (&Q)[N][3], double (&V)[N][3],
-                                        double (&acc)[N][3], const double inv_m0, const double h)
-{
-    const double hh = 0.5 * h;
-    mvs_drift<N>(m, Q, V, inv_m0, hh);
-    mvs_kick<N>(V, acc, hh);
-    bool bound = true;
-#pragma unroll
-    for (int i = 1; i < N; ++i) {
-        const double r2 = fma(Q[i][2], Q[i][2], fma(Q[i][1], Q[i][1], Q[i][0] * Q[i][0]));
-        const double v2 = fma(V[i][2], V[i][2], fma(V[i][1], V[i][1], V[i][0] * V[i][0]));
-        bound = bound && (2.0 / sqrt(r2) - v2 / m[0] > 0.0);
-    }
-    if (!bound) {
-        mvs_kick<N>(V, acc, -hh);
-        mvs_drift<N>(m, Q, V, inv_m0, -hh);
-        return ST_UNBOUND;
-    }
-#pragma unroll
-    for (int i = 1; i < N; ++i)
-        if (!kepler_drift(m[0], Q[i], V[i], h))
-            return ST_UNBOUND;
-    mvs_acc<N>(m, Q, acc);
-    mvs_kick<N>(V, acc, hh);
-    mvs_drift<N>(m, Q, V, inv_m0, hh);
-    return ST_ACTIVE;
-}
-
-template <int N>
-__device__ __forceinline__ void load_rows(const Bucket &B, int s, double (&m)[N], double (&x)[N][3],
-                                          double (&v)[N][3], double (&a)[N][3], bool with_a)
-{
-    const size_t pitch = B.pitch;
-#pragma unroll
-    for (int b = 0; b < N; ++b) {
-        m[b] = B.st[(R_M * N + b) * pitch + s];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            x[b][c] = B.st[((R_X + c) * N + b) * pitch + s];
-            v[b][c] = B.st[((R_V + c) * N + b) * pitch + s];
-            a[b][c] = with_a ? B.st[((R_A + c) * N + b) * pitch + s] : 0.0;
-        }
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void store_rows(const Bucket &B, int s, const double (&x)[N][3],
-                                           const double (&v)[N][3], const double (&a)[N][3],
-                                           bool with_a)
-{
-    const size_t pitch = B.pitch;
-#pragma unroll
-    for (int b = 0; b < N; ++b)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            B.st[((R_X + c) * N + b) * pitch + s] = x[b][c];
-            B.st[((R_V + c) * N + b) * pitch + s] = v[b][c];
-            if (with_a)
-                B.st[((R_A + c) * N + b) * pitch + s] = a[b][c];
-        }
-}
-
 // Inertial (x, v) -> MVS form in place: X, Vc in row 0, Q_i = x_i - x_0,
 // V_i = v_i - Vc, and the planet-planet accelerations at Q.
 template <int N>
@@ -1988,81 +1454,6 @@ __global__ __launch_bounds__(64) void k_mvs_leave(Bucket B)
     load_rows<N>(B, s, m, x, v, a, false);
     from_mvs<N>(m, x, v);
     store_rows<N>(B, s, x, v, a, false);
-}
-
-// Fixed-step MVS integration of one system per lane for at most P.quantum
-// steps: the run's whole steps, then the shortened final step if one is due
-// (the clock logic of the Hermite kernels).
-template <int N>
-__global__ __launch_bounds__(256) void k_plain_mvs(Bucket B, StepParams P)
-{
-    const int slot = blockIdx.x * blockDim.x + threadIdx.x;
-    if (slot >= B.count)
-        return;
-    Clock c = load_clock(B, slot);
-    if (c.status != ST_ACTIVE)
-        return;
-    double m[N], Q[N][3], V[N][3], acc[N][3];
-    load_rows<N>(B, slot, m, Q, V, acc, true);
-    const double inv_m0 = 1.0 / m[0];
-    int budget = P.quantum;
-#pragma unroll 1
-    for (int seg = 0; seg < 2 && c.status == ST_ACTIVE && budget > 0; ++seg) {
-        long long cnt = 0;
-        double h = c.dt;
-        if (seg == 0) {
-            cnt = c.nfull - c.k;
-            cnt = cnt < 0 ? 0 : cnt;
-        } else {
-            const double rem = c.t_end - c.t;
-            if (rem * c.dt > 1e-9 * c.dt * c.dt) {
-                cnt = 1;
-                h = rem;
-            } else {
-                c.t = c.t_end;
-                c.status = ST_DONE;
-            }
-        }
-        cnt = min(cnt, (long long)budget);
-        cnt = min(cnt, P.max_steps - c.steps);
-        const int nrun = cnt > 0 ? (int)cnt : 0;
-        int done = 0;
-#pragma unroll 1
-        for (; done < nrun; ++done) {
-            const int st = mvs_step<N>(m, Q, V, acc, inv_m0, h);
-            if (st != ST_ACTIVE) {
-                c.status = st;
-                break;
-            }
-        }
-        budget -= done;
-        c.steps += done;
-        if (seg == 0) {
-            c.k += done;
-            if (done > 0)
-                c.t = fma((double)c.k, c.dt, c.t0);
-            if (c.status == ST_ACTIVE && c.k >= c.nfull) {
-                const double rem = c.t_end - c.t;
-                if (!(rem * c.dt > 1e-9 * c.dt * c.dt)) {
-                    c.t = c.t_end;
-                    c.status = ST_DONE;
-                }
-            }
-        } else if (done > 0 && c.status == ST_ACTIVE) {
-            c.t = c.t_end;
-            c.status = ST_DONE;
-        }
-        if (c.status == ST_ACTIVE && c.steps >= P.max_steps)
-            c.status = ST_MAXSTEPS;
-    }
-    bool fin = true;
-#pragma unroll
-    for (int b = 0; b < N; ++b)
-        fin = fin && finite3(Q[b]) && finite3(V[b]);
-    if (!fin)
-        c.status = ST_NONFINITE;
-    store_rows<N>(B, slot, Q, V, acc, true);
-    store_clock(B, slot, c);
 }
 
 // State read-back of a bucket in MVS form: converted to inertial (x, v) on
@@ -2299,38 +1690,6 @@ void k_plain_rkck(Bucket B, StepParams P, double eps)
 // lane overwrites a copy only after the next evaluation's barrier, which
 // every reader of that copy has passed.
 
-// Lanes of the largest large-n workgroup (its LDS stays below 64 KiB).
-constexpr int kLargeMaxLanes = 512;
-
-// Dynamic LDS of a large-n workgroup holding T bodies: two copies of the
-// evaluation state (three 16-byte pairs per body each), the masses, one
-// reduction double and one int per body.
-__host__ __device__ constexpr size_t large_lds_bytes(int T)
-{
-    return (size_t)T * (6 * sizeof(double2) + 2 * sizeof(double) + sizeof(int));
-}
-
-struct LargeView {
-    double2 *xy, *zvx, *vyvz;   // copy c of lane l at [c * T + l]
-    double *m;
-    double *red;
-    int *flag;
-};
-
-__device__ __forceinline__ LargeView large_view(const int T)
-{
-    extern __shared__ char fb_dyn_lds[];
-    double2 *p = reinterpret_cast<double2 *>(fb_dyn_lds);
-    LargeView V;
-    V.xy = p;
-    V.zvx = p + 2 * T;
-    V.vyvz = p + 4 * T;
-    V.m = reinterpret_cast<double *>(p + 6 * T);
-    V.red = V.m + T;
-    V.flag = reinterpret_cast<int *>(V.red + T);
-    return V;
-}
-
 // One interaction of body i with the partner at LDS index idx of one copy
 // (Eq. 1 and its time derivative; the terms of bpl_interact).
 __device__ __forceinline__ void large_interact(const double2 *__restrict__ xy,
@@ -2392,25 +1751,6 @@ __device__ __forceinline__ void large_eval(const LargeView &V, const int T, cons
     large_interact(xy, zvx, vyvz, V.m, base + (b == 0 ? n - 1 : 0), xi, vi, a, jk);
 }
 
-// Lane geometry of a large-n workgroup.
-struct LargeLane {
-    int tid, sys, b, base, slot;
-    bool valid;
-};
-
-__device__ __forceinline__ LargeLane large_lane(const Bucket &B, const int S)
-{
-    LargeLane l;
-    l.tid = threadIdx.x;
-    l.sys = l.tid / B.n;
-    l.b = l.tid - l.sys * B.n;
-    l.base = l.sys * B.n;
-    const int slot = blockIdx.x * S + l.sys;
-    l.valid = l.sys < S && slot < B.count;
-    l.slot = l.valid ? slot : 0;
-    return l;
-}
-
 // Evaluation state of one body in the step kernel's LDS (48 bytes, so a
 // partner is three ds_read_b128 at immediate offsets from one address).
 struct LargeBody {
@@ -2440,11 +1780,6 @@ __device__ __forceinline__ LargeStepView large_step_view(const int E)
 static_assert(2 * sizeof(LargeBody) + 2 * sizeof(double) + sizeof(int) ==
                   6 * sizeof(double2) + 2 * sizeof(double) + sizeof(int),
               "step-kernel LDS view must match large_lds_bytes");
-
-// Squared separations are floored here before the inverse distance is taken:
-// a body's interaction with itself (r = u = 0) then contributes exact zeros
-// with every intermediate finite, and no real pair comes this close.
-constexpr double kLargeMinR2 = 1e-100;
 
 // One interaction of body i with a partner (Eq. 1 and its time derivative,
 // the terms of bpl_interact).  With TS, also the pair's step-rule quantity
@@ -3022,82 +2357,6 @@ __global__ __launch_bounds__(kLargeMaxLanes) void k_log_large(Bucket B, int S,
 // LDS.  Every lane reaches every barrier: a system's outcome (unbound,
 // Kepler failure) predicates its updates, never the control flow.
 
-// Over bodies b >= b0 of the lane's system: sum of w_b u_b (an fma chain in
-// body order) and the star's own u, to every valid lane.  Three barriers.
-__device__ __forceinline__ void large_sys_wsum3(const LargeView &V, const int T,
-                                                const LargeLane &l, const int n, const int b0,
-                                                const double w, const double (&u)[3],
-                                                double (&sum)[3], double (&star_u)[3])
-{
-    double2 *in0 = V.xy + T, *in1 = V.zvx + T, *res = V.vyvz + T;
-    in0[l.tid] = make_double2(u[0], u[1]);
-    in1[l.tid] = make_double2(u[2], w);
-    __syncthreads();
-    if (l.valid && l.b == 0) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for (int b = b0; b < n; ++b) {
-            const double2 p = in0[l.base + b], q = in1[l.base + b];
-            s0 = fma(q.y, p.x, s0);
-            s1 = fma(q.y, p.y, s1);
-            s2 = fma(q.y, q.x, s2);
-        }
-        res[l.base] = make_double2(s0, s1);
-        V.red[l.base] = s2;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        sum[c] = star_u[c] = 0.0;
-    if (l.valid) {
-        const double2 r = res[l.base], p = in0[l.base], q = in1[l.base];
-        sum[0] = r.x;
-        sum[1] = r.y;
-        sum[2] = V.red[l.base];
-        star_u[0] = p.x;
-        star_u[1] = p.y;
-        star_u[2] = q.x;
-    }
-    __syncthreads();
-}
-
-// OR of a per-lane flag over the lane's system, to every valid lane.
-__device__ __forceinline__ int large_sys_or(const LargeView &V, const LargeLane &l, const int n,
-                                            const int f)
-{
-    V.flag[l.tid] = f;
-    __syncthreads();
-    int r = 0;
-    if (l.valid)
-        for (int b = 0; b < n; ++b)
-            r |= V.flag[l.base + b];
-    __syncthreads();
-    return r;
-}
-
-// Planet-planet acceleration of this lane's planet at heliocentric positions
-// Q (each lane's own, published here); zero on the star's lane.
-__device__ __forceinline__ void large_mvs_acc(const LargeView &V, const LargeLane &l, const int n,
-                                              const double (&Q)[3], double (&acc)[3])
-{
-    V.xy[l.tid] = make_double2(Q[0], Q[1]);
-    V.zvx[l.tid] = make_double2(Q[2], 0.0);
-    __syncthreads();
-    acc[0] = acc[1] = acc[2] = 0.0;
-    if (l.valid && l.b > 0)
-        for (int j = 1; j < n; ++j) {
-            if (j == l.b)
-                continue;
-            const double2 p0 = V.xy[l.base + j], p1 = V.zvx[l.base + j];
-            const double d0 = p0.x - Q[0], d1 = p0.y - Q[1], d2 = p1.x - Q[2];
-            const double sr = rsqrt_nr(fma(d2, d2, fma(d1, d1, d0 * d0)));
-            const double mj = V.m[l.base + j] * (sr * sr * sr);
-            acc[0] = fma(mj, d0, acc[0]);
-            acc[1] = fma(mj, d1, acc[1]);
-            acc[2] = fma(mj, d2, acc[2]);
-        }
-    __syncthreads();
-}
-
 // MVS form -> inertial (x, v) of this lane's body (from_mvs): x_0 = X -
 // sum m_i Q_i / M, x_i = Q_i + x_0, v_0 = Vc - sum m_i V_i / m_0,
 // v_i = V_i + Vc.  V.m must hold the masses.
@@ -3121,43 +2380,6 @@ __device__ __forceinline__ void large_from_mvs(const LargeView &V, const int T, 
             x[c] += x0;
             v[c] += Vc[c];
         }
-    }
-}
-
-__device__ __forceinline__ void large_load_rows(const Bucket &B, const LargeLane &l, double &mi,
-                                                double (&x)[3], double (&v)[3], double (&a)[3])
-{
-    mi = 0.0;
-    const size_t pitch = B.pitch;
-    const int n = B.n;
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        x[c] = v[c] = a[c] = 0.0;
-    if (!l.valid)
-        return;
-    mi = B.st[(R_M * n + l.b) * pitch + l.slot];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        x[c] = B.st[((R_X + c) * n + l.b) * pitch + l.slot];
-        v[c] = B.st[((R_V + c) * n + l.b) * pitch + l.slot];
-        a[c] = B.st[((R_A + c) * n + l.b) * pitch + l.slot];
-    }
-}
-
-__device__ __forceinline__ void large_store_rows(const Bucket &B, const LargeLane &l,
-                                                 const double (&x)[3], const double (&v)[3],
-                                                 const double (&a)[3], bool with_a)
-{
-    if (!l.valid)
-        return;
-    const size_t pitch = B.pitch;
-    const int n = B.n;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        B.st[((R_X + c) * n + l.b) * pitch + l.slot] = x[c];
-        B.st[((R_V + c) * n + l.b) * pitch + l.slot] = v[c];
-        if (with_a)
-            B.st[((R_A + c) * n + l.b) * pitch + l.slot] = a[c];
     }
 }
 
@@ -3203,98 +2425,6 @@ __global__ __launch_bounds__(kLargeMaxLanes) void k_mvs_leave_large(Bucket B, in
     V.m[l.tid] = mi;
     large_from_mvs(V, T, l, B.n, mi, x, v);
     large_store_rows(B, l, x, v, a, false);
-}
-
-// Fixed-step MVS integration, one body per lane, for at most P.quantum steps
-// (the clock of the Hermite kernels; the steps of mvs_step, with the
-// outcomes of a system predicating its updates).  WAVES is the waves per
-// SIMD the register allocator targets: 2 (unspilled) for systems of up to 16
-// bodies, 4 (a few VGPRs spilled, twice the waves to hide the Kepler
-// solver's latency) for larger ones, where it measured 16-23% faster.
-template <int WAVES>
-__global__ __launch_bounds__(kLargeMaxLanes) __attribute__((amdgpu_waves_per_eu(WAVES)))
-void k_plain_mvs_large(Bucket B, StepParams P, int S)
-{
-    const int T = blockDim.x, n = B.n;
-    const LargeView V = large_view(T);
-    const LargeLane l = large_lane(B, S);
-    const bool planet = l.b > 0;
-    double mi, Q[3], W[3], acc[3];
-    large_load_rows(B, l, mi, Q, W, acc);
-    V.m[l.tid] = mi;
-    Clock c;
-    c.status = ST_DONE;
-    if (l.valid)
-        c = load_clock(B, l.slot);
-    __syncthreads();
-    const double m0 = l.valid ? V.m[l.base] : 1.0;
-    const double inv_m0 = 1.0 / m0;
-    // drift of Q (planets) by h sum_j m_j V_j / m0 and of X (star) by h Vc
-    auto drift = [&](const bool on, const double h) {
-        double Pm[3], unused[3];
-        large_sys_wsum3(V, T, l, n, 1, mi, W, Pm, unused);
-        if (!on)
-            return;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            if (planet)
-                Q[k] += h * Pm[k] * inv_m0;
-            else
-                Q[k] = fma(h, W[k], Q[k]);
-        }
-    };
-    for (int q = 0; q < P.quantum; ++q) {
-        double h = 0.0;
-        bool last = false;
-        const bool act = l.valid && plan_step(c, P, h, last);
-        if (!__syncthreads_or(act))
-            break;
-        const double hh = 0.5 * h;
-        drift(act, hh);
-        if (act && planet)
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                W[k] = fma(hh, acc[k], W[k]);
-        int unbound = 0;
-        if (act && planet) {
-            const double r2 = fma(Q[2], Q[2], fma(Q[1], Q[1], Q[0] * Q[0]));
-            const double v2 = fma(W[2], W[2], fma(W[1], W[1], W[0] * W[0]));
-            unbound = (2.0 / sqrt(r2) - v2 / m0 > 0.0) ? 0 : 1;
-        }
-        const int unbound_sys = large_sys_or(V, l, n, unbound);   // every lane: barriers inside
-        const bool undo = act && unbound_sys;
-        if (undo && planet)
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                W[k] = fma(-hh, acc[k], W[k]);
-        drift(undo, -hh);
-        const bool go = act && !undo;
-        const int kfail = (go && planet && !kepler_drift(m0, Q, W, h)) ? 1 : 0;
-        const int kfail_sys = large_sys_or(V, l, n, kfail);       // every lane: barriers inside
-        const bool failed = go && kfail_sys;
-        const bool ok = go && !failed;
-        double an[3];
-        large_mvs_acc(V, l, n, Q, an);
-        if (ok && planet)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                acc[k] = an[k];
-                W[k] = fma(hh, acc[k], W[k]);
-            }
-        drift(ok, hh);
-        if (ok)
-            finish_step(c, P, last, h, 0.0);
-        if (undo || failed)
-            c.status = ST_UNBOUND;
-    }
-    const int bad = large_sys_or(V, l, n, (l.valid && !(finite3(Q) && finite3(W))) ? 1 : 0);
-    if (!l.valid)
-        return;
-    if (bad)
-        c.status = ST_NONFINITE;
-    large_store_rows(B, l, Q, W, acc, true);
-    if (l.b == 0)
-        store_clock(B, l.slot, c);
 }
 
 // State read-back of a bucket in MVS form, converted to inertial (x, v) on
@@ -3504,8 +2634,6 @@ __global__ __launch_bounds__(256) void k_fma_probe(double *out, int iters, doubl
     out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = sum;
 }
 
-inline dim3 grid_for(int n, int block) { return dim3((unsigned)((n + block - 1) / block)); }
-
 // The device reciprocal square root of every pair evaluation, elementwise
 // over n values (a check of its accuracy against a correctly rounded
 // reference).
@@ -3621,18 +2749,6 @@ int large_bodies_per_lane(int n)
     return use2 >= use1 - 0.02 ? 2 : 1;
 }
 
-namespace {
-// Launch geometry of a large-n bucket with k bodies per lane: grid, lanes,
-// systems per workgroup.
-bool large_launch(const Bucket &B, int k, dim3 &grid, int &T, int &S)
-{
-    large_shape(B.n, k, T, S);
-    if (S < 1)
-        return false;
-    grid = dim3((unsigned)((B.count + S - 1) / S));
-    return true;
-}
-}  // namespace
 
 hipError_t launch_prepare(const Bucket &B, hipStream_t s)
 {
@@ -3901,30 +3017,6 @@ hipError_t launch_mvs_leave(const Bucket &B, hipStream_t s)
         return hipGetLastError();
     }
 #define FB_L(NN) hipLaunchKernelGGL(k_mvs_leave<NN>, grid_for(B.count, 64), dim3(64), 0, s, B)
-    FB_SWITCH_MVS(B.n, FB_L)
-#undef FB_L
-    return hipGetLastError();
-}
-
-hipError_t launch_plain_mvs(const Bucket &B, int mapping, int waves_per_group, const StepParams &P,
-                            hipStream_t s)
-{
-    if (B.count == 0)
-        return hipSuccess;
-    if (B.n > kMaxMvsBodies || mapping != MAP_SPL) {
-        dim3 lgrid;
-        int T, S;
-        if (!large_launch(B, 1, lgrid, T, S))
-            return hipErrorInvalidValue;
-        if (B.n > kMaxBodies)
-            hipLaunchKernelGGL(k_plain_mvs_large<4>, lgrid, dim3(T), large_lds_bytes(T), s, B, P, S);
-        else
-            hipLaunchKernelGGL(k_plain_mvs_large<2>, lgrid, dim3(T), large_lds_bytes(T), s, B, P, S);
-        return hipGetLastError();
-    }
-    const int W = waves_per_group < 1 ? 1 : (waves_per_group > 4 ? 4 : waves_per_group);
-    const dim3 grid = grid_for(B.count, 64 * W);
-#define FB_L(NN) hipLaunchKernelGGL(k_plain_mvs<NN>, grid, dim3(64 * W), 0, s, B, P)
     FB_SWITCH_MVS(B.n, FB_L)
 #undef FB_L
     return hipGetLastError();
