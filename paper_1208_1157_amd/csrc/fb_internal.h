@@ -44,6 +44,23 @@ struct Bucket {
     int n, pitch, count, pad;
 };
 
+// Several buckets of at most kMaxBodies bodies whose body-per-lane tiles
+// (floor(64 / n) systems each) share one launch: bucket k's tiles are
+// first[k] .. first[k + 1] - 1.  Passed to kernels by value.
+struct BucketSet {
+    Bucket b[kMaxBodies - 1];
+    int first[kMaxBodies];
+    int count;
+
+    void clear() { count = first[0] = 0; }
+    void add(const Bucket &B)
+    {
+        b[count] = B;
+        first[count + 1] = first[count] + (B.count + 64 / B.n - 1) / (64 / B.n);
+        ++count;
+    }
+};
+
 // One unit of persistent-schedule work: `count` systems of bucket `bucket`
 // starting at `first` (a slot, or an index into an active list).
 struct Tile {
@@ -121,10 +138,13 @@ hipError_t launch_plain_rkck(const Bucket &B, int waves_per_group, const StepPar
 // read-back of a bucket in MVS form as inertial positions and velocities.
 hipError_t launch_mvs_enter(const Bucket &B, hipStream_t s);
 hipError_t launch_mvs_leave(const Bucket &B, hipStream_t s);
-// mapping: MAP_SPL runs system per lane (n <= kMaxMvsBodies), MAP_BPL one
-// body per lane across a workgroup (any n); the two give identical results.
-hipError_t launch_plain_mvs(const Bucket &B, int mapping, int waves_per_group, const StepParams &P,
+// Three mappings that give identical results: system per lane (n <=
+// kMaxMvsBodies), one body per lane of a wavefront (every bucket of a set, n
+// <= kMaxBodies, in one launch) and one body per lane of a workgroup (any n).
+hipError_t launch_plain_mvs(const Bucket &B, int waves_per_group, const StepParams &P,
                             hipStream_t s);
+hipError_t launch_mvs_bpl(const BucketSet &set, const StepParams &P, hipStream_t s);
+hipError_t launch_plain_mvs_large(const Bucket &B, const StepParams &P, hipStream_t s);
 hipError_t launch_unpack_mvs(const Bucket &B, const long long *orig_off, double *pos,
                              double *vel, double *t, int *status, long long *steps,
                              hipStream_t s);

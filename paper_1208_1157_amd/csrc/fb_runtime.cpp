@@ -764,19 +764,32 @@ fb_status check_rk_opts(const fb_opts &o)
     return check_opts(o);
 }
 
-// MVS quanta: one system-per-lane launch per bucket and quantum.
+// MVS quanta: the Hermite plan's mapping rule within MVS's own limit (system
+// per lane when a bucket's 64-system tiles fill the device); the other
+// buckets of up to kMaxBodies bodies share one body-per-lane launch, larger
+// ones run a workgroup launch each.
 fb_status run_mvs(fb_ensemble *e, const fb_opts &o, long long step_bound)
 {
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
+    const StepParams P = make_params(o, quantum);
     for (;;) {
+        BucketSet set;
+        set.clear();
         for (const Bucket &B : e->buckets) {
-            const StepParams P = make_params(o, quantum);
+            if (B.n > kMaxBodies) {
+                ProfScope ps(e->stream);
+                FB_HIP(launch_plain_mvs_large(B, P, e->stream));
+            } else if (B.n <= kMaxMvsBodies &&
+                       plain_mapping(get_plan(B.n), B, false, e->num_cu) == MAP_SPL) {
+                ProfScope ps(e->stream);
+                FB_HIP(launch_plain_mvs(B, 1, P, e->stream));
+            } else {
+                set.add(B);
+            }
+        }
+        if (set.count) {
             ProfScope ps(e->stream);
-            // the Hermite plan's mapping rule (system per lane when its
-            // 64-system tiles fill the device), within MVS's own limit
-            const Plan p = B.n <= kMaxBodies ? get_plan(B.n) : Plan{MAP_BPL, 1, 0};
-            const int map = B.n > kMaxMvsBodies ? MAP_BPL : plain_mapping(p, B, false, e->num_cu);
-            FB_HIP(launch_plain_mvs(B, map, 1, P, e->stream));
+            FB_HIP(launch_mvs_bpl(set, P, e->stream));
         }
         if (quantum == INT_MAX)
             return FB_OK;
