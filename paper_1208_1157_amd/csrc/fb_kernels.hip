@@ -25,16 +25,11 @@
 //   v1 = vp - 1/2 (a0 - ak) h - (5 j0 + jk) h^2 / 12
 // The a0/j0 parts are folded into per-step bases, so each correction costs
 // four FMAs per component and does not need the corrected velocity.
-#include "fb_device.h"
+#include "fb_bpl.h"
 
 #include <algorithm>
 #include <climits>
 
-// Partner-loop unroll of the body-per-lane evaluation: full unrolling lets
-// the scheduler hoist every partner's LDS loads and costs occupancy.
-#ifndef FB_BPL_UNROLL
-#define FB_BPL_UNROLL 1
-#endif
 // Pairs per scheduling group in the system-per-lane evaluation of n >= 5.
 #ifndef FB_SPL_PAIR_GROUP
 #define FB_SPL_PAIR_GROUP 2
@@ -205,19 +200,6 @@ __device__ __forceinline__ double spl_step(const double (&m)[N], double (&x)[N][
             v[b][c] = vc[b][c];
         }
     return w;
-}
-
-// Stop-rule flags after a committed step: bit 0 non-finite, bit 1 two
-// planets within one mutual Hill radius, bit 2 a planet beyond r_eject.
-// The Hill test sep < ((m_i+m_j)/(3 m0))^(1/3) (r_i+r_j)/2 (r the astrocentric
-// distance) is evaluated without roots as
-// sep^6 < ((m_i+m_j)/(24 m0))^2 ((r_i+r_j)^2)^3.
-__device__ __forceinline__ bool hill_close(double sep2, double mi, double mj, double inv24m0,
-                                           double ri, double rj)
-{
-    const double mu = (mi + mj) * inv24m0;
-    const double w = (ri + rj) * (ri + rj);
-    return sep2 * sep2 * sep2 < mu * mu * (w * w * w);
 }
 
 template <int N>
@@ -407,405 +389,6 @@ __device__ __forceinline__ void spl_run(const Bucket &B, const int slot, const S
             B.st[((R_J + cc) * N + b) * pitch + slot] = jk[b][cc];
         }
     store_clock(B, slot, c);
-}
-
-// ---------------------------------------------------------------------------
-// body-per-lane (BPL)
-// ---------------------------------------------------------------------------
-
-// LDS slot of the k-th planet partner (0 <= k < N-2, the other planets in
-// ascending order) of body b of system s, with own = b S (the star lane
-// passes 64, past every body): (k + 1) S + s, moved one body up from b on.
-// The body offset (k + 1) S is uniform, so the slot costs a compare, a select
-// and an add per partner.
-template <int N>
-__device__ __forceinline__ int partner_slot(const int k, const int s, const int own)
-{
-    constexpr int S = 64 / N;
-    const int ks = (k + 1) * S;
-    return s + ks + (ks >= own ? S : 0);
-}
-
-// A partner's evaluation state as read from the wavefront's LDS slice.
-struct Partner {
-    double2 p0, p1, p2;   // (x, y), (z, vx), (vy, vz)
-    double mj;
-};
-
-__device__ __forceinline__ Partner bpl_partner(const BplLds &L, const int idx)
-{
-    return Partner{L.xy[idx], L.zvx[idx], L.vyvz[idx], L.mr[idx].x};
-}
-
-// One interaction of body i (this lane) with partner P: adds m_j A and m_j J
-// (Eq. 1 and its time derivative).
-template <bool TS>
-__device__ __forceinline__ void bpl_interact_p(const Partner &Pj, const double (&xi)[3],
-                                               const double (&vi)[3], double (&a)[3],
-                                               double (&jk)[3], double &wmax)
-{
-    const double2 p0 = Pj.p0, p1 = Pj.p1, p2 = Pj.p2;
-    const double mj = Pj.mj;
-    const double rx = p0.x - xi[0], ry = p0.y - xi[1], rz = p1.x - xi[2];
-    const double ux = p1.y - vi[0], uy = p2.x - vi[1], uz = p2.y - vi[2];
-    const double r2 = fma(rz, rz, fma(ry, ry, rx * rx));
-    const double ru = fma(rz, uz, fma(ry, uy, rx * ux));
-    const double ri = rsqrt_nr(r2);
-    const double ri2 = ri * ri;
-    const double mr3 = mj * (ri2 * ri);
-    const double al = 3.0 * ru * ri2;
-    a[0] = fma(mr3, rx, a[0]);
-    a[1] = fma(mr3, ry, a[1]);
-    a[2] = fma(mr3, rz, a[2]);
-    jk[0] = fma(mr3, fma(-al, rx, ux), jk[0]);
-    jk[1] = fma(mr3, fma(-al, ry, uy), jk[1]);
-    jk[2] = fma(mr3, fma(-al, rz, uz), jk[2]);
-    if (TS) {
-        const double u2 = fma(uz, uz, fma(uy, uy, ux * ux));
-        wmax = fmax(wmax, fma(al, ru, u2) * ri2);
-    }
-}
-
-// One interaction of body i (this lane) with the partner stored at LDS index
-// idx.
-template <bool TS>
-__device__ __forceinline__ void bpl_interact(const BplLds &L, const int idx,
-                                             const double (&xi)[3], const double (&vi)[3],
-                                             double (&a)[3], double (&jk)[3], double &wmax)
-{
-    bpl_interact_p<TS>(bpl_partner(L, idx), xi, vi, a, jk, wmax);
-}
-
-// Accelerations and jerks of this lane's body from all n-1 partners read
-// from the wavefront's LDS slice.  Partner order: the other planets in
-// ascending order, then the star (the star lane sums planets 1..n-1), so the
-// star's contribution is added last.  Branch-free: the n-2 planet partners
-// skip this lane's own index arithmetically and the last partner is peeled.
-// ILP unrolls the partner loop fully (the full-register-file kernel class,
-// where a wave has its SIMD to itself and needs independent interactions
-// in flight); the accumulation order is the same either way.
-template <int N, bool TS, bool ILP = false>
-__device__ __forceinline__ void bpl_eval(BplLds &L, const int lane, const int b, const int s,
-                                         const double (&xi)[3], const double (&vi)[3],
-                                         double (&a)[3], double (&jk)[3], double &wmax)
-{
-    constexpr int S = 64 / N;
-    L.xy[lane] = make_double2(xi[0], xi[1]);
-    L.zvx[lane] = make_double2(xi[2], vi[0]);
-    L.vyvz[lane] = make_double2(vi[1], vi[2]);
-    wave_sync();
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        a[c] = 0.0;
-        jk[c] = 0.0;
-    }
-    const int own = b == 0 ? 64 : b * S;
-    if constexpr (ILP) {
-#pragma unroll
-        for (int k = 0; k < N - 2; ++k)
-            bpl_interact<TS>(L, partner_slot<N>(k, s, own), xi, vi, a, jk, wmax);
-    } else {
-#pragma unroll FB_BPL_UNROLL
-        for (int k = 0; k < N - 2; ++k)
-            bpl_interact<TS>(L, partner_slot<N>(k, s, own), xi, vi, a, jk, wmax);
-    }
-    bpl_interact<TS>(L, (b == 0 ? N - 1 : 0) * S + s, xi, vi, a, jk, wmax);
-    wave_sync();
-}
-
-template <int N, bool ILP = false>
-__device__ __forceinline__ int bpl_stop_flags(BplLds &L, const int lane, const int b,
-                                              const int s, const double mi, const double inv24m0,
-                                              const double (&x)[3], const double (&v)[3],
-                                              const StepParams &P)
-{
-    constexpr int S = 64 / N;
-    int fl = (finite3(x) && finite3(v)) ? 0 : 1;
-    L.xy[lane] = make_double2(x[0], x[1]);
-    L.zvx[lane] = make_double2(x[2], 0.0);
-    wave_sync();
-    const double2 s0 = L.xy[s];
-    const double2 s1 = L.zvx[s];
-    const double dx = x[0] - s0.x, dy = x[1] - s0.y, dz = x[2] - s1.x;
-    const double rb = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
-    L.mr[lane].y = rb;
-    wave_sync();
-    if (b >= 1) {
-        if ((P.stop_rules & 2) && rb > P.r_eject)
-            fl |= 4;
-        if (P.stop_rules & 1) {
-            const int own = b * S;
-            auto hill = [&](const int k) {
-                const int idx = partner_slot<N>(k, s, own);
-                const double2 q0 = L.xy[idx];
-                const double2 q1 = L.zvx[idx];
-                const double ex = x[0] - q0.x, ey = x[1] - q0.y, ez = x[2] - q1.x;
-                const double sep2 = fma(ez, ez, fma(ey, ey, ex * ex));
-                if (hill_close(sep2, mi, L.mr[idx].x, inv24m0, rb, L.mr[idx].y))
-                    fl |= 2;
-            };
-            if constexpr (ILP) {
-#pragma unroll
-                for (int k = 0; k < N - 2; ++k)
-                    hill(k);
-            } else {
-#pragma unroll 1
-                for (int k = 0; k < N - 2; ++k)
-                    hill(k);
-            }
-        }
-    }
-    wave_sync();
-    return sys_or_flags<N>(s, fl);
-}
-
-// Full-register-file variants of the evaluation and of the stop-rule pass,
-// for a wave that has its SIMD to itself and so waits out every LDS round
-// trip and every dependent latency: the partner slots (pidx) and masses (pm)
-// of this lane's body, in evaluation order, are fixed over the run and held
-// in registers; all partner reads are issued before the first interaction.
-template <int N>
-__device__ __forceinline__ int eval_partner(const int k, const int b)
-{
-    const int skip = b == 0 ? (1 << 20) : b;
-    return k < N - 2 ? k + 1 + (k + 1 >= skip ? 1 : 0) : (b == 0 ? N - 1 : 0);
-}
-
-template <int N, bool TS>
-__device__ __forceinline__ void bpl_eval_regs(BplLds &L, const int lane, const int (&pidx)[N - 1],
-                                              const double (&pm)[N - 1], const double (&xi)[3],
-                                              const double (&vi)[3], double (&a)[3],
-                                              double (&jk)[3], double &wmax)
-{
-    L.xy[lane] = make_double2(xi[0], xi[1]);
-    L.zvx[lane] = make_double2(xi[2], vi[0]);
-    L.vyvz[lane] = make_double2(vi[1], vi[2]);
-    wave_sync();
-    Partner pj[N - 1];
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k)
-        pj[k] = Partner{L.xy[pidx[k]], L.zvx[pidx[k]], L.vyvz[pidx[k]], pm[k]};
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        a[c] = 0.0;
-        jk[c] = 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k)
-        bpl_interact_p<TS>(pj[k], xi, vi, a, jk, wmax);
-    wave_sync();
-}
-
-// Stop-rule flags (as bpl_stop_flags) and the system maximum of the step
-// rule's w (as sys_max): one exchange of each lane's position and w gives
-// the star's position, the partners' positions and every w; a second, of
-// the astrocentric distances, the Hill test's partner radii.
-template <int N>
-__device__ __forceinline__ int bpl_stop_flags_regs(BplLds &L, const int lane, const int b,
-                                                   const int s, const int (&pidx)[N - 1],
-                                                   const double (&pm)[N - 1], const double mi,
-                                                   const double inv24m0, const double (&x)[3],
-                                                   const double (&v)[3], const double w,
-                                                   double &wsys, const StepParams &P)
-{
-    int fl = (finite3(x) && finite3(v)) ? 0 : 1;
-    L.xy[lane] = make_double2(x[0], x[1]);
-    L.zvx[lane] = make_double2(x[2], w);
-    wave_sync();
-    double2 q0[N - 1], q1[N - 1];
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) {
-        q0[k] = L.xy[pidx[k]];
-        q1[k] = L.zvx[pidx[k]];
-    }
-    const double2 s0 = L.xy[s];
-    const double2 s1 = L.zvx[s];
-    wave_sync();
-    // max is exact, so the partners' order gives the body-order result
-    wsys = w;
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k)
-        wsys = fmax(wsys, q1[k].y);
-    const double dx = x[0] - s0.x, dy = x[1] - s0.y, dz = x[2] - s1.x;
-    const double rb = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
-    if (P.stop_rules & 1) {
-        // the partners' astrocentric distances: a second exchange is
-        // shorter than computing N - 2 more square roots per lane
-        double rp[N - 1];
-        L.mr[lane].y = rb;
-        wave_sync();
-#pragma unroll
-        for (int k = 0; k < N - 2; ++k)
-            rp[k] = L.mr[pidx[k]].y;
-        wave_sync();
-        if (b >= 1) {
-#pragma unroll
-            for (int k = 0; k < N - 2; ++k) {
-                const double ex = x[0] - q0[k].x, ey = x[1] - q0[k].y, ez = x[2] - q1[k].x;
-                const double sep2 = fma(ez, ez, fma(ey, ey, ex * ex));
-                if (hill_close(sep2, mi, pm[k], inv24m0, rb, rp[k]))
-                    fl |= 2;
-            }
-        }
-    }
-    if (b >= 1 && (P.stop_rules & 2) && rb > P.r_eject)
-        fl |= 4;
-    return sys_or_flags<N>(s, fl);
-}
-
-// Integrate one tile (floor(64/N) systems) with one body per lane for at
-// most P.quantum steps.  Every lane of the wavefront executes the same
-// control flow (the LDS exchanges need it); lanes of finished, padding or
-// absent systems compute but never commit.  Returns, on the star lane of each
-// present system, whether that system is still active.
-template <int N, bool ADV, bool WIDE>
-__device__ __forceinline__ bool bpl_run(const Bucket &B, const int first, const int count, const int *list,
-                        const StepParams &P, int &slot_out)
-{
-    constexpr int S = 64 / N;
-    BplLds &L = *reinterpret_cast<BplLds *>(wave_lds_base<sizeof(BplLds), WIDE>());
-    const int lane = threadIdx.x & 63;
-    const int braw = lane / S;
-    const int b = braw < N ? braw : N - 1;
-    const int s = lane - braw * S;
-    const bool valid = braw < N && s < count;
-    int slot = 0;
-    if (valid)
-        slot = list ? list[first + s] : first + s;
-    slot_out = slot;
-    const size_t pitch = B.pitch;
-    double mi = 0.0, x[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
-    double a0[3] = {0.0, 0.0, 0.0}, j0[3] = {0.0, 0.0, 0.0};
-    Clock c{};
-    c.status = ST_DONE;
-    if (valid) {
-        mi = B.st[(R_M * N + b) * pitch + slot];
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-            x[cc] = B.st[((R_X + cc) * N + b) * pitch + slot];
-            v[cc] = B.st[((R_V + cc) * N + b) * pitch + slot];
-            a0[cc] = B.st[((R_A + cc) * N + b) * pitch + slot];
-            j0[cc] = B.st[((R_J + cc) * N + b) * pitch + slot];
-        }
-        c = load_clock(B, slot);
-    }
-    L.mr[lane].x = mi;
-    wave_sync();
-    // Hill-test scale of the system's star, fixed over the run.
-    const double inv24m0 = ADV ? 1.0 / (24.0 * L.mr[s].x) : 0.0;
-    // The full-register-file class keeps the partner tables in registers.
-    constexpr bool REGS = WIDE && N <= 8;
-    int pidx[N - 1];
-    double pm[N - 1];
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) {
-        pidx[k] = REGS ? eval_partner<N>(k, b) * S + s : 0;
-        pm[k] = REGS ? L.mr[pidx[k]].x : 0.0;
-    }
-    for (int q = 0; q < P.quantum; ++q) {
-        double h = 0.0;
-        bool last = false;
-        bool act;
-        if constexpr (ADV && REGS)   // invalid lanes hold an inactive clock
-            act = P.adaptive ? plan_step_adaptive(c, P, h, last) : valid && plan_step(c, P, h, last);
-        else
-            act = valid && plan_step(c, P, h, last);
-        if (!__any(act))
-            break;
-        const Coef k = make_coef(h);
-        double xc[3], vc[3], bx[3], bv[3], ak[3], jk[3];
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            predict_comp(k, x[cc], v[cc], a0[cc], j0[cc], xc[cc], vc[cc], bx[cc], bv[cc]);
-        double w = 0.0;
-        if constexpr (REGS)
-            bpl_eval_regs<N, false>(L, lane, pidx, pm, xc, vc, ak, jk, w);
-        else
-            bpl_eval<N, false, WIDE>(L, lane, b, s, xc, vc, ak, jk, w);
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            correct_comp(k, bx[cc], bv[cc], ak[cc], jk[cc], xc[cc], vc[cc]);
-        if constexpr (REGS)
-            bpl_eval_regs<N, ADV>(L, lane, pidx, pm, xc, vc, ak, jk, w);
-        else
-            bpl_eval<N, ADV, WIDE>(L, lane, b, s, xc, vc, ak, jk, w);
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            correct_comp(k, bx[cc], bv[cc], ak[cc], jk[cc], xc[cc], vc[cc]);
-        if constexpr (ADV && REGS) {
-            // commit, then one exchange for the step rule's maximum and the
-            // stop rules (same values and order of decisions as below)
-            double dtp = 0.0;
-            if (P.adaptive == 2) {
-                const double aa = fma(ak[2], ak[2], fma(ak[1], ak[1], ak[0] * ak[0]));
-                const double jj = fma(jk[2], jk[2], fma(jk[1], jk[1], jk[0] * jk[0]));
-                dtp = P.eta * rsqrt_nr(sys_sum<N>(L, lane, s, jj / aa));
-            }
-            if (act) {
-#pragma unroll
-                for (int cc = 0; cc < 3; ++cc) {
-                    x[cc] = xc[cc];
-                    v[cc] = vc[cc];
-                    a0[cc] = ak[cc];
-                    j0[cc] = jk[cc];
-                }
-            }
-            double wsys = 0.0;
-            const int fl = bpl_stop_flags_regs<N>(L, lane, b, s, pidx, pm, mi, inv24m0, x, v, w,
-                                                  wsys, P);
-            if (P.adaptive == 1)
-                dtp = P.eta * rsqrt_nr(wsys);
-            if (P.adaptive) {
-                finish_step_adaptive(c, act, last, h, dtp, fl);
-            } else if (act) {
-                finish_step(c, P, last, h, dtp);
-                if (fl)
-                    c.status = status_of_flags(fl);
-            }
-            continue;
-        }
-        double dtp = 0.0;
-        if (ADV && P.adaptive == 1)
-            dtp = P.eta * rsqrt_nr(sys_max<N>(L, lane, s, w));
-        if (ADV && P.adaptive == 2) {
-            const double aa = fma(ak[2], ak[2], fma(ak[1], ak[1], ak[0] * ak[0]));
-            const double jj = fma(jk[2], jk[2], fma(jk[1], jk[1], jk[0] * jk[0]));
-            dtp = P.eta * rsqrt_nr(sys_sum<N>(L, lane, s, jj / aa));
-        }
-        if (act) {
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                x[cc] = xc[cc];
-                v[cc] = vc[cc];
-                a0[cc] = ak[cc];
-                j0[cc] = jk[cc];
-            }
-            finish_step(c, P, last, h, dtp);
-        }
-        if (ADV) {
-            const int fl = bpl_stop_flags<N, WIDE>(L, lane, b, s, mi, inv24m0, x, v, P);
-            if (act && fl)
-                c.status = status_of_flags(fl);
-        }
-    }
-    if (!ADV) {
-        const int fl = sys_or_flags<N>(s, (finite3(x) && finite3(v)) ? 0 : 1);
-        if (valid && fl)
-            c.status = ST_NONFINITE;
-    }
-    if (valid) {
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-            B.st[((R_X + cc) * N + b) * pitch + slot] = x[cc];
-            B.st[((R_V + cc) * N + b) * pitch + slot] = v[cc];
-            B.st[((R_A + cc) * N + b) * pitch + slot] = a0[cc];
-            B.st[((R_J + cc) * N + b) * pitch + slot] = j0[cc];
-        }
-        if (b == 0)
-            store_clock(B, slot, c);
-    }
-    return valid && b == 0 && braw == 0 && c.status == ST_ACTIVE;
 }
 
 // ---------------------------------------------------------------------------
