@@ -202,7 +202,8 @@ __device__ __forceinline__ void bpl_eval_regs(BplLds &L, const int lane, const i
 #pragma unroll
     for (int k = 0; k < N - 1; ++k)
         pj[k] = Partner{L.xy[pidx[k]], L.zvx[pidx[k]], L.vyvz[pidx[k]], pm[k]};
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (N <= 9)   // (more partners' state does not fit the VGPRs at once)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         a[c] = 0.0;
@@ -271,16 +272,98 @@ __device__ __forceinline__ int bpl_stop_flags_regs(BplLds &L, const int lane, co
     return sys_or_flags<N>(s, fl);
 }
 
+// One P(EC)^2 step with the coefficients k: (xc, vc) the corrected state, (ak,
+// jk) the last evaluation, w the step rule's quantity of it (TS).
+template <int N, bool TS, bool REGS, bool ILP>
+__device__ __forceinline__ void bpl_step(BplLds &L, const int lane, const int b, const int s,
+                                         const int (&pidx)[N - 1], const double (&pm)[N - 1],
+                                         const Coef &k, const double (&x)[3], const double (&v)[3],
+                                         const double (&a0)[3], const double (&j0)[3],
+                                         double (&xc)[3], double (&vc)[3], double (&ak)[3],
+                                         double (&jk)[3], double &w)
+{
+    double bx[3], bv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        predict_comp(k, x[c], v[c], a0[c], j0[c], xc[c], vc[c], bx[c], bv[c]);
+    if constexpr (REGS)
+        bpl_eval_regs<N, false>(L, lane, pidx, pm, xc, vc, ak, jk, w);
+    else
+        bpl_eval<N, false, ILP>(L, lane, b, s, xc, vc, ak, jk, w);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
+    if constexpr (REGS)
+        bpl_eval_regs<N, TS>(L, lane, pidx, pm, xc, vc, ak, jk, w);
+    else
+        bpl_eval<N, TS, ILP>(L, lane, b, s, xc, vc, ak, jk, w);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
+}
+
+// nrun fixed steps of this lane's system.  Where every running lane has the
+// same count (live lanes; the state of the others is never stored) the loop
+// carries no per-lane bookkeeping and the state needs no selects; otherwise a
+// lane past its count keeps its state.
+template <int N, bool REGS, bool ILP>
+__device__ __forceinline__ void bpl_fixed_steps(BplLds &L, const int lane, const int b,
+                                                const int s, const int (&pidx)[N - 1],
+                                                const double (&pm)[N - 1], const Coef &k,
+                                                const bool live, const int nrun, double (&x)[3],
+                                                double (&v)[3], double (&a0)[3], double (&j0)[3])
+{
+    const unsigned long long who = __ballot(live && nrun > 0);
+    if (who == 0ull)
+        return;
+    const int n0 = __builtin_amdgcn_readlane(nrun, __builtin_ctzll(who));
+    double w = 0.0;
+    if (__all(!live || nrun == n0)) {
+#pragma unroll 1
+        for (int q = 0; q < n0; ++q) {
+            double xc[3], vc[3], ak[3], jk[3];
+            bpl_step<N, false, REGS, ILP>(L, lane, b, s, pidx, pm, k, x, v, a0, j0, xc, vc, ak,
+                                          jk, w);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[c] = xc[c];
+                v[c] = vc[c];
+                a0[c] = ak[c];
+                j0[c] = jk[c];
+            }
+        }
+        return;
+    }
+    int q = 0;
+#pragma unroll 1
+    do {
+        const bool act = q < nrun;
+        double xc[3], vc[3], ak[3], jk[3];
+        bpl_step<N, false, REGS, ILP>(L, lane, b, s, pidx, pm, k, x, v, a0, j0, xc, vc, ak, jk, w);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            x[c] = act ? xc[c] : x[c];
+            v[c] = act ? vc[c] : v[c];
+            a0[c] = act ? ak[c] : a0[c];
+            j0[c] = act ? jk[c] : j0[c];
+        }
+        ++q;
+    } while (__any(q < nrun));
+}
+
 // Integrate one tile (floor(64/N) systems) with one body per lane for at
 // most P.quantum steps.  Every lane of the wavefront executes the same
 // control flow (the LDS exchanges need it); lanes of finished, padding or
-// absent systems compute but never commit.  Returns, on the star lane of each
-// present system, whether that system is still active.
-template <int N, bool ADV, bool WIDE>
+// absent systems compute but never commit.  REGS: the variants for a wave
+// that has its SIMD to itself; WIDE: the LDS stride of the system-per-lane
+// fused class.  Returns, on the star lane of each present system, whether that
+// system is still active.
+template <int N, bool ADV, bool WIDE, bool REGS>
 __device__ __forceinline__ bool bpl_run(const Bucket &B, const int first, const int count, const int *list,
                         const StepParams &P, int &slot_out)
 {
     constexpr int S = 64 / N;
+    constexpr bool ILP = WIDE || REGS;   // unrolled partner loops
     BplLds &L = *reinterpret_cast<BplLds *>(wave_lds_base<sizeof(BplLds), WIDE>());
     const int lane = threadIdx.x & 63;
     const int braw = lane / S;
@@ -307,12 +390,9 @@ __device__ __forceinline__ bool bpl_run(const Bucket &B, const int first, const 
         }
         c = load_clock(B, slot);
     }
+    const bool live = c.status == ST_ACTIVE;   // systems that may step: only they are stored
     L.mr[lane].x = mi;
     wave_sync();
-    // Hill-test scale of the system's star, fixed over the run.
-    const double inv24m0 = ADV ? 1.0 / (24.0 * L.mr[s].x) : 0.0;
-    // The full-register-file class keeps the partner tables in registers.
-    constexpr bool REGS = WIDE && N <= 8;
     int pidx[N - 1];
     double pm[N - 1];
 #pragma unroll
@@ -320,40 +400,36 @@ __device__ __forceinline__ bool bpl_run(const Bucket &B, const int first, const 
         pidx[k] = REGS ? eval_partner<N>(k, b) * S + s : 0;
         pm[k] = REGS ? L.mr[pidx[k]].x : 0.0;
     }
-    for (int q = 0; q < P.quantum; ++q) {
-        double h = 0.0;
-        bool last = false;
-        bool act;
-        if constexpr (ADV && REGS)   // invalid lanes hold an inactive clock
-            act = P.adaptive ? plan_step_adaptive(c, P, h, last) : valid && plan_step(c, P, h, last);
-        else
-            act = valid && plan_step(c, P, h, last);
-        if (!__any(act))
-            break;
-        const Coef k = make_coef(h);
-        double xc[3], vc[3], bx[3], bv[3], ak[3], jk[3];
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            predict_comp(k, x[cc], v[cc], a0[cc], j0[cc], xc[cc], vc[cc], bx[cc], bv[cc]);
-        double w = 0.0;
-        if constexpr (REGS)
-            bpl_eval_regs<N, false>(L, lane, pidx, pm, xc, vc, ak, jk, w);
-        else
-            bpl_eval<N, false, WIDE>(L, lane, b, s, xc, vc, ak, jk, w);
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            correct_comp(k, bx[cc], bv[cc], ak[cc], jk[cc], xc[cc], vc[cc]);
-        if constexpr (REGS)
-            bpl_eval_regs<N, ADV>(L, lane, pidx, pm, xc, vc, ak, jk, w);
-        else
-            bpl_eval<N, ADV, WIDE>(L, lane, b, s, xc, vc, ak, jk, w);
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            correct_comp(k, bx[cc], bv[cc], ak[cc], jk[cc], xc[cc], vc[cc]);
-        if constexpr (ADV && REGS) {
-            // commit, then one exchange for the step rule's maximum and the
-            // stop rules (same values and order of decisions as below)
+    if constexpr (!ADV) {
+        int budget = P.quantum;
+#pragma unroll 1
+        for (int seg = 0; seg < 2; ++seg) {
+            double h = c.dt;
+            const int nrun = run_segment(c, P, seg, budget, h);
+            bpl_fixed_steps<N, REGS, ILP>(L, lane, b, s, pidx, pm, make_coef(h), live, nrun, x, v,
+                                          a0, j0);
+            budget -= nrun;
+            run_segment_end(c, P, seg, nrun);
+        }
+    } else {
+        // Hill-test scale of the system's star, fixed over the run.
+        const double inv24m0 = 1.0 / (24.0 * L.mr[s].x);
+        for (int q = 0; q < P.quantum; ++q) {
+            double h = 0.0;
+            bool last = false;
+            bool act;
+            if constexpr (REGS)   // invalid lanes hold an inactive clock
+                act = P.adaptive ? plan_step_adaptive(c, P, h, last) : valid && plan_step(c, P, h, last);
+            else
+                act = valid && plan_step(c, P, h, last);
+            if (!__any(act))
+                break;
+            double xc[3], vc[3], ak[3], jk[3], w = 0.0;
+            bpl_step<N, true, REGS, ILP>(L, lane, b, s, pidx, pm, make_coef(h), x, v, a0, j0, xc,
+                                         vc, ak, jk, w);
             double dtp = 0.0;
+            if (!REGS && P.adaptive == 1)
+                dtp = P.eta * rsqrt_nr(sys_max<N>(L, lane, s, w));
             if (P.adaptive == 2) {
                 const double aa = fma(ak[2], ak[2], fma(ak[1], ak[1], ak[0] * ak[0]));
                 const double jj = fma(jk[2], jk[2], fma(jk[1], jk[1], jk[0] * jk[0]));
@@ -368,50 +444,36 @@ __device__ __forceinline__ bool bpl_run(const Bucket &B, const int first, const 
                     j0[cc] = jk[cc];
                 }
             }
-            double wsys = 0.0;
-            const int fl = bpl_stop_flags_regs<N>(L, lane, b, s, pidx, pm, mi, inv24m0, x, v, w,
-                                                  wsys, P);
-            if (P.adaptive == 1)
-                dtp = P.eta * rsqrt_nr(wsys);
-            if (P.adaptive) {
-                finish_step_adaptive(c, act, last, h, dtp, fl);
-            } else if (act) {
-                finish_step(c, P, last, h, dtp);
-                if (fl)
+            if constexpr (REGS) {
+                // one exchange for the step rule's maximum and the stop rules
+                // (same values and order of decisions as below)
+                double wsys = 0.0;
+                const int fl = bpl_stop_flags_regs<N>(L, lane, b, s, pidx, pm, mi, inv24m0, x, v,
+                                                      w, wsys, P);
+                if (P.adaptive == 1)
+                    dtp = P.eta * rsqrt_nr(wsys);
+                if (P.adaptive) {
+                    finish_step_adaptive(c, act, last, h, dtp, fl);
+                } else if (act) {
+                    finish_step(c, P, last, h, dtp);
+                    if (fl)
+                        c.status = status_of_flags(fl);
+                }
+            } else {
+                if (act)
+                    finish_step(c, P, last, h, dtp);
+                const int fl = bpl_stop_flags<N, WIDE>(L, lane, b, s, mi, inv24m0, x, v, P);
+                if (act && fl)
                     c.status = status_of_flags(fl);
             }
-            continue;
-        }
-        double dtp = 0.0;
-        if (ADV && P.adaptive == 1)
-            dtp = P.eta * rsqrt_nr(sys_max<N>(L, lane, s, w));
-        if (ADV && P.adaptive == 2) {
-            const double aa = fma(ak[2], ak[2], fma(ak[1], ak[1], ak[0] * ak[0]));
-            const double jj = fma(jk[2], jk[2], fma(jk[1], jk[1], jk[0] * jk[0]));
-            dtp = P.eta * rsqrt_nr(sys_sum<N>(L, lane, s, jj / aa));
-        }
-        if (act) {
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                x[cc] = xc[cc];
-                v[cc] = vc[cc];
-                a0[cc] = ak[cc];
-                j0[cc] = jk[cc];
-            }
-            finish_step(c, P, last, h, dtp);
-        }
-        if (ADV) {
-            const int fl = bpl_stop_flags<N, WIDE>(L, lane, b, s, mi, inv24m0, x, v, P);
-            if (act && fl)
-                c.status = status_of_flags(fl);
         }
     }
-    if (!ADV) {
+    if constexpr (!ADV) {
         const int fl = sys_or_flags<N>(s, (finite3(x) && finite3(v)) ? 0 : 1);
-        if (valid && fl)
+        if (live && fl)
             c.status = ST_NONFINITE;
     }
-    if (valid) {
+    if (live) {
 #pragma unroll
         for (int cc = 0; cc < 3; ++cc) {
             B.st[((R_X + cc) * N + b) * pitch + slot] = x[cc];

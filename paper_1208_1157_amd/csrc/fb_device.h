@@ -314,6 +314,60 @@ __device__ __forceinline__ void finish_step_adaptive(Clock &c, const bool act, c
     c.status = act ? st : c.status;
 }
 
+// Run control of fixed steps without a per-step clock.  Segment 0 is the
+// run's whole steps, segment 1 the shortened final step if one is due; the
+// number of steps of size h the system takes in the segment, at most
+// `budget` and P.max_steps allowing.
+__device__ __forceinline__ int run_segment(Clock &c, const StepParams &P, const int seg,
+                                           const int budget, double &h)
+{
+    if (c.status != ST_ACTIVE || budget <= 0)
+        return 0;
+    long long cnt = 0;
+    h = c.dt;
+    if (seg == 0) {
+        cnt = c.nfull - c.k;
+        cnt = cnt < 0 ? 0 : cnt;
+    } else {
+        const double rem = c.t_end - c.t;
+        if (rem * c.dt > 1e-9 * c.dt * c.dt) {
+            cnt = 1;
+            h = rem;
+        } else {
+            c.t = c.t_end;
+            c.status = ST_DONE;
+        }
+    }
+    cnt = min(cnt, (long long)budget);
+    cnt = min(cnt, P.max_steps - c.steps);
+    return cnt > 0 ? (int)cnt : 0;
+}
+
+// The clock after `done` steps of segment seg; `was_active`: the system
+// entered the segment active (its steps may have stopped it since).
+__device__ __forceinline__ void run_segment_end(Clock &c, const StepParams &P, const int seg,
+                                                const int done)
+{
+    c.steps += done;
+    if (seg == 0) {
+        c.k += done;
+        if (done > 0)
+            c.t = fma((double)c.k, c.dt, c.t0);
+        if (c.status == ST_ACTIVE && c.k >= c.nfull) {
+            const double rem = c.t_end - c.t;
+            if (!(rem * c.dt > 1e-9 * c.dt * c.dt)) {
+                c.t = c.t_end;
+                c.status = ST_DONE;
+            }
+        }
+    } else if (done > 0 && c.status == ST_ACTIVE) {
+        c.t = c.t_end;
+        c.status = ST_DONE;
+    }
+    if (c.status == ST_ACTIVE && c.steps >= P.max_steps)
+        c.status = ST_MAXSTEPS;
+}
+
 template <int N>
 __device__ __forceinline__ double sys_max(BplLds &L, int lane, int s, double v)
 {

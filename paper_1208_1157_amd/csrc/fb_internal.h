@@ -18,13 +18,17 @@ enum SysStatus {
     ST_NONFINITE = 4, ST_STALLED = 5, ST_MAXSTEPS = 6, ST_UNBOUND = 7
 };
 
-enum Mapping { MAP_SPL = 1, MAP_BPL = 2 };
+// MAP_BPLU is body per lane with unrolled partner loops (fb_unrolled.hip);
+// plans ask for either form as MAP_BPL.
+enum Mapping { MAP_SPL = 1, MAP_BPL = 2, MAP_BPLU = 3 };
 
 constexpr int kMaxBodies = 16;         // kernels specialised per n exist for n <= 16
 constexpr int kMaxLargeBodies = 512;   // larger systems run the runtime-n large-n kernels
 constexpr int kMaxSplBodies = 10;      // plain system-per-lane instances exist for n <= 10
 constexpr int kMaxSplAdv = 8;          // ... with adaptive steps / stop rules for n <= 8
 constexpr int kMaxSplPersistent = 0;   // the body-per-lane fused class runs no system-per-lane tiles
+constexpr int kMaxUnrolled = 12;       // body per lane: 4..12 bodies always run unrolled
+constexpr int kMaxUnrolledAdv = 10;    // ... with adaptive steps / stop rules 4..10
 constexpr int kMaxMvsBodies = 8;       // MVS kernels (system per lane) exist for n <= 8
 
 // Device view of one homogeneous body-count bucket.  Per-slot arrays have
@@ -104,6 +108,10 @@ hipError_t launch_begin_run(const Bucket &B, int fixed_steps, long long n_steps,
                             hipStream_t s);
 hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group,
                         const StepParams &P, hipStream_t s);
+// Wavefronts launch_unrolled starts for bucket B, and the launch (launch_plain with
+// MAP_BPLU comes here).
+int unrolled_tiles(const Bucket &B);
+hipError_t launch_unrolled(const Bucket &B, const StepParams &P, hipStream_t s);
 // spl_class: 0 = body-per-lane class fused kernel (<= 128 VGPRs; system-per-
 // lane tiles for n <= kMaxSplPersistent), 1 = system-per-lane class (full
 // register file; system-per-lane tiles for n <= kMaxSplBodies, or

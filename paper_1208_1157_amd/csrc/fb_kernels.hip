@@ -427,7 +427,7 @@ void k_plain_bpl(Bucket B, StepParams P)
         return;
     const int count = min(S, B.count - first);
     int slot;
-    bpl_run<N, ADV, false>(B, first, count, nullptr, P, slot);
+    bpl_run<N, ADV, false, false>(B, first, count, nullptr, P, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -479,7 +479,8 @@ __device__ __noinline__ bool bpl_tile(const Bucket &B, const Tile &T, const int 
                                       const StepParams &P, int &slot)
 {
     const StepParams Pr = uniform_params(P);
-    return bpl_run<N, ADV, CLS>(B, T.first, T.count, list, Pr, slot);
+    // the full-register class keeps the partner tables of up to 8 bodies in registers
+    return bpl_run<N, ADV, CLS, CLS && N <= 8>(B, T.first, T.count, list, Pr, slot);
 }
 
 // Tile dispatch.  The body-per-lane class (SPLC false) keeps the fused
@@ -2378,6 +2379,8 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
 {
     if (B.count == 0)
         return hipSuccess;
+    if (mapping == MAP_BPLU)   // (bpl_mapping)
+        return launch_unrolled(B, P, s);
     const int W = waves_per_group < 1 ? 1 : (waves_per_group > 4 ? 4 : waves_per_group);
     const bool adv = P.adaptive || P.stop_rules;
     if (B.n > kMaxBodies) {
@@ -2438,10 +2441,22 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
     const int tiles = (B.count + S - 1) / S;
     const dim3 grid((unsigned)((tiles + W - 1) / W));
     const size_t lds = sizeof(BplLds) * W;
-#define FB_L(NN)                                                                           \
-    if (adv) hipLaunchKernelGGL((k_plain_bpl<NN, true>), grid, dim3(64 * W), lds, s, B, P);  \
-    else hipLaunchKernelGGL((k_plain_bpl<NN, false>), grid, dim3(64 * W), lds, s, B, P)
-    FB_SWITCH_N(B.n, FB_L)
+#define FB_L(NN, ADV) case NN: hipLaunchKernelGGL((k_plain_bpl<NN, ADV>), grid, dim3(64 * W), lds, s, B, P); break
+    if (adv) {
+        static_assert(kMaxUnrolledAdv == 10, "the body counts that launch_unrolled does not always serve");
+        switch (B.n) {
+            FB_L(2, true); FB_L(3, true); FB_L(11, true); FB_L(12, true); FB_L(13, true);
+            FB_L(14, true); FB_L(15, true); FB_L(16, true);
+        default: return hipErrorInvalidValue;
+        }
+    } else {
+        static_assert(kMaxUnrolled == 12, "the body counts that launch_unrolled does not always serve");
+        switch (B.n) {
+            FB_L(2, false); FB_L(3, false); FB_L(13, false); FB_L(14, false); FB_L(15, false);
+            FB_L(16, false);
+        default: return hipErrorInvalidValue;
+        }
+    }
 #undef FB_L
     return hipGetLastError();
 }

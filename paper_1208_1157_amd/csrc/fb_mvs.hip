@@ -275,60 +275,6 @@ __device__ __forceinline__ void mvs_kepler(const double mu, const Orbit (&o)[N],
         mvs_kepler<N, I + 1>(mu, o, h, Q, V, solved);
 }
 
-// Run control of fixed steps without a per-step clock.  Segment 0 is the
-// run's whole steps, segment 1 the shortened final step if one is due; the
-// number of steps of size h the system takes in the segment, at most
-// `budget` and P.max_steps allowing.
-__device__ __forceinline__ int mvs_segment(Clock &c, const StepParams &P, const int seg,
-                                           const int budget, double &h)
-{
-    if (c.status != ST_ACTIVE || budget <= 0)
-        return 0;
-    long long cnt = 0;
-    h = c.dt;
-    if (seg == 0) {
-        cnt = c.nfull - c.k;
-        cnt = cnt < 0 ? 0 : cnt;
-    } else {
-        const double rem = c.t_end - c.t;
-        if (rem * c.dt > 1e-9 * c.dt * c.dt) {
-            cnt = 1;
-            h = rem;
-        } else {
-            c.t = c.t_end;
-            c.status = ST_DONE;
-        }
-    }
-    cnt = min(cnt, (long long)budget);
-    cnt = min(cnt, P.max_steps - c.steps);
-    return cnt > 0 ? (int)cnt : 0;
-}
-
-// The clock after `done` steps of segment seg; `was_active`: the system
-// entered the segment active (its steps may have stopped it since).
-__device__ __forceinline__ void mvs_segment_end(Clock &c, const StepParams &P, const int seg,
-                                                const int done)
-{
-    c.steps += done;
-    if (seg == 0) {
-        c.k += done;
-        if (done > 0)
-            c.t = fma((double)c.k, c.dt, c.t0);
-        if (c.status == ST_ACTIVE && c.k >= c.nfull) {
-            const double rem = c.t_end - c.t;
-            if (!(rem * c.dt > 1e-9 * c.dt * c.dt)) {
-                c.t = c.t_end;
-                c.status = ST_DONE;
-            }
-        }
-    } else if (done > 0 && c.status == ST_ACTIVE) {
-        c.t = c.t_end;
-        c.status = ST_DONE;
-    }
-    if (c.status == ST_ACTIVE && c.steps >= P.max_steps)
-        c.status = ST_MAXSTEPS;
-}
-
 // Fixed-step MVS integration of one system per lane for at most P.quantum
 // steps (the clock logic of the Hermite kernels).  Pm holds the planets'
 // momentum at a step's start and end: the closing drift of a step and the
@@ -353,7 +299,7 @@ __device__ __forceinline__ void mvs_spl_run(const Bucket &B, const int slot, con
 #pragma unroll 1
     for (int seg = 0; seg < 2; ++seg) {
         double hs = c.dt;
-        const int nrun = mvs_segment(c, P, seg, budget, hs);
+        const int nrun = run_segment(c, P, seg, budget, hs);
         int done = 0;
         double h = nrun > 0 ? hs : 0.0;   // 0: stopped
         if (__any(h != 0.0))
@@ -391,7 +337,7 @@ __device__ __forceinline__ void mvs_spl_run(const Bucket &B, const int slot, con
             h = done < nrun ? h : 0.0;
         } while (__any(h != 0.0));
         budget -= done;
-        mvs_segment_end(c, P, seg, done);
+        run_segment_end(c, P, seg, done);
     }
     if (!mvs_finite<N>(Q, V))
         c.status = ST_NONFINITE;
@@ -478,7 +424,7 @@ __device__ __forceinline__ void mvs_bpl_run(const Bucket &B, const int first, co
 #pragma unroll 1
     for (int seg = 0; seg < 2; ++seg) {
         double h = c.dt;
-        const int nrun = mvs_segment(c, P, seg, budget, h);
+        const int nrun = run_segment(c, P, seg, budget, h);
         const double hh = 0.5 * h, kd = planet ? hh * inv_m0 : hh;
         int done = 0;
         bool run = nrun > 0;
@@ -581,7 +527,7 @@ __device__ __forceinline__ void mvs_bpl_run(const Bucket &B, const int first, co
             }
         } while (__any(run));
         budget -= done;
-        mvs_segment_end(c, P, seg, done);
+        run_segment_end(c, P, seg, done);
     }
     const int bad = sys_or_flags<N>(s, (valid && !(finite3(Q) && finite3(W))) ? 1 : 0);
     if (!valid || !entered)

@@ -1505,7 +1505,7 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
             for (int W : {1, 2, 4}) {
                 if (B.n <= kMaxSplBodies)
                     cands.push_back({MAP_SPL, W});
-                cands.push_back({MAP_BPL, W});
+                cands.push_back({bpl_mapping(B, false, e->num_cu), W});
             }
             double best = 1e300;
             size_t best_i = 0;

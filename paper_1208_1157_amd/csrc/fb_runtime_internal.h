@@ -32,6 +32,22 @@ struct Plan {
 };
 Plan get_plan(int n);
 
+// Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the
+// unrolled kernels (fb_unrolled.hip, where both sides are measured) for 4..12
+// bodies (4..10 with adaptive steps or stop rules); for other body counts
+// while their wavefronts are few: 2 and 3 bodies to one per SIMD (the quad
+// layout holds 16 systems a wavefront, the rolled one 32 and 21), 13..16 to
+// four (beyond, loops that do not fit the instruction cache well lose), 11..16
+// with adaptive steps or stop rules to one (their registers leave one wave).
+inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
+{
+    if (B.n > kMaxBodies)
+        return MAP_BPL;
+    const bool always = B.n >= 4 && B.n <= (adv ? kMaxUnrolledAdv : kMaxUnrolled);
+    const int waves_per_simd = B.n >= 13 && !adv ? 4 : 1;
+    return always || unrolled_tiles(B) <= 4LL * num_cu * waves_per_simd ? MAP_BPLU : MAP_BPL;
+}
+
 // Lane mapping of a plain launch over bucket B: the plan's, or (auto)
 // system-per-lane when n allows it and the bucket's 64-system tiles give
 // every SIMD of the device a wavefront, else body-per-lane, whose n lanes
@@ -40,10 +56,10 @@ inline int plain_mapping(const Plan &p, const Bucket &B, bool adv, int num_cu)
 {
     const int lim = adv ? kMaxSplAdv : kMaxSplBodies;
     if (p.mapping == MAP_BPL || B.n > lim)
-        return MAP_BPL;
+        return bpl_mapping(B, adv, num_cu);
     if (p.mapping == MAP_SPL)
         return MAP_SPL;
-    return (B.count + 63) / 64 >= 4LL * num_cu ? MAP_SPL : MAP_BPL;
+    return (B.count + 63) / 64 >= 4LL * num_cu ? MAP_SPL : bpl_mapping(B, adv, num_cu);
 }
 
 // Fused persistent kernel class for a launch over buckets of these body
