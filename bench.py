@@ -243,8 +243,8 @@ def lifetimes_extras(fb, gen, torch, log, orbits=100.0, quantum=2000):
     23 s persistent and 83 s plain).  Plain: one launch per bucket, retired
     lanes idle until their wave's last system ends; persistent: quanta with
     in-kernel compaction of retired systems, the fused-kernel class chosen
-    automatically (body-per-lane, then the tail mode once the survivors'
-    waves no longer fill the device); and, for comparison, the body-per-lane
+    automatically (body-per-lane; the tiles run to their ends once each has a
+    SIMD of its own); and, for comparison, the body-per-lane
     class throughout."""
     import numpy as np
     ens, p = gen.workload("lifetimes_65536x4-8")

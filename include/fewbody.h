@@ -372,7 +372,7 @@ fb_status fb_hermite_steps_device_noalloc(int32_t n_sys, int32_t n, const double
  * the device a wavefront, and body-per-lane otherwise.  Entry n = 0 is the
  * fused persistent launch: its mapping selects the kernel class
  * (FB_MAP_SYSTEM_PER_LANE: full register file, system-per-lane tiles where n
- * allows; FB_MAP_BODY_PER_LANE: <= 128 VGPRs, body-per-lane tiles only;
+ * allows; FB_MAP_BODY_PER_LANE: 256 VGPRs, body-per-lane tiles only;
  * FB_MAP_AUTO: the former when every bucket allows it and its tiles give
  * every SIMD a wavefront), plus waves per workgroup and workgroups per CU
  * (1..32, 0 = default).  In the system-per-lane class a body count whose own

@@ -138,6 +138,8 @@ __device__ __forceinline__ int bpl_stop_flags(BplLds &L, const int lane, const i
 {
     constexpr int S = 64 / N;
     int fl = (finite3(x) && finite3(v)) ? 0 : 1;
+    if (!P.stop_rules)
+        return __any(fl) ? sys_or_flags<N>(s, fl) : 0;
     L.xy[lane] = make_double2(x[0], x[1]);
     L.zvx[lane] = make_double2(x[2], 0.0);
     wave_sync();
@@ -228,6 +230,10 @@ __device__ __forceinline__ int bpl_stop_flags_regs(BplLds &L, const int lane, co
                                                    double &wsys, const StepParams &P)
 {
     int fl = (finite3(x) && finite3(v)) ? 0 : 1;
+    if (!P.stop_rules) {
+        wsys = P.adaptive == 1 ? sys_max<N>(L, lane, s, w) : w;
+        return __any(fl) ? sys_or_flags<N>(s, fl) : 0;
+    }
     L.xy[lane] = make_double2(x[0], x[1]);
     L.zvx[lane] = make_double2(x[2], w);
     wave_sync();

@@ -112,7 +112,7 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group,
 // MAP_BPLU comes here).
 int unrolled_tiles(const Bucket &B);
 hipError_t launch_unrolled(const Bucket &B, const StepParams &P, hipStream_t s);
-// spl_class: 0 = body-per-lane class fused kernel (<= 128 VGPRs; system-per-
+// spl_class: 0 = body-per-lane class fused kernel (256 VGPRs; system-per-
 // lane tiles for n <= kMaxSplPersistent), 1 = system-per-lane class (full
 // register file; system-per-lane tiles for n <= kMaxSplBodies, or
 // kMaxSplAdv with adaptive steps / stop rules).

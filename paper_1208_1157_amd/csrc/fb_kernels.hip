@@ -34,9 +34,9 @@
 #ifndef FB_SPL_PAIR_GROUP
 #define FB_SPL_PAIR_GROUP 2
 #endif
-// Waves per SIMD the register allocator targets for the body-per-lane and
-// persistent kernels: 3 (168 VGPRs) leaves the adaptive variants unspilled and
-// measured faster than 4 (128 VGPRs, with spills) in fixed and adaptive runs.
+// Waves per SIMD the register allocator targets for the rolled body-per-lane
+// kernels: 3 (168 VGPRs) leaves the adaptive variants unspilled and measured
+// faster than 4 (128 VGPRs, with spills) in fixed and adaptive runs.
 #ifndef FB_BPL_WAVES
 #define FB_BPL_WAVES 3
 #endif
@@ -479,15 +479,25 @@ __device__ __noinline__ bool bpl_tile(const Bucket &B, const Tile &T, const int 
                                       const StepParams &P, int &slot)
 {
     const StepParams Pr = uniform_params(P);
-    // the full-register class keeps the partner tables of up to 8 bodies in registers
-    return bpl_run<N, ADV, CLS, CLS && N <= 8>(B, T.first, T.count, list, Pr, slot);
+    constexpr bool kRegs = N <= (ADV ? kMaxUnrolledAdv : kMaxUnrolled);
+    return bpl_run<N, ADV, CLS, kRegs>(B, T.first, T.count, list, Pr, slot);
 }
 
 // Tile dispatch.  The body-per-lane class (SPLC false) keeps the fused
-// kernel at <= 168 VGPRs (3 waves per SIMD) and runs every tile body-per-
-// lane; the system-per-lane class gives the kernel the full register file
-// (1 wave per SIMD) and runs system-per-lane tiles up to n = 10 (n = 8 with
+// kernel at 256 VGPRs (2 waves per SIMD) and runs every tile body-per-lane,
+// partner loops unrolled up to 12 bodies (10 with adaptive steps / stop
+// rules); the system-per-lane class gives the kernel the full register file (1
+// wave per SIMD) and runs system-per-lane tiles up to n = 10 (n = 8 with
 // adaptive steps / stop rules), body-per-lane beyond.
+// The body-per-lane class had rolled loops for every n and 3 waves per SIMD
+// (168 VGPRs), and a thinned population moved to the other class, one wave per
+// SIMD with the loops of up to 8 bodies unrolled.  Two waves serve both: a
+// wave alone on its SIMD runs as fast, and of two waves each takes 1.5 times
+// as long, not twice.  Best of 3, rolled and unrolled: 65536 systems of 3..15
+// bodies, 500 fixed steps 8.87 and 8.40 ms; 65536 of 4..8 bodies, adaptive
+// with stop rules, 10 orbits 78.4 and 72.6 ms; 16384 of them, 3 orbits, 11.4
+// and 10.6 ms; 24 requests to a server (a few hundred wavefronts) 22.4 and
+// 13.9 ms of kernels.
 template <bool ADV, bool SPLC>
 __device__ __forceinline__ bool run_tile(const Bucket &B, const Tile &T, const int *list,
                                          const StepParams &P, int &slot)
@@ -563,7 +573,7 @@ __device__ __forceinline__ void persistent_body(const Bucket *__restrict__ bucke
 }
 
 template <bool ADV, bool COMPACT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FB_BPL_WAVES)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_persistent(const Bucket *__restrict__ buckets, const Tile *__restrict__ tiles,
                   const int *__restrict__ ntiles_p, int *__restrict__ head, const int *lists,
                   StepParams P, ActiveLists AL)

@@ -408,14 +408,6 @@ fb_status count_active(fb_ensemble *e, int &out)
     return FB_OK;
 }
 
-// Waves per SIMD below which the survivors of a compacted persistent run
-// (automatic class) move to the full-register kernel class with body-per-
-// lane tiles and unrolled partner loops: one wave per SIMD, more work in
-// flight per wave.
-#ifndef FB_TAIL_WAVES_PER_SIMD
-#define FB_TAIL_WAVES_PER_SIMD 2
-#endif
-
 // Plain schedule: one launch per bucket (one per quantum if quanta are set).
 fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound)
 {
@@ -491,11 +483,9 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
                           e->stream));
     std::vector<int> mapping(nbk, MAP_BPL);
     int grid = 1;
-    // Per-bucket mappings and grid of fused-kernel class c; all_bpl runs
-    // every tile body-per-lane (in the system-per-lane class: one wave per
-    // SIMD with the full register file, partner loops unrolled).
-    auto set_class = [&](int c, bool all_bpl) -> hipError_t {
-        const int spl_lim = all_bpl ? 0 : persistent_spl_limit(c, adv ? 1 : 0);
+    // Per-bucket mappings and grid of fused-kernel class c.
+    auto set_class = [&](int c) -> hipError_t {
+        const int spl_lim = persistent_spl_limit(c, adv ? 1 : 0);
         for (int i = n_large; i < nbk; ++i) {
             const int n = e->buckets[i].n;
             const int m = get_plan(n).mapping;
@@ -516,8 +506,7 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
             err = hipStreamSynchronize(e->stream);
         return err;
     };
-    FB_HIP(set_class(cls, false));   // also waits for the copies above (host vectors die at return)
-    bool tail_mode = false;
+    FB_HIP(set_class(cls));   // also waits for the copies above (host vectors die at return)
 
     ActiveLists AL[2];
     for (int k = 0; k < 2; ++k) {
@@ -643,38 +632,23 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         // As survivors thin out (automatic class only): the system-per-lane
         // class runs one wavefront per SIMD, so once the survivors' 64-system
         // tiles no longer give every SIMD one, the body-per-lane class (a
-        // system over n lanes) keeps more of the device busy; once even its
-        // waves no longer give every SIMD two, each wave may as well have
-        // its SIMD's whole register file, and the full-register kernel runs
-        // the body-per-lane tiles with their partner loops unrolled (more
-        // independent work in flight per wave).  All these compute bitwise
-        // the same states, so the switches are invisible in the results.
+        // system over n lanes) keeps more of the device busy.  Both compute
+        // bitwise the same states, so the switch is invisible in the results.
         bool recapture = false;
-        if (compact && p0.mapping == 0 && !tail_mode) {
-            int to = -1;
-            bool all_bpl = false;
-            if (bpl_waves < (long long)FB_TAIL_WAVES_PER_SIMD * 4 * e->num_cu) {
-                to = 1;
-                all_bpl = true;
-            } else if (cls == 1 && spl_tiles < 4LL * e->num_cu) {
-                to = 0;
+        if (compact && p0.mapping == 0 && cls == 1 && spl_tiles < 4LL * e->num_cu) {
+            hipError_t err = set_class(0);
+            if (err != hipSuccess) {
+                result = hip_fail(err, "class switch");
+                break;
             }
-            if (to >= 0) {
-                hipError_t err = set_class(to, all_bpl);
-                if (err != hipSuccess) {
-                    result = hip_fail(err, "class switch");
-                    break;
-                }
-                tail_mode = all_bpl;
-                recapture = true;
-            }
+            recapture = true;
         }
-        // Once every surviving tile has a wave of its own, compaction has
+        // Once every surviving tile has a SIMD of its own, compaction has
         // nothing left to gain and a quantum boundary only makes each tile
         // wait for the slowest one (8-body tiles take about 1.7x as long per
         // step as 4-body ones, and the tiles' step counts differ), so the
         // tiles run on to their ends in one launch.
-        if (tail_mode && P.quantum == quantum && bpl_waves <= (long long)grid * W) {
+        if (compact && cls == 0 && p0.mapping == 0 && P.quantum == quantum && bpl_waves <= 4LL * e->num_cu) {
             P.quantum = INT_MAX / 2;
             recapture = true;
         }
