@@ -29,6 +29,7 @@ constexpr int kMaxSplAdv = 8;          // ... with adaptive steps / stop rules f
 constexpr int kMaxSplPersistent = 0;   // the body-per-lane fused class runs no system-per-lane tiles
 constexpr int kMaxUnrolled = 12;       // body per lane: 4..12 bodies always run unrolled
 constexpr int kMaxUnrolledAdv = 10;    // ... with adaptive steps / stop rules 4..10
+constexpr int kMaxRkckSpl = 6;         // fixed Cash-Karp steps system per lane exist for n <= 6
 constexpr int kMaxMvsBodies = 8;       // MVS kernels (system per lane) exist for n <= 8
 
 // Device view of one homogeneous body-count bucket.  Per-slot arrays have
@@ -96,7 +97,7 @@ inline int tile_systems(int mapping, int n) {
     return mapping == MAP_SPL ? spl_tile_systems() : bpl_tile_systems(n);
 }
 
-// ---- launchers (fb_kernels.hip; the MVS steps in fb_mvs.hip) --------------
+// ---- launchers (fb_kernels.hip; steps of MVS and Cash-Karp in their own) --
 // pad_tail: also initialise slots count..pitch-1 as inert padding (a whole
 // bucket); false for a view of a bucket shared with other owners.
 hipError_t launch_pack(const Bucket &B, const double *mass, const double *pos,
@@ -137,10 +138,13 @@ hipError_t launch_diag(const Bucket &B, double *energy, double *angmom, bool mvs
 // layout fb_log_bytes describes.
 hipError_t launch_log(const Bucket &B, const long long *orig_off, int kind, const double *los,
                       int k, int max_records, double *out, hipStream_t s);
-// Runge-Kutta Cash-Karp (body per lane, any n): fixed steps (eps == 0) or
-// adaptive steps with error tolerance eps (P.adaptive nonzero).
-hipError_t launch_plain_rkck(const Bucket &B, int waves_per_group, const StepParams &P,
-                             double eps, hipStream_t s);
+// Runge-Kutta Cash-Karp: fixed steps (eps == 0), or adaptive steps with error
+// tolerance eps (P.adaptive nonzero); system per lane for fixed steps (n <=
+// kMaxRkckSpl), one body per lane of a wavefront (every bucket of a set, n <=
+// kMaxBodies, in one launch; same results), or of a workgroup (larger n).
+hipError_t launch_rkck_spl(const Bucket &B, const StepParams &P, hipStream_t s);
+hipError_t launch_rkck_bpl(const BucketSet &set, const StepParams &P, double eps, hipStream_t s);
+hipError_t launch_rkck_large(const Bucket &B, const StepParams &P, double eps, hipStream_t s);
 // Mixed-variable symplectic integrator (n <= kMaxMvsBodies, system per
 // lane): conversion of a bucket to and from MVS form, fixed-step quanta, and
 // read-back of a bucket in MVS form as inertial positions and velocities.

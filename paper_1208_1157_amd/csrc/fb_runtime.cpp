@@ -685,17 +685,47 @@ fb_status ensure_xv(fb_ensemble *e)
     return FB_OK;
 }
 
-// Runge-Kutta quanta: one body-per-lane launch per bucket and quantum.
+// Whether fixed Cash-Karp steps of bucket B run system per lane: the plan's
+// mapping, or (auto) from the size on where its time, that of one wavefront
+// per SIMD, is below the body-per-lane tiles'.  Measured, 300 steps, system
+// per lane against body per lane: n = 3 438 us at any size up to one wavefront
+// per SIMD against 436 at 20000 systems; n = 4 739 against 765 at 20000; n = 5
+// 1339 against 1375 at 30000; n = 6 1976 against 1662 at 30000 and 3670 at
+// 65600.  So from 3/10 of the SIMDs with a wavefront on, or 6/10 for 5 and 6
+// bodies.
+bool rkck_spl(const Plan &p, const Bucket &B, int num_cu)
+{
+    if (B.n > kMaxRkckSpl || p.mapping == MAP_BPL)
+        return false;
+    return p.mapping == MAP_SPL || (B.count + 63) / 64 * 10LL >= (B.n <= 4 ? 3 : 6) * 4LL * num_cu;
+}
+
+// Runge-Kutta quanta: fixed steps of large buckets run system per lane; the
+// other buckets of up to kMaxBodies bodies share one body-per-lane launch,
+// larger ones run a workgroup launch each.
 fb_status run_rkck(fb_ensemble *e, const fb_opts &o, int adaptive, double eps,
                    long long step_bound)
 {
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
+    StepParams P = make_params(o, quantum);
+    P.adaptive = adaptive;
     for (;;) {
+        BucketSet set;
+        set.clear();
         for (const Bucket &B : e->buckets) {
-            StepParams P = make_params(o, quantum);
-            P.adaptive = adaptive;
+            if (B.n > kMaxBodies) {
+                ProfScope ps(e->stream);
+                FB_HIP(launch_rkck_large(B, P, eps, e->stream));
+            } else if (!adaptive && rkck_spl(get_plan(B.n), B, e->num_cu)) {
+                ProfScope ps(e->stream);
+                FB_HIP(launch_rkck_spl(B, P, e->stream));
+            } else {
+                set.add(B);
+            }
+        }
+        if (set.count) {
             ProfScope ps(e->stream);
-            FB_HIP(launch_plain_rkck(B, 2, P, eps, e->stream));
+            FB_HIP(launch_rkck_bpl(set, P, eps, e->stream));
         }
         if (quantum == INT_MAX)
             return FB_OK;
