@@ -166,8 +166,8 @@ hipError_t launch_count_active(const Bucket &B, int *count, hipStream_t s);
 // systems of H = ceil(n / k) lanes each; the T that leaves the fewest lanes
 // idle.  S = 0 if the system does not fit.
 void large_shape(int n, int k, int &T, int &S);
-// Bodies per lane (1 or 2) of the large-n step kernel for n-body systems.
-int large_bodies_per_lane(int n);
+// Hermite steps of a bucket of more than kMaxBodies bodies (fb_large.hip).
+hipError_t launch_large(const Bucket &B, const StepParams &P, int num_cu, hipStream_t s);
 // FP64 FMA issue-ceiling probe: blocks x 256 lanes, iters x kFmaChains FMAs
 // per lane (kFmaChains = 16); out holds blocks x 256 doubles.
 hipError_t launch_fma_probe(double *out, int blocks, int iters, hipStream_t s);

@@ -1156,344 +1156,6 @@ __device__ __forceinline__ void large_eval(const LargeView &V, const int T, cons
     large_interact(xy, zvx, vyvz, V.m, base + (b == 0 ? n - 1 : 0), xi, vi, a, jk);
 }
 
-// Evaluation state of one body in the step kernel's LDS (48 bytes, so a
-// partner is three ds_read_b128 at immediate offsets from one address).
-struct LargeBody {
-    double2 xy, zvx, vyvz;
-};
-
-// The step kernel's view of its dynamic LDS (E bodies): two copies of the
-// bodies' evaluation state, the masses and one int per body; the same bytes
-// as large_lds_bytes(E).
-struct LargeStepView {
-    LargeBody *st;   // copy c of body entry e at [c * E + e]
-    double *m;
-    double *red;
-    int *flag;
-};
-
-__device__ __forceinline__ LargeStepView large_step_view(const int E)
-{
-    extern __shared__ char fb_dyn_lds[];
-    LargeStepView V;
-    V.st = reinterpret_cast<LargeBody *>(fb_dyn_lds);
-    V.m = reinterpret_cast<double *>(V.st + 2 * E);
-    V.red = V.m + E;
-    V.flag = reinterpret_cast<int *>(V.red + E);
-    return V;
-}
-static_assert(2 * sizeof(LargeBody) + 2 * sizeof(double) + sizeof(int) ==
-                  6 * sizeof(double2) + 2 * sizeof(double) + sizeof(int),
-              "step-kernel LDS view must match large_lds_bytes");
-
-// One interaction of body i with a partner (Eq. 1 and its time derivative,
-// the terms of bpl_interact).  With TS, also the pair's step-rule quantity
-// (|u|^2 + 3 (r.u)^2/|r|^2) / |r|^2 into wmax (zero for the self term).
-template <bool TS>
-__device__ __forceinline__ void large_interact_p(const LargeBody &p, const double mj,
-                                                 const double (&xi)[3], const double (&vi)[3],
-                                                 double (&a)[3], double (&jk)[3], double &wmax)
-{
-    const double rx = p.xy.x - xi[0], ry = p.xy.y - xi[1], rz = p.zvx.x - xi[2];
-    const double ux = p.zvx.y - vi[0], uy = p.vyvz.x - vi[1], uz = p.vyvz.y - vi[2];
-    const double r2 = fmax(fma(rz, rz, fma(ry, ry, rx * rx)), kLargeMinR2);
-    const double ru = fma(rz, uz, fma(ry, uy, rx * ux));
-    const double ri = rsqrt_nr(r2);
-    const double ri2 = ri * ri;
-    const double mr3 = mj * (ri2 * ri);
-    const double al = 3.0 * ru * ri2;
-    a[0] = fma(mr3, rx, a[0]);
-    a[1] = fma(mr3, ry, a[1]);
-    a[2] = fma(mr3, rz, a[2]);
-    jk[0] = fma(mr3, fma(-al, rx, ux), jk[0]);
-    jk[1] = fma(mr3, fma(-al, ry, uy), jk[1]);
-    jk[2] = fma(mr3, fma(-al, rz, uz), jk[2]);
-    if (TS) {
-        const double u2 = fma(uz, uz, fma(uy, uy, ux * ux));
-        wmax = fmax(wmax, fma(al, ru, u2) * ri2);
-    }
-}
-
-// Waves per SIMD the register allocator targets for the large-n step kernel.
-#ifndef FB_LARGE_WAVES
-#define FB_LARGE_WAVES 2
-#endif
-
-// The evaluation of the K-body step kernel: publish this lane's bodies in
-// copy `cp` (entry system base + body), wait for the workgroup, then sum
-// each owned body's interactions: planets 1..n-1 in ascending order (its own
-// index contributing zeros), then the star.
-template <int K, bool TS>
-__device__ __forceinline__ void large_eval_k(const LargeStepView &V, const int E, const int cp,
-                                             const int base, const int n, const bool live,
-                                             const int (&bk)[K], const bool (&own)[K],
-                                             const double (&xi)[K][3], const double (&vi)[K][3],
-                                             double (&a)[K][3], double (&jk)[K][3],
-                                             double (&w)[K])
-{
-    LargeBody *st = V.st + cp * E + base;
-    const double *mm = V.m + base;
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (own[k]) {
-            LargeBody &q = st[bk[k]];
-            q.xy = make_double2(xi[k][0], xi[k][1]);
-            q.zvx = make_double2(xi[k][2], vi[k][0]);
-            q.vyvz = make_double2(vi[k][1], vi[k][2]);
-        }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        w[k] = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            a[k][c] = 0.0;
-            jk[k][c] = 0.0;
-        }
-    }
-    if (!live)
-        return;
-#pragma unroll 2
-    for (int j = 1; j < n; ++j) {
-        const LargeBody p = st[j];
-        const double mj = mm[j];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            large_interact_p<TS>(p, mj, xi[k], vi[k], a[k], jk[k], w[k]);
-    }
-    const LargeBody p = st[0];
-    const double m0 = mm[0];
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        large_interact_p<TS>(p, m0, xi[k], vi[k], a[k], jk[k], w[k]);
-}
-
-// Per-system reduction of one value per owned body, in body order (max, or
-// sum); every valid lane gets its system's result.  Two barriers.
-template <int K, bool MAXOP>
-__device__ __forceinline__ double large_sys_reduce(double *red, const int base, const int n,
-                                                   const bool valid, const int (&bk)[K],
-                                                   const bool (&own)[K], const double (&val)[K])
-{
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (own[k])
-            red[base + bk[k]] = val[k];
-    __syncthreads();
-    double r = 0.0;
-    if (valid) {
-        r = red[base];
-        for (int b = 1; b < n; ++b)
-            r = MAXOP ? fmax(r, red[base + b]) : r + red[base + b];
-    }
-    __syncthreads();
-    return r;
-}
-
-// Stop-rule flags of each system after a committed step (the bits of
-// bpl_stop_flags: 1 non-finite, 2 two planets within one mutual Hill radius,
-// 4 a planet beyond r_eject), OR-ed over the system; positions go through
-// copy 0 of the evaluation state, free until the next step's first
-// evaluation.
-template <int K>
-__device__ __forceinline__ int large_stop_flags(const LargeStepView &V, const int base,
-                                                const int n, const bool valid, const int (&bk)[K],
-                                                const bool (&own)[K], const double (&x)[K][3],
-                                                const double (&v)[K][3], const StepParams &P)
-{
-    int fl = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (own[k]) {
-            fl |= (finite3(x[k]) && finite3(v[k])) ? 0 : 1;
-            V.st[base + bk[k]].xy = make_double2(x[k][0], x[k][1]);
-            V.st[base + bk[k]].zvx.x = x[k][2];
-        }
-    __syncthreads();
-    double rb[K];
-    if (valid) {
-        const LargeBody s0 = V.st[base];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const double dx = x[k][0] - s0.xy.x, dy = x[k][1] - s0.xy.y, dz = x[k][2] - s0.zvx.x;
-            rb[k] = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
-            if (own[k])
-                V.red[base + bk[k]] = rb[k];
-        }
-    }
-    __syncthreads();
-    if (valid) {
-        const double inv24m0 = 1.0 / (24.0 * V.m[base]);
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (!own[k] || bk[k] == 0)
-                continue;
-            if ((P.stop_rules & 2) && rb[k] > P.r_eject)
-                fl |= 4;
-            if (P.stop_rules & 1) {
-                const double mi = V.m[base + bk[k]];
-                for (int j = 1; j < n; ++j) {
-                    if (j == bk[k])
-                        continue;
-                    const LargeBody q = V.st[base + j];
-                    const double ex = x[k][0] - q.xy.x, ey = x[k][1] - q.xy.y, ez = x[k][2] - q.zvx.x;
-                    const double sep2 = fma(ez, ez, fma(ey, ey, ex * ex));
-                    if (hill_close(sep2, mi, V.m[base + j], inv24m0, rb[k], V.red[base + j]))
-                        fl |= 2;
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (own[k])
-                V.flag[base + bk[k]] = k == 0 ? fl : 0;
-    }
-    __syncthreads();
-    int r = 0;
-    if (valid)
-        for (int b = 0; b < n; ++b)
-            r |= V.flag[base + b];
-    __syncthreads();
-    return r;
-}
-
-// Fixed Hermite P(EC)^2 steps (Algorithm 1's loop, Algorithm 2's step) for
-// at most P.quantum steps.  Lane h of a system owns bodies h, h + H, ...,
-// h + (K-1) H with H = ceil(n / K); S = floor(T / H) systems per workgroup
-// of T lanes.  The LDS arrays hold K T bodies, system s's at s n + body.
-// Every lane commits every iteration (so the pre-step state need not stay
-// live through the evaluations); a system's state is written back as soon
-// as it stops stepping, and its registers are ignored after that.
-template <int K, bool ADV>
-__global__ __launch_bounds__(kLargeMaxLanes / K) __attribute__((amdgpu_waves_per_eu(FB_LARGE_WAVES)))
-void k_plain_large(Bucket B, StepParams P, int S)
-{
-    const int T = blockDim.x, n = B.n, H = (n + K - 1) / K, E = K * T;
-    const LargeStepView V = large_step_view(E);
-    const int tid = threadIdx.x;
-    const int sys = tid / H, h = tid - sys * H;
-    const int slot0 = blockIdx.x * S + sys;
-    const bool valid = sys < S && slot0 < B.count;
-    const int slot = valid ? slot0 : 0;
-    const int base = sys * n;
-    const size_t pitch = B.pitch;
-    int bk[K];
-    bool own[K];
-    double x[K][3], v[K][3], a0[K][3], j0[K][3];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        bk[k] = h + k * H;
-        own[k] = valid && bk[k] < n;
-        const int b = own[k] ? bk[k] : 0;
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-            x[k][cc] = v[k][cc] = a0[k][cc] = j0[k][cc] = 0.0;
-            if (own[k]) {
-                x[k][cc] = B.st[((R_X + cc) * n + b) * pitch + slot];
-                v[k][cc] = B.st[((R_V + cc) * n + b) * pitch + slot];
-                a0[k][cc] = B.st[((R_A + cc) * n + b) * pitch + slot];
-                j0[k][cc] = B.st[((R_J + cc) * n + b) * pitch + slot];
-            }
-        }
-        if (own[k])   // ordered before any read by the loop's first barrier
-            V.m[base + b] = B.st[(R_M * n + b) * pitch + slot];
-    }
-    Clock c;
-    c.status = ST_DONE;
-    if (valid)
-        c = load_clock(B, slot);
-    bool pending = false;   // registers hold committed steps not yet written back
-    int bad = 0;            // non-finite state written back
-    auto write_back = [&]() {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (!own[k])
-                continue;
-            const int b = bk[k];
-            bad |= (finite3(x[k]) && finite3(v[k])) ? 0 : 1;
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                B.st[((R_X + cc) * n + b) * pitch + slot] = x[k][cc];
-                B.st[((R_V + cc) * n + b) * pitch + slot] = v[k][cc];
-                B.st[((R_A + cc) * n + b) * pitch + slot] = a0[k][cc];
-                B.st[((R_J + cc) * n + b) * pitch + slot] = j0[k][cc];
-            }
-        }
-        pending = false;
-    };
-    for (int q = 0; q < P.quantum; ++q) {
-        double hs = 0.0;
-        bool last = false;
-        const bool act = valid && plan_step(c, P, hs, last);
-        if (pending && !act)
-            write_back();
-        if (!__syncthreads_or(act))
-            break;
-        const Coef cf = make_coef(hs);
-        double xc[K][3], vc[K][3], bx[K][3], bv[K][3], ak[K][3], jk[K][3];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc)
-                predict_comp(cf, x[k][cc], v[k][cc], a0[k][cc], j0[k][cc], xc[k][cc], vc[k][cc],
-                             bx[k][cc], bv[k][cc]);
-        double w[K];
-        large_eval_k<K, false>(V, E, 0, base, n, act, bk, own, xc, vc, ak, jk, w);
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc)
-                correct_comp(cf, bx[k][cc], bv[k][cc], ak[k][cc], jk[k][cc], xc[k][cc], vc[k][cc]);
-        large_eval_k<K, ADV>(V, E, 1, base, n, act, bk, own, xc, vc, ak, jk, w);
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                correct_comp(cf, bx[k][cc], bv[k][cc], ak[k][cc], jk[k][cc], x[k][cc], v[k][cc]);
-                a0[k][cc] = ak[k][cc];
-                j0[k][cc] = jk[k][cc];
-            }
-        double dtp = 0.0;
-        if (ADV && P.adaptive == 1)   // the pairwise rule: max over the system's pairs
-            dtp = P.eta * rsqrt_nr(large_sys_reduce<K, true>(V.red, base, n, valid, bk, own, w));
-        if (ADV && P.adaptive == 2) { // Eq. 5: sum over the system's bodies
-            double q[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const double aa = fma(ak[k][2], ak[k][2], fma(ak[k][1], ak[k][1], ak[k][0] * ak[k][0]));
-                const double jj = fma(jk[k][2], jk[k][2], fma(jk[k][1], jk[k][1], jk[k][0] * jk[k][0]));
-                q[k] = jj / aa;
-            }
-            dtp = P.eta * rsqrt_nr(large_sys_reduce<K, false>(V.red, base, n, valid, bk, own, q));
-        }
-        if (act) {
-            finish_step(c, P, last, hs, dtp);
-            pending = true;
-        }
-        if (ADV) {
-            const int fl = large_stop_flags<K>(V, base, n, valid, bk, own, x, v, P);
-            if (act && fl)
-                c.status = status_of_flags(fl);
-        }
-    }
-    if (pending)
-        write_back();
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (own[k])
-            V.flag[base + bk[k]] = bad;
-    __syncthreads();
-    if (valid && h == 0) {   // the lane of the star
-        int fl = 0;
-        if (!ADV)            // (with ADV the stop flags checked every step)
-            for (int b = 0; b < n; ++b)
-                fl |= V.flag[base + b];
-        if (fl)
-            c.status = ST_NONFINITE;
-        store_clock(B, slot, c);
-    }
-}
-
 // Algorithm 1's "prepare" for large n: (a0, j0) at the current state.
 __global__ __launch_bounds__(kLargeMaxLanes) void k_prepare_large(Bucket B, int S)
 {
@@ -1984,23 +1646,6 @@ void large_shape(int n, int k, int &T, int &S)
     }
 }
 
-int large_bodies_per_lane(int n)
-{
-    // Two bodies per lane halve the LDS reads per interaction; one is kept
-    // where pairing would idle clearly more body slots (odd n with few
-    // systems per workgroup).
-    int T1, S1, T2, S2;
-    large_shape(n, 1, T1, S1);
-    large_shape(n, 2, T2, S2);
-    if (S2 < 1)
-        return 1;
-    if (S1 < 1)
-        return 2;
-    const double use1 = (double)S1 * n / T1, use2 = (double)S2 * n / (2.0 * T2);
-    return use2 >= use1 - 0.02 ? 2 : 1;
-}
-
-
 hipError_t launch_prepare(const Bucket &B, hipStream_t s)
 {
     if (B.count == 0)
@@ -2050,23 +1695,6 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
         return launch_unrolled(B, P, s);
     const int W = waves_per_group < 1 ? 1 : (waves_per_group > 4 ? 4 : waves_per_group);
     const bool adv = P.adaptive || P.stop_rules;
-    if (B.n > kMaxBodies) {
-        dim3 grid;
-        int T, S;
-        const int K = large_bodies_per_lane(B.n);
-        if (!large_launch(B, K, grid, T, S))
-            return hipErrorInvalidValue;
-        const size_t lds = large_lds_bytes(K * T);
-        if (K == 2 && adv)
-            hipLaunchKernelGGL((k_plain_large<2, true>), grid, dim3(T), lds, s, B, P, S);
-        else if (K == 2)
-            hipLaunchKernelGGL((k_plain_large<2, false>), grid, dim3(T), lds, s, B, P, S);
-        else if (adv)
-            hipLaunchKernelGGL((k_plain_large<1, true>), grid, dim3(T), lds, s, B, P, S);
-        else
-            hipLaunchKernelGGL((k_plain_large<1, false>), grid, dim3(T), lds, s, B, P, S);
-        return hipGetLastError();
-    }
     if (mapping == MAP_SPL && B.n <= (adv ? kMaxSplAdv : kMaxSplBodies)) {
         const dim3 grid = grid_for(B.count, 64 * W);
 #define FB_LA(NN)                                                                       \

@@ -414,10 +414,14 @@ fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound)
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
     for (;;) {
         for (const Bucket &B : e->buckets) {
-            const Plan p = B.n <= kMaxBodies ? get_plan(B.n) : Plan{MAP_BPL, 1, 0};
             const StepParams P = make_params(o, quantum);
-            const int map = plain_mapping(p, B, P.adaptive || P.stop_rules, e->num_cu);
             ProfScope ps(e->stream);
+            if (B.n > kMaxBodies) {
+                FB_HIP(launch_large(B, P, e->num_cu, e->stream));
+                continue;
+            }
+            const Plan p = get_plan(B.n);
+            const int map = plain_mapping(p, B, P.adaptive || P.stop_rules, e->num_cu);
             FB_HIP(launch_plain(B, map, p.waves_per_group, P, e->stream));
         }
         if (quantum == INT_MAX)
@@ -525,7 +529,7 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         if (!compact)
             k = 0;
         for (int i = 0; i < n_large; ++i) {
-            const hipError_t err = launch_plain(e->buckets[i], MAP_BPL, 1, P, s);
+            const hipError_t err = launch_large(e->buckets[i], P, e->num_cu, s);
             if (err != hipSuccess)
                 return err;
         }
