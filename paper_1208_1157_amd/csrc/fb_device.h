@@ -418,6 +418,51 @@ __device__ __forceinline__ int sys_or_flags(int s, int v)
     return r;
 }
 
+// The clock part of a run's start for slot s, at time t with status st (systems
+// stopped by a rule keep theirs); true when an adaptive step
+// (rule 1 or 2) must still be proposed from the system's state.
+__device__ __forceinline__ bool begin_run_clock(const Bucket &B, const int s, const int st,
+                                                const double t, const RunStart &run)
+{
+    if (st != ST_ACTIVE && st != ST_DONE && st != ST_MAXSTEPS)
+        return false;
+    const double dt = run.dt, t_end = run.t_end;
+    B.t0run[s] = t;
+    B.krun[s] = 0;
+    if (run.fixed_steps) {
+        B.dt[s] = dt;
+        B.nfull[s] = run.n_steps;
+        B.t_end[s] = fma((double)run.n_steps, dt, t);
+        B.status[s] = run.n_steps > 0 ? ST_ACTIVE : ST_DONE;
+        return false;
+    }
+    B.t_end[s] = t_end;
+    if (run.adaptive == 3) {   // Runge-Kutta Cash-Karp: dt is the first trial step
+        B.nfull[s] = 0;
+        B.dt[s] = 0.0;
+        B.dtn[s] = dt;
+        B.status[s] = t < t_end ? ST_ACTIVE : ST_DONE;
+        return false;
+    }
+    if (run.adaptive) {
+        B.nfull[s] = 0;
+        B.dt[s] = 0.0;
+        B.status[s] = t < t_end ? ST_ACTIVE : ST_DONE;
+        // Eq. 5's step depends only on the stored (a0, j0), so it is always
+        // recomputed (identical to the carried value); the pairwise rule's
+        // carried step comes from the last evaluation's state and is kept.
+        return run.adaptive == 2 || !(B.dtn[s] > 0.0);
+    }
+    B.dt[s] = dt;
+    const double span = (t_end - t) / dt;
+    long long nf = span > 0.0 ? (long long)floor(span) : 0;
+    while (nf > 0 && (fma((double)nf, dt, t) - t_end) * dt > 0.0)
+        --nf;
+    B.nfull[s] = nf;
+    B.status[s] = (t_end - t) * dt > 0.0 ? ST_ACTIVE : ST_DONE;
+    return false;
+}
+
 template <int N>
 __device__ __forceinline__ void load_rows(const Bucket &B, int s, double (&m)[N], double (&x)[N][3],
                                           double (&v)[N][3], double (&a)[N][3], bool with_a)

@@ -49,22 +49,73 @@ struct Bucket {
     int n, pitch, count, pad;
 };
 
-// Several buckets of at most kMaxBodies bodies whose body-per-lane tiles
-// (floor(64 / n) systems each) share one launch: bucket k's tiles are
-// first[k] .. first[k + 1] - 1.  Passed to kernels by value.
+// Several buckets that share one launch: bucket k's tiles are first[k] ..
+// first[k + 1] - 1, body-per-lane tiles of floor(64 / n) systems each or
+// what the kernel takes as a unit.  Passed to kernels by value.
 struct BucketSet {
-    Bucket b[kMaxBodies - 1];
-    int first[kMaxBodies];
+    static constexpr int kMost = kMaxBodies - 1;   // every n up to kMaxBodies
+    Bucket b[kMost];
+    int first[kMost + 1];
     int count;
 
     void clear() { count = first[0] = 0; }
-    void add(const Bucket &B)
+    void add(const Bucket &B, int tiles)
     {
         b[count] = B;
-        first[count + 1] = first[count] + (B.count + 64 / B.n - 1) / (64 / B.n);
+        first[count + 1] = first[count] + tiles;
         ++count;
     }
+    void add(const Bucket &B) { add(B, (B.count + 64 / B.n - 1) / (64 / B.n)); }
 };
+
+// The caller's arrays, system by system, and where its systems' bodies start
+// (null: system o is slot o of the only bucket, its bodies from o n on).
+struct CallerArrays {
+    const double *mass = nullptr, *pos = nullptr, *vel = nullptr;
+    const double *t0 = nullptr;              // null: all zero
+    const long long *orig_off = nullptr;
+    int *bad = nullptr;                      // set to 1 by an invalid input, if not null
+    int pad = 0;   // also initialise slots count..pitch-1 as inert padding (a
+                   // whole bucket); 0 for a view of a bucket shared with others
+};
+
+// Read-back targets in the caller's order, each optional; orig_off as above.
+struct StateOut {
+    const long long *orig_off = nullptr;
+    double *pos = nullptr, *vel = nullptr, *acc = nullptr, *jerk = nullptr, *t = nullptr;
+    int *status = nullptr;
+    long long *steps = nullptr;
+    double *dtn = nullptr;
+};
+
+// How a run starts: exactly n_steps steps of dt (fixed_steps), or to t_end in
+// steps of dt (adaptive 0), adaptive steps (1 pairwise rule, 2 Eq. 5; eta) or
+// Cash-Karp steps from a first trial step dt (3).
+struct RunStart {
+    int on = 0;
+    int fixed_steps = 0;
+    int adaptive = 0;
+    long long n_steps = 0;
+    double t_end = 0.0, dt = 0.0, eta = 0.0;
+};
+inline RunStart start_steps(long long n_steps, double dt)
+{
+    RunStart r;
+    r.on = r.fixed_steps = 1;
+    r.n_steps = n_steps;
+    r.dt = dt;
+    return r;
+}
+inline RunStart start_to(double t_end, double dt, int adaptive, double eta)
+{
+    RunStart r;
+    r.on = 1;
+    r.t_end = t_end;
+    r.dt = dt;
+    r.adaptive = adaptive;
+    r.eta = eta;
+    return r;
+}
 
 // One unit of persistent-schedule work: `count` systems of bucket `bucket`
 // starting at `first` (a slot, or an index into an active list).
@@ -97,16 +148,23 @@ inline int tile_systems(int mapping, int n) {
     return mapping == MAP_SPL ? spl_tile_systems() : bpl_tile_systems(n);
 }
 
-// ---- launchers (fb_kernels.hip; steps of MVS and Cash-Karp in their own) --
-// pad_tail: also initialise slots count..pitch-1 as inert padding (a whole
-// bucket); false for a view of a bucket shared with other owners.
-hipError_t launch_pack(const Bucket &B, const double *mass, const double *pos,
-                       const double *vel, const double *t0,
-                       const long long *orig_off, int *bad, bool pad_tail, hipStream_t s);
-hipError_t launch_prepare(const Bucket &B, hipStream_t s);
-hipError_t launch_begin_run(const Bucket &B, int fixed_steps, long long n_steps,
-                            double t_end, double dt, int adaptive, double eta,
+// ---- set-up, start of a run, read-back (fb_setup.hip) ------------------
+// Each takes any buckets and as few launches as their kinds need.
+// Layout of the caller's arrays and the set-up evaluation, and (systems of at
+// most kMaxBodies bodies) the start of a run, if run.on, without adaptive steps.
+hipError_t launch_create(const Bucket *b, int nb, const CallerArrays &in, const RunStart &run,
+                         hipStream_t s);
+hipError_t launch_prepare(const Bucket *b, int nb, hipStream_t s);
+hipError_t launch_begin_run(const Bucket *b, int nb, const RunStart &run, hipStream_t s);
+// mvs_form: converted to inertial form on the way; acc, jerk and dtn null.
+hipError_t launch_read_back(const Bucket *b, int nb, const StateOut &out, bool mvs_form,
                             hipStream_t s);
+
+// ---- launchers (fb_kernels.hip; steps of MVS and Cash-Karp in their own) --
+hipError_t launch_prepare_large(const Bucket &B, hipStream_t s);
+hipError_t launch_unpack_mvs_large(const Bucket &B, const StateOut &out, hipStream_t s);
+// A run with adaptive steps of either rule, its first one proposed.
+hipError_t launch_begin_adaptive(const Bucket &B, const RunStart &run, hipStream_t s);
 hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group,
                         const StepParams &P, hipStream_t s);
 // Wavefronts launch_unrolled starts for bucket B, and the launch (launch_plain with
@@ -127,11 +185,8 @@ hipError_t launch_build_tiles(const Bucket *d_buckets, int n_buckets,
                               ActiveLists L, Tile *d_tiles, int *d_ntiles,
                               int *d_head, hipStream_t s);
 hipError_t launch_reset_counter(int *p, int n, hipStream_t s);
-hipError_t launch_unpack(const Bucket &B, const long long *orig_off, double *pos,
-                         double *vel, double *acc, double *jerk, double *t,
-                         int *status, long long *steps, double *dt_next,
-                         hipStream_t s);
-hipError_t launch_diag(const Bucket &B, double *energy, double *angmom, bool mvs_form,
+// Energy and angular momentum of every system of the buckets.
+hipError_t launch_diag(const Bucket *b, int nb, double *energy, double *angmom, bool mvs_form,
                        hipStream_t s);
 // Monitor record k of every system of B (kind 0 state, 1 star RV along the
 // unit vector los, 2 energy and angular momentum) into a log buffer whose
@@ -146,8 +201,7 @@ hipError_t launch_rkck_spl(const Bucket &B, const StepParams &P, hipStream_t s);
 hipError_t launch_rkck_bpl(const BucketSet &set, const StepParams &P, double eps, hipStream_t s);
 hipError_t launch_rkck_large(const Bucket &B, const StepParams &P, double eps, hipStream_t s);
 // Mixed-variable symplectic integrator (n <= kMaxMvsBodies, system per
-// lane): conversion of a bucket to and from MVS form, fixed-step quanta, and
-// read-back of a bucket in MVS form as inertial positions and velocities.
+// lane): conversion of a bucket to and from MVS form, fixed-step quanta.
 hipError_t launch_mvs_enter(const Bucket &B, hipStream_t s);
 hipError_t launch_mvs_leave(const Bucket &B, hipStream_t s);
 // Three mappings that give identical results: system per lane (n <=
@@ -157,9 +211,6 @@ hipError_t launch_plain_mvs(const Bucket &B, int waves_per_group, const StepPara
                             hipStream_t s);
 hipError_t launch_mvs_bpl(const BucketSet &set, const StepParams &P, hipStream_t s);
 hipError_t launch_plain_mvs_large(const Bucket &B, const StepParams &P, hipStream_t s);
-hipError_t launch_unpack_mvs(const Bucket &B, const long long *orig_off, double *pos,
-                             double *vel, double *t, int *status, long long *steps,
-                             hipStream_t s);
 hipError_t launch_count_active(const Bucket &B, int *count, hipStream_t s);
 // Workgroup shape of the large-n kernels (n > kMaxBodies) with k bodies per
 // lane: T lanes, a multiple of 64 up to 512 / k, holding S = floor(T / H)
@@ -178,9 +229,6 @@ hipError_t launch_rsqrt(const double *in, double *out, long long n, hipStream_t 
 hipError_t launch_restore(const Bucket &B, const long long *orig_off, const double *acc,
                           const double *jerk, const double *dtn, const long long *steps,
                           const int *status, hipStream_t s);
-// Identity slot map and body offsets (o * n) of a single homogeneous bucket
-// holding the caller's systems in order; clears *bad.
-hipError_t launch_identity_tables(const Bucket &B, long long *orig_off, int *bad, hipStream_t s);
 size_t persistent_lds_bytes(int spl_class, int waves_per_group);
 int persistent_max_groups_per_cu(int adv, int spl_class, int waves_per_group);
 // Largest n a persistent tile runs system-per-lane for, by kernel class.

@@ -647,52 +647,6 @@ __global__ void k_fill_int(int *p, int n, int value)
 // set-up, run control, layout and diagnostics kernels (one thread per slot)
 // ---------------------------------------------------------------------------
 
-// AoS (caller order) -> bucket SoA; validates the inputs.
-__global__ void k_pack(Bucket B, const double *__restrict__ mass, const double *__restrict__ pos,
-                       const double *__restrict__ vel, const double *__restrict__ t0,
-                       const long long *__restrict__ orig_off, int *bad, int limit)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= limit)
-        return;
-    const size_t pitch = B.pitch;
-    const int n = B.n;
-    if (s >= B.count) {   // padding slots: inert, finished
-        B.status[s] = ST_DONE;
-        B.t[s] = 0.0;
-        B.steps[s] = 0;
-        return;
-    }
-    const int o = B.orig[s];
-    const long long base = orig_off[o];
-    bool ok = true;
-    for (int b = 0; b < n; ++b) {
-        const double m = mass[base + b];
-        ok = ok && __builtin_isfinite(m) && m >= 0.0;
-        B.st[(R_M * n + b) * pitch + s] = m;
-        for (int c = 0; c < 3; ++c) {
-            const double xv = pos[3 * (base + b) + c];
-            const double vv = vel[3 * (base + b) + c];
-            ok = ok && __builtin_isfinite(xv) && __builtin_isfinite(vv);
-            B.st[((R_X + c) * n + b) * pitch + s] = xv;
-            B.st[((R_V + c) * n + b) * pitch + s] = vv;
-        }
-    }
-    const double tt = t0 ? t0[o] : 0.0;
-    ok = ok && __builtin_isfinite(tt);
-    B.t[s] = tt;
-    B.t0run[s] = tt;
-    B.t_end[s] = tt;
-    B.dt[s] = 0.0;
-    B.dtn[s] = 0.0;
-    B.krun[s] = 0;
-    B.nfull[s] = 0;
-    B.steps[s] = 0;
-    B.status[s] = ST_DONE;
-    if (!ok)
-        atomicOr(bad, 1);
-}
-
 template <int N>
 __device__ __forceinline__ void load_xv(const Bucket &B, int s, double (&m)[N], double (&x)[N][3],
                                         double (&v)[N][3])
@@ -709,89 +663,19 @@ __device__ __forceinline__ void load_xv(const Bucket &B, int s, double (&m)[N], 
     }
 }
 
-// Algorithm 1's "prepare": (a0, j0) at the initial state.
+// Start of a run with adaptive steps (one thread per slot): the clock, and the
+// step proposed from the current state when none is carried yet.
 template <int N>
-__global__ void k_prepare(Bucket B)
+__global__ void k_begin_run(Bucket B, RunStart run)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= B.count)
         return;
-    double m[N], x[N][3], v[N][3], a[N][3], jk[N][3];
-    load_xv<N>(B, s, m, x, v);
-    double w = 0.0;
-    spl_accjerk<N, false>(m, x, v, a, jk, w);
-    const size_t pitch = B.pitch;
-#pragma unroll
-    for (int b = 0; b < N; ++b)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            B.st[((R_A + c) * N + b) * pitch + s] = a[b][c];
-            B.st[((R_J + c) * N + b) * pitch + s] = jk[b][c];
-        }
-}
-
-// Start a run.  fixed_steps: exactly n_steps steps of dt.  Otherwise to
-// t_end, with fixed dt or (adaptive) the carried step, proposing one from
-// the current state when none is carried yet.  Systems stopped by a rule
-// keep their status.
-// The clock part of a run's start for slot s; true when an adaptive step
-// (rule 1 or 2) must still be proposed from the system's state.
-__device__ __forceinline__ bool begin_run_clock(const Bucket &B, const int s, int fixed_steps,
-                                                long long n_steps, double t_end, double dt,
-                                                int adaptive)
-{
-    const int st = B.status[s];
-    if (st != ST_ACTIVE && st != ST_DONE && st != ST_MAXSTEPS)
-        return false;
-    const double t = B.t[s];
-    B.t0run[s] = t;
-    B.krun[s] = 0;
-    if (fixed_steps) {
-        B.dt[s] = dt;
-        B.nfull[s] = n_steps;
-        B.t_end[s] = fma((double)n_steps, dt, t);
-        B.status[s] = n_steps > 0 ? ST_ACTIVE : ST_DONE;
-        return false;
-    }
-    B.t_end[s] = t_end;
-    if (adaptive == 3) {   // Runge-Kutta Cash-Karp: dt is the first trial step
-        B.nfull[s] = 0;
-        B.dt[s] = 0.0;
-        B.dtn[s] = dt;
-        B.status[s] = t < t_end ? ST_ACTIVE : ST_DONE;
-        return false;
-    }
-    if (adaptive) {
-        B.nfull[s] = 0;
-        B.dt[s] = 0.0;
-        B.status[s] = t < t_end ? ST_ACTIVE : ST_DONE;
-        // Eq. 5's step depends only on the stored (a0, j0), so it is always
-        // recomputed (identical to the carried value); the pairwise rule's
-        // carried step comes from the last evaluation's state and is kept.
-        return adaptive == 2 || !(B.dtn[s] > 0.0);
-    }
-    B.dt[s] = dt;
-    const double span = (t_end - t) / dt;
-    long long nf = span > 0.0 ? (long long)floor(span) : 0;
-    while (nf > 0 && (fma((double)nf, dt, t) - t_end) * dt > 0.0)
-        --nf;
-    B.nfull[s] = nf;
-    B.status[s] = (t_end - t) * dt > 0.0 ? ST_ACTIVE : ST_DONE;
-    return false;
-}
-
-template <int N>
-__global__ void k_begin_run(Bucket B, int fixed_steps, long long n_steps, double t_end,
-                            double dt, int adaptive, double eta)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B.count)
-        return;
-    if (!begin_run_clock(B, s, fixed_steps, n_steps, t_end, dt, adaptive))
+    if (!begin_run_clock(B, s, B.status[s], B.t[s], run))
         return;
     double m[N], x[N][3], v[N][3], a[N][3], jk[N][3];
     load_xv<N>(B, s, m, x, v);
-    if (adaptive == 2) {
+    if (run.adaptive == 2) {
         const size_t pitch = B.pitch;
 #pragma unroll
         for (int b = 0; b < N; ++b)
@@ -800,38 +684,12 @@ __global__ void k_begin_run(Bucket B, int fixed_steps, long long n_steps, double
                 a[b][c] = B.st[((R_A + c) * N + b) * pitch + s];
                 jk[b][c] = B.st[((R_J + c) * N + b) * pitch + s];
             }
-        B.dtn[s] = paper_dt<N>(a, jk, eta);
+        B.dtn[s] = paper_dt<N>(a, jk, run.eta);
     } else {
         double w = 0.0;
         spl_accjerk<N, true>(m, x, v, a, jk, w);
-        B.dtn[s] = eta * rsqrt_nr(w);
+        B.dtn[s] = run.eta * rsqrt_nr(w);
     }
-}
-
-// bucket SoA -> AoS rows in caller order (any output may be null).
-__global__ void k_unpack(Bucket B, const long long *__restrict__ orig_off, double *pos,
-                         double *vel, double *acc, double *jerk, double *t, int *status,
-                         long long *steps, double *dtn)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B.count)
-        return;
-    const size_t pitch = B.pitch;
-    const int n = B.n;
-    const int o = B.orig[s];
-    const long long base = orig_off[o];
-    for (int b = 0; b < n; ++b)
-        for (int c = 0; c < 3; ++c) {
-            const size_t row = 3 * (base + b) + c;
-            if (pos) pos[row] = B.st[((R_X + c) * n + b) * pitch + s];
-            if (vel) vel[row] = B.st[((R_V + c) * n + b) * pitch + s];
-            if (acc) acc[row] = B.st[((R_A + c) * n + b) * pitch + s];
-            if (jerk) jerk[row] = B.st[((R_J + c) * n + b) * pitch + s];
-        }
-    if (t) t[o] = B.t[s];
-    if (status) status[o] = B.status[s];
-    if (steps) steps[o] = B.steps[s];
-    if (dtn) dtn[o] = B.dtn[s];
 }
 
 template <int N>
@@ -865,14 +723,12 @@ __device__ __forceinline__ void sys_energy(const double (&m)[N], const double (&
     L[2] = L2;
 }
 
-// Energy and angular momentum of every system of a bucket in inertial form
-// or (MVS) in MVS form, converted first.
+// Energy and angular momentum of one system in inertial form or (MVS) in MVS
+// form, converted first.
 template <int N, bool MVS>
-__global__ void k_diag(Bucket B, double *energy, double *angmom)
+__device__ __forceinline__ void diag_run(const Bucket &B, const int s, double *energy,
+                                         double *angmom)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B.count)
-        return;
     double m[N], x[N][3], v[N][3];
     load_xv<N>(B, s, m, x, v);
     if (MVS)
@@ -886,6 +742,29 @@ __global__ void k_diag(Bucket B, double *energy, double *angmom)
         angmom[3 * o + 0] = L[0];
         angmom[3 * o + 1] = L[1];
         angmom[3 * o + 2] = L[2];
+    }
+}
+
+// Of every system of a set of buckets, 64 a workgroup.
+template <bool MVS>
+__global__ __launch_bounds__(64) void k_diag(BucketSet set, double *energy, double *angmom)
+{
+    const int tile = blockIdx.x;
+    int k = 0;
+    while (k < set.count && tile >= set.first[k + 1])
+        ++k;
+    if (k >= set.count)
+        return;
+    const Bucket B = set.b[k];
+    const int s = (tile - set.first[k]) * 64 + threadIdx.x;
+    if (s >= B.count)
+        return;
+    switch (B.n) {
+#define FB_C(NN) case NN: diag_run<NN, MVS>(B, s, energy, angmom); break;
+        FB_C(2) FB_C(3) FB_C(4) FB_C(5) FB_C(6) FB_C(7) FB_C(8) FB_C(9) FB_C(10) FB_C(11)
+        FB_C(12) FB_C(13) FB_C(14) FB_C(15) FB_C(16)
+#undef FB_C
+    default: break;
     }
 }
 
@@ -1048,38 +927,6 @@ __global__ __launch_bounds__(64) void k_mvs_leave(Bucket B)
     load_rows<N>(B, s, m, x, v, a, false);
     from_mvs<N>(m, x, v);
     store_rows<N>(B, s, x, v, a, false);
-}
-
-// State read-back of a bucket in MVS form: converted to inertial (x, v) on
-// the way out; the stored form is left as it is.
-template <int N>
-__global__ __launch_bounds__(64) void k_unpack_mvs(Bucket B, const long long *__restrict__ orig_off,
-                                                   double *pos, double *vel, double *t, int *status,
-                                                   long long *steps)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B.count)
-        return;
-    double m[N], x[N][3], v[N][3], a[N][3];
-    load_rows<N>(B, s, m, x, v, a, false);
-    from_mvs<N>(m, x, v);
-    const int o = B.orig[s];
-    const long long base = orig_off[o];
-#pragma unroll
-    for (int b = 0; b < N; ++b)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if (pos)
-                pos[3 * (base + b) + c] = x[b][c];
-            if (vel)
-                vel[3 * (base + b) + c] = v[b][c];
-        }
-    if (t)
-        t[o] = B.t[s];
-    if (status)
-        status[o] = B.status[s];
-    if (steps)
-        steps[o] = B.steps[s];
 }
 
 // ---------------------------------------------------------------------------
@@ -1260,17 +1107,14 @@ __device__ __forceinline__ void large_load_xv(const Bucket &B, const LargeLane &
 // star's lane, then, for systems that need one, the first adaptive step from
 // the stored (a0, j0) (Eq. 5) or from the pairwise rule at the current state
 // (the proposals of k_begin_run).
-__global__ __launch_bounds__(kLargeMaxLanes) void k_begin_run_large(Bucket B, int S,
-                                                                    int fixed_steps,
-                                                                    long long n_steps,
-                                                                    double t_end, double dt,
-                                                                    int adaptive, double eta)
+__global__ __launch_bounds__(kLargeMaxLanes) void k_begin_run_large(Bucket B, int S, RunStart run)
 {
+    const int adaptive = run.adaptive;
     const int T = blockDim.x, n = B.n;
     const LargeView V = large_view(T);
     const LargeLane l = large_lane(B, S);
     if (l.valid && l.b == 0)
-        V.flag[l.base] = begin_run_clock(B, l.slot, fixed_steps, n_steps, t_end, dt, adaptive);
+        V.flag[l.base] = begin_run_clock(B, l.slot, B.status[l.slot], B.t[l.slot], run);
     __syncthreads();
     const bool need = l.valid && V.flag[l.base] != 0;
     if (!__syncthreads_or(need))
@@ -1320,7 +1164,7 @@ __global__ __launch_bounds__(kLargeMaxLanes) void k_begin_run_large(Bucket B, in
         double r = V.red[l.base];
         for (int b = 1; b < n; ++b)
             r = adaptive == 2 ? r + V.red[l.base + b] : fmax(r, V.red[l.base + b]);
-        B.dtn[l.slot] = eta * rsqrt_nr(r);
+        B.dtn[l.slot] = run.eta * rsqrt_nr(r);
     }
 }
 
@@ -1495,10 +1339,8 @@ __global__ __launch_bounds__(kLargeMaxLanes) void k_mvs_leave_large(Bucket B, in
 }
 
 // State read-back of a bucket in MVS form, converted to inertial (x, v) on
-// the way out (the layouts of k_unpack).
-__global__ __launch_bounds__(kLargeMaxLanes) void k_unpack_mvs_large(
-    Bucket B, int S, const long long *__restrict__ orig_off, double *pos, double *vel, double *t,
-    int *status, long long *steps)
+// the way out.
+__global__ __launch_bounds__(kLargeMaxLanes) void k_unpack_mvs_large(Bucket B, int S, StateOut out)
 {
     const int T = blockDim.x;
     const LargeView V = large_view(T);
@@ -1510,17 +1352,17 @@ __global__ __launch_bounds__(kLargeMaxLanes) void k_unpack_mvs_large(
     if (!l.valid)
         return;
     const int o = B.orig[l.slot];
-    const long long base = orig_off[o];
+    const long long base = out.orig_off[o];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const size_t row = 3 * (base + l.b) + c;
-        if (pos) pos[row] = x[c];
-        if (vel) vel[row] = v[c];
+        if (out.pos) out.pos[row] = x[c];
+        if (out.vel) out.vel[row] = v[c];
     }
     if (l.b == 0) {
-        if (t) t[o] = B.t[l.slot];
-        if (status) status[o] = B.status[l.slot];
-        if (steps) steps[o] = B.steps[l.slot];
+        if (out.t) out.t[o] = B.t[l.slot];
+        if (out.status) out.status[o] = B.status[l.slot];
+        if (out.steps) out.steps[o] = B.steps[l.slot];
     }
 }
 
@@ -1583,20 +1425,6 @@ __global__ void k_restore(Bucket B, const long long *__restrict__ orig_off,
     B.status[s] = status[o];
 }
 
-// Tables of a single homogeneous bucket whose slots are the caller's
-// systems in order: slot -> system (padding slots -> 0), body offsets
-// o * n, and the input-check flag cleared.
-__global__ void k_identity_tables(Bucket B, long long *__restrict__ orig_off, int *bad)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < B.pitch)
-        B.orig[s] = s < B.count ? s : 0;
-    if (s <= B.count)
-        orig_off[s] = (long long)s * B.n;
-    if (s == 0)
-        *bad = 0;
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1611,18 +1439,6 @@ __global__ void k_identity_tables(Bucket B, long long *__restrict__ orig_off, in
     case 14: MACRO(14); break; case 15: MACRO(15); break; case 16: MACRO(16); break;    \
     default: return hipErrorInvalidValue;                                               \
     }
-
-hipError_t launch_pack(const Bucket &B, const double *mass, const double *pos,
-                       const double *vel, const double *t0, const long long *orig_off, int *bad,
-                       bool pad_tail, hipStream_t s)
-{
-    const int limit = pad_tail ? B.pitch : B.count;
-    if (limit == 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_pack, grid_for(limit, 256), dim3(256), 0, s, B, mass, pos, vel, t0,
-                       orig_off, bad, limit);
-    return hipGetLastError();
-}
 
 void large_shape(int n, int k, int &T, int &S)
 {
@@ -1646,26 +1462,19 @@ void large_shape(int n, int k, int &T, int &S)
     }
 }
 
-hipError_t launch_prepare(const Bucket &B, hipStream_t s)
+hipError_t launch_prepare_large(const Bucket &B, hipStream_t s)
 {
     if (B.count == 0)
         return hipSuccess;
-    if (B.n > kMaxBodies) {
-        dim3 grid;
-        int T, S;
-        if (!large_launch(B, 1, grid, T, S))
-            return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_prepare_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
-        return hipGetLastError();
-    }
-#define FB_L(NN) hipLaunchKernelGGL(k_prepare<NN>, grid_for(B.count, 64), dim3(64), 0, s, B)
-    FB_SWITCH_N(B.n, FB_L)
-#undef FB_L
+    dim3 grid;
+    int T, S;
+    if (!large_launch(B, 1, grid, T, S))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_prepare_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
     return hipGetLastError();
 }
 
-hipError_t launch_begin_run(const Bucket &B, int fixed_steps, long long n_steps, double t_end,
-                            double dt, int adaptive, double eta, hipStream_t s)
+hipError_t launch_begin_adaptive(const Bucket &B, const RunStart &run, hipStream_t s)
 {
     if (B.count == 0)
         return hipSuccess;
@@ -1674,13 +1483,10 @@ hipError_t launch_begin_run(const Bucket &B, int fixed_steps, long long n_steps,
         int T, S;
         if (!large_launch(B, 1, grid, T, S))
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_begin_run_large, grid, dim3(T), large_lds_bytes(T), s, B, S,
-                           fixed_steps, n_steps, t_end, dt, adaptive, eta);
+        hipLaunchKernelGGL(k_begin_run_large, grid, dim3(T), large_lds_bytes(T), s, B, S, run);
         return hipGetLastError();
     }
-#define FB_L(NN)                                                                        \
-    hipLaunchKernelGGL(k_begin_run<NN>, grid_for(B.count, 64), dim3(64), 0, s, B,       \
-                       fixed_steps, n_steps, t_end, dt, adaptive, eta)
+#define FB_L(NN) hipLaunchKernelGGL(k_begin_run<NN>, grid_for(B.count, 64), dim3(64), 0, s, B, run)
     FB_SWITCH_N(B.n, FB_L)
 #undef FB_L
     return hipGetLastError();
@@ -1827,23 +1633,21 @@ hipError_t launch_reset_counter(int *p, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_unpack(const Bucket &B, const long long *orig_off, double *pos, double *vel,
-                         double *acc, double *jerk, double *t, int *status, long long *steps,
-                         double *dt_next, hipStream_t s)
-{
-    if (B.count == 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_unpack, grid_for(B.count, 256), dim3(256), 0, s, B, orig_off, pos, vel,
-                       acc, jerk, t, status, steps, dt_next);
-    return hipGetLastError();
-}
-
-hipError_t launch_diag(const Bucket &B, double *energy, double *angmom, bool mvs_form,
+hipError_t launch_diag(const Bucket *b, int nb, double *energy, double *angmom, bool mvs_form,
                        hipStream_t s)
 {
-    if (B.count == 0)
-        return hipSuccess;
-    if (B.n > kMaxBodies || (mvs_form && B.n > kMaxMvsBodies)) {
+    BucketSet set;
+    set.clear();
+    for (int i = 0; i < nb; ++i) {
+        const Bucket &B = b[i];
+        if (B.count == 0)
+            continue;
+        if (B.n <= kMaxBodies) {   // at most one bucket of each n
+            if (set.count == BucketSet::kMost)
+                return hipErrorInvalidValue;
+            set.add(B, (B.count + 63) / 64);
+            continue;
+        }
         dim3 grid;
         int T, S;
         if (!large_launch(B, 1, grid, T, S))
@@ -1854,19 +1658,17 @@ hipError_t launch_diag(const Bucket &B, double *energy, double *angmom, bool mvs
         else
             hipLaunchKernelGGL(k_diag_large<false>, grid, dim3(T), large_lds_bytes(T), s, B, S,
                                energy, angmom);
-        return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
     }
-    if (mvs_form) {
-        if (B.n > kMaxMvsBodies)
-            return hipErrorInvalidValue;
-#define FB_L(NN) hipLaunchKernelGGL((k_diag<NN, true>), grid_for(B.count, 64), dim3(64), 0, s, B, energy, angmom)
-        FB_SWITCH_N(B.n, FB_L)
-#undef FB_L
-    } else {
-#define FB_L(NN) hipLaunchKernelGGL((k_diag<NN, false>), grid_for(B.count, 64), dim3(64), 0, s, B, energy, angmom)
-        FB_SWITCH_N(B.n, FB_L)
-#undef FB_L
-    }
+    if (set.count == 0)
+        return hipSuccess;
+    const dim3 grid((unsigned)set.first[set.count]);
+    if (mvs_form)
+        hipLaunchKernelGGL(k_diag<true>, grid, dim3(64), 0, s, set, energy, angmom);
+    else
+        hipLaunchKernelGGL(k_diag<false>, grid, dim3(64), 0, s, set, energy, angmom);
     return hipGetLastError();
 }
 
@@ -1915,24 +1717,15 @@ hipError_t launch_mvs_leave(const Bucket &B, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_unpack_mvs(const Bucket &B, const long long *orig_off, double *pos, double *vel,
-                             double *t, int *status, long long *steps, hipStream_t s)
+hipError_t launch_unpack_mvs_large(const Bucket &B, const StateOut &out, hipStream_t s)
 {
     if (B.count == 0)
         return hipSuccess;
-    if (B.n > kMaxMvsBodies) {
-        dim3 grid;
-        int T, S;
-        if (!large_launch(B, 1, grid, T, S))
-            return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_unpack_mvs_large, grid, dim3(T), large_lds_bytes(T), s, B, S, orig_off,
-                           pos, vel, t, status, steps);
-        return hipGetLastError();
-    }
-#define FB_L(NN) hipLaunchKernelGGL(k_unpack_mvs<NN>, grid_for(B.count, 64), dim3(64), 0, s, B, \
-                                    orig_off, pos, vel, t, status, steps)
-    FB_SWITCH_MVS(B.n, FB_L)
-#undef FB_L
+    dim3 grid;
+    int T, S;
+    if (!large_launch(B, 1, grid, T, S))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_unpack_mvs_large, grid, dim3(T), large_lds_bytes(T), s, B, S, out);
     return hipGetLastError();
 }
 
@@ -1990,13 +1783,6 @@ hipError_t launch_restore(const Bucket &B, const long long *orig_off, const doub
         return hipSuccess;
     hipLaunchKernelGGL(k_restore, grid_for(B.count, 256), dim3(256), 0, s, B, orig_off, acc, jerk,
                        dtn, steps, status);
-    return hipGetLastError();
-}
-
-hipError_t launch_identity_tables(const Bucket &B, long long *orig_off, int *bad, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_identity_tables, grid_for(B.pitch + 1, 256), dim3(256), 0, s, B,
-                       orig_off, bad);
     return hipGetLastError();
 }
 

@@ -319,6 +319,11 @@ fb_status upload_tables(fb_ensemble *e)
     return FB_OK;
 }
 
+hipError_t begin_run(fb_ensemble *e, const RunStart &run)
+{
+    return launch_begin_run(e->buckets.data(), (int)e->buckets.size(), run, e->stream);
+}
+
 fb_status finish_create(fb_ensemble *e, const double *d_mass, const double *d_pos,
                         const double *d_vel, const double *d_t0)
 {
@@ -326,10 +331,15 @@ fb_status finish_create(fb_ensemble *e, const double *d_mass, const double *d_po
     if (st != FB_OK)
         return st;
     FB_HIP(launch_reset_counter(e->d_ints, 64, e->stream));
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_pack(B, d_mass, d_pos, d_vel, d_t0, e->d_orig_off, e->d_ints, true, e->stream));
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_prepare(B, e->stream));
+    CallerArrays in;
+    in.mass = d_mass;
+    in.pos = d_pos;
+    in.vel = d_vel;
+    in.t0 = d_t0;
+    in.orig_off = e->d_orig_off;
+    in.bad = e->d_ints;
+    in.pad = 1;
+    FB_HIP(launch_create(e->buckets.data(), (int)e->buckets.size(), in, RunStart(), e->stream));
     FB_HIP(hipMemcpyAsync(e->h_pinned, e->d_ints, sizeof(int), hipMemcpyDeviceToHost, e->stream));
     FB_HIP(hipStreamSynchronize(e->stream));
     if (e->h_pinned[0])
@@ -669,11 +679,10 @@ fb_status ensure_inertial(fb_ensemble *e)
 {
     if (e->form == fb_ensemble::FORM_HERMITE)
         return FB_OK;
-    for (const Bucket &B : e->buckets) {
-        if (e->form == fb_ensemble::FORM_MVS)
+    if (e->form == fb_ensemble::FORM_MVS)
+        for (const Bucket &B : e->buckets)
             FB_HIP(launch_mvs_leave(B, e->stream));
-        FB_HIP(launch_prepare(B, e->stream));
-    }
+    FB_HIP(launch_prepare(e->buckets.data(), (int)e->buckets.size(), e->stream));
     e->form = fb_ensemble::FORM_HERMITE;
     return FB_OK;
 }
@@ -1073,8 +1082,7 @@ fb_status fb_integrate_steps(fb_ensemble *e, int64_t n_steps, double dt, const f
     st = ensure_inertial(e);
     if (st != FB_OK)
         return st;
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_begin_run(B, 1, n_steps, 0.0, dt, 0, 0.0, e->stream));
+    FB_HIP(begin_run(e, start_steps(n_steps, dt)));
     return run(e, o, o.stop_rules ? -1 : n_steps);
 }
 
@@ -1103,8 +1111,7 @@ fb_status fb_integrate_mvs(fb_ensemble *e, int64_t n_steps, double dt, const fb_
             FB_HIP(launch_mvs_enter(B, e->stream));
         e->form = fb_ensemble::FORM_MVS;
     }
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_begin_run(B, 1, n_steps, 0.0, dt, 0, 0.0, e->stream));
+    FB_HIP(begin_run(e, start_steps(n_steps, dt)));
     return run_mvs(e, o, n_steps);
 }
 
@@ -1168,8 +1175,7 @@ fb_status fb_integrate_steps_logged(fb_ensemble *e, int64_t n_steps, double dt, 
         FB_HIP(launch_log(B, e->d_orig_off, log->kind, los, k, log->max_records, out, e->stream));
     ++k;
     if (n_steps > 0) {
-        for (const Bucket &B : e->buckets)
-            FB_HIP(launch_begin_run(B, 1, n_steps, 0.0, dt, 0, 0.0, e->stream));
+        FB_HIP(begin_run(e, start_steps(n_steps, dt)));
         fb_opts oq = o;
         oq.steps_per_quantum = log->every;
         for (long long done = 0; done < n_steps; done += log->every) {
@@ -1223,8 +1229,7 @@ fb_status fb_integrate_to_times(fb_ensemble *e, int32_t n_times, const double *t
     double *out = static_cast<double *>(log->d_buffer);
     const int rule = o.adaptive == 2 ? 2 : (o.adaptive ? 1 : 0);
     for (int32_t k = 0; k < n_times; ++k) {
-        for (const Bucket &B : e->buckets)
-            FB_HIP(launch_begin_run(B, 0, 0, t_obs[k], dt, rule, o.eta, e->stream));
+        FB_HIP(begin_run(e, start_to(t_obs[k], dt, rule, o.eta)));
         st = run(e, o, -1);
         if (st != FB_OK)
             return st;
@@ -1257,8 +1262,7 @@ fb_status fb_integrate_rkck_steps(fb_ensemble *e, int64_t n_steps, double dt, co
     st = ensure_xv(e);
     if (st != FB_OK)
         return st;
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_begin_run(B, 1, n_steps, 0.0, dt, 0, 0.0, e->stream));
+    FB_HIP(begin_run(e, start_steps(n_steps, dt)));
     e->form = fb_ensemble::FORM_XV;
     return run_rkck(e, o, 0, 0.0, n_steps);
 }
@@ -1286,8 +1290,7 @@ fb_status fb_integrate_rkck(fb_ensemble *e, double t_end, double dt, double eps,
     st = ensure_xv(e);
     if (st != FB_OK)
         return st;
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_begin_run(B, 0, 0, t_end, dt, 3, 0.0, e->stream));
+    FB_HIP(begin_run(e, start_to(t_end, dt, 3, 0.0)));
     e->form = fb_ensemble::FORM_XV;
     return run_rkck(e, o, 3, eps, -1);
 }
@@ -1315,9 +1318,7 @@ fb_status fb_integrate(fb_ensemble *e, double t_end, double dt, const fb_opts *p
     st = ensure_inertial(e);
     if (st != FB_OK)
         return st;
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_begin_run(B, 0, 0, t_end, dt, o.adaptive == 2 ? 2 : (o.adaptive ? 1 : 0),
-                                o.eta, e->stream));
+    FB_HIP(begin_run(e, start_to(t_end, dt, o.adaptive == 2 ? 2 : (o.adaptive ? 1 : 0), o.eta)));
     return run(e, o, -1);
 }
 
@@ -1340,16 +1341,14 @@ fb_status fb_get_state(fb_ensemble *e, double *pos, double *vel, double *t, int3
     double *d_pos = e->d_staging, *d_vel = d_pos + 3 * N, *d_t = d_vel + 3 * N;
     long long *d_steps = (long long *)(d_t + ns);
     int *d_status = (int *)(d_steps + ns);
-    for (const Bucket &B : e->buckets) {
-        if (e->mvs_form())
-            FB_HIP(launch_unpack_mvs(B, e->d_orig_off, pos ? d_pos : nullptr, vel ? d_vel : nullptr,
-                                     t ? d_t : nullptr, status ? d_status : nullptr,
-                                     steps ? d_steps : nullptr, e->stream));
-        else
-            FB_HIP(launch_unpack(B, e->d_orig_off, pos ? d_pos : nullptr, vel ? d_vel : nullptr,
-                                 nullptr, nullptr, t ? d_t : nullptr, status ? d_status : nullptr,
-                                 steps ? d_steps : nullptr, nullptr, e->stream));
-    }
+    StateOut out;
+    out.orig_off = e->d_orig_off;
+    out.pos = pos ? d_pos : nullptr;
+    out.vel = vel ? d_vel : nullptr;
+    out.t = t ? d_t : nullptr;
+    out.status = status ? d_status : nullptr;
+    out.steps = steps ? d_steps : nullptr;
+    FB_HIP(launch_read_back(e->buckets.data(), (int)e->buckets.size(), out, e->mvs_form(), e->stream));
     if (pos)
         FB_HIP(hipMemcpyAsync(pos, d_pos, 24 * N, hipMemcpyDeviceToHost, e->stream));
     if (vel)
@@ -1380,10 +1379,12 @@ fb_status fb_get_hermite_state(fb_ensemble *e, double *acc0, double *jerk0, doub
     if (ns == 0)
         return FB_OK;
     double *d_acc = e->d_staging, *d_jerk = d_acc + 3 * N, *d_dtn = d_jerk + 3 * N;
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_unpack(B, e->d_orig_off, nullptr, nullptr, acc0 ? d_acc : nullptr,
-                             jerk0 ? d_jerk : nullptr, nullptr, nullptr, nullptr,
-                             dt_next ? d_dtn : nullptr, e->stream));
+    StateOut out;
+    out.orig_off = e->d_orig_off;
+    out.acc = acc0 ? d_acc : nullptr;
+    out.jerk = jerk0 ? d_jerk : nullptr;
+    out.dtn = dt_next ? d_dtn : nullptr;
+    FB_HIP(launch_read_back(e->buckets.data(), (int)e->buckets.size(), out, false, e->stream));
     if (acc0)
         FB_HIP(hipMemcpyAsync(acc0, d_acc, 24 * N, hipMemcpyDeviceToHost, e->stream));
     if (jerk0)
@@ -1402,8 +1403,7 @@ fb_status fb_diagnostics(fb_ensemble *e, double *energy, double *angmom)
     if (ns == 0)
         return FB_OK;
     double *d_E = e->d_diag, *d_L = d_E + ns;
-    for (const Bucket &B : e->buckets)
-        FB_HIP(launch_diag(B, d_E, d_L, e->mvs_form(), e->stream));
+    FB_HIP(launch_diag(e->buckets.data(), (int)e->buckets.size(), d_E, d_L, e->mvs_form(), e->stream));
     if (energy)
         FB_HIP(hipMemcpyAsync(energy, d_E, 8 * ns, hipMemcpyDeviceToHost, e->stream));
     if (angmom)
@@ -1519,10 +1519,10 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
             size_t best_i = 0;
             for (const Cand &c : cands) {
                 FB_HIP(restore());
-                FB_HIP(launch_begin_run(B, 1, 1, 0.0, dt, 0, 0.0, e->stream));
+                FB_HIP(launch_begin_run(&B, 1, start_steps(1, dt), e->stream));
                 FB_HIP(launch_plain(B, c.map, c.W, P, e->stream));   // warm-up (code load)
                 FB_HIP(restore());
-                FB_HIP(launch_begin_run(B, 1, steps, 0.0, dt, 0, 0.0, e->stream));
+                FB_HIP(launch_begin_run(&B, 1, start_steps(steps, dt), e->stream));
                 FB_HIP(hipEventRecord(ev0, e->stream));
                 FB_HIP(launch_plain(B, c.map, c.W, P, e->stream));
                 FB_HIP(hipEventRecord(ev1, e->stream));
@@ -1571,8 +1571,7 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
                 if (st != FB_OK)
                     return st;
                 FB_HIP(restore());
-                for (const Bucket &B : e->buckets)
-                    FB_HIP(launch_begin_run(B, 1, steps, 0.0, dt, 0, 0.0, e->stream));
+                FB_HIP(begin_run(e, start_steps(steps, dt)));
                 FB_HIP(hipEventRecord(ev0, e->stream));
                 st = run_persistent(e, po, steps);
                 if (st != FB_OK)

@@ -466,14 +466,20 @@ fb_status admit_one(fb_server *S, Request *R)
         FB_HIP(hipMemcpyAsync(stg + N, R->pos.data(), 24 * N, hipMemcpyHostToDevice, S->stream));
         FB_HIP(hipMemcpyAsync(stg + 4 * N, R->vel.data(), 24 * N, hipMemcpyHostToDevice, S->stream));
     }
+    std::vector<Bucket> views;
     for (const Piece &p : R->pieces) {
-        const Bucket V = p.view();
-        FB_HIP(hipMemcpyAsync(V.orig, p.orig.data(), sizeof(int) * p.count, hipMemcpyHostToDevice,
-                              S->stream));
-        FB_HIP(launch_pack(V, stg, stg + N, stg + 4 * N, nullptr, d_off, d_flag, false, S->stream));
-        FB_HIP(launch_prepare(V, S->stream));
-        FB_HIP(launch_begin_run(V, 0, 0, R->t_end, R->dt, 0, 0.0, S->stream));
+        views.push_back(p.view());
+        FB_HIP(hipMemcpyAsync(views.back().orig, p.orig.data(), sizeof(int) * p.count,
+                              hipMemcpyHostToDevice, S->stream));
     }
+    CallerArrays in;
+    in.mass = stg;
+    in.pos = stg + N;
+    in.vel = stg + 4 * N;
+    in.orig_off = d_off;
+    in.bad = d_flag;
+    FB_HIP(launch_create(views.data(), (int)views.size(), in, start_to(R->t_end, R->dt, 0, 0.0),
+                         S->stream));
     R->total_steps = schedule_steps(0.0, R->t_end, R->dt);
     R->done_steps = 0;
     return FB_OK;
@@ -488,9 +494,17 @@ fb_status finish_one(fb_server *S, Request *R)
     double *d_pos = stg, *d_vel = stg + 3 * N, *d_t = stg + 6 * N;
     long long *d_steps = reinterpret_cast<long long *>(d_t + ns);
     int *d_status = reinterpret_cast<int *>(d_steps + ns);
+    std::vector<Bucket> views;
     for (const Piece &p : R->pieces)
-        FB_HIP(launch_unpack(p.view(), d_off, d_pos, d_vel, nullptr, nullptr, d_t, d_status,
-                             d_steps, nullptr, S->stream));
+        views.push_back(p.view());
+    StateOut out;
+    out.orig_off = d_off;
+    out.pos = d_pos;
+    out.vel = d_vel;
+    out.t = d_t;
+    out.status = d_status;
+    out.steps = d_steps;
+    FB_HIP(launch_read_back(views.data(), (int)views.size(), out, false, S->stream));
     R->out_pos.resize(3 * N);
     R->out_vel.resize(3 * N);
     R->out_t.resize(ns);

@@ -124,8 +124,6 @@ fb_status solo_run(char *base, const SoloLayout &L, const double *d_mass, double
                    bool timed)
 {
     const Bucket B = solo_view(base, L);
-    long long *orig_off = reinterpret_cast<long long *>(base + L.orig_off);
-    int *bad = reinterpret_cast<int *>(base + L.ints);
     int dev = 0, num_cu = 0;
     FB_HIP(hipGetDevice(&dev));
     FB_HIP(hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -139,11 +137,13 @@ fb_status solo_run(char *base, const SoloLayout &L, const double *d_mass, double
     P.quantum = INT_MAX;
     P.pad = 0;
     const int map = plain_mapping(p, B, false, num_cu > 0 ? num_cu : 256);
-    FB_HIP(launch_identity_tables(B, orig_off, bad, s));
-    FB_HIP(launch_pack(B, d_mass, d_pos, d_vel, nullptr, orig_off, bad, true, s));
-    FB_HIP(launch_prepare(B, s));
+    CallerArrays in;
+    in.mass = d_mass;
+    in.pos = d_pos;
+    in.vel = d_vel;
+    in.pad = 1;
+    FB_HIP(launch_create(&B, 1, in, n_steps > 0 ? start_steps(n_steps, dt) : RunStart(), s));
     if (n_steps > 0) {
-        FB_HIP(launch_begin_run(B, 1, n_steps, 0.0, dt, 0, 0.0, s));
         if (timed) {
             ProfScope ps(s);
             FB_HIP(launch_plain(B, map, p.waves_per_group, P, s));
@@ -151,8 +151,11 @@ fb_status solo_run(char *base, const SoloLayout &L, const double *d_mass, double
             FB_HIP(launch_plain(B, map, p.waves_per_group, P, s));
         }
     }
-    FB_HIP(launch_unpack(B, orig_off, d_pos, d_vel, nullptr, nullptr, nullptr, d_status, nullptr,
-                         nullptr, s));
+    StateOut out;
+    out.pos = d_pos;
+    out.vel = d_vel;
+    out.status = d_status;
+    FB_HIP(launch_read_back(&B, 1, out, false, s));
     return FB_OK;
 }
 
