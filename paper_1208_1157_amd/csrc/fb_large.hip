@@ -180,20 +180,43 @@ __device__ __forceinline__ void large_eval_k(const LargeStepView &V, const int E
     if (!live)
         return;
     const double *mm = V.m + s.base;
-    // every lane takes n / G partners (a scalar count), some one more
+    if constexpr (K == 2 && !SPLIT) {
+#pragma unroll 4
+        for (int p = 0; p < s.n; ++p) {
+            const LargeBody q = st[p];
+            const double mj = mm[p];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                large_interact_p<TS>(q, mj, xi[k], vi[k], a[k], jk[k], w[k]);
+        }
+        return;
+    }
+    // Every lane takes n / G partners (a scalar count), some one more.  The
+    // next one is read before the interaction with this one: 1024 x 64 12.4 ->
+    // 11.6 us a step, unrolling by 4 instead 12.05; a full device of two bodies
+    // a lane, above, prefers the latter (4096 x 64: 38.6 against 39.2).
     const int G = SPLIT ? s.G : 1, whole = SPLIT ? s.n >> s.log_g : s.n;
     int p = SPLIT ? s.share : 0;
+    LargeBody q = st[p];
+    double mj = mm[p];
 #pragma unroll 2
-    for (int i = 0; i < whole; ++i, p += G) {
-        const LargeBody q = st[p];
-        const double mj = mm[p];
+    for (int i = 1; i < whole; ++i) {
+        p += G;
+        const LargeBody next = st[p];
+        const double m_next = mm[p];
 #pragma unroll
         for (int k = 0; k < K; ++k)
             large_interact_p<TS>(q, mj, xi[k], vi[k], a[k], jk[k], w[k]);
+        q = next;
+        mj = m_next;
     }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        large_interact_p<TS>(q, mj, xi[k], vi[k], a[k], jk[k], w[k]);
+    p += G;
     if (SPLIT && p < s.n) {
-        const LargeBody q = st[p];
-        const double mj = mm[p];
+        q = st[p];
+        mj = mm[p];
 #pragma unroll
         for (int k = 0; k < K; ++k)
             large_interact_p<TS>(q, mj, xi[k], vi[k], a[k], jk[k], w[k]);
@@ -319,10 +342,9 @@ __device__ __forceinline__ int large_stop_flags(const LargeStepView &V, const La
 // copies of them instead of a second barrier an evaluation.  256 VGPRs: two
 // bodies a lane would spill at 128.  Fixed steps, us a step, against one
 // lane per one to four bodies with a structure of arrays in LDS: 17 bodies
-// 4.2 -> 2.3 (64 systems), 6.6 -> 6.2 (4096); 64 bodies 20.8 -> 4.5,
-// 22.3 -> 12.2 (1024), 39.3 -> 39.3 (4096: 26 us of FP64 issue, both sides of
-// every pair); 128 bodies 40.8 -> 12.2, 76.8 -> 41.4 (1024); 512 bodies
-// 161 -> 153.
+// 4.2 -> 2.0 (64 systems), 6.6 -> 6.5 (4096); 64 bodies 20.8 -> 4.3,
+// 22.3 -> 11.6 (1024), 39.3 -> 38.6 (4096: 26 us of FP64 issue, both sides of
+// every pair); 128 bodies 40.8 -> 11.6 (256); 512 bodies 161 -> 144.
 template <int K, bool SPLIT, bool ADV>
 __global__ __launch_bounds__(kLargeMaxLanes) __attribute__((amdgpu_waves_per_eu(2)))
 void k_plain_large(Bucket B, StepParams P, int S, int log_g)
