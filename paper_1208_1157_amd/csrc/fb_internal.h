@@ -69,11 +69,16 @@ struct BucketSet {
 };
 
 // The caller's arrays, system by system, and where its systems' bodies start
-// (null: system o is slot o of the only bucket, its bodies from o n on).
+// (null: system o is slot o of the only bucket, its bodies from o n on).  The
+// system of a slot is B.orig's, or `origins`[B.pad + slot], or (identity) the
+// slot itself; the latter two are stored in B.orig, and identity also fills
+// orig_off if it is not null.
 struct CallerArrays {
     const double *mass = nullptr, *pos = nullptr, *vel = nullptr;
     const double *t0 = nullptr;              // null: all zero
-    const long long *orig_off = nullptr;
+    long long *orig_off = nullptr;
+    const int *origins = nullptr;
+    int identity = 0;
     int *bad = nullptr;                      // set to 1 by an invalid input, if not null
     int pad = 0;   // also initialise slots count..pitch-1 as inert padding (a
                    // whole bucket); 0 for a view of a bucket shared with others
@@ -155,6 +160,18 @@ inline int tile_systems(int mapping, int n) {
 hipError_t launch_create(const Bucket *b, int nb, const CallerArrays &in, const RunStart &run,
                          hipStream_t s);
 hipError_t launch_prepare(const Bucket *b, int nb, hipStream_t s);
+// Tables of a fused launch over the small buckets: bucket views from entry
+// first_bucket on with their order, mapping (system per lane where spl_mask
+// has the bit) and list offsets (from first_entry on), and, if lists is not
+// null, the counts and the identity lists.
+struct PersistentTables {
+    Bucket *buckets;
+    int *order, *mapping, *list_base, *counts, *lists;
+    int first_bucket, first_entry;
+    unsigned spl_mask;
+};
+hipError_t launch_persistent_tables(const Bucket *small, int nb, const PersistentTables &t,
+                                    hipStream_t s);
 hipError_t launch_begin_run(const Bucket *b, int nb, const RunStart &run, hipStream_t s);
 // mvs_form: converted to inertial form on the way; acc, jerk and dtn null.
 hipError_t launch_read_back(const Bucket *b, int nb, const StateOut &out, bool mvs_form,

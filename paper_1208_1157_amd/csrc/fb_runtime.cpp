@@ -17,6 +17,7 @@
 #include <climits>
 #include <cmath>
 #include <cstdarg>
+#include <array>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -124,13 +125,19 @@ bool make_layout(int32_t n_sys, const int32_t *n_body, Layout &L)
 {
     if (n_sys < 0 || (n_sys > 0 && !n_body))
         return false;
-    std::vector<int> cnt(kMaxLargeBodies + 1, 0);
-    int64_t nb = 0;
+    // four counters for each n, taken in turn: equal neighbours would wait for
+    // each other's store (131072 x 3: 0.2 ms with one)
+    std::vector<std::array<int, 4>> part(kMaxLargeBodies + 1, {0, 0, 0, 0});
     for (int s = 0; s < n_sys; ++s) {
         if (n_body[s] < 2 || n_body[s] > kMaxLargeBodies)
             return false;
-        cnt[n_body[s]]++;
-        nb += n_body[s];
+        part[n_body[s]][s & 3]++;
+    }
+    std::vector<int> cnt(kMaxLargeBodies + 1, 0);
+    int64_t nb = 0;
+    for (int n = 2; n <= kMaxLargeBodies; ++n) {
+        cnt[n] = part[n][0] + part[n][1] + part[n][2] + part[n][3];
+        nb += (int64_t)n * cnt[n];
     }
     L.n_bodies = nb;
     size_t off = 0;
@@ -208,17 +215,6 @@ std::vector<Bucket> bucket_views(char *base, const Layout &L)
     return out;
 }
 
-std::vector<int> slot_origins(const std::vector<int32_t> &n_body, const Bucket &B)
-{
-    std::vector<int> v;
-    v.reserve(B.pitch);
-    for (size_t s = 0; s < n_body.size(); ++s)
-        if (n_body[s] == B.n)
-            v.push_back((int)s);
-    v.resize(B.pitch, 0);
-    return v;
-}
-
 }  // namespace rt
 }  // namespace fb
 
@@ -246,7 +242,8 @@ struct fb_ensemble {
     int *d_counts[2] = {nullptr, nullptr};
     int *d_order = nullptr;
     int *d_mapping = nullptr;
-    int *h_pinned = nullptr;        // pinned host ints for control reads
+    HostBlock host;                 // pinned page for control reads
+    int *h_pinned = nullptr;        // ... as ints
     hipStream_t capture_stream = nullptr;
     // What the state rows hold: (x, v, a0, j0) ready for Hermite; the MVS
     // variables; or (x, v) with (a0, j0) stale after a Runge-Kutta run.
@@ -281,67 +278,80 @@ fb_status bind_layout(fb_ensemble *e)
     return FB_OK;
 }
 
-// Upload the host-side tables (bucket views, slot -> caller index map, body
-// offsets, list bases) with synchronous copies; the staging of the inputs
-// must already be enqueued or resident.
-fb_status upload_tables(fb_ensemble *e)
-{
-    const int ns = e->n_sys;
-    std::vector<long long> off(ns + 1, 0);
-    for (int s = 0; s < ns; ++s)
-        off[s + 1] = off[s] + e->n_body[s];
-    FB_HIP(hipMemcpyAsync(e->d_orig_off, off.data(), sizeof(long long) * (ns + 1),
-                          hipMemcpyHostToDevice, e->stream));
-    std::vector<int> list_base;
-    int acc = 0;
-    std::vector<std::vector<int>> origins;
-    for (const Bucket &B : e->buckets) {
-        origins.push_back(slot_origins(e->n_body, B));
-        FB_HIP(hipMemcpyAsync(B.orig, origins.back().data(), sizeof(int) * B.pitch,
-                              hipMemcpyHostToDevice, e->stream));
-        list_base.push_back(acc);
-        acc += B.pitch;
-    }
-    const int nbk = (int)e->buckets.size();
-    if (nbk) {
-        FB_HIP(hipMemcpyAsync(e->d_buckets, e->buckets.data(), sizeof(Bucket) * nbk,
-                              hipMemcpyHostToDevice, e->stream));
-        FB_HIP(hipMemcpyAsync(e->d_list_base, list_base.data(), sizeof(int) * nbk,
-                              hipMemcpyHostToDevice, e->stream));
-        std::vector<int> order(nbk);
-        for (int i = 0; i < nbk; ++i)
-            order[i] = i;   // buckets are laid out in descending n already
-        FB_HIP(hipMemcpyAsync(e->d_order, order.data(), sizeof(int) * nbk, hipMemcpyHostToDevice,
-                              e->stream));
-    }
-    // the vectors above die at return: wait for the copies
-    FB_HIP(hipStreamSynchronize(e->stream));
-    return FB_OK;
-}
-
 hipError_t begin_run(fb_ensemble *e, const RunStart &run)
 {
     return launch_begin_run(e->buckets.data(), (int)e->buckets.size(), run, e->stream);
 }
 
+// Lay out the inputs and evaluate (a0, j0).  Systems of one body count are
+// their own slots and k_create fills the tables; otherwise the body offsets
+// and, bucket by bucket, the systems in slot order come from here, the latter
+// through the end of the staging area, past what fb_ensemble_create put there.
 fb_status finish_create(fb_ensemble *e, const double *d_mass, const double *d_pos,
                         const double *d_vel, const double *d_t0)
 {
-    fb_status st = upload_tables(e);
-    if (st != FB_OK)
-        return st;
-    FB_HIP(launch_reset_counter(e->d_ints, 64, e->stream));
+    const int nbk = (int)e->buckets.size();
+    const size_t ns = (size_t)e->n_sys;
     CallerArrays in;
     in.mass = d_mass;
     in.pos = d_pos;
     in.vel = d_vel;
     in.t0 = d_t0;
-    in.orig_off = e->d_orig_off;
     in.bad = e->d_ints;
     in.pad = 1;
-    FB_HIP(launch_create(e->buckets.data(), (int)e->buckets.size(), in, RunStart(), e->stream));
-    FB_HIP(hipMemcpyAsync(e->h_pinned, e->d_ints, sizeof(int), hipMemcpyDeviceToHost, e->stream));
-    FB_HIP(hipStreamSynchronize(e->stream));
+    in.orig_off = e->d_orig_off;
+    std::vector<Bucket> views = e->buckets;
+    HostBlock block;
+    std::vector<char> spill;
+    if (nbk == 1) {
+        in.identity = 1;
+    } else if (nbk > 1) {
+        int *d_origins = reinterpret_cast<int *>(e->d_staging + 7 * (size_t)e->L.n_bodies + ns);
+        const size_t off_bytes = sizeof(long long) * (ns + 1), bytes = off_bytes + sizeof(int) * ns;
+        char *host = nullptr;
+        if (bytes <= kHostBlock) {
+            const fb_status st = take_block(bytes, block);
+            if (st != FB_OK)
+                return st;
+            host = block.p;
+        } else {
+            spill.resize(bytes);
+            host = spill.data();
+        }
+        long long *off = reinterpret_cast<long long *>(host);
+        int *origins = reinterpret_cast<int *>(host + off_bytes);
+        int at[kMaxLargeBodies + 1] = {0}, acc = 0;
+        for (Bucket &B : views) {
+            B.pad = at[B.n] = acc;
+            acc += B.count;
+        }
+        long long bodies = 0;
+        for (size_t k = 0; k < ns; ++k) {
+            const int n = e->n_body[k];
+            off[k] = bodies;
+            bodies += n;
+            origins[at[n]++] = (int)k;
+        }
+        off[ns] = bodies;
+        in.origins = d_origins;
+        hipError_t err = hipMemcpyAsync(e->d_orig_off, off, off_bytes, hipMemcpyHostToDevice, e->stream);
+        if (err == hipSuccess)
+            err = hipMemcpyAsync(d_origins, origins, sizeof(int) * ns, hipMemcpyHostToDevice, e->stream);
+        if (err != hipSuccess) {
+            (void)hipStreamSynchronize(e->stream);
+            give_block(block);
+            return hip_fail(err, "table upload");
+        }
+    }
+    hipError_t err = launch_reset_counter(e->d_ints, 64, e->stream);
+    if (err == hipSuccess)
+        err = launch_create(views.data(), nbk, in, RunStart(), e->stream);
+    if (err == hipSuccess)
+        err = hipMemcpyAsync(e->h_pinned, e->d_ints, sizeof(int), hipMemcpyDeviceToHost, e->stream);
+    const hipError_t es = hipStreamSynchronize(e->stream);   // also: the host tables die here
+    give_block(block);
+    FB_HIP(err);
+    FB_HIP(es);
     if (e->h_pinned[0])
         return fail(FB_E_INVAL, "mass must be finite and >= 0; pos, vel and t0 finite");
     return FB_OK;
@@ -351,11 +361,12 @@ fb_status alloc_common(fb_ensemble *e, void *hip_stream)
 {
     e->stream = (hipStream_t)hip_stream;
     FB_HIP(hipGetDevice(&e->device));
-    hipDeviceProp_t prop;
-    FB_HIP(hipGetDeviceProperties(&prop, e->device));
-    e->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-    FB_HIP(hipHostMalloc((void **)&e->h_pinned, 64 * sizeof(int), hipHostMallocDefault));
-    return FB_OK;
+    int cu = 0;
+    FB_HIP(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, e->device));
+    e->num_cu = cu > 0 ? cu : 256;
+    const fb_status st = take_block(kHostPage, e->host);
+    e->h_pinned = reinterpret_cast<int *>(e->host.p);
+    return st;
 }
 
 void free_ensemble(fb_ensemble *e)
@@ -364,8 +375,7 @@ void free_ensemble(fb_ensemble *e)
         return;
     if (e->owns && e->base)
         (void)hipFree(e->base);
-    if (e->h_pinned)
-        (void)hipHostFree(e->h_pinned);
+    give_block(e->host);
     if (e->capture_stream)
         (void)hipStreamDestroy(e->capture_stream);
     delete e;
@@ -477,36 +487,30 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     const bool compact = o.compact != 0;
     int cls = persistent_class(p0, small, adv, e->num_cu);
 
-    // Lists (identity) and counts of every bucket; mapping and tile order of
-    // the small buckets.
-    std::vector<int> counts(nbk, 0), order, ident;
-    for (int i = n_large; i < nbk; ++i) {
-        order.push_back(i);
-        counts[i] = e->buckets[i].count;
-    }
-    ident.reserve(e->L.list_total);
-    for (const Bucket &B : e->buckets)
-        for (int s = 0; s < B.pitch; ++s)
-            ident.push_back(s);
-    if (nb_small)
-        FB_HIP(hipMemcpyAsync(e->d_order, order.data(), sizeof(int) * nb_small,
-                              hipMemcpyHostToDevice, e->stream));
-    FB_HIP(hipMemcpyAsync(e->d_lists[0], ident.data(), sizeof(int) * ident.size(),
-                          hipMemcpyHostToDevice, e->stream));
-    FB_HIP(hipMemcpyAsync(e->d_counts[0], counts.data(), sizeof(int) * nbk, hipMemcpyHostToDevice,
-                          e->stream));
-    std::vector<int> mapping(nbk, MAP_BPL);
+    // Identity lists, counts, mapping and tile order of the small buckets.
+    PersistentTables tables;
+    tables.buckets = e->d_buckets;
+    tables.order = e->d_order;
+    tables.mapping = e->d_mapping;
+    tables.list_base = e->d_list_base;
+    tables.counts = e->d_counts[0];
+    tables.lists = e->d_lists[0];
+    tables.first_bucket = n_large;
+    tables.first_entry = 0;
+    for (int i = 0; i < n_large; ++i)
+        tables.first_entry += e->buckets[i].pitch;
     int grid = 1;
     // Per-bucket mappings and grid of fused-kernel class c.
     auto set_class = [&](int c) -> hipError_t {
         const int spl_lim = persistent_spl_limit(c, adv ? 1 : 0);
-        for (int i = n_large; i < nbk; ++i) {
-            const int n = e->buckets[i].n;
+        tables.spl_mask = 0;
+        for (int i = 0; i < nb_small; ++i) {
+            const int n = small[i].n;
             const int m = get_plan(n).mapping;
             // in the system-per-lane class every bucket that can runs system-
             // per-lane, unless its plan asks for body-per-lane
-            mapping[i] = (n <= spl_lim && m != MAP_BPL && (m == MAP_SPL || c == 1)) ? MAP_SPL
-                                                                                   : MAP_BPL;
+            if (n <= spl_lim && m != MAP_BPL && (m == MAP_SPL || c == 1))
+                tables.spl_mask |= 1u << i;
         }
         int gpc = p0.groups_per_cu > 0 ? p0.groups_per_cu : 8;
         const int occ = persistent_max_groups_per_cu(adv ? 1 : 0, c, W);
@@ -514,13 +518,10 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
             gpc = std::min(gpc, occ);
         grid = std::max(1, gpc * e->num_cu);
         cls = c;
-        hipError_t err = hipMemcpyAsync(e->d_mapping, mapping.data(), sizeof(int) * nbk,
-                                        hipMemcpyHostToDevice, e->stream);
-        if (err == hipSuccess)   // the host vector is rewritten by the next switch
-            err = hipStreamSynchronize(e->stream);
-        return err;
+        return nb_small ? launch_persistent_tables(small.data(), nb_small, tables, e->stream) : hipSuccess;
     };
-    FB_HIP(set_class(cls));   // also waits for the copies above (host vectors die at return)
+    FB_HIP(set_class(cls));
+    tables.lists = nullptr;   // a class switch rewrites the mapping only
 
     ActiveLists AL[2];
     for (int k = 0; k < 2; ++k) {
@@ -1349,18 +1350,9 @@ fb_status fb_get_state(fb_ensemble *e, double *pos, double *vel, double *t, int3
     out.status = status ? d_status : nullptr;
     out.steps = steps ? d_steps : nullptr;
     FB_HIP(launch_read_back(e->buckets.data(), (int)e->buckets.size(), out, e->mvs_form(), e->stream));
-    if (pos)
-        FB_HIP(hipMemcpyAsync(pos, d_pos, 24 * N, hipMemcpyDeviceToHost, e->stream));
-    if (vel)
-        FB_HIP(hipMemcpyAsync(vel, d_vel, 24 * N, hipMemcpyDeviceToHost, e->stream));
-    if (t)
-        FB_HIP(hipMemcpyAsync(t, d_t, 8 * ns, hipMemcpyDeviceToHost, e->stream));
-    if (steps)
-        FB_HIP(hipMemcpyAsync(steps, d_steps, 8 * ns, hipMemcpyDeviceToHost, e->stream));
-    if (status)
-        FB_HIP(hipMemcpyAsync(status, d_status, 4 * ns, hipMemcpyDeviceToHost, e->stream));
-    FB_HIP(hipStreamSynchronize(e->stream));
-    return FB_OK;
+    const HostPart parts[] = {{pos, d_pos, 24 * N}, {vel, d_vel, 24 * N}, {t, d_t, 8 * ns},
+                              {steps, d_steps, 8 * ns}, {status, d_status, 4 * ns}};
+    return read_to_host(parts, 5, e->stream);
 }
 
 fb_status fb_get_hermite_state(fb_ensemble *e, double *acc0, double *jerk0, double *dt_next)
@@ -1385,14 +1377,8 @@ fb_status fb_get_hermite_state(fb_ensemble *e, double *acc0, double *jerk0, doub
     out.jerk = jerk0 ? d_jerk : nullptr;
     out.dtn = dt_next ? d_dtn : nullptr;
     FB_HIP(launch_read_back(e->buckets.data(), (int)e->buckets.size(), out, false, e->stream));
-    if (acc0)
-        FB_HIP(hipMemcpyAsync(acc0, d_acc, 24 * N, hipMemcpyDeviceToHost, e->stream));
-    if (jerk0)
-        FB_HIP(hipMemcpyAsync(jerk0, d_jerk, 24 * N, hipMemcpyDeviceToHost, e->stream));
-    if (dt_next)
-        FB_HIP(hipMemcpyAsync(dt_next, d_dtn, 8 * ns, hipMemcpyDeviceToHost, e->stream));
-    FB_HIP(hipStreamSynchronize(e->stream));
-    return FB_OK;
+    const HostPart parts[] = {{acc0, d_acc, 24 * N}, {jerk0, d_jerk, 24 * N}, {dt_next, d_dtn, 8 * ns}};
+    return read_to_host(parts, 3, e->stream);
 }
 
 fb_status fb_diagnostics(fb_ensemble *e, double *energy, double *angmom)
@@ -1404,12 +1390,8 @@ fb_status fb_diagnostics(fb_ensemble *e, double *energy, double *angmom)
         return FB_OK;
     double *d_E = e->d_diag, *d_L = d_E + ns;
     FB_HIP(launch_diag(e->buckets.data(), (int)e->buckets.size(), d_E, d_L, e->mvs_form(), e->stream));
-    if (energy)
-        FB_HIP(hipMemcpyAsync(energy, d_E, 8 * ns, hipMemcpyDeviceToHost, e->stream));
-    if (angmom)
-        FB_HIP(hipMemcpyAsync(angmom, d_L, 24 * ns, hipMemcpyDeviceToHost, e->stream));
-    FB_HIP(hipStreamSynchronize(e->stream));
-    return FB_OK;
+    const HostPart parts[] = {{energy, d_E, 8 * ns}, {angmom, d_L, 24 * ns}};
+    return read_to_host(parts, 2, e->stream);
 }
 
 fb_status fb_ensemble_shape(const fb_ensemble *e, int32_t *n_sys, int64_t *n_bodies)

@@ -119,8 +119,29 @@ struct Layout {
 
 bool make_layout(int32_t n_sys, const int32_t *n_body, Layout &L);
 std::vector<Bucket> bucket_views(char *base, const Layout &L);
-// Caller's system index of every slot of bucket B (padding slots -> 0).
-std::vector<int> slot_origins(const std::vector<int32_t> &n_body, const Bucket &B);
+
+// ---- transfers (fb_transfer.cpp) ------------------------------------------
+// Pinned host memory of the current device: kHostPage bytes, or kHostBlock for
+// more.  Whoever takes a block gives it back once nothing on the device uses
+// it; a few of each size are kept for the next taker.
+constexpr size_t kHostPage = 4096, kHostBlock = 1 << 20;
+constexpr int kReadWorkers = 4;
+struct HostBlock {
+    char *p = nullptr;
+    size_t bytes = 0;
+    hipStream_t stream = nullptr;   // for transfers of its own, made by the first one
+    int device = -1;
+};
+fb_status take_block(size_t bytes, HostBlock &out);
+void give_block(HostBlock &b);
+// Device ranges of one allocation -> host arrays (parts with a null `to` are
+// left out), after the work on stream s; returns when they are there.
+struct HostPart {
+    void *to;
+    const void *from;
+    size_t bytes;
+};
+fb_status read_to_host(const HostPart *parts, int n, hipStream_t s);
 
 }  // namespace rt
 }  // namespace fb

@@ -223,7 +223,8 @@ struct Request {
     size_t aux_off = 0;
     bool has_aux = false;
     std::vector<Piece> pieces;
-    std::vector<long long> off;
+    std::vector<char> image;      // upload that did not fit the pinned memory
+    const char *read_at = nullptr;   // its results there, until the quantum has ended
     long long total_steps = 0, done_steps = 0;
     double flops_per_step = 0.0;   // all its systems, one step each
     double t_submit = 0.0, t_admit = 0.0, t_done = 0.0;
@@ -286,16 +287,17 @@ struct fb_server {
     char *d_arena = nullptr;
     Arena arena;
     std::vector<std::unique_ptr<Chunk>> pool[kMaxBodies + 1];
-    Bucket *d_buckets = nullptr;
-    int cap_buckets = 0;
-    Tile *d_tiles = nullptr;
-    int cap_tiles = 0;
-    int *d_list = nullptr;
-    size_t cap_list = 0;
-    int *d_ints = nullptr;   // [0] ntiles, [1] head
+    char *d_tables = nullptr;   // a quantum's control ints, buckets, tiles and slot list
+    size_t cap_tables = 0;
     std::vector<Bucket> h_buckets;
     std::vector<Tile> h_tiles;
     std::vector<int> h_list;
+    // Pinned memory that a cycle's uploads and read-backs go through, as far as
+    // they fit (the rest through ordinary memory); free again after the
+    // quantum's synchronisation.
+    HostBlock host;
+    size_t host_used = 0;
+    std::vector<char> h_tables;
 
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -430,6 +432,7 @@ void drop_payload(Request *R, bool outputs)
     std::vector<double>().swap(R->mass);
     std::vector<double>().swap(R->pos);
     std::vector<double>().swap(R->vel);
+    std::vector<char>().swap(R->image);
     if (outputs) {
         std::vector<double>().swap(R->out_pos);
         std::vector<double>().swap(R->out_vel);
@@ -448,36 +451,56 @@ void release_request(fb_server *S, Request *R)
     }
 }
 
+// `bytes` of this cycle's pinned memory; null if it does not hold them.
+char *host_take(fb_server *S, size_t bytes)
+{
+    if (!S->host.p || bytes > S->host.bytes - S->host_used)
+        return nullptr;
+    char *p = S->host.p + S->host_used;
+    S->host_used += std::min(align_up(bytes, 64), S->host.bytes - S->host_used);
+    return p;
+}
+
+// Upload a request (offsets, mass, pos, vel and its systems in slot order:
+// one image of its aux block) and lay it out.
 fb_status admit_one(fb_server *S, Request *R)
 {
     char *aux = S->arena.base() + R->aux_off;
-    const int ns = R->n_sys;
-    const size_t N = (size_t)R->n_bodies;
-    R->off.assign(ns + 1, 0);
-    for (int s = 0; s < ns; ++s)
-        R->off[s + 1] = R->off[s] + R->n_body[s];
-    long long *d_off = reinterpret_cast<long long *>(aux + R->aux.off_idx);
-    double *stg = reinterpret_cast<double *>(aux + R->aux.staging);
-    int *d_flag = reinterpret_cast<int *>(aux + R->aux.flag);
-    FB_HIP(hipMemcpyAsync(d_off, R->off.data(), sizeof(long long) * (ns + 1), hipMemcpyHostToDevice,
-                          S->stream));
-    if (N) {
-        FB_HIP(hipMemcpyAsync(stg, R->mass.data(), 8 * N, hipMemcpyHostToDevice, S->stream));
-        FB_HIP(hipMemcpyAsync(stg + N, R->pos.data(), 24 * N, hipMemcpyHostToDevice, S->stream));
-        FB_HIP(hipMemcpyAsync(stg + 4 * N, R->vel.data(), 24 * N, hipMemcpyHostToDevice, S->stream));
+    const size_t N = (size_t)R->n_bodies, ns = (size_t)R->n_sys;
+    const size_t stg_at = R->aux.staging - R->aux.off_idx;
+    const size_t origins_at = stg_at + 8 * std::max(7 * N, 6 * N + 2 * ns);
+    const size_t bytes = origins_at + 4 * ns;
+    char *h = host_take(S, bytes);
+    if (!h) {
+        R->image.resize(bytes);
+        h = R->image.data();
     }
+    long long *off = reinterpret_cast<long long *>(h);
+    off[0] = 0;
+    for (size_t s = 0; s < ns; ++s)
+        off[s + 1] = off[s] + R->n_body[s];
+    double *hs = reinterpret_cast<double *>(h + stg_at);
+    std::copy(R->mass.begin(), R->mass.end(), hs);
+    std::copy(R->pos.begin(), R->pos.end(), hs + N);
+    std::copy(R->vel.begin(), R->vel.end(), hs + 4 * N);
+    int *origins = reinterpret_cast<int *>(h + origins_at);
     std::vector<Bucket> views;
+    int at = 0;
     for (const Piece &p : R->pieces) {
         views.push_back(p.view());
-        FB_HIP(hipMemcpyAsync(views.back().orig, p.orig.data(), sizeof(int) * p.count,
-                              hipMemcpyHostToDevice, S->stream));
+        views.back().pad = at;
+        std::copy(p.orig.begin(), p.orig.end(), origins + at);
+        at += p.count;
     }
+    FB_HIP(hipMemcpyAsync(aux + R->aux.off_idx, h, bytes, hipMemcpyHostToDevice, S->stream));
+    const double *stg = reinterpret_cast<const double *>(aux + R->aux.staging);
     CallerArrays in;
     in.mass = stg;
     in.pos = stg + N;
     in.vel = stg + 4 * N;
-    in.orig_off = d_off;
-    in.bad = d_flag;
+    in.orig_off = reinterpret_cast<long long *>(aux + R->aux.off_idx);
+    in.origins = reinterpret_cast<const int *>(aux + R->aux.off_idx + origins_at);
+    in.bad = reinterpret_cast<int *>(aux + R->aux.flag);
     FB_HIP(launch_create(views.data(), (int)views.size(), in, start_to(R->t_end, R->dt, 0, 0.0),
                          S->stream));
     R->total_steps = schedule_steps(0.0, R->t_end, R->dt);
@@ -485,11 +508,12 @@ fb_status admit_one(fb_server *S, Request *R)
     return FB_OK;
 }
 
+// Enqueue a request's read-back: pos | vel | t | steps | status in one copy
+// to pinned memory (finish_copy takes them from there), or into its results.
 fb_status finish_one(fb_server *S, Request *R)
 {
     char *aux = S->arena.base() + R->aux_off;
     const size_t N = (size_t)R->n_bodies, ns = (size_t)R->n_sys;
-    const long long *d_off = reinterpret_cast<const long long *>(aux + R->aux.off_idx);
     double *stg = reinterpret_cast<double *>(aux + R->aux.staging);
     double *d_pos = stg, *d_vel = stg + 3 * N, *d_t = stg + 6 * N;
     long long *d_steps = reinterpret_cast<long long *>(d_t + ns);
@@ -498,7 +522,7 @@ fb_status finish_one(fb_server *S, Request *R)
     for (const Piece &p : R->pieces)
         views.push_back(p.view());
     StateOut out;
-    out.orig_off = d_off;
+    out.orig_off = reinterpret_cast<const long long *>(aux + R->aux.off_idx);
     out.pos = d_pos;
     out.vel = d_vel;
     out.t = d_t;
@@ -510,18 +534,38 @@ fb_status finish_one(fb_server *S, Request *R)
     R->out_t.resize(ns);
     R->out_status.resize(ns);
     R->out_steps.resize(ns);
-    if (N) {
-        FB_HIP(hipMemcpyAsync(R->out_pos.data(), d_pos, 24 * N, hipMemcpyDeviceToHost, S->stream));
-        FB_HIP(hipMemcpyAsync(R->out_vel.data(), d_vel, 24 * N, hipMemcpyDeviceToHost, S->stream));
+    if (ns == 0)
+        return FB_OK;
+    const size_t bytes = 8 * (6 * N + 2 * ns) + 4 * ns;
+    char *h = host_take(S, bytes);
+    R->read_at = h;
+    if (h) {
+        FB_HIP(hipMemcpyAsync(h, stg, bytes, hipMemcpyDeviceToHost, S->stream));
+        return FB_OK;
     }
-    if (ns) {
-        FB_HIP(hipMemcpyAsync(R->out_t.data(), d_t, 8 * ns, hipMemcpyDeviceToHost, S->stream));
-        FB_HIP(hipMemcpyAsync(R->out_steps.data(), d_steps, 8 * ns, hipMemcpyDeviceToHost,
-                              S->stream));
-        FB_HIP(hipMemcpyAsync(R->out_status.data(), d_status, 4 * ns, hipMemcpyDeviceToHost,
-                              S->stream));
-    }
+    FB_HIP(hipMemcpyAsync(R->out_pos.data(), d_pos, 24 * N, hipMemcpyDeviceToHost, S->stream));
+    FB_HIP(hipMemcpyAsync(R->out_vel.data(), d_vel, 24 * N, hipMemcpyDeviceToHost, S->stream));
+    FB_HIP(hipMemcpyAsync(R->out_t.data(), d_t, 8 * ns, hipMemcpyDeviceToHost, S->stream));
+    FB_HIP(hipMemcpyAsync(R->out_steps.data(), d_steps, 8 * ns, hipMemcpyDeviceToHost, S->stream));
+    FB_HIP(hipMemcpyAsync(R->out_status.data(), d_status, 4 * ns, hipMemcpyDeviceToHost, S->stream));
     return FB_OK;
+}
+
+void finish_copy(Request *R)
+{
+    if (!R->read_at)
+        return;
+    const char *h = R->read_at;
+    auto take = [&](void *to, size_t bytes) {
+        std::memcpy(to, h, bytes);
+        h += bytes;
+    };
+    take(R->out_pos.data(), 8 * R->out_pos.size());
+    take(R->out_vel.data(), 8 * R->out_vel.size());
+    take(R->out_t.data(), 8 * R->out_t.size());
+    take(R->out_steps.data(), 8 * R->out_steps.size());
+    take(R->out_status.data(), 4 * R->out_status.size());
+    R->read_at = nullptr;
 }
 
 template <class T>
@@ -735,25 +779,26 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
     for (const Item &it : items)
         S->h_tiles.push_back(it.t);
     const int nb = (int)S->h_buckets.size(), nt = (int)S->h_tiles.size();
-    size_t cb = (size_t)S->cap_buckets, ct = (size_t)S->cap_tiles;
-    fb_status stc = grow(S->d_buckets, cb, (size_t)nb);
-    if (stc == FB_OK)
-        stc = grow(S->d_tiles, ct, (size_t)nt);
-    if (stc == FB_OK)
-        stc = grow(S->d_list, S->cap_list, S->h_list.size());
-    S->cap_buckets = (int)cb;
-    S->cap_tiles = (int)ct;
-    if (stc != FB_OK)
-        return stc;
-    int ints[2] = {nt, 0};   // must outlive the asynchronous copy (synchronised below)
     if (nt > 0) {
-        FB_HIP(hipMemcpyAsync(S->d_buckets, S->h_buckets.data(), sizeof(Bucket) * nb,
-                              hipMemcpyHostToDevice, S->stream));
-        FB_HIP(hipMemcpyAsync(S->d_tiles, S->h_tiles.data(), sizeof(Tile) * nt,
-                              hipMemcpyHostToDevice, S->stream));
-        FB_HIP(hipMemcpyAsync(S->d_list, S->h_list.data(), sizeof(int) * S->h_list.size(),
-                              hipMemcpyHostToDevice, S->stream));
-        FB_HIP(hipMemcpyAsync(S->d_ints, ints, sizeof ints, hipMemcpyHostToDevice, S->stream));
+        const size_t buckets_at = 256, tiles_at = buckets_at + align_up(sizeof(Bucket) * nb, 64),
+                     list_at = tiles_at + align_up(sizeof(Tile) * nt, 64),
+                     bytes = list_at + sizeof(int) * S->h_list.size();
+        const fb_status stc = grow(S->d_tables, S->cap_tables, bytes);
+        if (stc != FB_OK)
+            return stc;
+        char *h = host_take(S, bytes);
+        if (!h) {
+            S->h_tables.resize(bytes);
+            h = S->h_tables.data();
+        }
+        int *ints = reinterpret_cast<int *>(h);
+        ints[0] = nt;   // tiles, and the head of their queue
+        ints[1] = 0;
+        std::memcpy(h + buckets_at, S->h_buckets.data(), sizeof(Bucket) * nb);
+        std::memcpy(h + tiles_at, S->h_tiles.data(), sizeof(Tile) * nt);
+        std::memcpy(h + list_at, S->h_list.data(), sizeof(int) * S->h_list.size());
+        FB_HIP(hipMemcpyAsync(S->d_tables, h, bytes, hipMemcpyHostToDevice, S->stream));
+        int *d_ints = reinterpret_cast<int *>(S->d_tables);
         StepParams P;
         P.adaptive = 0;
         P.stop_rules = 0;
@@ -764,7 +809,9 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
         P.pad = 0;
         const int grid = std::max(1, std::min(gpc * S->num_cu, nt));
         ProfScope ps(S->stream);
-        FB_HIP(launch_persistent(S->d_buckets, S->d_tiles, S->d_ints, S->d_ints + 1, S->d_list, P,
+        FB_HIP(launch_persistent(reinterpret_cast<const Bucket *>(S->d_tables + buckets_at),
+                                 reinterpret_cast<const Tile *>(S->d_tables + tiles_at), d_ints,
+                                 d_ints + 1, reinterpret_cast<const int *>(S->d_tables + list_at), P,
                                  0, cls, grid, W, nullptr, S->stream));
     }
     for (Request *R : sched) {
@@ -779,6 +826,8 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
                 return s2;
         }
     FB_HIP(hipStreamSynchronize(S->stream));
+    for (Request *R : finished)
+        finish_copy(R);
     return FB_OK;
 }
 
@@ -816,6 +865,7 @@ void worker_main(fb_server *S)
             }
         }
         fb_status err = FB_OK;
+        S->host_used = 0;   // the last quantum synchronised
         for (Request *R : admitted) {
             err = admit_one(S, R);
             if (err != FB_OK)
@@ -979,9 +1029,9 @@ fb_status fb_server_create(const fb_server_opts *po, void *hip_stream, fb_server
     S->opts = o;
     std::memset(&S->st, 0, sizeof S->st);
     FB_HIP(hipGetDevice(&S->device));
-    hipDeviceProp_t prop;
-    FB_HIP(hipGetDeviceProperties(&prop, S->device));
-    S->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+    int cu = 0;
+    FB_HIP(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, S->device));
+    S->num_cu = cu > 0 ? cu : 256;
     const Plan p0 = get_plan(0);
     S->cls = p0.mapping == MAP_SPL ? 1 : 0;
     S->waves_per_group = std::max(1, std::min(4, p0.waves_per_group));
@@ -1004,12 +1054,12 @@ fb_status fb_server_create(const fb_server_opts *po, void *hip_stream, fb_server
         return hip_fail(e, "hipMalloc(server budget)");
     }
     S->arena.reset(S->d_arena, o.budget_bytes);
-    e = hipMalloc((void **)&S->d_ints, 64 * sizeof(int));
-    if (e != hipSuccess) {
+    const fb_status sb = take_block(kHostBlock, S->host);
+    if (sb != FB_OK) {
         (void)hipFree(S->d_arena);
         if (S->own_stream)
             (void)hipStreamDestroy(S->stream);
-        return hip_fail(e, "hipMalloc(server control)");
+        return sb;
     }
     fb_server *raw = S.release();
     raw->worker = std::thread(worker_main, raw);
@@ -1194,14 +1244,9 @@ fb_status fb_server_destroy(fb_server *S)
     if (S->worker.joinable())
         S->worker.join();
     (void)hipStreamSynchronize(S->stream);
-    if (S->d_tiles)
-        (void)hipFree(S->d_tiles);
-    if (S->d_list)
-        (void)hipFree(S->d_list);
-    if (S->d_buckets)
-        (void)hipFree(S->d_buckets);
-    if (S->d_ints)
-        (void)hipFree(S->d_ints);
+    if (S->d_tables)
+        (void)hipFree(S->d_tables);
+    give_block(S->host);
     if (S->d_arena)
         (void)hipFree(S->d_arena);
     if (S->own_stream)

@@ -11,6 +11,8 @@
 // 131072 x 3 in 20 us (20 before) and 18 (29).
 #include "fb_bpl.h"
 
+#include <algorithm>
+
 namespace fb {
 namespace {
 
@@ -23,6 +25,27 @@ __device__ __forceinline__ int bucket_of(const BucketSet &set, const int tile)
     while (k < set.count && tile >= set.first[k + 1])
         ++k;
     return k;
+}
+
+// The caller's system in a slot; the storing lane keeps it in the tables.
+__device__ __forceinline__ int origin_of(const CallerArrays &in, const Bucket &B, const int slot,
+                                         const bool store)
+{
+    if (in.identity) {
+        if (store && in.orig_off) {
+            B.orig[slot] = slot;
+            in.orig_off[slot] = (long long)slot * B.n;
+            if (slot == B.count - 1)
+                in.orig_off[slot + 1] = (long long)(slot + 1) * B.n;
+        }
+        return slot;
+    }
+    if (!in.origins)
+        return B.orig[slot];
+    const int o = in.origins[B.pad + slot];
+    if (store)
+        B.orig[slot] = o;
+    return o;
 }
 
 // Layout of the caller's arrays (or, AOS false, of the rows already there)
@@ -54,8 +77,8 @@ __global__ __launch_bounds__(kBlock) void k_create(BucketSet set, CallerArrays i
     double m = 0.0, x[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
     if (own) {
         if (AOS) {
-            const int o = in.orig_off ? B.orig[slot] : slot;
-            const long long row = (in.orig_off ? in.orig_off[o] : (long long)slot * n) + b;
+            const int o = origin_of(in, B, slot, b == 0);
+            const long long row = (in.identity ? (long long)slot * n : in.orig_off[o]) + b;
             m = in.mass[row];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -132,8 +155,8 @@ __global__ __launch_bounds__(kBlock) void k_layout(Bucket B, CallerArrays in)
         }
         return;
     }
-    const int o = B.orig[slot];
-    const long long row = in.orig_off[o] + b;
+    const int o = origin_of(in, B, slot, b == 0);
+    const long long row = (in.identity ? (long long)slot * n : in.orig_off[o]) + b;
     const double m = in.mass[row];
     bool ok = __builtin_isfinite(m) && m >= 0.0;
     B.st[(R_M * n + b) * pitch + slot] = m;
@@ -282,6 +305,29 @@ __global__ __launch_bounds__(kBlock) void k_read_back_mvs(BucketSet set, StateOu
     }
 }
 
+__global__ __launch_bounds__(kBlock) void k_persistent_tables(BucketSet set, PersistentTables t)
+{
+    int base = t.first_entry;
+    for (int k = 0; k < set.count; ++k) {
+        const Bucket &B = set.b[k];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            const int i = t.first_bucket + k;
+            t.buckets[i] = B;
+            t.order[k] = i;   // buckets are laid out in descending n: longest work first
+            t.mapping[i] = (t.spl_mask >> k) & 1 ? MAP_SPL : MAP_BPL;
+            t.list_base[i] = base;
+            if (t.lists)
+                t.counts[i] = B.count;
+        }
+        if (t.lists && (int)blockIdx.x >= set.first[k] && (int)blockIdx.x < set.first[k + 1]) {
+            const int slot = (blockIdx.x - set.first[k]) * kBlock + threadIdx.x;
+            if (slot < B.pitch)
+                t.lists[base + slot] = slot;
+        }
+        base += B.pitch;
+    }
+}
+
 // Launch over the buckets for which take(B) holds, a set at a time; units(B)
 // is a bucket's number of tiles and `per` the tiles a workgroup takes.
 template <class Take, class Units, class Launch>
@@ -322,7 +368,7 @@ hipError_t launch_create(const Bucket *b, int nb, const CallerArrays &in, const 
         });
     for (int i = 0; i < nb && e == hipSuccess; ++i)
         if (!is_small(b[i]) && b[i].count > 0) {
-            if (!in.orig_off || run.on)
+            if (run.on)
                 return hipErrorInvalidValue;
             const size_t bodies = (size_t)(in.pad ? b[i].pitch : b[i].count) * b[i].n;
             hipLaunchKernelGGL(k_layout, dim3((unsigned)((bodies + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, b[i], in);
@@ -372,6 +418,20 @@ hipError_t launch_read_back(const Bucket *b, int nb, const StateOut &out, bool m
         if (!is_small(b[i]))
             e = launch_unpack_mvs_large(b[i], out, s);
     return e;
+}
+
+hipError_t launch_persistent_tables(const Bucket *small, int nb, const PersistentTables &t,
+                                    hipStream_t s)
+{
+    if (nb > BucketSet::kMost)
+        return hipErrorInvalidValue;
+    BucketSet set;
+    set.clear();
+    for (int i = 0; i < nb; ++i)
+        set.add(small[i], t.lists ? (small[i].pitch + kBlock - 1) / kBlock : 0);
+    hipLaunchKernelGGL(k_persistent_tables, dim3((unsigned)std::max(1, set.first[nb])), dim3(kBlock), 0,
+                       s, set, t);
+    return hipGetLastError();
 }
 
 }  // namespace fb

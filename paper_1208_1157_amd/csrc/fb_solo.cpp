@@ -141,6 +141,7 @@ fb_status solo_run(char *base, const SoloLayout &L, const double *d_mass, double
     in.mass = d_mass;
     in.pos = d_pos;
     in.vel = d_vel;
+    in.identity = 1;
     in.pad = 1;
     FB_HIP(launch_create(&B, 1, in, n_steps > 0 ? start_steps(n_steps, dt) : RunStart(), s));
     if (n_steps > 0) {
