@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libfewbody.so")
-SOURCES = ["fb_kernels.hip", "fb_unrolled.hip", "fb_large.hip", "fb_setup.hip", "fb_mvs.hip", "fb_rkck.hip",
+SOURCES = ["fb_kernels.hip", "fb_unrolled.hip", "fb_split.hip", "fb_large.hip", "fb_setup.hip", "fb_mvs.hip", "fb_rkck.hip",
            "fb_runtime.cpp", "fb_transfer.cpp", "fb_server.cpp",
            "fb_solo.cpp", "fb_probes.hip"]
 

@@ -19,8 +19,9 @@ enum SysStatus {
 };
 
 // MAP_BPLU is body per lane with unrolled partner loops (fb_unrolled.hip);
-// plans ask for either form as MAP_BPL.
-enum Mapping { MAP_SPL = 1, MAP_BPL = 2, MAP_BPLU = 3 };
+// MAP_SPLIT2 and MAP_SPLIT4 give a body 2 or 4 lanes (fb_split.h); plans ask
+// for any of these as MAP_BPL.
+enum Mapping { MAP_SPL = 1, MAP_BPL = 2, MAP_BPLU = 3, MAP_SPLIT2 = 4, MAP_SPLIT4 = 5 };
 
 constexpr int kMaxBodies = 16;         // kernels specialised per n exist for n <= 16
 constexpr int kMaxLargeBodies = 512;   // larger systems run the runtime-n large-n kernels
@@ -147,10 +148,14 @@ struct ActiveLists {
     int *next_count;     // [n_buckets]
 };
 
-inline int spl_tile_systems() { return 64; }
-inline int bpl_tile_systems(int n) { return 64 / n; }
-inline int tile_systems(int mapping, int n) {
-    return mapping == MAP_SPL ? spl_tile_systems() : bpl_tile_systems(n);
+// Systems of a wavefront that gives each body G lanes.
+constexpr int split_systems(int n, int G) { return 64 / (n * G); }
+constexpr int kMinSplit = 5;   // fewer bodies: quads, or too few partners to share
+// Systems of a tile.
+constexpr int tile_systems(int mapping, int n)
+{
+    return mapping == MAP_SPL ? 64
+                              : split_systems(n, mapping == MAP_SPLIT4 ? 4 : mapping == MAP_SPLIT2 ? 2 : 1);
 }
 
 // ---- set-up, start of a run, read-back (fb_setup.hip) ------------------
@@ -161,14 +166,14 @@ hipError_t launch_create(const Bucket *b, int nb, const CallerArrays &in, const 
                          hipStream_t s);
 hipError_t launch_prepare(const Bucket *b, int nb, hipStream_t s);
 // Tables of a fused launch over the small buckets: bucket views from entry
-// first_bucket on with their order, mapping (system per lane where spl_mask
-// has the bit) and list offsets (from first_entry on), and, if lists is not
+// first_bucket on with their order, mapping (map[k] of the k-th) and list
+// offsets (from first_entry on), and, if lists is not
 // null, the counts and the identity lists.
 struct PersistentTables {
     Bucket *buckets;
     int *order, *mapping, *list_base, *counts, *lists;
     int first_bucket, first_entry;
-    unsigned spl_mask;
+    unsigned char map[BucketSet::kMost];
 };
 hipError_t launch_persistent_tables(const Bucket *small, int nb, const PersistentTables &t,
                                     hipStream_t s);
@@ -188,6 +193,9 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group,
 // MAP_BPLU comes here).
 int unrolled_tiles(const Bucket &B);
 hipError_t launch_unrolled(const Bucket &B, const StepParams &P, hipStream_t s);
+// Fixed steps with G (2 or 4) lanes a body, kMinSplit bodies and more
+// (launch_plain with MAP_SPLIT2 and MAP_SPLIT4 comes here).
+hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t s);
 // spl_class: 0 = body-per-lane class fused kernel (256 VGPRs; system-per-
 // lane tiles for n <= kMaxSplPersistent), 1 = system-per-lane class (full
 // register file; system-per-lane tiles for n <= kMaxSplBodies, or

@@ -25,7 +25,7 @@
 //   v1 = vp - 1/2 (a0 - ak) h - (5 j0 + jk) h^2 / 12
 // The a0/j0 parts are folded into per-step bases, so each correction costs
 // four FMAs per component and does not need the corrected velocity.
-#include "fb_bpl.h"
+#include "fb_split.h"
 
 #include <algorithm>
 #include <climits>
@@ -483,6 +483,15 @@ __device__ __noinline__ bool bpl_tile(const Bucket &B, const Tile &T, const int 
     return bpl_run<N, ADV, CLS, kRegs>(B, T.first, T.count, list, Pr, slot);
 }
 
+template <int N, int G>
+__device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const int *list,
+                                        const StepParams &P, int &slot)
+{
+    const StepParams Pr = uniform_params(P);
+    return split_run<N, G>(*reinterpret_cast<BplLds *>(wave_lds_base<sizeof(BplLds), false>()), B,
+                           T.first, T.count, list, Pr, slot);
+}
+
 // Tile dispatch.  The body-per-lane class (SPLC false) keeps the fused
 // kernel at 256 VGPRs (2 waves per SIMD) and runs every tile body-per-lane,
 // partner loops unrolled up to 12 bodies (10 with adaptive steps / stop
@@ -522,6 +531,20 @@ __device__ __forceinline__ bool run_tile(const Bucket &B, const Tile &T, const i
                 case 10: return spl_tile<10, false>(B, T, list, P, slot);
                 default: break;
                 }
+            }
+        }
+    }
+    if constexpr (!ADV && !SPLC) {
+        if (map == MAP_SPLIT4 || map == MAP_SPLIT2) {
+            switch (map == MAP_SPLIT4 ? 32 + n : n) {
+#define FB_SPLIT_CASE(NN)                                        \
+    case NN: return split_tile<NN, 2>(B, T, list, P, slot);      \
+    case 32 + NN: return split_tile<NN, 4>(B, T, list, P, slot);
+                FB_SPLIT_CASE(5) FB_SPLIT_CASE(6) FB_SPLIT_CASE(7) FB_SPLIT_CASE(8)
+                FB_SPLIT_CASE(9) FB_SPLIT_CASE(10) FB_SPLIT_CASE(11) FB_SPLIT_CASE(12)
+                FB_SPLIT_CASE(13) FB_SPLIT_CASE(14) FB_SPLIT_CASE(15) FB_SPLIT_CASE(16)
+#undef FB_SPLIT_CASE
+            default: return false;
             }
         }
     }
@@ -607,7 +630,7 @@ __global__ void k_build_tiles(const Bucket *__restrict__ buckets, int nb,
         for (int i = 0; i < nb; ++i) {
             const int bk = order[i];
             const int n = buckets[bk].n;
-            const int c = (mapping[bk] == MAP_SPL) ? 64 : 64 / n;
+            const int c = tile_systems(mapping[bk], n);
             cap[i] = c;
             start[i] = acc;
             acc += (AL.cur_count[bk] + c - 1) / c;
@@ -1499,6 +1522,8 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
         return hipSuccess;
     if (mapping == MAP_BPLU)   // (bpl_mapping)
         return launch_unrolled(B, P, s);
+    if (mapping == MAP_SPLIT2 || mapping == MAP_SPLIT4)
+        return launch_split(B, mapping == MAP_SPLIT4 ? 4 : 2, P, s);
     const int W = waves_per_group < 1 ? 1 : (waves_per_group > 4 ? 4 : waves_per_group);
     const bool adv = P.adaptive || P.stop_rules;
     if (mapping == MAP_SPL && B.n <= (adv ? kMaxSplAdv : kMaxSplBodies)) {

@@ -500,23 +500,34 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     for (int i = 0; i < n_large; ++i)
         tables.first_entry += e->buckets[i].pitch;
     int grid = 1;
+    Tile *d_tiles = e->d_tiles;
     // Per-bucket mappings and grid of fused-kernel class c.
     auto set_class = [&](int c) -> hipError_t {
         const int spl_lim = persistent_spl_limit(c, adv ? 1 : 0);
-        tables.spl_mask = 0;
-        for (int i = 0; i < nb_small; ++i) {
-            const int n = small[i].n;
-            const int m = get_plan(n).mapping;
-            // in the system-per-lane class every bucket that can runs system-
-            // per-lane, unless its plan asks for body-per-lane
-            if (n <= spl_lim && m != MAP_BPL && (m == MAP_SPL || c == 1))
-                tables.spl_mask |= 1u << i;
-        }
         int gpc = p0.groups_per_cu > 0 ? p0.groups_per_cu : 8;
         const int occ = persistent_max_groups_per_cu(adv ? 1 : 0, c, W);
         if (occ > 0)
             gpc = std::min(gpc, occ);
         grid = std::max(1, gpc * e->num_cu);
+        int body_map = MAP_BPL;
+        if (!adv && c == 0) {
+            std::vector<std::pair<int, long long>> sizes;
+            for (const Bucket &B : small)
+                sizes.emplace_back(B.n, B.count);
+            body_map = fused_split(sizes, e->num_cu, (long long)grid * W);
+        }
+        // (more tiles than one lane a body has: the staging area holds 96
+        // bytes a body and is free during a run)
+        d_tiles = body_map == MAP_BPL ? e->d_tiles : reinterpret_cast<Tile *>(e->d_staging);
+        for (int i = 0; i < nb_small; ++i) {
+            const int n = small[i].n;
+            const int m = get_plan(n).mapping;
+            // in the system-per-lane class every bucket that can runs system-
+            // per-lane, unless its plan asks for body-per-lane
+            tables.map[i] = n <= spl_lim && m != MAP_BPL && (m == MAP_SPL || c == 1) ? MAP_SPL
+                            : n >= kMinSplit                                      ? body_map
+                                                                                  : MAP_BPL;
+        }
         cls = c;
         return nb_small ? launch_persistent_tables(small.data(), nb_small, tables, e->stream) : hipSuccess;
     };
@@ -547,11 +558,11 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         if (nb_small == 0)
             return hipSuccess;
         hipError_t err = launch_build_tiles(e->d_buckets, nb_small, e->d_order, e->d_mapping,
-                                            AL[k], e->d_tiles, d_ntiles, d_head, s);
+                                            AL[k], d_tiles, d_ntiles, d_head, s);
         if (err != hipSuccess)
             return err;
         ActiveLists al = AL[k];
-        return launch_persistent(e->d_buckets, e->d_tiles, d_ntiles, d_head, e->d_lists[k], P,
+        return launch_persistent(e->d_buckets, d_tiles, d_ntiles, d_head, e->d_lists[k], P,
                                  adv ? 1 : 0, cls, grid, W, compact ? &al : nullptr, s);
     };
 

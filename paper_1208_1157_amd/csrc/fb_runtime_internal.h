@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -32,8 +33,37 @@ struct Plan {
 };
 Plan get_plan(int n);
 
+// Wavefronts of `count` n-body systems with a body's partners shared by
+// several lanes, as a SIMD counts them: 5 and 6 bodies fill one with four
+// lanes a body as fast as with two, so they are counted twice there.
+inline long long split_tiles(int n, long long count, int map)
+{
+    const int S = tile_systems(map, n);
+    return (count + S - 1) / S * (map == MAP_SPLIT4 && n <= 6 ? 2 : 1);
+}
+
+// Mapping of the body-per-lane tiles of a fused launch over buckets of
+// (n, count), fixed steps, `waves` of them resident: four lanes a body, or
+// two, from kMinSplit bodies on while all tiles have a wavefront each and no
+// SIMD more than one (fb_split.h has both sides measured), else one.
+template <class Counts>
+int fused_split(const Counts &counts, int num_cu, long long waves)
+{
+    for (int map : {MAP_SPLIT4, MAP_SPLIT2}) {
+        long long tiles = 0;
+        for (const auto &c : counts)
+            tiles += c.first >= kMinSplit ? split_tiles(c.first, c.second, map)
+                                          : (c.second + 64 / c.first - 1) / (64 / c.first);
+        if (tiles <= std::min(4LL * num_cu, waves))
+            return map;
+    }
+    return MAP_BPL;
+}
+
 // Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the
-// unrolled kernels (fb_unrolled.hip, where both sides are measured) for 4..12
+// several-lanes-a-body ones (fb_split.h, measured there) for fixed steps while
+// no SIMD gets more than one of their wavefronts, or the unrolled kernels
+// (fb_unrolled.hip, where both sides are measured) for 4..12
 // bodies (4..10 with adaptive steps or stop rules); for other body counts
 // while their wavefronts are few: 2 and 3 bodies to one per SIMD (the quad
 // layout holds 16 systems a wavefront, the rolled one 32 and 21), 13..16 to
@@ -43,6 +73,10 @@ inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
 {
     if (B.n > kMaxBodies)
         return MAP_BPL;
+    if (!adv && B.n >= kMinSplit)
+        for (int map : {MAP_SPLIT4, MAP_SPLIT2})
+            if (split_tiles(B.n, B.count, map) <= 4LL * num_cu)
+                return map;
     const bool always = B.n >= 4 && B.n <= (adv ? kMaxUnrolledAdv : kMaxUnrolled);
     const int waves_per_simd = B.n >= 13 && !adv ? 4 : 1;
     return always || unrolled_tiles(B) <= 4LL * num_cu * waves_per_simd ? MAP_BPLU : MAP_BPL;

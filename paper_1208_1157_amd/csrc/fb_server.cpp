@@ -741,6 +741,15 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
             groups[order[k]].map = MAP_BPL;
         spread = best_k > 0;
     }
+    if (cls == 0) {
+        std::vector<std::pair<int, long long>> sizes;
+        for (const Group &G : groups)
+            sizes.emplace_back(G.n, G.len);
+        const int map = fused_split(sizes, S->num_cu, (long long)resident_waves);
+        for (Group &G : groups)
+            if (G.n >= kMinSplit)
+                G.map = map;
+    }
     struct Item {
         Tile t;
         double cost;

@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kBlock) void k_persistent_tables(BucketSet set, Per
             const int i = t.first_bucket + k;
             t.buckets[i] = B;
             t.order[k] = i;   // buckets are laid out in descending n: longest work first
-            t.mapping[i] = (t.spl_mask >> k) & 1 ? MAP_SPL : MAP_BPL;
+            t.mapping[i] = t.map[k];
             t.list_base[i] = base;
             if (t.lists)
                 t.counts[i] = B.count;

@@ -1,0 +1,298 @@
+// fb_split.h -- fixed Hermite steps with two or four lanes a body, for wavefronts
+// that are alone on their SIMD.
+#pragma once
+
+#include "fb_bpl.h"
+
+namespace fb {
+namespace {
+
+// A lone wavefront is bound by its own instructions, an interaction after
+// another: 33 each, one evaluation of N - 1 of them after the other.  Here G
+// neighbouring lanes, 2 or 4, hold the same body.  Each works out the terms of
+// its share of the partners (27 instructions each), and the sums run on in the
+// order of bpl_eval: the first lane adds its terms, the next takes the sums
+// over (a quad permute) and adds its own, and the last one's go to all.  So
+// every bit is that of the other Hermite kernels, for three quarters (G = 2) or
+// half to two thirds (4) of the instructions and as many fewer LDS reads.  A
+// wavefront holds a G-th of the systems, so it pays while the device has SIMDs
+// to spare.  Microseconds a step, one lane a body (fb_unrolled.hip), 2, 4, with
+// 0.1 and 1 wavefronts of four lanes a body on a SIMD:
+//   n = 5    0.75 0.62 0.60   0.77 0.68 0.72     n = 10   1.50 1.07 0.89   1.52 1.14 1.05
+//       6    0.89 0.76 0.69   0.91 0.81 0.82         12   1.86 1.25 0.96   1.89 1.30 1.11
+//       8    1.19 0.92 0.76   1.18 0.99 0.90         16   2.38 1.57 1.16   2.42 1.60 1.36
+// and with 1 and 2 wavefronts of two lanes a body, one lane against two:
+//   n = 5    0.83 0.77   1.08 1.26               n = 10   1.67 1.32   2.00 2.34
+//       6    0.98 0.93   1.27 1.58                   12   1.98 1.50   2.21 2.70
+//       8    1.30 1.16   1.65 1.93                   16   2.49 1.88   2.93 3.55
+// hence the lines of bpl_mapping and fused_split.  1000 steps of 1000 x 6 915
+// -> 725 us; 24 requests to a server (3..10 bodies) 15.5 -> 10.4 ms.
+
+// quad_perm controls: every lane of a body's G reads the lane before it (the
+// first itself), or lane k of them.
+template <int G>
+constexpr int share_before()
+{
+    return G == 2 ? 0 | (0 << 2) | (2 << 4) | (2 << 6) : 0 | (0 << 2) | (1 << 4) | (2 << 6);
+}
+template <int G>
+constexpr int share_of(int k)
+{
+    return G == 2 ? k | (k << 2) | ((2 + k) << 4) | ((2 + k) << 6) : k | (k << 2) | (k << 4) | (k << 6);
+}
+
+template <int CTRL>
+__device__ __forceinline__ void share_read3(double (&a)[3])
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const unsigned long long u = __double_as_longlong(a[c]);
+        const int lo = __builtin_amdgcn_mov_dpp((int)(u & 0xffffffffull), CTRL, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, true);
+        a[c] = __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+    }
+}
+
+// One partner's terms: a += mr3 r, j += mr3 w.
+struct SplitTerm {
+    double mr3, r[3], w[3];
+};
+
+// (the expressions of bpl_interact_p)
+__device__ __forceinline__ SplitTerm split_term(const Partner &Pj, const double (&xi)[3],
+                                                const double (&vi)[3])
+{
+    SplitTerm t;
+    const double2 p0 = Pj.p0, p1 = Pj.p1, p2 = Pj.p2;
+    const double rx = p0.x - xi[0], ry = p0.y - xi[1], rz = p1.x - xi[2];
+    const double ux = p1.y - vi[0], uy = p2.x - vi[1], uz = p2.y - vi[2];
+    const double r2 = fma(rz, rz, fma(ry, ry, rx * rx));
+    const double ru = fma(rz, uz, fma(ry, uy, rx * ux));
+    const double ri = rsqrt_nr(r2);
+    const double ri2 = ri * ri;
+    t.mr3 = Pj.mj * (ri2 * ri);
+    const double al = 3.0 * ru * ri2;
+    t.r[0] = rx;
+    t.r[1] = ry;
+    t.r[2] = rz;
+    t.w[0] = fma(-al, rx, ux);
+    t.w[1] = fma(-al, ry, uy);
+    t.w[2] = fma(-al, rz, uz);
+    return t;
+}
+
+__device__ __forceinline__ void split_add(const SplitTerm &t, double (&a)[3], double (&jk)[3])
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        a[c] = fma(t.mr3, t.r[c], a[c]);
+        jk[c] = fma(t.mr3, t.w[c], jk[c]);
+    }
+}
+
+// Place of a lane: its body's LDS entry, which of the body's lanes it is, and
+// its partners' entries and masses.
+template <int N, int G>
+struct SplitSeat {
+    static constexpr int kTerms = (N - 1 + G - 1) / G;            // of every lane but the last
+    static constexpr int kLast = (N - 1 + kTerms - 1) / kTerms - 1;   // the lane of the last partner
+    int entry, share, idx[kTerms];
+    double m[kTerms];
+};
+
+// The sums of lanes K.. of a body, in turn (every lane goes through all turns;
+// lane k's sums are right after turn k).
+template <int N, int G, int K>
+__device__ __forceinline__ void split_turns(const SplitTerm (&t)[SplitSeat<N, G>::kTerms],
+                                            double (&a)[3], double (&jk)[3])
+{
+    using Seat = SplitSeat<N, G>;
+    constexpr int kAdd = K < Seat::kLast ? Seat::kTerms : N - 1 - Seat::kLast * Seat::kTerms;
+#pragma unroll
+    for (int k = 0; k < kAdd; ++k)
+        split_add(t[k], a, jk);
+    if constexpr (K < Seat::kLast) {
+        share_read3<share_before<G>()>(a);
+        share_read3<share_before<G>()>(jk);
+        split_turns<N, G, K + 1>(t, a, jk);
+    }
+}
+
+template <int N, int G>
+__device__ __forceinline__ void split_eval(BplLds &L, const SplitSeat<N, G> &s,
+                                           const double (&xi)[3], const double (&vi)[3],
+                                           double (&a)[3], double (&jk)[3])
+{
+    using Seat = SplitSeat<N, G>;
+    if (s.share == 0) {
+        L.xy[s.entry] = make_double2(xi[0], xi[1]);
+        L.zvx[s.entry] = make_double2(xi[2], vi[0]);
+        L.vyvz[s.entry] = make_double2(vi[1], vi[2]);
+    }
+    wave_sync();
+    Partner p[Seat::kTerms];
+#pragma unroll
+    for (int k = 0; k < Seat::kTerms; ++k)
+        p[k] = Partner{L.xy[s.idx[k]], L.zvx[s.idx[k]], L.vyvz[s.idx[k]], s.m[k]};
+    __builtin_amdgcn_sched_barrier(0);
+    SplitTerm t[Seat::kTerms];
+#pragma unroll
+    for (int k = 0; k < Seat::kTerms; ++k)
+        t[k] = split_term(p[k], xi, vi);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        a[c] = 0.0;
+        jk[c] = 0.0;
+    }
+    split_turns<N, G, 0>(t, a, jk);
+    share_read3<share_of<G>(Seat::kLast)>(a);
+    share_read3<share_of<G>(Seat::kLast)>(jk);
+    wave_sync();
+}
+
+template <int N, int G>
+__device__ __forceinline__ void split_step(BplLds &L, const SplitSeat<N, G> &s, const Coef &k,
+                                           const double (&x)[3], const double (&v)[3],
+                                           const double (&a0)[3], const double (&j0)[3],
+                                           double (&xc)[3], double (&vc)[3], double (&ak)[3],
+                                           double (&jk)[3])
+{
+    double bx[3], bv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        predict_comp(k, x[c], v[c], a0[c], j0[c], xc[c], vc[c], bx[c], bv[c]);
+    split_eval<N, G>(L, s, xc, vc, ak, jk);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
+    split_eval<N, G>(L, s, xc, vc, ak, jk);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
+}
+
+// nrun fixed steps of this lane's system (bpl_fixed_steps).
+template <int N, int G>
+__device__ __forceinline__ void split_fixed_steps(BplLds &L, const SplitSeat<N, G> &s, const Coef &k,
+                                                  const bool live, const int nrun, double (&x)[3],
+                                                  double (&v)[3], double (&a0)[3], double (&j0)[3])
+{
+    const unsigned long long who = __ballot(live && nrun > 0);
+    if (who == 0ull)
+        return;
+    const int n0 = __builtin_amdgcn_readlane(nrun, __builtin_ctzll(who));
+    if (__all(!live || nrun == n0)) {
+#pragma unroll 1
+        for (int q = 0; q < n0; ++q) {
+            double xc[3], vc[3], ak[3], jk[3];
+            split_step<N, G>(L, s, k, x, v, a0, j0, xc, vc, ak, jk);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[c] = xc[c];
+                v[c] = vc[c];
+                a0[c] = ak[c];
+                j0[c] = jk[c];
+            }
+        }
+        return;
+    }
+    int q = 0;
+#pragma unroll 1
+    do {
+        const bool act = q < nrun;
+        double xc[3], vc[3], ak[3], jk[3];
+        split_step<N, G>(L, s, k, x, v, a0, j0, xc, vc, ak, jk);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            x[c] = act ? xc[c] : x[c];
+            v[c] = act ? vc[c] : v[c];
+            a0[c] = act ? ak[c] : a0[c];
+            j0[c] = act ? jk[c] : j0[c];
+        }
+        ++q;
+    } while (__any(q < nrun));
+}
+
+// Integrate one tile (at most split_systems(N, G) systems) for at most P.quantum
+// fixed steps; bpl_run's contract.
+template <int N, int G>
+__device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int first,
+                                          const int count, const int *list, const StepParams &P,
+                                          int &slot_out)
+{
+    constexpr int S = split_systems(N, G), kTerms = SplitSeat<N, G>::kTerms;
+    const int lane = threadIdx.x & 63, j = lane / G;
+    const int braw = j / S;
+    const int b = braw < N ? braw : N - 1;
+    const int sys = j - braw * S;
+    const bool valid = braw < N && sys < count;
+    int slot = 0;
+    if (valid)
+        slot = list ? list[first + sys] : first + sys;
+    slot_out = slot;
+    const size_t pitch = B.pitch;
+    double mi = 0.0, x[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+    double a0[3] = {0.0, 0.0, 0.0}, j0[3] = {0.0, 0.0, 0.0};
+    Clock c{};
+    c.status = ST_DONE;
+    if (valid) {
+        mi = B.st[(R_M * N + b) * pitch + slot];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            x[k] = B.st[((R_X + k) * N + b) * pitch + slot];
+            v[k] = B.st[((R_V + k) * N + b) * pitch + slot];
+            a0[k] = B.st[((R_A + k) * N + b) * pitch + slot];
+            j0[k] = B.st[((R_J + k) * N + b) * pitch + slot];
+        }
+        c = load_clock(B, slot);
+    }
+    const bool live = c.status == ST_ACTIVE;
+    SplitSeat<N, G> s;
+    s.entry = j;   // = braw S + sys
+    s.share = lane & (G - 1);
+    if (s.share == 0)
+        L.mr[j].x = mi;
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k) {
+        // what is past the last partner is not added: any entry
+        const int kk = min(s.share * kTerms + k, N - 2);
+        const int skip = b == 0 ? 1 << 20 : b;
+        const int p = kk < N - 2 ? kk + 1 + (kk + 1 >= skip ? 1 : 0) : (b == 0 ? N - 1 : 0);
+        s.idx[k] = p * S + sys;
+        s.m[k] = L.mr[s.idx[k]].x;
+    }
+    int budget = P.quantum;
+#pragma unroll 1
+    for (int seg = 0; seg < 2; ++seg) {
+        double h = c.dt;
+        const int nrun = run_segment(c, P, seg, budget, h);
+        split_fixed_steps<N, G>(L, s, make_coef(h), live, nrun, x, v, a0, j0);
+        budget -= nrun;
+        run_segment_end(c, P, seg, nrun);
+    }
+    constexpr unsigned long long kBase = [] {
+        unsigned long long m = 0;
+        for (int k = 0; k < N; ++k)
+            m |= 1ull << (G * k * S);
+        return m;
+    }();
+    const unsigned long long bad = __ballot(!(finite3(x) && finite3(v)));
+    if (live && (bad & (kBase << (G * sys))))
+        c.status = ST_NONFINITE;
+    if (live && s.share == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            B.st[((R_X + k) * N + b) * pitch + slot] = x[k];
+            B.st[((R_V + k) * N + b) * pitch + slot] = v[k];
+            B.st[((R_A + k) * N + b) * pitch + slot] = a0[k];
+            B.st[((R_J + k) * N + b) * pitch + slot] = j0[k];
+        }
+        if (b == 0)
+            store_clock(B, slot, c);
+    }
+    return valid && braw == 0 && s.share == 0 && c.status == ST_ACTIVE;
+}
+
+}  // namespace
+}  // namespace fb

@@ -1,0 +1,43 @@
+// fb_split.hip -- fixed Hermite steps of one bucket with two or four lanes a
+// body (fb_split.h).
+#include "fb_split.h"
+
+namespace fb {
+namespace {
+
+template <int N, int G>
+__global__ __launch_bounds__(64) void k_bpl_split(Bucket B, StepParams P)
+{
+    extern __shared__ char fb_dyn_lds[];
+    constexpr int S = split_systems(N, G);
+    const int first = blockIdx.x * S;
+    int slot;
+    split_run<N, G>(*reinterpret_cast<BplLds *>(fb_dyn_lds), B, first, min(S, B.count - first),
+                    nullptr, P, slot);
+}
+
+}  // namespace
+
+hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t s)
+{
+    if (B.count == 0)
+        return hipSuccess;
+    if (P.adaptive || P.stop_rules || (G != 2 && G != 4) || B.n < kMinSplit)
+        return hipErrorInvalidValue;
+    const int S = split_systems(B.n, G);
+    const dim3 grid((unsigned)((B.count + S - 1) / S));
+#define FB_L(NN)                                                                              \
+    case NN:                                                                                  \
+        if (G == 4) hipLaunchKernelGGL((k_bpl_split<NN, 4>), grid, dim3(64), sizeof(BplLds), s, B, P); \
+        else hipLaunchKernelGGL((k_bpl_split<NN, 2>), grid, dim3(64), sizeof(BplLds), s, B, P);        \
+        break
+    switch (B.n) {
+        FB_L(5); FB_L(6); FB_L(7); FB_L(8); FB_L(9); FB_L(10);
+        FB_L(11); FB_L(12); FB_L(13); FB_L(14); FB_L(15); FB_L(16);
+    default: return hipErrorInvalidValue;
+    }
+#undef FB_L
+    return hipGetLastError();
+}
+
+}  // namespace fb
