@@ -68,7 +68,7 @@ __device__ __forceinline__ StepParams uniform_params(const StepParams &P)
     u.r_eject = uniform_d(P.r_eject);
     u.max_steps = uniform_ll(P.max_steps);
     u.quantum = uniform_i(P.quantum);
-    u.pad = 0;
+    u.simds = P.simds;
     return u;
 }
 

@@ -136,7 +136,8 @@ struct StepParams {
     double r_eject;
     long long max_steps; // per-system cap (LLONG_MAX: none)
     int quantum;         // at most this many steps per system per launch
-    int pad;
+    int simds;           // fused launch in one-wavefront workgroups: the device's
+                         // SIMDs, for the placing of a single round (else 0)
 };
 
 // Compaction bookkeeping for the persistent schedule (device memory).

@@ -398,7 +398,7 @@ StepParams make_params(const fb_opts &o, int quantum)
     P.r_eject = o.r_eject;
     P.max_steps = o.max_steps > 0 ? (long long)o.max_steps : LLONG_MAX;
     P.quantum = quantum;
-    P.pad = 0;
+    P.simds = 0;
     return P;
 }
 
@@ -480,12 +480,19 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     const int nb_small = nbk - n_large;
     const std::vector<Bucket> small(e->buckets.begin() + n_large, e->buckets.end());
     const Plan p0 = get_plan(0);
-    const int W = std::max(1, std::min(4, p0.waves_per_group));
     const bool adv = o.adaptive || o.stop_rules;
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
     StepParams P = make_params(o, quantum);
     const bool compact = o.compact != 0;
     int cls = persistent_class(p0, small, adv, e->num_cu);
+    // Tiles that all run at once are placed one by one (place_tile), unless a
+    // plan asks for a class and with it for its workgroups.
+    long long tiles0 = 0;
+    for (const Bucket &B : small)
+        tiles0 += (B.count + 64 / B.n - 1) / (64 / B.n);
+    const bool placed = p0.mapping == 0 && cls == 0 && tiles0 <= 8LL * e->num_cu;
+    const int W = placed ? 1 : std::max(1, std::min(4, p0.waves_per_group));
+    P.simds = placed ? 4 * e->num_cu : 0;
 
     // Identity lists, counts, mapping and tile order of the small buckets.
     PersistentTables tables;

@@ -815,7 +815,7 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
         P.r_eject = 0.0;
         P.max_steps = LLONG_MAX;
         P.quantum = Q;
-        P.pad = 0;
+        P.simds = 0;
         const int grid = std::max(1, std::min(gpc * S->num_cu, nt));
         ProfScope ps(S->stream);
         FB_HIP(launch_persistent(reinterpret_cast<const Bucket *>(S->d_tables + buckets_at),

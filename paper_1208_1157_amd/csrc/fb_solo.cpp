@@ -135,7 +135,7 @@ fb_status solo_run(char *base, const SoloLayout &L, const double *d_mass, double
     P.r_eject = 100.0;
     P.max_steps = LLONG_MAX;
     P.quantum = INT_MAX;
-    P.pad = 0;
+    P.simds = 0;
     const int map = plain_mapping(p, B, false, num_cu > 0 ? num_cu : 256);
     CallerArrays in;
     in.mass = d_mass;
