@@ -194,7 +194,7 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group,
 // MAP_BPLU comes here).
 int unrolled_tiles(const Bucket &B);
 hipError_t launch_unrolled(const Bucket &B, const StepParams &P, hipStream_t s);
-// Fixed steps with G (2 or 4) lanes a body, kMinSplit bodies and more
+// Steps with G (2 or 4) lanes a body, kMinSplit bodies and more
 // (launch_plain with MAP_SPLIT2 and MAP_SPLIT4 comes here).
 hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t s);
 // spl_class: 0 = body-per-lane class fused kernel (256 VGPRs; system-per-

@@ -483,12 +483,12 @@ __device__ __noinline__ bool bpl_tile(const Bucket &B, const Tile &T, const int 
     return bpl_run<N, ADV, CLS, kRegs>(B, T.first, T.count, list, Pr, slot);
 }
 
-template <int N, int G>
+template <int N, int G, bool ADV>
 __device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const int *list,
                                         const StepParams &P, int &slot)
 {
     const StepParams Pr = uniform_params(P);
-    return split_run<N, G>(*reinterpret_cast<BplLds *>(wave_lds_base<sizeof(BplLds), false>()), B,
+    return split_run<N, G, ADV>(*reinterpret_cast<BplLds *>(wave_lds_base<sizeof(BplLds), false>()), B,
                            T.first, T.count, list, Pr, slot);
 }
 
@@ -534,12 +534,12 @@ __device__ __forceinline__ bool run_tile(const Bucket &B, const Tile &T, const i
             }
         }
     }
-    if constexpr (!ADV && !SPLC) {
+    if constexpr (!SPLC) {
         if (map == MAP_SPLIT4 || map == MAP_SPLIT2) {
             switch (map == MAP_SPLIT4 ? 32 + n : n) {
 #define FB_SPLIT_CASE(NN)                                        \
-    case NN: return split_tile<NN, 2>(B, T, list, P, slot);      \
-    case 32 + NN: return split_tile<NN, 4>(B, T, list, P, slot);
+    case NN: return split_tile<NN, 2, ADV>(B, T, list, P, slot);      \
+    case 32 + NN: return split_tile<NN, 4, ADV>(B, T, list, P, slot);
                 FB_SPLIT_CASE(5) FB_SPLIT_CASE(6) FB_SPLIT_CASE(7) FB_SPLIT_CASE(8)
                 FB_SPLIT_CASE(9) FB_SPLIT_CASE(10) FB_SPLIT_CASE(11) FB_SPLIT_CASE(12)
                 FB_SPLIT_CASE(13) FB_SPLIT_CASE(14) FB_SPLIT_CASE(15) FB_SPLIT_CASE(16)

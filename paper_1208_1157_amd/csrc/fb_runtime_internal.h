@@ -43,7 +43,7 @@ inline long long split_tiles(int n, long long count, int map)
 }
 
 // Mapping of the body-per-lane tiles of a fused launch over buckets of
-// (n, count), fixed steps, `waves` of them resident: four lanes a body, or
+// (n, count), `waves` of them resident: four lanes a body, or
 // two, from kMinSplit bodies on while all tiles have a wavefront each and no
 // SIMD more than one (fb_split.h has both sides measured), else one.
 template <class Counts>
@@ -61,7 +61,7 @@ int fused_split(const Counts &counts, int num_cu, long long waves)
 }
 
 // Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the
-// several-lanes-a-body ones (fb_split.h, measured there) for fixed steps while
+// several-lanes-a-body ones (fb_split.h, measured there) while
 // no SIMD gets more than one of their wavefronts, or the unrolled kernels
 // (fb_unrolled.hip, where both sides are measured) for 4..12
 // bodies (4..10 with adaptive steps or stop rules); for other body counts
@@ -73,7 +73,7 @@ inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
 {
     if (B.n > kMaxBodies)
         return MAP_BPL;
-    if (!adv && B.n >= kMinSplit)
+    if (B.n >= kMinSplit)
         for (int map : {MAP_SPLIT4, MAP_SPLIT2})
             if (split_tiles(B.n, B.count, map) <= 4LL * num_cu)
                 return map;

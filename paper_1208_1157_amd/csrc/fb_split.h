@@ -1,8 +1,10 @@
-// fb_split.h -- fixed Hermite steps with two or four lanes a body, for wavefronts
+// fb_split.h -- Hermite steps with two or four lanes a body, for wavefronts
 // that are alone on their SIMD.
 #pragma once
 
 #include "fb_bpl.h"
+
+#include <type_traits>
 
 namespace fb {
 namespace {
@@ -25,6 +27,11 @@ namespace {
 //   n = 5    0.83 0.77   1.08 1.26               n = 10   1.67 1.32   2.00 2.34
 //       6    0.98 0.93   1.27 1.58                   12   1.98 1.50   2.21 2.70
 //       8    1.30 1.16   1.65 1.93                   16   2.49 1.88   2.93 3.55
+// and with adaptive steps and both stop rules, one lane against the kernel
+// taken, with 0.1 and 1 wavefronts of two lanes a body:
+//   n = 5    1.47 1.26   1.58 1.52               n = 10   2.61 1.76   2.82 2.29
+//       6    1.65 1.41   1.75 1.71                   12   3.19 1.83   3.31 2.54
+//       8    2.02 1.50   2.17 2.00                   16   4.22 2.11   4.48 3.25
 // hence the lines of bpl_mapping and fused_split.  1000 steps of 1000 x 6 915
 // -> 725 us; 24 requests to a server (3..10 bodies) 15.5 -> 10.4 ms.
 
@@ -59,8 +66,9 @@ struct SplitTerm {
 };
 
 // (the expressions of bpl_interact_p)
+template <bool TS>
 __device__ __forceinline__ SplitTerm split_term(const Partner &Pj, const double (&xi)[3],
-                                                const double (&vi)[3])
+                                                const double (&vi)[3], double &wmax)
 {
     SplitTerm t;
     const double2 p0 = Pj.p0, p1 = Pj.p1, p2 = Pj.p2;
@@ -78,6 +86,10 @@ __device__ __forceinline__ SplitTerm split_term(const Partner &Pj, const double 
     t.w[0] = fma(-al, rx, ux);
     t.w[1] = fma(-al, ry, uy);
     t.w[2] = fma(-al, rz, uz);
+    if (TS) {
+        const double u2 = fma(uz, uz, fma(uy, uy, ux * ux));
+        wmax = fmax(wmax, fma(al, ru, u2) * ri2);
+    }
     return t;
 }
 
@@ -118,10 +130,26 @@ __device__ __forceinline__ void split_turns(const SplitTerm (&t)[SplitSeat<N, G>
     }
 }
 
-template <int N, int G>
+// Maximum over the lanes of a body, to all of them.
+template <int G>
+__device__ __forceinline__ double share_max(double v)
+{
+    auto other = [&](auto ctrl) {
+        double t[3] = {v, v, v};
+        share_read3<decltype(ctrl)::value>(t);
+        v = fmax(v, t[0]);
+    };
+    other(std::integral_constant<int, 1 | (0 << 2) | (3 << 4) | (2 << 6)>());
+    if constexpr (G == 4)
+        other(std::integral_constant<int, 2 | (3 << 2) | (0 << 4) | (1 << 6)>());
+    return v;
+}
+
+// With TS, also the step rule's quantity over this lane's own partners.
+template <int N, int G, bool TS>
 __device__ __forceinline__ void split_eval(BplLds &L, const SplitSeat<N, G> &s,
                                            const double (&xi)[3], const double (&vi)[3],
-                                           double (&a)[3], double (&jk)[3])
+                                           double (&a)[3], double (&jk)[3], double &w)
 {
     using Seat = SplitSeat<N, G>;
     if (s.share == 0) {
@@ -138,7 +166,7 @@ __device__ __forceinline__ void split_eval(BplLds &L, const SplitSeat<N, G> &s,
     SplitTerm t[Seat::kTerms];
 #pragma unroll
     for (int k = 0; k < Seat::kTerms; ++k)
-        t[k] = split_term(p[k], xi, vi);
+        t[k] = split_term<TS>(p[k], xi, vi, w);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         a[c] = 0.0;
@@ -150,22 +178,22 @@ __device__ __forceinline__ void split_eval(BplLds &L, const SplitSeat<N, G> &s,
     wave_sync();
 }
 
-template <int N, int G>
+template <int N, int G, bool TS>
 __device__ __forceinline__ void split_step(BplLds &L, const SplitSeat<N, G> &s, const Coef &k,
                                            const double (&x)[3], const double (&v)[3],
                                            const double (&a0)[3], const double (&j0)[3],
                                            double (&xc)[3], double (&vc)[3], double (&ak)[3],
-                                           double (&jk)[3])
+                                           double (&jk)[3], double &w)
 {
     double bx[3], bv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         predict_comp(k, x[c], v[c], a0[c], j0[c], xc[c], vc[c], bx[c], bv[c]);
-    split_eval<N, G>(L, s, xc, vc, ak, jk);
+    split_eval<N, G, false>(L, s, xc, vc, ak, jk, w);
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
-    split_eval<N, G>(L, s, xc, vc, ak, jk);
+    split_eval<N, G, TS>(L, s, xc, vc, ak, jk, w);
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
@@ -181,11 +209,12 @@ __device__ __forceinline__ void split_fixed_steps(BplLds &L, const SplitSeat<N, 
     if (who == 0ull)
         return;
     const int n0 = __builtin_amdgcn_readlane(nrun, __builtin_ctzll(who));
+    double w = 0.0;
     if (__all(!live || nrun == n0)) {
 #pragma unroll 1
         for (int q = 0; q < n0; ++q) {
             double xc[3], vc[3], ak[3], jk[3];
-            split_step<N, G>(L, s, k, x, v, a0, j0, xc, vc, ak, jk);
+            split_step<N, G, false>(L, s, k, x, v, a0, j0, xc, vc, ak, jk, w);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 x[c] = xc[c];
@@ -201,7 +230,7 @@ __device__ __forceinline__ void split_fixed_steps(BplLds &L, const SplitSeat<N, 
     do {
         const bool act = q < nrun;
         double xc[3], vc[3], ak[3], jk[3];
-        split_step<N, G>(L, s, k, x, v, a0, j0, xc, vc, ak, jk);
+        split_step<N, G, false>(L, s, k, x, v, a0, j0, xc, vc, ak, jk, w);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             x[c] = act ? xc[c] : x[c];
@@ -213,9 +242,103 @@ __device__ __forceinline__ void split_fixed_steps(BplLds &L, const SplitSeat<N, 
     } while (__any(q < nrun));
 }
 
-// Integrate one tile (at most split_systems(N, G) systems) for at most P.quantum
-// fixed steps; bpl_run's contract.
+// OR of the stop-flag bits (1, 2, 4) over the lanes of system sys.
 template <int N, int G>
+__device__ __forceinline__ int split_or_flags(const int sys, const int v)
+{
+    constexpr int S = split_systems(N, G);
+    constexpr unsigned long long kBase = [] {
+        unsigned long long m = 0;
+        for (int k = 0; k < N; ++k)
+            m |= ((1ull << G) - 1) << (G * k * S);
+        return m;
+    }();
+    const unsigned long long sm = kBase << (G * sys);
+    int r = 0;
+#pragma unroll
+    for (int bit = 1; bit <= 4; bit <<= 1)
+        if (__ballot((v & bit) != 0) & sm)
+            r |= bit;
+    return r;
+}
+
+// Stop-rule flags and the system's maximum of w (bpl_stop_flags_regs): every
+// lane tests its body with its own share of the partners.
+template <int N, int G>
+__device__ __forceinline__ int split_stop_flags(BplLds &L, const SplitSeat<N, G> &s, const int b,
+                                                const int sys, const double mi,
+                                                const double inv24m0, const double (&x)[3],
+                                                const double (&v)[3], const double w,
+                                                double &wsys, const StepParams &P)
+{
+    constexpr int kTerms = SplitSeat<N, G>::kTerms;
+    int fl = (finite3(x) && finite3(v)) ? 0 : 1;
+    wsys = share_max<G>(w);
+    if (!P.stop_rules) {
+        if (P.adaptive == 1) {
+            if (s.share == 0)
+                L.mr[s.entry].y = wsys;
+            wave_sync();
+            double r[kTerms];
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k)
+                r[k] = L.mr[s.idx[k]].y;
+            wave_sync();
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k)
+                wsys = fmax(wsys, r[k]);
+            wsys = share_max<G>(wsys);
+        }
+        return __any(fl) ? split_or_flags<N, G>(sys, fl) : 0;
+    }
+    if (s.share == 0) {
+        L.xy[s.entry] = make_double2(x[0], x[1]);
+        L.zvx[s.entry] = make_double2(x[2], wsys);
+    }
+    wave_sync();
+    double2 q0[kTerms], q1[kTerms];
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k) {
+        q0[k] = L.xy[s.idx[k]];
+        q1[k] = L.zvx[s.idx[k]];
+    }
+    const double2 s0 = L.xy[sys];
+    const double2 s1 = L.zvx[sys];
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k)
+        wsys = fmax(wsys, q1[k].y);
+    wsys = share_max<G>(wsys);
+    const double dx = x[0] - s0.x, dy = x[1] - s0.y, dz = x[2] - s1.x;
+    const double rb = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
+    if (P.stop_rules & 1) {
+        double rp[kTerms];
+        if (s.share == 0)
+            L.mr[s.entry].y = rb;
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k)
+            rp[k] = L.mr[s.idx[k]].y;
+        wave_sync();
+        if (b >= 1) {
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k) {
+                const double ex = x[0] - q0[k].x, ey = x[1] - q0[k].y, ez = x[2] - q1[k].x;
+                const double sep2 = fma(ez, ez, fma(ey, ey, ex * ex));
+                // (the last partner in evaluation order is the star)
+                if (s.share * kTerms + k < N - 2 && hill_close(sep2, mi, s.m[k], inv24m0, rb, rp[k]))
+                    fl |= 2;
+            }
+        }
+    }
+    if (b >= 1 && (P.stop_rules & 2) && rb > P.r_eject)
+        fl |= 4;
+    return split_or_flags<N, G>(sys, fl);
+}
+
+// Integrate one tile (at most split_systems(N, G) systems) for at most P.quantum
+// steps; bpl_run's contract.
+template <int N, int G, bool ADV>
 __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int first,
                                           const int count, const int *list, const StepParams &P,
                                           int &slot_out)
@@ -262,24 +385,66 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
         s.idx[k] = p * S + sys;
         s.m[k] = L.mr[s.idx[k]].x;
     }
-    int budget = P.quantum;
+    if constexpr (!ADV) {
+        int budget = P.quantum;
 #pragma unroll 1
-    for (int seg = 0; seg < 2; ++seg) {
-        double h = c.dt;
-        const int nrun = run_segment(c, P, seg, budget, h);
-        split_fixed_steps<N, G>(L, s, make_coef(h), live, nrun, x, v, a0, j0);
-        budget -= nrun;
-        run_segment_end(c, P, seg, nrun);
+        for (int seg = 0; seg < 2; ++seg) {
+            double h = c.dt;
+            const int nrun = run_segment(c, P, seg, budget, h);
+            split_fixed_steps<N, G>(L, s, make_coef(h), live, nrun, x, v, a0, j0);
+            budget -= nrun;
+            run_segment_end(c, P, seg, nrun);
+        }
+        const int fl = split_or_flags<N, G>(sys, (finite3(x) && finite3(v)) ? 0 : 1);
+        if (live && fl)
+            c.status = ST_NONFINITE;
+    } else {
+        const double inv24m0 = 1.0 / (24.0 * L.mr[sys].x);
+        for (int q = 0; q < P.quantum; ++q) {
+            double h = 0.0;
+            bool last = false;
+            const bool act = P.adaptive ? plan_step_adaptive(c, P, h, last)
+                                        : valid && plan_step(c, P, h, last);
+            if (!__any(act))
+                break;
+            double xc[3], vc[3], ak[3], jk[3], w = 0.0;
+            split_step<N, G, true>(L, s, make_coef(h), x, v, a0, j0, xc, vc, ak, jk, w);
+            double dtp = 0.0;
+            if (P.adaptive == 2) {
+                const double aa = fma(ak[2], ak[2], fma(ak[1], ak[1], ak[0] * ak[0]));
+                const double jj = fma(jk[2], jk[2], fma(jk[1], jk[1], jk[0] * jk[0]));
+                if (s.share == 0)
+                    L.mr[s.entry].y = jj / aa;
+                wave_sync();
+                double r = L.mr[sys].y;   // body order
+#pragma unroll
+                for (int k = 1; k < N; ++k)
+                    r += L.mr[k * S + sys].y;
+                wave_sync();
+                dtp = P.eta * rsqrt_nr(r);
+            }
+            if (act) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    x[k] = xc[k];
+                    v[k] = vc[k];
+                    a0[k] = ak[k];
+                    j0[k] = jk[k];
+                }
+            }
+            double wsys = 0.0;
+            const int fl = split_stop_flags<N, G>(L, s, b, sys, mi, inv24m0, x, v, w, wsys, P);
+            if (P.adaptive == 1)
+                dtp = P.eta * rsqrt_nr(wsys);
+            if (P.adaptive) {
+                finish_step_adaptive(c, act, last, h, dtp, fl);
+            } else if (act) {
+                finish_step(c, P, last, h, dtp);
+                if (fl)
+                    c.status = status_of_flags(fl);
+            }
+        }
     }
-    constexpr unsigned long long kBase = [] {
-        unsigned long long m = 0;
-        for (int k = 0; k < N; ++k)
-            m |= 1ull << (G * k * S);
-        return m;
-    }();
-    const unsigned long long bad = __ballot(!(finite3(x) && finite3(v)));
-    if (live && (bad & (kBase << (G * sys))))
-        c.status = ST_NONFINITE;
     if (live && s.share == 0) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {

@@ -1,18 +1,18 @@
-// fb_split.hip -- fixed Hermite steps of one bucket with two or four lanes a
+// fb_split.hip -- Hermite steps of one bucket with two or four lanes a
 // body (fb_split.h).
 #include "fb_split.h"
 
 namespace fb {
 namespace {
 
-template <int N, int G>
+template <int N, int G, bool ADV>
 __global__ __launch_bounds__(64) void k_bpl_split(Bucket B, StepParams P)
 {
     extern __shared__ char fb_dyn_lds[];
     constexpr int S = split_systems(N, G);
     const int first = blockIdx.x * S;
     int slot;
-    split_run<N, G>(*reinterpret_cast<BplLds *>(fb_dyn_lds), B, first, min(S, B.count - first),
+    split_run<N, G, ADV>(*reinterpret_cast<BplLds *>(fb_dyn_lds), B, first, min(S, B.count - first),
                     nullptr, P, slot);
 }
 
@@ -22,14 +22,16 @@ hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t
 {
     if (B.count == 0)
         return hipSuccess;
-    if (P.adaptive || P.stop_rules || (G != 2 && G != 4) || B.n < kMinSplit)
+    if ((G != 2 && G != 4) || B.n < kMinSplit)
         return hipErrorInvalidValue;
     const int S = split_systems(B.n, G);
     const dim3 grid((unsigned)((B.count + S - 1) / S));
-#define FB_L(NN)                                                                              \
-    case NN:                                                                                  \
-        if (G == 4) hipLaunchKernelGGL((k_bpl_split<NN, 4>), grid, dim3(64), sizeof(BplLds), s, B, P); \
-        else hipLaunchKernelGGL((k_bpl_split<NN, 2>), grid, dim3(64), sizeof(BplLds), s, B, P);        \
+    const bool adv = P.adaptive || P.stop_rules;
+#define FB_K(NN, GG, A) hipLaunchKernelGGL((k_bpl_split<NN, GG, A>), grid, dim3(64), sizeof(BplLds), s, B, P)
+#define FB_L(NN)                                                         \
+    case NN:                                                             \
+        if (G == 4) { if (adv) FB_K(NN, 4, true); else FB_K(NN, 4, false); } \
+        else { if (adv) FB_K(NN, 2, true); else FB_K(NN, 2, false); }    \
         break
     switch (B.n) {
         FB_L(5); FB_L(6); FB_L(7); FB_L(8); FB_L(9); FB_L(10);
@@ -37,6 +39,7 @@ hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t
     default: return hipErrorInvalidValue;
     }
 #undef FB_L
+#undef FB_K
     return hipGetLastError();
 }
 

@@ -70,3 +70,43 @@ def test_mixed_fused_launch_and_failing_systems(plans, ora):
     ex = per_system_rel_err(ens.n_body, st["pos"], x)[ok]
     ev = per_system_rel_err(ens.n_body, st["vel"], v)[ok]
     assert ex.max() <= 1e-10 and ev.max() <= 1e-10
+
+
+@pytest.mark.parametrize("n", range(5, 17))
+@pytest.mark.parametrize("count", [1, 3, 700, 1500])
+def test_adaptive_equals_one_lane_a_body(plans, n, count):
+    """Both step rules and the stop rules (tightly packed systems, so that some stop), and fixed steps with them."""
+    fb = plans
+    fb.set_plan(n, fb.MAP_BPL, 1)
+    big = gen.ragged_hill(FULL // 2, 150 + n, n_lo=n, n_hi=n, mlo=1e-5, mhi=1e-3, k_lo=3.0, k_hi=6.0, e_hi=0.2)
+    ens = big.subset(range(count))
+    print("[case] split adaptive", n, count, flush=True)
+    rules = fb.STOP_ENCOUNTER | fb.STOP_EJECT
+    for kw in ({"adaptive": 1, "eta": 0.02, "stop_rules": rules}, {"adaptive": 1, "eta": 0.02},
+               {"adaptive": 2, "eta": 0.03}, {"stop_rules": rules, "r_eject": 0.6}):
+        go = lambda E, o: E.integrate(0.15, 0.0 if o.adaptive else 0.004, o)
+        want = run(fb, big, go, opts=fb.Opts(**kw))
+        same(run(fb, ens, go, opts=fb.Opts(**kw)), want, n, count)
+        same(run(fb, ens, go, opts=fb.Opts(schedule=fb.SCHED_PERSISTENT, steps_per_quantum=5, compact=True, **kw)),
+             want, n, count)
+
+
+def test_compaction_through_every_mapping(plans):
+    """One run whose survivors thin out from one lane a body to two and four, against plain launches."""
+    fb = plans
+    parts = [gen.ragged_hill(5000, 60 + n, n_lo=n, n_hi=n, mlo=1e-5, mhi=1e-3, k_lo=3.0, k_hi=4.0, e_hi=0.3)
+             for n in (4, 6, 8)]
+    ens = gen.Ensemble(*(np.concatenate([getattr(p, f) for p in parts]) for f in ("n_body", "mass", "pos", "vel")))
+    t0 = np.random.default_rng(3).uniform(0.0, 2.0, ens.n_sys) ** 0.2   # few systems with a long way to go
+    print("[case] split compaction", flush=True)
+    got = {}
+    for sched in (fb.SCHED_PLAIN, fb.SCHED_PERSISTENT):
+        kw = {"steps_per_quantum": 10, "compact": True} if sched == fb.SCHED_PERSISTENT else {}
+        E = fb.Ensemble(ens.n_body, ens.mass, ens.pos, ens.vel, t0=t0)
+        E.integrate(1.2, 0.0, fb.Opts(adaptive=1, eta=0.02, stop_rules=3, schedule=sched, **kw))
+        got[sched] = E.state()
+        E.close()
+    a, b = got[fb.SCHED_PLAIN], got[fb.SCHED_PERSISTENT]
+    assert len(set(a["steps"].tolist())) > 20
+    for key in a:
+        assert np.array_equal(a[key], b[key], equal_nan=True), key
