@@ -509,10 +509,9 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     int grid = 1;
     Tile *d_tiles = e->d_tiles;
     // Systems of each small bucket that may still step.
-    std::vector<std::pair<int, long long>> sizes;
+    std::vector<FusedGroup> sizes;
     for (const Bucket &B : small)
-        sizes.emplace_back(B.n, B.count);
-    int body_map = MAP_BPL;
+        sizes.push_back({B.n, B.count, 1.0, MAP_BPL});
     // Per-bucket mappings and grid of fused-kernel class c.
     auto set_class = [&](int c) -> hipError_t {
         const int spl_lim = persistent_spl_limit(c, adv ? 1 : 0);
@@ -521,17 +520,21 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         if (occ > 0)
             gpc = std::min(gpc, occ);
         grid = std::max(1, gpc * e->num_cu);
-        body_map = c == 0 ? fused_split(sizes, e->num_cu, (long long)grid * W) : MAP_BPL;
-        // (more tiles than one lane a body has: the staging area holds 96
-        // bytes a body and is free during a run)
-        d_tiles = body_map == MAP_BPL ? e->d_tiles : reinterpret_cast<Tile *>(e->d_staging);
+        if (c == 0)
+            fused_split(sizes, e->num_cu, (long long)grid * W);
+        // (tiles of several lanes a body are more than those of one: the
+        // staging area holds 96 bytes a body and is free during a run)
+        d_tiles = e->d_tiles;
+        for (const FusedGroup &g : sizes)
+            if (c == 0 && g.map != MAP_BPL)
+                d_tiles = reinterpret_cast<Tile *>(e->d_staging);
         for (int i = 0; i < nb_small; ++i) {
             const int n = small[i].n;
             const int m = get_plan(n).mapping;
             // in the system-per-lane class every bucket that can runs system-
             // per-lane, unless its plan asks for body-per-lane
             tables.map[i] = n <= spl_lim && m != MAP_BPL && (m == MAP_SPL || c == 1) ? MAP_SPL
-                            : n >= kMinSplit                                      ? body_map
+                            : c == 0                                              ? sizes[i].map
                                                                                   : MAP_BPL;
         }
         cls = c;
@@ -642,7 +645,7 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
                 act += c;
                 spl_tiles += (c + 63) / 64;
                 bpl_waves += (c + per - 1) / per;
-                sizes[i].second = c;
+                sizes[i].count = c;
             }
             if (n_large) {   // the large buckets keep no survivor lists
                 FB_HIP(launch_reset_counter(e->d_ints + 3, 1, e->stream));
@@ -684,12 +687,10 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         // as the survivors leave SIMDs for.  (Further quanta until they are
         // few enough for four lanes: 16384 systems 9.5 ms against 9.0.)
         if (compact && cls == 0 && p0.mapping == 0 && P.quantum == quantum && bpl_waves <= 4LL * e->num_cu) {
-            if (fused_split(sizes, e->num_cu, (long long)grid * W) != body_map) {
-                hipError_t err = set_class(0);
-                if (err != hipSuccess) {
-                    result = hip_fail(err, "mapping switch");
-                    break;
-                }
+            hipError_t err = set_class(0);
+            if (err != hipSuccess) {
+                result = hip_fail(err, "mapping switch");
+                break;
             }
             P.quantum = INT_MAX / 2;
             recapture = true;

@@ -42,22 +42,46 @@ inline long long split_tiles(int n, long long count, int map)
     return (count + S - 1) / S * (map == MAP_SPLIT4 && n <= 6 ? 2 : 1);
 }
 
-// Mapping of the body-per-lane tiles of a fused launch over buckets of
-// (n, count), `waves` of them resident: four lanes a body, or
-// two, from kMinSplit bodies on while all tiles have a wavefront each and no
-// SIMD more than one (fb_split.h has both sides measured), else one.
-template <class Counts>
-int fused_split(const Counts &counts, int num_cu, long long waves)
+// Relative time of a step of a lone body-per-lane tile (fb_split.h's figures).
+inline double lone_step(int n, int map)
 {
-    for (int map : {MAP_SPLIT4, MAP_SPLIT2}) {
-        long long tiles = 0;
-        for (const auto &c : counts)
-            tiles += c.first >= kMinSplit ? split_tiles(c.first, c.second, map)
-                                          : (c.second + 64 / c.first - 1) / (64 / c.first);
-        if (tiles <= std::min(4LL * num_cu, waves))
-            return map;
+    return map == MAP_SPLIT4 ? 0.37 + 0.05 * n : map == MAP_SPLIT2 ? 0.12 + 0.095 * n : 0.15 * n;
+}
+
+// One body count of a fused launch: `count` systems, the most `steps` of which
+// any takes, and the mapping of its body-per-lane tiles.
+struct FusedGroup {
+    int n;
+    long long count;
+    double steps;
+    int map;
+};
+
+// Mappings of the tiles of a fused launch with `waves` wavefronts resident: as
+// long as all tiles have a wavefront each and no SIMD more than one, the group
+// that takes longest gets two lanes a body, then four (kMinSplit bodies and
+// more), since the launch lasts as long as its slowest tile.  24 requests to a
+// server (3..10 bodies): 9.4 ms; one choice for all groups 10.4.
+inline void fused_split(std::vector<FusedGroup> &groups, int num_cu, long long waves)
+{
+    const long long most = std::min(4LL * num_cu, waves);
+    long long tiles = 0;
+    for (FusedGroup &g : groups) {
+        g.map = MAP_BPL;
+        tiles += split_tiles(g.n, g.count, MAP_BPL);
     }
-    return MAP_BPL;
+    while (tiles <= most) {
+        FusedGroup *slow = nullptr;
+        for (FusedGroup &g : groups)
+            if (g.count > 0 && (!slow || g.steps * lone_step(g.n, g.map) > slow->steps * lone_step(slow->n, slow->map)))
+                slow = &g;
+        if (!slow || slow->n < kMinSplit || slow->map == MAP_SPLIT4)
+            break;
+        const int next = slow->map == MAP_BPL ? MAP_SPLIT2 : MAP_SPLIT4;
+        tiles += split_tiles(slow->n, slow->count, next) - split_tiles(slow->n, slow->count, slow->map);
+        if (tiles <= most)
+            slow->map = next;
+    }
 }
 
 // Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the

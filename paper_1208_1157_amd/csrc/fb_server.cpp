@@ -281,6 +281,7 @@ struct fb_server {
     // auto meaning body-per-lane; per-n mappings), so a request's arithmetic
     // never depends on what else is resident or on later plan changes.
     int cls = 0, waves_per_group = 2, groups_per_cu = 8;
+    bool place = false;   // entry 0 is auto
     int mapping[kMaxBodies + 1] = {0};
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -742,13 +743,12 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
         spread = best_k > 0;
     }
     if (cls == 0) {
-        std::vector<std::pair<int, long long>> sizes;
+        std::vector<FusedGroup> sizes;
         for (const Group &G : groups)
-            sizes.emplace_back(G.n, G.len);
-        const int map = fused_split(sizes, S->num_cu, (long long)resident_waves);
-        for (Group &G : groups)
-            if (G.n >= kMinSplit)
-                G.map = map;
+            sizes.push_back({G.n, G.len, (double)G.adv, MAP_BPL});
+        fused_split(sizes, S->num_cu, (long long)resident_waves);
+        for (size_t g = 0; g < groups.size(); ++g)
+            groups[g].map = sizes[g].map;
     }
     struct Item {
         Tile t;
@@ -815,13 +815,17 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
         P.r_eject = 0.0;
         P.max_steps = LLONG_MAX;
         P.quantum = Q;
-        P.simds = 0;
-        const int grid = std::max(1, std::min(gpc * S->num_cu, nt));
+        // Tiles that all run at once are placed one by one (place_tile), unless
+        // a plan asked for a class and with it for its workgroups.
+        const bool placed = S->place && cls == 0 && nt <= 8 * S->num_cu;
+        P.simds = placed ? 4 * S->num_cu : 0;
+        const int Wl = placed ? 1 : W;
+        const int grid = std::max(1, std::min(placed ? 8 * S->num_cu : gpc * S->num_cu, nt));
         ProfScope ps(S->stream);
         FB_HIP(launch_persistent(reinterpret_cast<const Bucket *>(S->d_tables + buckets_at),
                                  reinterpret_cast<const Tile *>(S->d_tables + tiles_at), d_ints,
                                  d_ints + 1, reinterpret_cast<const int *>(S->d_tables + list_at), P,
-                                 0, cls, grid, W, nullptr, S->stream));
+                                 0, cls, grid, Wl, nullptr, S->stream));
     }
     for (Request *R : sched) {
         R->done_steps = std::min(R->total_steps, R->done_steps + Q);
@@ -1043,6 +1047,7 @@ fb_status fb_server_create(const fb_server_opts *po, void *hip_stream, fb_server
     S->num_cu = cu > 0 ? cu : 256;
     const Plan p0 = get_plan(0);
     S->cls = p0.mapping == MAP_SPL ? 1 : 0;
+    S->place = p0.mapping == 0;
     S->waves_per_group = std::max(1, std::min(4, p0.waves_per_group));
     S->groups_per_cu = p0.groups_per_cu > 0 ? p0.groups_per_cu : 8;
     const int occ = persistent_max_groups_per_cu(0, S->cls, S->waves_per_group);

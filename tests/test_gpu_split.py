@@ -110,3 +110,23 @@ def test_compaction_through_every_mapping(plans):
     assert len(set(a["steps"].tolist())) > 20
     for key in a:
         assert np.array_equal(a[key], b[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("per_n", [1, 40, 300, 900])
+def test_server_and_fused_mixes(plans, per_n):
+    """Groups of every body count get one, two or four lanes a body as SIMDs allow: a server's requests and a fused
+    launch against plain launches, bitwise."""
+    fb = plans
+    ens = gen.ragged_hill(15 * per_n, 300, n_lo=2, n_hi=16)
+    t_end = 60.4 * DT
+    print("[case] split mixes", per_n, flush=True)
+    want = run(fb, ens, lambda E, o: E.integrate(t_end, DT, o))
+    fused = run(fb, ens, lambda E, o: E.integrate(t_end, DT, o), opts=fb.Opts(schedule=fb.SCHED_PERSISTENT))
+    with fb.Server(budget_bytes=512 << 20, steps_per_quantum=25) as srv:
+        ids = [srv.submit_gen(ens, t_end, DT), srv.submit_gen(ens.subset(range(0, ens.n_sys, 2)), t_end / 2, DT)]
+        for rid in ids:
+            assert srv.wait(rid, 60.0) == fb.REQ_DONE
+        got = srv.result(ids[0])
+    for key in ("pos", "vel", "t", "steps", "status"):
+        assert np.array_equal(want[key], fused[key]), key
+        assert np.array_equal(want[key], got[key]), key
