@@ -192,6 +192,44 @@ __device__ __forceinline__ Clock load_clock(const Bucket &B, int s)
     return c;
 }
 
+// The clock of a system of a SoloIO batch at its start.
+__device__ __forceinline__ Clock solo_clock(const SoloIO &io)
+{
+    Clock c{};
+    c.dt = io.dt;
+    c.nfull = io.n_steps;
+    c.t_end = fma((double)io.n_steps, io.dt, 0.0);
+    c.status = io.n_steps > 0 ? ST_ACTIVE : ST_DONE;
+    return c;
+}
+
+// Body b of system s of a SoloIO batch.
+__device__ __forceinline__ void solo_load(const SoloIO &io, const int n, const int s, const int b,
+                                          double &m, double (&x)[3], double (&v)[3])
+{
+    const size_t row = (size_t)s * n + b;
+    m = io.mass[row];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        x[k] = io.pos[3 * row + k];
+        v[k] = io.vel[3 * row + k];
+    }
+}
+
+__device__ __forceinline__ void solo_store(const SoloIO &io, const int n, const int s, const int b,
+                                           const double (&x)[3], const double (&v)[3],
+                                           const int status)
+{
+    const size_t row = (size_t)s * n + b;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        io.pos[3 * row + k] = x[k];
+        io.vel[3 * row + k] = v[k];
+    }
+    if (b == 0 && io.status)
+        io.status[s] = status;
+}
+
 __device__ __forceinline__ void store_clock(const Bucket &B, int s, const Clock &c)
 {
     B.t[s] = c.t;

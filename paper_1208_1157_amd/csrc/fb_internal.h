@@ -194,6 +194,24 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group,
 // MAP_BPLU comes here).
 int unrolled_tiles(const Bucket &B);
 hipError_t launch_unrolled(const Bucket &B, const StepParams &P, hipStream_t s);
+// A batch of n_sys equal systems in the caller's arrays, system after system,
+// advanced in place by n_steps fixed steps of dt; status may be null.
+struct SoloIO {
+    const double *mass;
+    double *pos, *vel;
+    int *status;
+    int n_sys;
+    long long n_steps;
+    double dt;
+};
+// Set-up, steps and results of such a batch in one launch, with the kernels of
+// `mapping`: MAP_SPLIT2 and MAP_SPLIT4, and MAP_BPLU up to 4 bodies.
+inline bool solo_in_one(int n, int mapping)
+{
+    return mapping == MAP_SPLIT2 || mapping == MAP_SPLIT4 || (mapping == MAP_BPLU && n <= 4);
+}
+hipError_t launch_solo_split(const SoloIO &io, int n, int G, const StepParams &P, hipStream_t s);
+hipError_t launch_solo_quads(const SoloIO &io, int n, const StepParams &P, hipStream_t s);
 // Steps with G (2 or 4) lanes a body, kMinSplit bodies and more
 // (launch_plain with MAP_SPLIT2 and MAP_SPLIT4 comes here).
 hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t s);

@@ -337,11 +337,12 @@ __device__ __forceinline__ int split_stop_flags(BplLds &L, const SplitSeat<N, G>
 }
 
 // Integrate one tile (at most split_systems(N, G) systems) for at most P.quantum
-// steps; bpl_run's contract.
-template <int N, int G, bool ADV>
+// steps; bpl_run's contract.  SOLO: of the batch io instead of the bucket,
+// with the evaluation it starts from.
+template <int N, int G, bool ADV, bool SOLO = false>
 __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int first,
                                           const int count, const int *list, const StepParams &P,
-                                          int &slot_out)
+                                          int &slot_out, const SoloIO &io = SoloIO())
 {
     constexpr int S = split_systems(N, G), kTerms = SplitSeat<N, G>::kTerms;
     const int lane = threadIdx.x & 63, j = lane / G;
@@ -353,12 +354,16 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
     if (valid)
         slot = list ? list[first + sys] : first + sys;
     slot_out = slot;
-    const size_t pitch = B.pitch;
+    const size_t pitch = SOLO ? 0 : B.pitch;
     double mi = 0.0, x[3] = {0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
     double a0[3] = {0.0, 0.0, 0.0}, j0[3] = {0.0, 0.0, 0.0};
     Clock c{};
     c.status = ST_DONE;
-    if (valid) {
+    if (SOLO && valid) {
+        solo_load(io, N, slot, b, mi, x, v);
+        c = solo_clock(io);
+    }
+    if (!SOLO && valid) {
         mi = B.st[(R_M * N + b) * pitch + slot];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -384,6 +389,10 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
         const int p = kk < N - 2 ? kk + 1 + (kk + 1 >= skip ? 1 : 0) : (b == 0 ? N - 1 : 0);
         s.idx[k] = p * S + sys;
         s.m[k] = L.mr[s.idx[k]].x;
+    }
+    if constexpr (SOLO) {
+        double w = 0.0;
+        split_eval<N, G, false>(L, s, x, v, a0, j0, w);
     }
     if constexpr (!ADV) {
         int budget = P.quantum;
@@ -445,7 +454,9 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
             }
         }
     }
-    if (live && s.share == 0) {
+    if (SOLO && live && s.share == 0)
+        solo_store(io, N, slot, b, x, v, c.status);
+    if (!SOLO && live && s.share == 0) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             B.st[((R_X + k) * N + b) * pitch + slot] = x[k];

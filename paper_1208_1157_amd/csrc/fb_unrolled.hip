@@ -255,22 +255,28 @@ __device__ __forceinline__ void quad_masses(const double mi, double (&pm)[N - 1]
 
 constexpr int kQuadSystems = 16;   // systems per wavefront
 
-template <int N, bool ADV>
+// SOLO: of the batch io instead of the bucket, with the evaluation it starts
+// from.
+template <int N, bool ADV, bool SOLO = false>
 __device__ __forceinline__ void quad_run(const Bucket &B, const int first, const int count,
-                                         const StepParams &P)
+                                         const StepParams &P, const SoloIO &io = SoloIO())
 {
     static_assert(N >= 2 && N <= 4, "a quad holds up to four bodies");
     const int lane = threadIdx.x & 63;
     const int s = lane >> 2, b = lane & 3;
     const bool valid = b < N && s < count;
     const int slot = valid ? first + s : first;
-    const size_t pitch = B.pitch;
+    const size_t pitch = SOLO ? 0 : B.pitch;
     // idle lanes: apart from the star, so that nothing they compute is special
     double mi = 0.0, x[3] = {(double)(2 + b), 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
     double a0[3] = {0.0, 0.0, 0.0}, j0[3] = {0.0, 0.0, 0.0};
     Clock c{};
     c.status = ST_DONE;
-    if (valid) {
+    if (SOLO && valid) {
+        solo_load(io, N, slot, b, mi, x, v);
+        c = solo_clock(io);
+    }
+    if (!SOLO && valid) {
         mi = B.st[(R_M * N + b) * pitch + slot];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -284,6 +290,10 @@ __device__ __forceinline__ void quad_run(const Bucket &B, const int first, const
     const bool live = c.status == ST_ACTIVE;
     double pm[N - 1];
     quad_masses<N, 0>(mi, pm);
+    if constexpr (SOLO) {
+        double w = 0.0;
+        quad_eval<N, false>(pm, x, v, a0, j0, w);
+    }
     if constexpr (!ADV) {
         int budget = P.quantum;
 #pragma unroll 1
@@ -331,7 +341,9 @@ __device__ __forceinline__ void quad_run(const Bucket &B, const int first, const
             }
         }
     }
-    if (live) {
+    if (SOLO && live)
+        solo_store(io, N, slot, b, x, v, c.status);
+    if (!SOLO && live) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             B.st[((R_X + k) * N + b) * pitch + slot] = x[k];
@@ -362,7 +374,30 @@ __global__ __launch_bounds__(64) void k_bpl_unrolled(Bucket B, StepParams P)
     }
 }
 
+template <int N>
+__global__ __launch_bounds__(64) void k_solo_quads(SoloIO io, StepParams P)
+{
+    const int first = blockIdx.x * kQuadSystems;
+    quad_run<N, false, true>(Bucket(), first, min(kQuadSystems, io.n_sys - first), P, io);
+}
+
 }  // namespace
+
+hipError_t launch_solo_quads(const SoloIO &io, int n, const StepParams &P, hipStream_t s)
+{
+    if (io.n_sys <= 0)
+        return hipSuccess;
+    if (P.adaptive || P.stop_rules)
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((io.n_sys + kQuadSystems - 1) / kQuadSystems));
+    switch (n) {
+    case 2: hipLaunchKernelGGL(k_solo_quads<2>, grid, dim3(64), 0, s, io, P); break;
+    case 3: hipLaunchKernelGGL(k_solo_quads<3>, grid, dim3(64), 0, s, io, P); break;
+    case 4: hipLaunchKernelGGL(k_solo_quads<4>, grid, dim3(64), 0, s, io, P); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
 
 int unrolled_tiles(const Bucket &B)
 {
