@@ -28,7 +28,8 @@ namespace {
 //       6    0.98 0.93   1.27 1.58                   12   1.98 1.50   2.21 2.70
 //       8    1.30 1.16   1.65 1.93                   16   2.49 1.88   2.93 3.55
 // and with adaptive steps and both stop rules, one lane against the kernel
-// taken, with 0.1 and 1 wavefronts of two lanes a body:
+// taken, with 0.1 and 1 wavefronts of two lanes a body (all without HillBound,
+// which takes 5 to 15% off either):
 //   n = 5    1.47 1.26   1.58 1.52               n = 10   2.61 1.76   2.82 2.29
 //       6    1.65 1.41   1.75 1.71                   12   3.19 1.83   3.31 2.54
 //       8    2.02 1.50   2.17 2.00                   16   4.22 2.11   4.48 3.25
@@ -68,13 +69,13 @@ struct SplitTerm {
 // (the expressions of bpl_interact_p)
 template <bool TS>
 __device__ __forceinline__ SplitTerm split_term(const Partner &Pj, const double (&xi)[3],
-                                                const double (&vi)[3], double &wmax)
+                                                const double (&vi)[3], double &wmax, double &r2)
 {
     SplitTerm t;
     const double2 p0 = Pj.p0, p1 = Pj.p1, p2 = Pj.p2;
     const double rx = p0.x - xi[0], ry = p0.y - xi[1], rz = p1.x - xi[2];
     const double ux = p1.y - vi[0], uy = p2.x - vi[1], uz = p2.y - vi[2];
-    const double r2 = fma(rz, rz, fma(ry, ry, rx * rx));
+    r2 = fma(rz, rz, fma(ry, ry, rx * rx));
     const double ru = fma(rz, uz, fma(ry, uy, rx * ux));
     const double ri = rsqrt_nr(r2);
     const double ri2 = ri * ri;
@@ -145,11 +146,14 @@ __device__ __forceinline__ double share_max(double v)
     return v;
 }
 
-// With TS, also the step rule's quantity over this lane's own partners.
+// With TS, also the step rule's quantity w and the stop rules' bound hb over
+// this lane's own partners, ic2 their 1 / c^2 (ri2 by the star's lane only).
 template <int N, int G, bool TS>
 __device__ __forceinline__ void split_eval(BplLds &L, const SplitSeat<N, G> &s,
                                            const double (&xi)[3], const double (&vi)[3],
-                                           double (&a)[3], double (&jk)[3], double &w)
+                                           double (&a)[3], double (&jk)[3], double &w,
+                                           const double (&ic2)[SplitSeat<N, G>::kTerms],
+                                           HillBound &hb)
 {
     using Seat = SplitSeat<N, G>;
     if (s.share == 0) {
@@ -164,9 +168,17 @@ __device__ __forceinline__ void split_eval(BplLds &L, const SplitSeat<N, G> &s,
         p[k] = Partner{L.xy[s.idx[k]], L.zvx[s.idx[k]], L.vyvz[s.idx[k]], s.m[k]};
     __builtin_amdgcn_sched_barrier(0);
     SplitTerm t[Seat::kTerms];
+    hb.least = DBL_MAX;
 #pragma unroll
-    for (int k = 0; k < Seat::kTerms; ++k)
-        t[k] = split_term<TS>(p[k], xi, vi, w);
+    for (int k = 0; k < Seat::kTerms; ++k) {
+        double r2;
+        t[k] = split_term<TS>(p[k], xi, vi, w, r2);
+        if (TS) {
+            hb.least = fmin(hb.least, r2 * ic2[k]);   // (the star's 1 / c^2 here is DBL_MAX)
+            if (k == N - 2 - Seat::kLast * Seat::kTerms)
+                hb.ri2 = r2;   // the star on lane kLast
+        }
+    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         a[c] = 0.0;
@@ -183,20 +195,27 @@ __device__ __forceinline__ void split_step(BplLds &L, const SplitSeat<N, G> &s, 
                                            const double (&x)[3], const double (&v)[3],
                                            const double (&a0)[3], const double (&j0)[3],
                                            double (&xc)[3], double (&vc)[3], double (&ak)[3],
-                                           double (&jk)[3], double &w)
+                                           double (&jk)[3], double &w,
+                                           const double (&ic2)[SplitSeat<N, G>::kTerms],
+                                           HillBound &hb, double &moved2)
 {
     double bx[3], bv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         predict_comp(k, x[c], v[c], a0[c], j0[c], xc[c], vc[c], bx[c], bv[c]);
-    split_eval<N, G, false>(L, s, xc, vc, ak, jk, w);
+    split_eval<N, G, false>(L, s, xc, vc, ak, jk, w, ic2, hb);
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
-    split_eval<N, G, TS>(L, s, xc, vc, ak, jk, w);
+    const double x1[3] = {xc[0], xc[1], xc[2]};
+    split_eval<N, G, TS>(L, s, xc, vc, ak, jk, w, ic2, hb);
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
+    if (TS) {
+        const double d0 = xc[0] - x1[0], d1 = xc[1] - x1[1], d2 = xc[2] - x1[2];
+        moved2 = fma(d2, d2, fma(d1, d1, d0 * d0));
+    }
 }
 
 // nrun fixed steps of this lane's system (bpl_fixed_steps).
@@ -209,12 +228,13 @@ __device__ __forceinline__ void split_fixed_steps(BplLds &L, const SplitSeat<N, 
     if (who == 0ull)
         return;
     const int n0 = __builtin_amdgcn_readlane(nrun, __builtin_ctzll(who));
-    double w = 0.0;
+    double w = 0.0, moved2 = 0.0;
+    HillBound hb;
     if (__all(!live || nrun == n0)) {
 #pragma unroll 1
         for (int q = 0; q < n0; ++q) {
             double xc[3], vc[3], ak[3], jk[3];
-            split_step<N, G, false>(L, s, k, x, v, a0, j0, xc, vc, ak, jk, w);
+            split_step<N, G, false>(L, s, k, x, v, a0, j0, xc, vc, ak, jk, w, s.m, hb, moved2);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 x[c] = xc[c];
@@ -230,7 +250,7 @@ __device__ __forceinline__ void split_fixed_steps(BplLds &L, const SplitSeat<N, 
     do {
         const bool act = q < nrun;
         double xc[3], vc[3], ak[3], jk[3];
-        split_step<N, G, false>(L, s, k, x, v, a0, j0, xc, vc, ak, jk, w);
+        split_step<N, G, false>(L, s, k, x, v, a0, j0, xc, vc, ak, jk, w, s.m, hb, moved2);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             x[c] = act ? xc[c] : x[c];
@@ -269,7 +289,9 @@ __device__ __forceinline__ int split_stop_flags(BplLds &L, const SplitSeat<N, G>
                                                 const int sys, const double mi,
                                                 const double inv24m0, const double (&x)[3],
                                                 const double (&v)[3], const double w,
-                                                double &wsys, const StepParams &P)
+                                                double &wsys, const HillBound &part,
+                                                const double moved2, const double move2_most,
+                                                const bool act, const StepParams &P)
 {
     constexpr int kTerms = SplitSeat<N, G>::kTerms;
     int fl = (finite3(x) && finite3(v)) ? 0 : 1;
@@ -291,9 +313,35 @@ __device__ __forceinline__ int split_stop_flags(BplLds &L, const SplitSeat<N, G>
         }
         return __any(fl) ? split_or_flags<N, G>(sys, fl) : 0;
     }
+    // the system's maxima of w and of how far its bodies moved, and whether its
+    // planets can trigger at all
+    if (s.share == 0)
+        L.xy[s.entry] = make_double2(wsys, moved2);
+    wave_sync();
+    double2 mx[kTerms];
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k)
+        mx[k] = L.xy[s.idx[k]];
+    wave_sync();
+    double d2 = moved2;
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k) {
+        wsys = fmax(wsys, mx[k].x);
+        d2 = fmax(d2, mx[k].y);
+    }
+    wsys = share_max<G>(wsys);
+    d2 = share_max<G>(d2);
+    HillBound hb = part;
+    {
+        double t[3] = {hb.ri2, 0.0, 0.0};
+        share_read3<share_of<G>(SplitSeat<N, G>::kLast)>(t);
+        hb.ri2 = t[0];
+    }
+    if (!__any(act && b >= 1 && may_stop(hb, d2, move2_most, P)))
+        return __any(fl) ? split_or_flags<N, G>(sys, fl) : 0;
     if (s.share == 0) {
         L.xy[s.entry] = make_double2(x[0], x[1]);
-        L.zvx[s.entry] = make_double2(x[2], wsys);
+        L.zvx[s.entry] = make_double2(x[2], 0.0);
     }
     wave_sync();
     double2 q0[kTerms], q1[kTerms];
@@ -305,10 +353,6 @@ __device__ __forceinline__ int split_stop_flags(BplLds &L, const SplitSeat<N, G>
     const double2 s0 = L.xy[sys];
     const double2 s1 = L.zvx[sys];
     wave_sync();
-#pragma unroll
-    for (int k = 0; k < kTerms; ++k)
-        wsys = fmax(wsys, q1[k].y);
-    wsys = share_max<G>(wsys);
     const double dx = x[0] - s0.x, dy = x[1] - s0.y, dz = x[2] - s1.x;
     const double rb = sqrt(fma(dz, dz, fma(dy, dy, dx * dx)));
     if (P.stop_rules & 1) {
@@ -392,7 +436,8 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
     }
     if constexpr (SOLO) {
         double w = 0.0;
-        split_eval<N, G, false>(L, s, x, v, a0, j0, w);
+        HillBound hb;
+        split_eval<N, G, false>(L, s, x, v, a0, j0, w, s.m, hb);
     }
     if constexpr (!ADV) {
         int budget = P.quantum;
@@ -409,6 +454,14 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
             c.status = ST_NONFINITE;
     } else {
         const double inv24m0 = 1.0 / (24.0 * L.mr[sys].x);
+        double ic2[kTerms], ic2_most = 0.0;
+#pragma unroll
+        for (int k = 0; k < kTerms; ++k) {
+            const bool planet = s.share * kTerms + k < N - 2;
+            ic2[k] = planet && P.stop_rules ? hill_scale(mi, s.m[k], inv24m0) : DBL_MAX;
+            ic2_most = fmax(ic2_most, planet ? ic2[k] : 0.0);
+        }
+        const double move2_most = move_scale(share_max<G>(ic2_most));
         for (int q = 0; q < P.quantum; ++q) {
             double h = 0.0;
             bool last = false;
@@ -416,8 +469,10 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
                                         : valid && plan_step(c, P, h, last);
             if (!__any(act))
                 break;
-            double xc[3], vc[3], ak[3], jk[3], w = 0.0;
-            split_step<N, G, true>(L, s, make_coef(h), x, v, a0, j0, xc, vc, ak, jk, w);
+            double xc[3], vc[3], ak[3], jk[3], w = 0.0, moved2 = 0.0;
+            HillBound hb;
+            split_step<N, G, true>(L, s, make_coef(h), x, v, a0, j0, xc, vc, ak, jk, w, ic2, hb,
+                                   moved2);
             double dtp = 0.0;
             if (P.adaptive == 2) {
                 const double aa = fma(ak[2], ak[2], fma(ak[1], ak[1], ak[0] * ak[0]));
@@ -442,7 +497,8 @@ __device__ __forceinline__ bool split_run(BplLds &L, const Bucket &B, const int 
                 }
             }
             double wsys = 0.0;
-            const int fl = split_stop_flags<N, G>(L, s, b, sys, mi, inv24m0, x, v, w, wsys, P);
+            const int fl = split_stop_flags<N, G>(L, s, b, sys, mi, inv24m0, x, v, w, wsys,
+                                                  hb, moved2, move2_most, act, P);
             if (P.adaptive == 1)
                 dtp = P.eta * rsqrt_nr(wsys);
             if (P.adaptive) {
