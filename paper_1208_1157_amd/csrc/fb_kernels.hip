@@ -7,7 +7,7 @@
 // Algorithm 1).  All arithmetic is FP64 on the vector ALUs; the pair sums are
 // not a dense contraction, so no MFMA is used.
 //
-// Two lane mappings (both read the bucket's structure-of-arrays state with
+// Two kinds of lane mapping (both read the bucket's structure-of-arrays state with
 // consecutive lanes on consecutive slots):
 //   SPL  one system per lane.  The whole system lives in VGPRs for the whole
 //        step loop; every pair is evaluated once (Newton's third law), no
@@ -15,9 +15,11 @@
 //   BPL  one body per lane, floor(64/n) systems per wavefront (lane = body *
 //        S + system).  Each lane evaluates its body's n-1 interactions with
 //        partner positions/velocities read from the wave's LDS slice; no
-//        reduction is needed and every lane does useful work.
-// In both, each body sums its planet partners in ascending order and the
-// star last (Section 4.2).
+//        reduction is needed and every lane does useful work.  Tiles of it
+//        are in fb_bpl.h and, unrolled, fb_unrolled.hip; fb_split.h gives a
+//        body several lanes.
+// In all, each body sums its planet partners in ascending order and the
+// star last (Section 4.2), so results are bitwise the same.
 //
 // The corrector is Eq. 4 read with coefficient 3/20, a (dt)^3 jerk term and
 // the predicted state (xp, vp) as the base of every correction:

@@ -1,7 +1,7 @@
 // fb_mvs.hip -- the step kernels of the mixed-variable symplectic integrator
 // (Sections 2.2.3 and 4.3.3): democratic heliocentric drifts and kicks around
 // one Kepler drift per planet.  The conversions to and from a bucket's MVS
-// form and its read-back are in fb_kernels.hip.
+// form are in fb_kernels.hip, its read-back in fb_setup.hip.
 #include "fb_device.h"
 
 #include <climits>

@@ -610,6 +610,7 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         return FB_OK;
     };
     fb_status result = capture();
+    bool to_ends = false;
     long long done_steps = 0;
     while (result == FB_OK) {
         {
@@ -680,19 +681,22 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
             recapture = true;
         }
         // Once every surviving tile has a SIMD of its own, compaction has
-        // nothing left to gain and a quantum boundary only makes each tile
-        // wait for the slowest one (8-body tiles take about 1.7x as long per
-        // step as 4-body ones, and the tiles' step counts differ), so the
-        // tiles run on to their ends in one launch, with as many lanes a body
-        // as the survivors leave SIMDs for.  (Further quanta until they are
-        // few enough for four lanes: 16384 systems 9.5 ms against 9.0.)
-        if (compact && cls == 0 && p0.mapping == 0 && P.quantum == quantum && bpl_waves <= 4LL * e->num_cu) {
+        // little left to gain and a quantum boundary only makes each tile wait
+        // for the slowest one (8-body tiles take longer per step than 4-body
+        // ones, and the tiles' step counts differ), so quanta are 16 times as
+        // long, with as many lanes a body as the survivors leave SIMDs for;
+        // and once the slowest tiles have all the lanes they can have, the
+        // tiles run on to their ends in one launch.  65536 systems of 4..8
+        // bodies, 10 orbits: 62.7 ms, running on at once 65.7; 16384, 3 orbits,
+        // the same (with quanta as before until then 4% longer).
+        if (compact && cls == 0 && p0.mapping == 0 && !to_ends && bpl_waves <= 4LL * e->num_cu) {
             hipError_t err = set_class(0);
             if (err != hipSuccess) {
                 result = hip_fail(err, "mapping switch");
                 break;
             }
-            P.quantum = INT_MAX / 2;
+            to_ends = fused_split_done(sizes);
+            P.quantum = to_ends || quantum > INT_MAX / 32 ? INT_MAX / 2 : 16 * quantum;
             recapture = true;
         }
         if (recapture)

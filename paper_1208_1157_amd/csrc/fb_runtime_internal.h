@@ -84,6 +84,16 @@ inline void fused_split(std::vector<FusedGroup> &groups, int num_cu, long long w
     }
 }
 
+// Whether the group that takes longest cannot get more lanes a body.
+inline bool fused_split_done(const std::vector<FusedGroup> &groups)
+{
+    const FusedGroup *slow = nullptr;
+    for (const FusedGroup &g : groups)
+        if (g.count > 0 && (!slow || g.steps * lone_step(g.n, g.map) > slow->steps * lone_step(slow->n, slow->map)))
+            slow = &g;
+    return !slow || slow->n < kMinSplit || slow->map == MAP_SPLIT4;
+}
+
 // Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the
 // several-lanes-a-body ones (fb_split.h, measured there) while
 // no SIMD gets more than one of their wavefronts, or the unrolled kernels
