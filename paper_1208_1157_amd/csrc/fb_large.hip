@@ -508,7 +508,8 @@ double large_step_us(int K, int log_g, int parts, int waves, int now)
         per_simd = 1.2 * std::max(2.0, per_simd);
     const double chain = 0.7 + parts * (K == 1 ? 0.17 : 0.29) + 0.2 * K * log_g + 0.13 * waves;
     const double issue = per_simd * (parts * (K == 1 ? 0.16 : 0.29) + 0.6 * K);
-    return std::pow(std::pow(chain, 8.0) + std::pow(issue, 8.0), 0.125);
+    const double c2 = chain * chain, c4 = c2 * c2, i2 = issue * issue, i4 = i2 * i2;
+    return std::sqrt(std::sqrt(std::sqrt(c4 * c4 + i4 * i4)));   // (8th powers)
 }
 
 // The layout with the least estimated time.  A CU takes 8 wavefronts at a
