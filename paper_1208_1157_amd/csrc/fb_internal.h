@@ -178,6 +178,7 @@ struct PersistentTables {
 };
 hipError_t launch_persistent_tables(const Bucket *small, int nb, const PersistentTables &t,
                                     hipStream_t s);
+hipError_t launch_mvs_enter(const Bucket *b, int nb, hipStream_t s);
 hipError_t launch_begin_run(const Bucket *b, int nb, const RunStart &run, hipStream_t s);
 // mvs_form: converted to inertial form on the way; acc, jerk and dtn null.
 hipError_t launch_read_back(const Bucket *b, int nb, const StateOut &out, bool mvs_form,
@@ -246,7 +247,7 @@ hipError_t launch_rkck_bpl(const BucketSet &set, const StepParams &P, double eps
 hipError_t launch_rkck_large(const Bucket &B, const StepParams &P, double eps, hipStream_t s);
 // Mixed-variable symplectic integrator (n <= kMaxMvsBodies, system per
 // lane): conversion of a bucket to and from MVS form, fixed-step quanta.
-hipError_t launch_mvs_enter(const Bucket &B, hipStream_t s);
+hipError_t launch_mvs_enter_large(const Bucket &B, hipStream_t s);
 hipError_t launch_mvs_leave(const Bucket &B, hipStream_t s);
 // Three mappings that give identical results: system per lane (n <=
 // kMaxMvsBodies), one body per lane of a wavefront (every bucket of a set, n

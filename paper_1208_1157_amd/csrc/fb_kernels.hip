@@ -888,34 +888,6 @@ __global__ void k_count_active(Bucket B, int *count)
 // planet-planet accelerations at Q, which the next step's first kick reuses:
 // the drifts move all Q_i together, so the separations do not change.
 
-// Inertial (x, v) -> MVS form in place: X, Vc in row 0, Q_i = x_i - x_0,
-// V_i = v_i - Vc, and the planet-planet accelerations at Q.
-template <int N>
-__device__ __forceinline__ void to_mvs(const double (&m)[N], double (&x)[N][3], double (&v)[N][3])
-{
-    double M = 0.0;
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        M += m[i];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double sx = 0.0, sv = 0.0;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            sx = fma(m[i], x[i][c], sx);
-            sv = fma(m[i], v[i][c], sv);
-        }
-        const double X = sx / M, Vc = sv / M, x0 = x[0][c];
-#pragma unroll
-        for (int i = 1; i < N; ++i) {
-            x[i][c] -= x0;
-            v[i][c] -= Vc;
-        }
-        x[0][c] = X;
-        v[0][c] = Vc;
-    }
-}
-
 // MVS form -> inertial in place: x_0 = X - sum m_i Q_i / M, x_i = x_0 + Q_i,
 // v_0 = Vc - sum m_i V_i / m0, v_i = Vc + V_i.
 template <int N>
@@ -942,20 +914,6 @@ __device__ __forceinline__ void from_mvs(const double (&m)[N], double (&x)[N][3]
             v[i][c] += Vc;
         }
     }
-}
-
-template <int N>
-__global__ __launch_bounds__(64) void k_mvs_enter(Bucket B)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B.count)
-        return;
-    double m[N], x[N][3], v[N][3], a[N][3];
-    load_rows<N>(B, s, m, x, v, a, false);
-    to_mvs<N>(m, x, v);
-    mvs_acc<N>(m, x, a);
-    a[0][0] = a[0][1] = a[0][2] = 0.0;
-    store_rows<N>(B, s, x, v, a, true);
 }
 
 template <int N>
@@ -1335,7 +1293,7 @@ __device__ __forceinline__ void large_from_mvs(const LargeView &V, const int T, 
     }
 }
 
-// Inertial -> MVS form of a bucket (to_mvs), with the planet-planet
+// Inertial -> MVS form of a bucket (X, Vc in row 0, Q_i = x_i - x_0, V_i = v_i - Vc), with the planet-planet
 // accelerations at Q in the a0 rows.
 __global__ __launch_bounds__(kLargeMaxLanes) void k_mvs_enter_large(Bucket B, int S)
 {
@@ -1724,21 +1682,15 @@ hipError_t launch_diag(const Bucket *b, int nb, double *energy, double *angmom, 
     }
 static_assert(kMaxMvsBodies == 8, "FB_SWITCH_MVS covers n = 2..kMaxMvsBodies");
 
-hipError_t launch_mvs_enter(const Bucket &B, hipStream_t s)
+hipError_t launch_mvs_enter_large(const Bucket &B, hipStream_t s)
 {
     if (B.count == 0)
         return hipSuccess;
-    if (B.n > kMaxMvsBodies) {
-        dim3 grid;
-        int T, S;
-        if (!large_launch(B, 1, grid, T, S))
-            return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_mvs_enter_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
-        return hipGetLastError();
-    }
-#define FB_L(NN) hipLaunchKernelGGL(k_mvs_enter<NN>, grid_for(B.count, 64), dim3(64), 0, s, B)
-    FB_SWITCH_MVS(B.n, FB_L)
-#undef FB_L
+    dim3 grid;
+    int T, S;
+    if (!large_launch(B, 1, grid, T, S))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mvs_enter_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
     return hipGetLastError();
 }
 

@@ -1140,8 +1140,7 @@ fb_status fb_integrate_mvs(fb_ensemble *e, int64_t n_steps, double dt, const fb_
     if (n_steps == 0 || e->n_sys == 0)
         return FB_OK;
     if (!e->mvs_form()) {
-        for (const Bucket &B : e->buckets)
-            FB_HIP(launch_mvs_enter(B, e->stream));
+        FB_HIP(launch_mvs_enter(e->buckets.data(), (int)e->buckets.size(), e->stream));
         e->form = fb_ensemble::FORM_MVS;
     }
     FB_HIP(begin_run(e, start_steps(n_steps, dt)));
