@@ -276,15 +276,18 @@ __device__ __forceinline__ void mvs_kepler(const double mu, const Orbit (&o)[N],
 }
 
 // Fixed-step MVS integration of one system per lane for at most P.quantum
-// steps (the clock logic of the Hermite kernels).  Pm holds the planets'
-// momentum at a step's start and end: the closing drift of a step and the
-// opening one of the next use the same velocities.  Every lane takes every
-// step of its wavefront, one whose system has stopped with h = 0 (which
-// changes nothing), so the state is updated in place: a branch around the
-// step, or a break out of it, cost a copy of the state each step (about as
-// many moves as the step has FP64 instructions).  Bound by FP64 issue.
-// 131072 x 3 bodies, 4000 steps: 6.53 ms (8.0e10 system-steps/s); 22.3 ms
-// with the eccentric-anomaly drift and the branches.
+// steps (the clock logic of the Hermite kernels; a run is whole steps, so it
+// has no shortened last one).  Pm holds the planets' momentum at a step's start
+// and end: the closing drift of a step and the opening one of the next use the
+// same velocities.  Every lane takes every step of its wavefront, so the state
+// is updated in place: a branch around the step, or a break out of it, cost a
+// copy of the state each step (about as many moves as the step has FP64
+// instructions).  A lane that stops before the others is stored before its next
+// Kepler drift and goes on with h = 0 on registers that nothing reads any more:
+// the accelerations they come to hold are those after the closing drift, not
+// the carried ones to the last bit.
+// Bound by FP64 issue.  131072 x 3 bodies, 4000 steps: 6.53 ms (8.0e10
+// system-steps/s); 22.3 ms with the eccentric-anomaly drift and the branches.
 template <int N>
 __device__ __forceinline__ void mvs_spl_run(const Bucket &B, const int slot, const StepParams &P)
 {
@@ -295,53 +298,63 @@ __device__ __forceinline__ void mvs_spl_run(const Bucket &B, const int slot, con
     load_rows<N>(B, slot, m, Q, V, acc, true);
     const double inv_m0 = 1.0 / m[0];
     mvs_momentum<N>(m, V, Pm);
-    int budget = P.quantum;
+    double hs = c.dt;
+    const int nrun = run_segment(c, P, 0, P.quantum, hs);
+    int done = 0;
+    double h = nrun > 0 ? hs : 0.0;   // 0: stopped
+    bool live = nrun > 0;             // its registers are its state
+    bool finite = mvs_finite<N>(Q, V);
+    auto keep = [&]() {
+        finite = mvs_finite<N>(Q, V);
+        store_rows<N>(B, slot, Q, V, acc, true);
+        live = false;
+    };
+    // lanes that step, and lanes whose registers are their state
+    unsigned long long going = __ballot(h != 0.0), owed = going;
+    if (going != 0ull)
 #pragma unroll 1
-    for (int seg = 0; seg < 2; ++seg) {
-        double hs = c.dt;
-        const int nrun = run_segment(c, P, seg, budget, hs);
-        int done = 0;
-        double h = nrun > 0 ? hs : 0.0;   // 0: stopped
-        if (__any(h != 0.0))
-#pragma unroll 1
-        do {
-            double hh = 0.5 * h;
-            mvs_drift<N>(Q, V, Pm, inv_m0, hh);
-            mvs_kick<N>(V, acc, hh);
-            bool solved = true;
-            Orbit o[N];
-            const bool bound = mvs_orbits<N>(m[0], Q, V, o);
-            if (__any(!bound && h != 0.0)) {   // rare: undo the half step and stop
-                const double back = bound ? 0.0 : -hh;
-                mvs_kick<N>(V, acc, back);
-                mvs_momentum<N>(m, V, Pm);
-                mvs_drift<N>(Q, V, Pm, inv_m0, back);
-                if (!bound && h != 0.0) {
-                    c.status = ST_UNBOUND;
-                    h = hh = 0.0;
-                }
-                (void)mvs_orbits<N>(m[0], Q, V, o);
-            }
-            mvs_kepler<N, 1>(m[0], o, h, Q, V, solved);
-            if (__any(!solved && h != 0.0)) {
-                if (!solved && h != 0.0) {
-                    c.status = ST_UNBOUND;
-                    h = hh = 0.0;
-                }
-            }
-            mvs_acc<N>(m, Q, acc);
-            mvs_kick<N>(V, acc, hh);
+    do {
+        double hh = 0.5 * h;
+        mvs_drift<N>(Q, V, Pm, inv_m0, hh);
+        mvs_kick<N>(V, acc, hh);
+        bool solved = true;
+        Orbit o[N];
+        const bool bound = mvs_orbits<N>(m[0], Q, V, o);
+        if ((__ballot(!bound) & going) | (owed & ~going)) {   // rare
+            // undo the half step and stop
+            const double back = bound ? 0.0 : -hh;
+            mvs_kick<N>(V, acc, back);
             mvs_momentum<N>(m, V, Pm);
-            mvs_drift<N>(Q, V, Pm, inv_m0, hh);
-            done += h != 0.0 ? 1 : 0;
-            h = done < nrun ? h : 0.0;
-        } while (__any(h != 0.0));
-        budget -= done;
-        run_segment_end(c, P, seg, done);
-    }
-    if (!mvs_finite<N>(Q, V))
+            mvs_drift<N>(Q, V, Pm, inv_m0, back);
+            if (!bound && h != 0.0) {
+                c.status = ST_UNBOUND;
+                h = hh = 0.0;
+            }
+            if (live && h == 0.0)   // stopped here, or in the step before
+                keep();
+            owed = __ballot(live);
+            (void)mvs_orbits<N>(m[0], Q, V, o);
+        }
+        mvs_kepler<N, 1>(m[0], o, h, Q, V, solved);
+        if (__any(!solved && h != 0.0)) {
+            if (!solved && h != 0.0) {
+                c.status = ST_UNBOUND;
+                h = hh = 0.0;
+            }
+        }
+        mvs_acc<N>(m, Q, acc);
+        mvs_kick<N>(V, acc, hh);
+        mvs_momentum<N>(m, V, Pm);
+        mvs_drift<N>(Q, V, Pm, inv_m0, hh);
+        done += h != 0.0 ? 1 : 0;
+        h = done < nrun ? h : 0.0;
+        going = __ballot(h != 0.0);
+    } while (going != 0ull);
+    if (live)
+        keep();
+    run_segment_end(c, P, 0, done);
+    if (!finite)
         c.status = ST_NONFINITE;
-    store_rows<N>(B, slot, Q, V, acc, true);
     store_clock(B, slot, c);
 }
 
