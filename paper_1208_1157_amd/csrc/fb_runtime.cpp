@@ -1383,7 +1383,7 @@ fb_status fb_get_state(fb_ensemble *e, double *pos, double *vel, double *t, int3
     FB_HIP(launch_read_back(e->buckets.data(), (int)e->buckets.size(), out, e->mvs_form(), e->stream));
     const HostPart parts[] = {{pos, d_pos, 24 * N}, {vel, d_vel, 24 * N}, {t, d_t, 8 * ns},
                               {steps, d_steps, 8 * ns}, {status, d_status, 4 * ns}};
-    return read_to_host(parts, 5, e->stream);
+    return read_to_host(parts, 5, e->stream, e->device);
 }
 
 fb_status fb_get_hermite_state(fb_ensemble *e, double *acc0, double *jerk0, double *dt_next)
@@ -1409,7 +1409,7 @@ fb_status fb_get_hermite_state(fb_ensemble *e, double *acc0, double *jerk0, doub
     out.dtn = dt_next ? d_dtn : nullptr;
     FB_HIP(launch_read_back(e->buckets.data(), (int)e->buckets.size(), out, false, e->stream));
     const HostPart parts[] = {{acc0, d_acc, 24 * N}, {jerk0, d_jerk, 24 * N}, {dt_next, d_dtn, 8 * ns}};
-    return read_to_host(parts, 3, e->stream);
+    return read_to_host(parts, 3, e->stream, e->device);
 }
 
 fb_status fb_diagnostics(fb_ensemble *e, double *energy, double *angmom)
@@ -1422,7 +1422,7 @@ fb_status fb_diagnostics(fb_ensemble *e, double *energy, double *angmom)
     double *d_E = e->d_diag, *d_L = d_E + ns;
     FB_HIP(launch_diag(e->buckets.data(), (int)e->buckets.size(), d_E, d_L, e->mvs_form(), e->stream));
     const HostPart parts[] = {{energy, d_E, 8 * ns}, {angmom, d_L, 24 * ns}};
-    return read_to_host(parts, 2, e->stream);
+    return read_to_host(parts, 2, e->stream, e->device);
 }
 
 fb_status fb_ensemble_shape(const fb_ensemble *e, int32_t *n_sys, int64_t *n_bodies)

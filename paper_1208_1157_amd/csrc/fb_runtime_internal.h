@@ -202,14 +202,16 @@ struct HostBlock {
 };
 fb_status take_block(size_t bytes, HostBlock &out);
 void give_block(HostBlock &b);
-// Device ranges of one allocation -> host arrays (parts with a null `to` are
-// left out), after the work on stream s; returns when they are there.
+// Device ranges of one allocation on `device` -> host arrays (at most
+// kMostParts; parts with a null `to` are left out), after the work on stream s;
+// returns when they are there.  Throws nothing.
 struct HostPart {
     void *to;
     const void *from;
     size_t bytes;
 };
-fb_status read_to_host(const HostPart *parts, int n, hipStream_t s);
+constexpr int kMostParts = 8;
+fb_status read_to_host(const HostPart *parts, int n, hipStream_t s, int device);
 
 }  // namespace rt
 }  // namespace fb

@@ -5,8 +5,9 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
+#include <exception>
 #include <mutex>
-#include <system_error>
+#include <new>
 #include <thread>
 #include <vector>
 
@@ -79,24 +80,42 @@ void give_block(HostBlock &b)
 
 namespace {
 
-// Chunk of a read-back.
-struct Piece {
-    char *to;
-    const char *from;
-    size_t bytes;
+// The chunks of a read-back: megabytes of one part after another.
+struct Chunks {
+    const HostPart *parts;
+    int n;
+
+    static size_t of(const HostPart &p) { return p.to ? (p.bytes + kHostBlock - 1) / kHostBlock : 0; }
+    size_t count() const
+    {
+        size_t c = 0;
+        for (int i = 0; i < n; ++i)
+            c += of(parts[i]);
+        return c;
+    }
+    HostPart at(size_t k) const
+    {
+        int i = 0;
+        for (; k >= of(parts[i]); ++i)
+            k -= of(parts[i]);
+        const HostPart &p = parts[i];
+        const size_t off = k * kHostBlock;
+        return HostPart{static_cast<char *>(p.to) + off, static_cast<const char *>(p.from) + off,
+                        std::min(kHostBlock, p.bytes - off)};
+    }
 };
 
-// One worker's share of the pieces: each through this worker's own block and
+// One worker's share of the chunks: each through this worker's own block and
 // stream, so while one copies out of its block another's transfer runs.
-hipError_t drain(const std::vector<Piece> &pieces, std::atomic<size_t> &next, HostBlock &b)
+hipError_t drain(const Chunks &chunks, const size_t count, std::atomic<size_t> &next, HostBlock &b)
 {
     if (!b.stream) {
         const hipError_t e = hipStreamCreateWithFlags(&b.stream, hipStreamNonBlocking);
         if (e != hipSuccess)
             return e;
     }
-    for (size_t i; (i = next.fetch_add(1)) < pieces.size();) {
-        const Piece &p = pieces[i];
+    for (size_t k; (k = next.fetch_add(1)) < count;) {
+        const HostPart p = chunks.at(k);
         hipError_t e = hipMemcpyAsync(b.p, p.from, p.bytes, hipMemcpyDeviceToHost, b.stream);
         if (e == hipSuccess)
             e = hipStreamSynchronize(b.stream);
@@ -117,6 +136,45 @@ bool is_pinned(const void *p)
     return a.type == hipMemoryTypeHost;
 }
 
+// All chunks into the host arrays by several workers, on the current device.
+fb_status drain_all(const Chunks &chunks)
+{
+    const size_t count = chunks.count();
+    if (count == 0)
+        return FB_OK;
+    HostBlock own;
+    const fb_status st = take_block(kHostBlock, own);
+    if (st != FB_OK)
+        return st;
+    std::atomic<size_t> next{0};
+    std::atomic<int> failed{(int)hipSuccess};
+    std::thread threads[kReadWorkers - 1];
+    for (int k = 0; k < kReadWorkers - 1 && (size_t)k + 1 < count; ++k) {
+        try {
+            threads[k] = std::thread([&, dev = own.device] {
+                HostBlock b;
+                hipError_t e = hipSetDevice(dev);
+                if (e == hipSuccess && take_block(kHostBlock, b) == FB_OK) {
+                    e = drain(chunks, count, next, b);
+                    give_block(b);
+                }   // without a block the other workers take all chunks
+                if (e != hipSuccess)
+                    failed = (int)e;
+            });
+        } catch (const std::exception &) {
+            break;   // no thread, or no memory for one: those that there are take all chunks
+        }
+    }
+    hipError_t err = drain(chunks, count, next, own);
+    for (std::thread &t : threads)
+        if (t.joinable())
+            t.join();
+    if (err == hipSuccess)
+        err = (hipError_t)failed.load();
+    give_block(own);
+    return err == hipSuccess ? FB_OK : hip_fail(err, "read-back");
+}
+
 }  // namespace
 
 // The caller's arrays are ordinary memory, often fresh: a copy straight into
@@ -125,8 +183,10 @@ bool is_pinned(const void *p)
 // stream, a megabyte at a time: 131072 x 3 bodies (21.5 MB) 1290 -> 590 us
 // (two workers 820, half megabytes 590, quarters 700, six workers with halves
 // 540), 16384 x 6 (5 MB) 200.  What fits one block is a single transfer.
-fb_status read_to_host(const HostPart *parts, int n, hipStream_t s)
+fb_status read_to_host(const HostPart *parts, int n, hipStream_t s, int device)
 {
+    if (n > kMostParts)
+        return fail(FB_E_INVAL, "too many parts");
     size_t total = 0;
     const char *lo = nullptr, *hi = nullptr;
     for (int i = 0; i < n; ++i) {
@@ -141,11 +201,11 @@ fb_status read_to_host(const HostPart *parts, int n, hipStream_t s)
         FB_HIP(hipStreamSynchronize(s));
         return FB_OK;
     }
-    HostBlock own;
-    fb_status st = take_block(kHostBlock, own);
-    if (st != FB_OK)
-        return st;
-    if ((size_t)(hi - lo) <= own.bytes) {
+    if ((size_t)(hi - lo) <= kHostBlock) {
+        HostBlock own;
+        const fb_status st = take_block(kHostBlock, own);
+        if (st != FB_OK)
+            return st;
         hipError_t e = hipMemcpyAsync(own.p, lo, (size_t)(hi - lo), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess)
             e = hipStreamSynchronize(s);
@@ -156,51 +216,28 @@ fb_status read_to_host(const HostPart *parts, int n, hipStream_t s)
         give_block(own);
         return e == hipSuccess ? FB_OK : hip_fail(e, "read-back");
     }
+    HostPart rest[kMostParts];
     hipError_t err = hipSuccess;
-    std::vector<Piece> pieces;
-    for (int i = 0; i < n && err == hipSuccess; ++i) {
-        char *to = static_cast<char *>(parts[i].to);
-        const char *from = static_cast<const char *>(parts[i].from);
-        if (!to || !parts[i].bytes)
-            continue;
-        if (is_pinned(to)) {   // no second copy needed
-            err = hipMemcpyAsync(to, from, parts[i].bytes, hipMemcpyDeviceToHost, s);
-            continue;
+    for (int i = 0; i < n; ++i) {
+        rest[i] = parts[i];
+        if (err == hipSuccess && parts[i].to && parts[i].bytes && is_pinned(parts[i].to)) {   // no second copy needed
+            err = hipMemcpyAsync(parts[i].to, parts[i].from, parts[i].bytes, hipMemcpyDeviceToHost, s);
+            rest[i].to = nullptr;
         }
-        for (size_t at = 0; at < parts[i].bytes; at += kHostBlock)
-            pieces.push_back({to + at, from + at, std::min(kHostBlock, parts[i].bytes - at)});
     }
-    std::atomic<size_t> next{0};
-    std::atomic<int> failed{(int)hipSuccess};
-    if (err == hipSuccess)   // the workers copy on streams of their own
-        err = hipStreamSynchronize(s);
-    const int workers = (int)std::min<size_t>(pieces.size(), kReadWorkers);
-    std::vector<std::thread> threads;
-    if (err == hipSuccess) {
-        for (int k = 1; k < workers; ++k) {
-            try {
-                threads.emplace_back([&, dev = own.device] {
-                    HostBlock b;
-                    hipError_t e = hipSetDevice(dev);
-                    if (e == hipSuccess && take_block(kHostBlock, b) == FB_OK) {
-                        e = drain(pieces, next, b);
-                        give_block(b);
-                    }   // without a block the other workers take all pieces
-                    if (e != hipSuccess)
-                        failed = (int)e;
-                });
-            } catch (const std::system_error &) {
-                break;   // no more threads: those that there are take all pieces
-            }
-        }
-        err = drain(pieces, next, own);
-        for (std::thread &t : threads)
-            t.join();
-        if (err == hipSuccess)
-            err = (hipError_t)failed.load();
-    }
-    give_block(own);
-    return err == hipSuccess ? FB_OK : hip_fail(err, "read-back");
+    // the workers copy on streams of their own; and no copy of s is left
+    // behind by an error
+    const hipError_t es = hipStreamSynchronize(s);
+    FB_HIP(err);
+    FB_HIP(es);
+    int current = device;
+    FB_HIP(hipGetDevice(&current));
+    if (current == device)
+        return drain_all(Chunks{rest, n});
+    FB_HIP(hipSetDevice(device));   // the streams belong where the data is
+    const fb_status st = drain_all(Chunks{rest, n});
+    FB_HIP(hipSetDevice(current));
+    return st;
 }
 
 }  // namespace rt
