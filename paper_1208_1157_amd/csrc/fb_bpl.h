@@ -225,11 +225,14 @@ __device__ __forceinline__ int bpl_stop_flags(BplLds &L, const int lane, const i
     return sys_or_flags<N>(s, fl);
 }
 
-// Full-register-file variants of the evaluation and of the stop-rule pass,
-// for a wave that has its SIMD to itself and so waits out every LDS round
-// trip and every dependent latency: the partner slots (pidx) and masses (pm)
-// of this lane's body, in evaluation order, are fixed over the run and held
-// in registers; all partner reads are issued before the first interaction.
+// Unrolled variants of the evaluation and of the stop-rule pass, for a wave
+// that has its SIMD to itself or shares it with one other and so waits out most
+// LDS round trips and dependent latencies: the partner slots (pidx) and masses
+// (pm) of this lane's body, in evaluation order, are fixed over the run and held
+// in registers, and partners are read before the first interaction: all of
+// them, or (PARTS) a part of them at a time, where all would not leave room for
+// a second wave (14 and more bodies in fixed steps, which that wave gains: 240
+// VGPRs instead of 340).
 template <int N>
 __device__ __forceinline__ int eval_partner(const int k, const int b)
 {
@@ -237,8 +240,41 @@ __device__ __forceinline__ int eval_partner(const int k, const int b)
     return k < N - 2 ? k + 1 + (k + 1 >= skip ? 1 : 0) : (b == 0 ? N - 1 : 0);
 }
 
+// Interactions with the partners of part PART of PARTS, all read before the
+// first of them, and of the parts after it.
+template <int N, bool TS, int PART, int PARTS>
+__device__ __forceinline__ void bpl_partners(const BplLds &L, const int (&pidx)[N - 1],
+                                             const double (&pm)[N - 1], const double (&xi)[3],
+                                             const double (&vi)[3], double (&a)[3],
+                                             double (&jk)[3], double &wmax,
+                                             const double (&ic2)[N - 1], HillBound &hb)
+{
+    constexpr int K0 = PART * (N - 1) / PARTS, K1 = (PART + 1) * (N - 1) / PARTS;
+    Partner pj[K1 - K0];
+#pragma unroll
+    for (int k = K0; k < K1; ++k)
+        pj[k - K0] = Partner{L.xy[pidx[k]], L.zvx[pidx[k]], L.vyvz[pidx[k]], pm[k]};
+    if constexpr (N <= 9 || PARTS > 1)   // (more partners' state does not fit the VGPRs at once)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = K0; k < K1; ++k) {
+        double r2;
+        bpl_interact_p<TS>(pj[k - K0], xi, vi, a, jk, wmax, &r2);
+        if (TS) {
+            if (k < N - 2)
+                hb.least = fmin(hb.least, r2 * ic2[k]);
+            else
+                hb.ri2 = r2;
+        }
+    }
+    if constexpr (PART + 1 < PARTS) {
+        __builtin_amdgcn_sched_barrier(0);
+        bpl_partners<N, TS, PART + 1, PARTS>(L, pidx, pm, xi, vi, a, jk, wmax, ic2, hb);
+    }
+}
+
 // With TS, also the bound hb of the stop rules, with the pairs' 1 / c^2 in ic2.
-template <int N, bool TS>
+template <int N, bool TS, int PARTS>
 __device__ __forceinline__ void bpl_eval_regs(BplLds &L, const int lane, const int (&pidx)[N - 1],
                                               const double (&pm)[N - 1], const double (&xi)[3],
                                               const double (&vi)[3], double (&a)[3],
@@ -249,29 +285,13 @@ __device__ __forceinline__ void bpl_eval_regs(BplLds &L, const int lane, const i
     L.zvx[lane] = make_double2(xi[2], vi[0]);
     L.vyvz[lane] = make_double2(vi[1], vi[2]);
     wave_sync();
-    Partner pj[N - 1];
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k)
-        pj[k] = Partner{L.xy[pidx[k]], L.zvx[pidx[k]], L.vyvz[pidx[k]], pm[k]};
-    if constexpr (N <= 9)   // (more partners' state does not fit the VGPRs at once)
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         a[c] = 0.0;
         jk[c] = 0.0;
     }
     hb.least = DBL_MAX;
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) {
-        double r2;
-        bpl_interact_p<TS>(pj[k], xi, vi, a, jk, wmax, &r2);
-        if (TS) {
-            if (k < N - 2)
-                hb.least = fmin(hb.least, r2 * ic2[k]);
-            else
-                hb.ri2 = r2;
-        }
-    }
+    bpl_partners<N, TS, 0, PARTS>(L, pidx, pm, xi, vi, a, jk, wmax, ic2, hb);
     wave_sync();
 }
 
@@ -363,12 +383,13 @@ __device__ __forceinline__ void bpl_step(BplLds &L, const int lane, const int b,
                                          double (&jk)[3], double &w, const double (&ic2)[N - 1],
                                          HillBound &hb, double &moved2)
 {
+    constexpr int PARTS = !TS && N >= 14 ? 3 : 1;
     double bx[3], bv[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         predict_comp(k, x[c], v[c], a0[c], j0[c], xc[c], vc[c], bx[c], bv[c]);
     if constexpr (REGS)
-        bpl_eval_regs<N, false>(L, lane, pidx, pm, xc, vc, ak, jk, w, ic2, hb);
+        bpl_eval_regs<N, false, PARTS>(L, lane, pidx, pm, xc, vc, ak, jk, w, ic2, hb);
     else
         bpl_eval<N, false, ILP>(L, lane, b, s, xc, vc, ak, jk, w);
 #pragma unroll
@@ -376,7 +397,7 @@ __device__ __forceinline__ void bpl_step(BplLds &L, const int lane, const int b,
         correct_comp(k, bx[c], bv[c], ak[c], jk[c], xc[c], vc[c]);
     const double x1[3] = {xc[0], xc[1], xc[2]};
     if constexpr (REGS)
-        bpl_eval_regs<N, TS>(L, lane, pidx, pm, xc, vc, ak, jk, w, ic2, hb);
+        bpl_eval_regs<N, TS, PARTS>(L, lane, pidx, pm, xc, vc, ak, jk, w, ic2, hb);
     else
         bpl_eval<N, TS, ILP>(L, lane, b, s, xc, vc, ak, jk, w);
 #pragma unroll

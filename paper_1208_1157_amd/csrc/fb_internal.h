@@ -28,8 +28,8 @@ constexpr int kMaxLargeBodies = 512;   // larger systems run the runtime-n large
 constexpr int kMaxSplBodies = 10;      // plain system-per-lane instances exist for n <= 10
 constexpr int kMaxSplAdv = 8;          // ... with adaptive steps / stop rules for n <= 8
 constexpr int kMaxSplPersistent = 0;   // the body-per-lane fused class runs no system-per-lane tiles
-constexpr int kMaxUnrolled = 12;       // body per lane: 4..12 bodies always run unrolled
-constexpr int kMaxUnrolledAdv = 10;    // ... with adaptive steps / stop rules 4..10
+constexpr int kMaxUnrolledAdv = 10;    // body per lane: 4 and more bodies always run unrolled, with
+                                       // adaptive steps / stop rules 4..10
 constexpr int kMaxRkckSpl = 6;         // fixed Cash-Karp steps system per lane exist for n <= 6
 constexpr int kMaxMvsBodies = 8;       // MVS kernels (system per lane) exist for n <= 8
 

@@ -481,7 +481,7 @@ __device__ __noinline__ bool bpl_tile(const Bucket &B, const Tile &T, const int 
                                       const StepParams &P, int &slot)
 {
     const StepParams Pr = uniform_params(P);
-    constexpr bool kRegs = N <= (ADV ? kMaxUnrolledAdv : kMaxUnrolled);
+    constexpr bool kRegs = !ADV || N <= kMaxUnrolledAdv;
     return bpl_run<N, ADV, CLS, kRegs>(B, T.first, T.count, list, Pr, slot);
 }
 
@@ -496,8 +496,7 @@ __device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const in
 
 // Tile dispatch.  The body-per-lane class (SPLC false) keeps the fused
 // kernel at 256 VGPRs (2 waves per SIMD) and runs every tile body-per-lane,
-// partner loops unrolled up to 12 bodies (10 with adaptive steps / stop
-// rules); the system-per-lane class gives the kernel the full register file (1
+// partner loops unrolled (up to 10 bodies with adaptive steps / stop rules); the system-per-lane class gives the kernel the full register file (1
 // wave per SIMD) and runs system-per-lane tiles up to n = 10 (n = 8 with
 // adaptive steps / stop rules), body-per-lane beyond.
 // The body-per-lane class had rolled loops for every n and 3 waves per SIMD
@@ -508,7 +507,10 @@ __device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const in
 // bodies, 500 fixed steps 8.87 and 8.40 ms; 65536 of 4..8 bodies, adaptive
 // with stop rules, 10 orbits 78.4 and 72.6 ms; 16384 of them, 3 orbits, 11.4
 // and 10.6 ms; 24 requests to a server (a few hundred wavefronts) 22.4 and
-// 13.9 ms of kernels.
+// 13.9 ms of kernels.  13..16 bodies, fixed steps, 16000 and 65536 systems of 14:
+// three waves rolled 707 and 2457 us, two rolled 811 and 2555, two unrolled (the
+// partners in three parts) 550 and 2130.  11..16 with rules stay rolled: two waves take
+// 0.94 to 0.99 of three waves' time with adaptive steps.
 template <bool ADV, bool SPLC>
 __device__ __forceinline__ bool run_tile(const Bucket &B, const Tile &T, const int *list,
                                          const StepParams &P, int &slot)
@@ -1552,10 +1554,8 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
         default: return hipErrorInvalidValue;
         }
     } else {
-        static_assert(kMaxUnrolled == 12, "the body counts that launch_unrolled does not always serve");
-        switch (B.n) {
-            FB_L(2, false); FB_L(3, false); FB_L(13, false); FB_L(14, false); FB_L(15, false);
-            FB_L(16, false);
+        switch (B.n) {   // the body counts that launch_unrolled does not always serve
+            FB_L(2, false); FB_L(3, false);
         default: return hipErrorInvalidValue;
         }
     }

@@ -97,12 +97,11 @@ inline bool fused_split_done(const std::vector<FusedGroup> &groups)
 // Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the
 // several-lanes-a-body ones (fb_split.h, measured there) while
 // no SIMD gets more than one of their wavefronts, or the unrolled kernels
-// (fb_unrolled.hip, where both sides are measured) for 4..12
+// (fb_unrolled.hip, where both sides are measured) for 4..16
 // bodies (4..10 with adaptive steps or stop rules); for other body counts
-// while their wavefronts are few: 2 and 3 bodies to one per SIMD (the quad
-// layout holds 16 systems a wavefront, the rolled one 32 and 21), 13..16 to
-// four (beyond, loops that do not fit the instruction cache well lose), 11..16
-// with adaptive steps or stop rules to one (their registers leave one wave).
+// while their wavefronts are no more than one per SIMD: 2 and 3 bodies (the quad
+// layout holds 16 systems a wavefront, the rolled one 32 and 21), and 11..16
+// with adaptive steps or stop rules (their registers leave one wave).
 inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
 {
     if (B.n > kMaxBodies)
@@ -111,9 +110,8 @@ inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
         for (int map : {MAP_SPLIT4, MAP_SPLIT2})
             if (split_tiles(B.n, B.count, map) <= 4LL * num_cu)
                 return map;
-    const bool always = B.n >= 4 && B.n <= (adv ? kMaxUnrolledAdv : kMaxUnrolled);
-    const int waves_per_simd = B.n >= 13 && !adv ? 4 : 1;
-    return always || unrolled_tiles(B) <= 4LL * num_cu * waves_per_simd ? MAP_BPLU : MAP_BPL;
+    const bool always = B.n >= 4 && (!adv || B.n <= kMaxUnrolledAdv);
+    return always || unrolled_tiles(B) <= 4LL * num_cu ? MAP_BPLU : MAP_BPL;
 }
 
 // Lane mapping of a plain launch over bucket B: the plan's, or (auto)

@@ -11,12 +11,15 @@
 // rolled loops' address arithmetic and the dependent chain of one interaction
 // after another still cost issue slots.  Microseconds per step against the
 // rolled loops of k_plain_bpl (3 waves per SIMD), fixed steps:
-//   waves per SIMD     n = 3        4           6           8          12          16
-//   0.1             0.64 0.46  0.95 0.62  1.40 0.92  1.91 1.18  2.80 1.90  3.83 2.42
-//   1               0.72 0.55  1.45 0.76  2.10 1.32  2.81 1.77  4.14 2.48  5.61 3.15
-//   2               1.06 1.05  1.69 1.45  2.50 2.26  3.30 2.91  4.91 4.20  6.48 5.99
-//   4                                     4.46 4.15  5.90 5.42  8.75 7.72  11.4 10.9
-//   8                                                           15.8 14.6  20.9 21.2
+//   waves per SIMD     n = 3        4           6           8          12
+//   0.1             0.64 0.46  0.95 0.62  1.40 0.92  1.91 1.18  2.80 1.90
+//   1               0.72 0.55  1.45 0.76  2.10 1.32  2.81 1.77  4.14 2.48
+//   2               1.06 1.05  1.69 1.45  2.50 2.26  3.30 2.91  4.91 4.20
+//   4                                     4.46 4.15  5.90 5.42  8.75 7.72
+//   8                                                           15.8 14.6
+// 13..16 bodies, where two wavefronts on a SIMD hold a part of the partners at a
+// time: 60 steps of 16 bodies, 8192 systems (2 wavefronts a SIMD) 540 and 350
+// us, 16000 730 and 645, 32000 1402 and 1240, 131072 4977 and 4574;
 // and with adaptive steps and the stop rules, 1 and 4 waves per SIMD: n = 8
 // 1.68x and 1.17x, n = 12 1.63x and 0.93x (its registers leave one wave per
 // SIMD), n = 2 and 3 past one wave 0.94x and 0.88x.  bpl_mapping draws the line.
@@ -361,7 +364,8 @@ __device__ __forceinline__ void quad_run(const Bucket &B, const int first, const
 // ---------------------------------------------------------------------------
 
 template <int N, bool ADV>
-__global__ __launch_bounds__(64) void k_bpl_unrolled(Bucket B, StepParams P)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(N >= 14 && !ADV ? 2 : 1)))
+void k_bpl_unrolled(Bucket B, StepParams P)
 {
     if constexpr (N <= 4) {
         const int first = blockIdx.x * kQuadSystems;
