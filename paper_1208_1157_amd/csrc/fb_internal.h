@@ -30,6 +30,7 @@ constexpr int kMaxSplAdv = 8;          // ... with adaptive steps / stop rules f
 constexpr int kMaxSplPersistent = 0;   // the body-per-lane fused class runs no system-per-lane tiles
 constexpr int kMaxUnrolledAdv = 10;    // body per lane: 4 and more bodies always run unrolled, with
                                        // adaptive steps / stop rules 4..10
+constexpr int kMaxUnrolledStops = 8;   // ... with stop rules in fixed steps 4..8
 constexpr int kMaxRkckSpl = 6;         // fixed Cash-Karp steps system per lane exist for n <= 6
 constexpr int kMaxMvsBodies = 8;       // MVS kernels (system per lane) exist for n <= 8
 

@@ -1547,10 +1547,10 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
     const size_t lds = sizeof(BplLds) * W;
 #define FB_L(NN, ADV) case NN: hipLaunchKernelGGL((k_plain_bpl<NN, ADV>), grid, dim3(64 * W), lds, s, B, P); break
     if (adv) {
-        static_assert(kMaxUnrolledAdv == 10, "the body counts that launch_unrolled does not always serve");
+        static_assert(kMaxUnrolledStops == 8, "the body counts that launch_unrolled does not always serve");
         switch (B.n) {
-            FB_L(2, true); FB_L(3, true); FB_L(11, true); FB_L(12, true); FB_L(13, true);
-            FB_L(14, true); FB_L(15, true); FB_L(16, true);
+            FB_L(2, true); FB_L(3, true); FB_L(9, true); FB_L(10, true); FB_L(11, true);
+            FB_L(12, true); FB_L(13, true); FB_L(14, true); FB_L(15, true); FB_L(16, true);
         default: return hipErrorInvalidValue;
         }
     } else {

@@ -441,7 +441,7 @@ fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound)
                 continue;
             }
             const Plan p = get_plan(B.n);
-            const int map = plain_mapping(p, B, P.adaptive || P.stop_rules, e->num_cu);
+            const int map = plain_mapping(p, B, P.adaptive != 0, P.stop_rules != 0, e->num_cu);
             FB_HIP(launch_plain(B, map, p.waves_per_group, P, e->stream));
         }
         if (quantum == INT_MAX)
@@ -471,15 +471,23 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     const int nbk = (int)e->buckets.size();
     if (nbk == 0)
         return FB_OK;
+    const Plan p0 = get_plan(0);
     // Buckets are laid out in descending n: the large-n ones (n > kMaxBodies)
     // come first and run their own plain launches inside every quantum; the
-    // fused launch's tile queue covers the others.
+    // fused launch's tile queue covers the others.  Fixed steps with stop rules
+    // of 10 and more bodies, uncompacted, join them where a bucket gives every
+    // SIMD two wavefronts: the plain launch runs three there, the fused one two
+    // (60 steps of 16000 systems of 10 bodies 519 and 593 us, of 16 1082 and
+    // 1190; of 65536 of 16 3651 and 3936).
+    auto own_launch = [&](const Bucket &B) {
+        return B.n > kMaxBodies || (o.stop_rules && !o.adaptive && !o.compact && p0.mapping != MAP_SPL &&
+                                    B.n >= 10 && B.count / (64 / B.n) >= 8 * e->num_cu);
+    };
     int n_large = 0;
-    while (n_large < nbk && e->buckets[n_large].n > kMaxBodies)
+    while (n_large < nbk && own_launch(e->buckets[n_large]))
         ++n_large;
     const int nb_small = nbk - n_large;
     const std::vector<Bucket> small(e->buckets.begin() + n_large, e->buckets.end());
-    const Plan p0 = get_plan(0);
     const bool adv = o.adaptive || o.stop_rules;
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
     StepParams P = make_params(o, quantum);
@@ -521,7 +529,7 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
             gpc = std::min(gpc, occ);
         grid = std::max(1, gpc * e->num_cu);
         if (c == 0)
-            fused_split(sizes, e->num_cu, (long long)grid * W);
+            fused_split(sizes, e->num_cu, (long long)grid * W, fused_two_most(o.adaptive != 0, o.stop_rules != 0));
         // (tiles of several lanes a body are more than those of one: the
         // staging area holds 96 bytes a body and is free during a run)
         d_tiles = e->d_tiles;
@@ -560,7 +568,15 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         if (!compact)
             k = 0;
         for (int i = 0; i < n_large; ++i) {
-            const hipError_t err = launch_large(e->buckets[i], P, e->num_cu, s);
+            const Bucket &B = e->buckets[i];
+            hipError_t err;
+            if (B.n > kMaxBodies) {
+                err = launch_large(B, P, e->num_cu, s);
+            } else {
+                const Plan p = get_plan(B.n);
+                err = launch_plain(B, plain_mapping(p, B, P.adaptive != 0, P.stop_rules != 0, e->num_cu),
+                                   p.waves_per_group, P, s);
+            }
             if (err != hipSuccess)
                 return err;
         }
@@ -830,7 +846,7 @@ fb_status run_mvs(fb_ensemble *e, const fb_opts &o, long long step_bound)
                 ProfScope ps(e->stream);
                 FB_HIP(launch_plain_mvs_large(B, P, e->stream));
             } else if (B.n <= kMaxMvsBodies &&
-                       plain_mapping(get_plan(B.n), B, false, e->num_cu) == MAP_SPL) {
+                       plain_mapping(get_plan(B.n), B, false, false, e->num_cu) == MAP_SPL) {
                 ProfScope ps(e->stream);
                 FB_HIP(launch_plain_mvs(B, 1, P, e->stream));
             } else {
@@ -1526,7 +1542,7 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
             for (int W : {1, 2, 4}) {
                 if (B.n <= kMaxSplBodies)
                     cands.push_back({MAP_SPL, W});
-                cands.push_back({bpl_mapping(B, false, e->num_cu), W});
+                cands.push_back({bpl_mapping(B, false, false, e->num_cu), W});
             }
             double best = 1e300;
             size_t best_i = 0;

@@ -57,12 +57,24 @@ struct FusedGroup {
     int map;
 };
 
+// With two lanes a body a lane holds the terms of up to 8 partners, which spill
+// from a fused launch's 256 VGPRs beside the state of a run with rules: 60
+// fixed steps with stop rules of 2000 systems, two lanes and one (rolled, three
+// waves a SIMD), 11 bodies 208 and 302 us, 12 380 and 328, 14 509 and 379, 16 554
+// and 422; adaptive (Eq. 5) 13 bodies 2.75 and 3.29 ms, 14 2.54 and 2.26, 16 2.91
+// and 2.47.
+inline int fused_two_most(bool adaptive, bool stops)
+{
+    return adaptive ? 13 : stops ? 11 : kMaxBodies;
+}
+
 // Mappings of the tiles of a fused launch with `waves` wavefronts resident: as
 // long as all tiles have a wavefront each and no SIMD more than one, the group
 // that takes longest gets two lanes a body, then four (kMinSplit bodies and
 // more), since the launch lasts as long as its slowest tile.  24 requests to a
-// server (3..10 bodies): 9.4 ms; one choice for all groups 10.4.
-inline void fused_split(std::vector<FusedGroup> &groups, int num_cu, long long waves)
+// server (3..10 bodies): 9.4 ms; one choice for all groups 10.4.  two_most is the
+// most bodies that get two lanes (fused_two_most), larger ones four at once.
+inline void fused_split(std::vector<FusedGroup> &groups, int num_cu, long long waves, int two_most)
 {
     const long long most = std::min(4LL * num_cu, waves);
     long long tiles = 0;
@@ -77,7 +89,7 @@ inline void fused_split(std::vector<FusedGroup> &groups, int num_cu, long long w
                 slow = &g;
         if (!slow || slow->n < kMinSplit || slow->map == MAP_SPLIT4)
             break;
-        const int next = slow->map == MAP_BPL ? MAP_SPLIT2 : MAP_SPLIT4;
+        const int next = slow->map == MAP_BPL && slow->n <= two_most ? MAP_SPLIT2 : MAP_SPLIT4;
         tiles += split_tiles(slow->n, slow->count, next) - split_tiles(slow->n, slow->count, slow->map);
         if (tiles <= most)
             slow->map = next;
@@ -101,8 +113,12 @@ inline bool fused_split_done(const std::vector<FusedGroup> &groups)
 // bodies (4..10 with adaptive steps or stop rules); for other body counts
 // while their wavefronts are no more than one per SIMD: 2 and 3 bodies (the quad
 // layout holds 16 systems a wavefront, the rolled one 32 and 21), and 11..16
-// with adaptive steps or stop rules (their registers leave one wave).
-inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
+// with adaptive steps or stop rules (their registers leave one wave).  With stop
+// rules in fixed steps 9 and 10 bodies, which they leave one wave too, to two per
+// SIMD: 60 steps of 9 bodies, unrolled and rolled, 12000 systems 385 and 390 us,
+// 16000 478 and 455, 50000 1130 and 1022; of 10 16000 570 and 516, 50000 1568 and
+// 1378 (with adaptive steps, a longer chain to hide, one wave is faster there).
+inline int bpl_mapping(const Bucket &B, bool adaptive, bool stops, int num_cu)
 {
     if (B.n > kMaxBodies)
         return MAP_BPL;
@@ -110,22 +126,24 @@ inline int bpl_mapping(const Bucket &B, bool adv, int num_cu)
         for (int map : {MAP_SPLIT4, MAP_SPLIT2})
             if (split_tiles(B.n, B.count, map) <= 4LL * num_cu)
                 return map;
-    const bool always = B.n >= 4 && (!adv || B.n <= kMaxUnrolledAdv);
-    return always || unrolled_tiles(B) <= 4LL * num_cu ? MAP_BPLU : MAP_BPL;
+    const int most = adaptive ? kMaxUnrolledAdv : stops ? kMaxUnrolledStops : kMaxBodies;
+    const bool always = B.n >= 4 && B.n <= most;
+    const int waves_per_simd = !adaptive && stops && B.n > kMaxUnrolledStops && B.n <= kMaxUnrolledAdv ? 2 : 1;
+    return always || unrolled_tiles(B) <= 4LL * num_cu * waves_per_simd ? MAP_BPLU : MAP_BPL;
 }
 
 // Lane mapping of a plain launch over bucket B: the plan's, or (auto)
 // system-per-lane when n allows it and the bucket's 64-system tiles give
 // every SIMD of the device a wavefront, else body-per-lane, whose n lanes
 // per system spread a small bucket over more of the device.
-inline int plain_mapping(const Plan &p, const Bucket &B, bool adv, int num_cu)
+inline int plain_mapping(const Plan &p, const Bucket &B, bool adaptive, bool stops, int num_cu)
 {
-    const int lim = adv ? kMaxSplAdv : kMaxSplBodies;
+    const int lim = adaptive || stops ? kMaxSplAdv : kMaxSplBodies;
     if (p.mapping == MAP_BPL || B.n > lim)
-        return bpl_mapping(B, adv, num_cu);
+        return bpl_mapping(B, adaptive, stops, num_cu);
     if (p.mapping == MAP_SPL)
         return MAP_SPL;
-    return (B.count + 63) / 64 >= 4LL * num_cu ? MAP_SPL : bpl_mapping(B, adv, num_cu);
+    return (B.count + 63) / 64 >= 4LL * num_cu ? MAP_SPL : bpl_mapping(B, adaptive, stops, num_cu);
 }
 
 // Fused persistent kernel class for a launch over buckets of these body

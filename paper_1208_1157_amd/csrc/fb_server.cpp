@@ -746,7 +746,7 @@ fb_status run_quantum(fb_server *S, std::vector<Request *> &finished, double &sy
         std::vector<FusedGroup> sizes;
         for (const Group &G : groups)
             sizes.push_back({G.n, G.len, (double)G.adv, MAP_BPL});
-        fused_split(sizes, S->num_cu, (long long)resident_waves);
+        fused_split(sizes, S->num_cu, (long long)resident_waves, fused_two_most(false, false));
         for (size_t g = 0; g < groups.size(); ++g)
             groups[g].map = sizes[g].map;
     }
