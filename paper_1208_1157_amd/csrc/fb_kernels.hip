@@ -707,9 +707,11 @@ __device__ __forceinline__ void load_xv(const Bucket &B, int s, double (&m)[N], 
 }
 
 // Start of a run with adaptive steps (one thread per slot): the clock, and the
-// step proposed from the current state when none is carried yet.
+// step proposed from the current state when none is carried yet.  One wavefront a
+// workgroup, told to the compiler, so that a system's bodies fit the registers
+// (6000 x 16 bodies 52 us with the default bound and its scratch, 12 without).
 template <int N>
-__global__ void k_begin_run(Bucket B, RunStart run)
+__global__ __launch_bounds__(64) void k_begin_run(Bucket B, RunStart run)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= B.count)
@@ -818,8 +820,9 @@ __global__ __launch_bounds__(64) void k_diag(BucketSet set, double *energy, doub
 //   kind 1 (RV):     [o][k][2] = t and the star's velocity relative to the
 //                    system's centre of mass along the unit line of sight l;
 //   kind 2 (energy): [o][k][5] = t, E, L.
+// Bound as k_begin_run (a record of 6000 x 14 bodies 37 us with scratch, 9.5 without).
 template <int N>
-__global__ void k_log(Bucket B, const long long *__restrict__ orig_off, int kind, double lx,
+__global__ __launch_bounds__(64) void k_log(Bucket B, const long long *__restrict__ orig_off, int kind, double lx,
                       double ly, double lz, int k, int max_records, double *out)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
