@@ -494,56 +494,111 @@ struct LargeShape {
     int K, G, T, S;
 };
 
+// What a run does besides fixed steps.
+struct LargeRules {
+    bool adaptive, stops;
+};
+
 // Estimated time (us) of a step while `now` workgroups of `waves` wavefronts
 // share a CU: either the chain of one lane's interactions (0.17 us a partner
 // of one body, 0.29 us of two; 0.2 us to add the shares of two lanes; 0.13 us
 // of barrier a wavefront) or the issue of a SIMD's wavefronts (0.16 or 0.29 us
 // a partner and wavefront, 0.6 us a body and wavefront for the rest of the
 // step), the larger and a little more.  Workgroups of 2 or 3 wavefronts load
-// the SIMDs unevenly.
-double large_step_us(int K, int log_g, int parts, int waves, int now)
+// the SIMDs unevenly.  The rules add to it: two bodies a lane cost a little more
+// a partner (their step-rule quantities; more where lanes share partners), the
+// stop rules a pass over the partners, the step rule a pass over the system.
+double large_step_us(int K, int log_g, int n, int waves, int now, LargeRules r)
 {
+    const int parts = (n + (1 << log_g) - 1) >> log_g;
     double per_simd = (now * waves + 3) / 4;
     if (now > 1 && (waves == 2 || waves == 3))
         per_simd = 1.2 * std::max(2.0, per_simd);
-    const double chain = 0.7 + parts * (K == 1 ? 0.17 : 0.29) + 0.2 * K * log_g + 0.13 * waves;
-    const double issue = per_simd * (parts * (K == 1 ? 0.16 : 0.29) + 0.6 * K);
+    double chain = 0.7 + parts * (K == 1 ? 0.17 : 0.29) + 0.2 * K * log_g + 0.13 * waves;
+    double issue = per_simd * (parts * (K == 1 ? 0.16 : 0.29) + 0.6 * K);
+    if (r.adaptive || r.stops) {
+        const double pair = K == 1 ? 0.0 : log_g == 0 ? 0.0053 : 0.0202;
+        chain += pair * parts;
+        issue += per_simd * pair * parts;
+    }
+    if (r.stops) {
+        chain += (K == 1 ? 0.0552 : 0.0448) * parts;
+        issue += per_simd * (K == 1 ? 0.0079 : 0.0302) * parts;
+    }
+    if (r.adaptive)
+        chain += 0.0517 * n;
     const double c2 = chain * chain, c4 = c2 * c2, i2 = issue * issue, i4 = i2 * i2;
     return std::sqrt(std::sqrt(std::sqrt(c4 * c4 + i4 * i4)));   // (8th powers)
 }
 
-// The layout with the least estimated time.  A CU takes 8 wavefronts at a
-// time, 2 a SIMD, so a run is so many full rounds and one of the workgroups
-// left over.  The constants are a fit to 3300 timed layouts (31 body counts
-// of 17..512, 1..6000 systems); the pick is 1.5% slower than the best of them
-// on average and 14% at worst (350 bodies, 1024 systems: 425 against 373 us).
-// Few systems spread out (64 bodies: 8 lanes a body up to 256 systems, 4.2-5.1
-// us a step against 11-12.5 with one; 4 lanes to 512, 7.9 us); a full device
-// does not split (4096 x 64: two bodies a lane 40 us, one body on 4 lanes
-// 46-56).
-LargeShape large_layout(int n, int count, int num_cu)
+// Estimated time (us a step) of a run of `count` systems.  A CU takes 8
+// wavefronts at a time, 2 a SIMD, so a run is so many full rounds and one of
+// the workgroups left over.  With adaptive steps the systems take different
+// numbers of steps, and the slowest several times the mean: a workgroup lasts
+// as long as the slowest of its S systems (0.186 ln S more), and the last ones
+// run with the device to themselves (3.59 steps more).
+double large_run_us(const LargeShape &f, int n, int count, int num_cu, LargeRules r)
+{
+    int log_g = 0;
+    while ((1 << log_g) < f.G)
+        ++log_g;
+    const int waves = f.T / 64, at_once = std::max(1, 8 / waves);
+    const int per_cu = ((count + f.S - 1) / f.S + num_cu - 1) / num_cu;   // workgroups
+    const int left = per_cu % at_once;
+    const double t = per_cu / at_once * large_step_us(f.K, log_g, n, waves, at_once, r) +
+                     (left ? large_step_us(f.K, log_g, n, waves, left, r) : 0.0);
+    if (!r.adaptive)
+        return t;
+    return t * (1.0 + 0.186 * std::log((double)f.S)) + 3.59 * large_step_us(f.K, log_g, n, waves, 1, r);
+}
+
+LargeShape large_best(int n, int count, int num_cu, LargeRules r)
 {
     LargeShape best{1, 1, 0, 0};
     double least = 0.0;
     for (int K = 1; K <= 2; ++K)
-        for (int log_g = 0; log_g <= 3; ++log_g) {
-            const int G = 1 << log_g, L = (n + K - 1) / K * G, parts = (n + G - 1) / G;
+        for (int G = 1; G <= 8; G *= 2) {
+            const int L = (n + K - 1) / K * G;
             for (int T = 64; T <= kLargeMaxLanes; T += 64) {
                 const int S = std::min(std::min(T / L, kLargeMaxLanes / n), count);
                 if (S < 1 || S * L <= T - 64)   // (a smaller T holds as many)
                     continue;
-                const int waves = T / 64, at_once = std::max(1, 8 / waves);
-                const int per_cu = ((count + S - 1) / S + num_cu - 1) / num_cu;   // workgroups
-                const int left = per_cu % at_once;
-                const double t = per_cu / at_once * large_step_us(K, log_g, parts, waves, at_once) +
-                                 (left ? large_step_us(K, log_g, parts, waves, left) : 0.0);
+                const LargeShape f{K, G, T, S};
+                const double t = large_run_us(f, n, count, num_cu, r);
                 if (best.S == 0 || t < least) {
                     least = t;
-                    best = LargeShape{K, G, T, S};
+                    best = f;
                 }
             }
         }
     return best;
+}
+
+// The layout with the least estimated time.  For fixed steps the constants are
+// a fit to 3300 timed layouts (31 body counts of 17..512, 1..6000 systems); the
+// pick is 1.5% slower than the best of them on average and 14% at worst (350
+// bodies, 1024 systems: 425 against 373 us).  Few systems spread out (64 bodies:
+// 8 lanes a body up to 256 systems, 4.2-5.1 us a step against 11-12.5 with one;
+// 4 lanes to 512, 7.9 us); a full device does not split (4096 x 64: two bodies a
+// lane 40 us, one body on 4 lanes 46-56).
+// Runs with rules spread out more.  The rules' constants are a fit to 372 runs
+// (17..512 bodies, 4..6000 systems; adaptive with and without stop rules, fixed
+// steps with them; 28 layouts each on average): the pick is 2% slower than the
+// best on average and 38% at worst (40 bodies, 3000 systems), the layout for
+// fixed steps 11% and 3.2 times.  80 bodies, 3000 systems, adaptive 14.9 -> 6.6
+// ms, 200 bodies, 1000 systems 22.2 -> 15.7.  The layout for fixed steps stays
+// where another is not clearly better, a tenth with adaptive steps alone and a
+// twentieth with stop rules alone: closer ones the estimate does not tell apart
+// (33 bodies, 1000 systems, adaptive, 303 and 343 us; 200 bodies, 4 systems, stop
+// rules, 1.20 and 1.26 ms).
+LargeShape large_layout(int n, int count, int num_cu, LargeRules r)
+{
+    const LargeShape f = large_best(n, count, num_cu, r);
+    if (r.adaptive == r.stops)
+        return f;
+    const LargeShape g = large_best(n, count, num_cu, LargeRules{false, false});
+    const double clear = r.adaptive ? 0.9 : 0.95;
+    return large_run_us(f, n, count, num_cu, r) > clear * large_run_us(g, n, count, num_cu, r) ? g : f;
 }
 
 template <int K, bool SPLIT>
@@ -566,7 +621,7 @@ hipError_t launch_large(const Bucket &B, const StepParams &P, int num_cu, hipStr
 {
     if (B.count == 0)
         return hipSuccess;
-    const LargeShape f = large_layout(B.n, B.count, num_cu);
+    const LargeShape f = large_layout(B.n, B.count, num_cu, LargeRules{P.adaptive != 0, P.stop_rules != 0});
     if (f.S < 1)
         return hipErrorInvalidValue;
     if (f.K == 1 && f.G == 1)
