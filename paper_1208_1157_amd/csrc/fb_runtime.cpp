@@ -524,6 +524,8 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     auto set_class = [&](int c) -> hipError_t {
         const int spl_lim = persistent_spl_limit(c, adv ? 1 : 0);
         int gpc = p0.groups_per_cu > 0 ? p0.groups_per_cu : 8;
+        if (placed)   // the plan's wavefronts, a workgroup each
+            gpc *= std::max(1, std::min(4, p0.waves_per_group));
         const int occ = persistent_max_groups_per_cu(adv ? 1 : 0, c, W);
         if (occ > 0)
             gpc = std::min(gpc, occ);
