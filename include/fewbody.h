@@ -388,9 +388,12 @@ fb_status fb_get_plan(int32_t n, int32_t *mapping, int32_t *waves_per_group,
  * measurement as its Section 5.3 recommends).  On ensemble e, for every body
  * count it holds, times `steps` fixed steps of dt with each candidate plan
  * of the plain schedule (mapping x waves per group), then the fused
- * persistent launch over the whole ensemble (waves per group x groups per
- * CU), and installs the fastest as the plans (fb_set_plan).  The ensemble's
- * state is restored afterwards.  out[0..max_out) receives every candidate
+ * persistent launch over the whole ensemble (class x waves per group x groups
+ * per CU), and installs the fastest as the plans (fb_set_plan); where that is
+ * the persistent launch's body-per-lane class, FB_MAP_AUTO with the same
+ * workgroups instead, unless it takes more than 2% longer.  Body-per-lane plain
+ * launches that do not depend on the waves per group are timed once.  The
+ * ensemble's state is restored afterwards.  out[0..max_out) receives every candidate
  * timed (n = 0 for the persistent launch); *n_out their count.  Allocates a
  * temporary copy of the ensemble's device state. */
 typedef struct {

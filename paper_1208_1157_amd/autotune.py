@@ -2,8 +2,9 @@
 
 The search itself is native (fb_autotune): for every body count of a
 calibration ensemble it times each lane mapping x waves-per-group of the
-plain schedule, then the fused persistent launch's waves-per-group x
-groups-per-CU, and installs the fastest.  This module chooses the
+plain schedule, then the fused persistent launch's class x waves-per-group x
+groups-per-CU, and installs the fastest (the automatic class where an explicit
+body-per-lane one is no faster).  This module chooses the
 calibration length, stores the chosen plans keyed by (GPU architecture, body
 count) and re-applies them without re-timing.
 """

@@ -1541,10 +1541,14 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
                 continue;
             struct Cand { int map, W; };
             std::vector<Cand> cands;
+            const int bpl = bpl_mapping(B, false, false, e->num_cu);
+            if (bpl != MAP_BPL)   // one wavefront a workgroup, whatever the plan
+                cands.push_back({bpl, get_plan(B.n).waves_per_group});
             for (int W : {1, 2, 4}) {
                 if (B.n <= kMaxSplBodies)
                     cands.push_back({MAP_SPL, W});
-                cands.push_back({bpl_mapping(B, false, false, e->num_cu), W});
+                if (bpl == MAP_BPL)
+                    cands.push_back({bpl, W});
             }
             double best = 1e300;
             size_t best_i = 0;
@@ -1580,10 +1584,33 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
                 return st;
         }
         // persistent launch: waves per group x groups per CU
-        const Plan keep0 = get_plan(0);
         fb_opts po;
         fb_opts_default(&po);
         po.schedule = FB_SCHED_PERSISTENT;
+        auto time_fused = [&](int mapping, int W, int g) -> fb_status {
+            fb_status st = fb_set_plan(0, mapping, W, g);
+            if (st != FB_OK)
+                return st;
+            FB_HIP(restore());
+            FB_HIP(begin_run(e, start_steps(steps, dt)));
+            FB_HIP(hipEventRecord(ev0, e->stream));
+            st = run_persistent(e, po, steps);
+            if (st != FB_OK)
+                return st;
+            FB_HIP(hipEventRecord(ev1, e->stream));
+            FB_HIP(hipEventSynchronize(ev1));
+            float ms = 0.0f;
+            FB_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+            fb_tune_entry t;
+            std::memset(&t, 0, sizeof t);
+            t.n = 0;
+            t.mapping = mapping;
+            t.waves_per_group = W;
+            t.groups_per_cu = g;
+            t.ms = ms;
+            entries.push_back(t);
+            return FB_OK;
+        };
         double best = 1e300;
         size_t best_i = 0;
         for (int cls : {0, 1})
@@ -1597,38 +1624,30 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
             for (int g : counts) {
                 if (occ > 0 && g > occ)
                     continue;
-                const int cmap = cls ? FB_MAP_SYSTEM_PER_LANE : FB_MAP_BODY_PER_LANE;
-                fb_status st = fb_set_plan(0, cmap, W, g);
+                const fb_status st = time_fused(cls ? FB_MAP_SYSTEM_PER_LANE : FB_MAP_BODY_PER_LANE, W, g);
                 if (st != FB_OK)
                     return st;
-                FB_HIP(restore());
-                FB_HIP(begin_run(e, start_steps(steps, dt)));
-                FB_HIP(hipEventRecord(ev0, e->stream));
-                st = run_persistent(e, po, steps);
-                if (st != FB_OK)
-                    return st;
-                FB_HIP(hipEventRecord(ev1, e->stream));
-                FB_HIP(hipEventSynchronize(ev1));
-                float ms = 0.0f;
-                FB_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-                fb_tune_entry t;
-                std::memset(&t, 0, sizeof t);
-                t.n = 0;
-                t.mapping = cmap;
-                t.waves_per_group = W;
-                t.groups_per_cu = g;
-                t.ms = ms;
-                entries.push_back(t);
-                if (ms < best) {
-                    best = ms;
+                if (entries.back().ms < best) {
+                    best = entries.back().ms;
                     best_i = entries.size() - 1;
                 }
             }
         }
-        (void)keep0;
+        // The automatic class runs body-per-lane tiles too where that class is
+        // the faster, places them where they all run at once, and serves other
+        // ensembles by their own sizes: it stays unless an explicit class is
+        // faster by more than two runs of one differ.
+        if (entries[best_i].mapping == FB_MAP_BODY_PER_LANE) {
+            const fb_status st = time_fused(FB_MAP_AUTO, entries[best_i].waves_per_group,
+                                            entries[best_i].groups_per_cu);
+            if (st != FB_OK)
+                return st;
+            if (entries.back().ms <= 1.02 * best)
+                best_i = entries.size() - 1;
+        }
         entries[best_i].chosen = 1;
-        fb_status st = fb_set_plan(0, entries[best_i].mapping, entries[best_i].waves_per_group,
-                                   entries[best_i].groups_per_cu);
+        const fb_status st = fb_set_plan(0, entries[best_i].mapping, entries[best_i].waves_per_group,
+                                         entries[best_i].groups_per_cu);
         if (st != FB_OK)
             return st;
         FB_HIP(restore());
