@@ -145,9 +145,9 @@ __device__ __forceinline__ void bpl_interact(const BplLds &L, const int idx,
 // ascending order, then the star (the star lane sums planets 1..n-1), so the
 // star's contribution is added last.  Branch-free: the n-2 planet partners
 // skip this lane's own index arithmetically and the last partner is peeled.
-// ILP unrolls the partner loop fully (the full-register-file kernel class,
-// where a wave has its SIMD to itself and needs independent interactions
-// in flight); the accumulation order is the same either way.
+// ILP unrolls the partner loop fully (kernels with one or two waves a SIMD,
+// which need independent interactions in flight); the accumulation order is
+// the same either way.
 template <int N, bool TS, bool ILP = false>
 __device__ __forceinline__ void bpl_eval(BplLds &L, const int lane, const int b, const int s,
                                          const double (&xi)[3], const double (&vi)[3],
@@ -463,9 +463,9 @@ __device__ __forceinline__ void bpl_fixed_steps(BplLds &L, const int lane, const
 // Integrate one tile (floor(64/N) systems) with one body per lane for at
 // most P.quantum steps.  Every lane of the wavefront executes the same
 // control flow (the LDS exchanges need it); lanes of finished, padding or
-// absent systems compute but never commit.  REGS: the variants for a wave
-// that has its SIMD to itself; WIDE: the LDS stride of the system-per-lane
-// fused class.  Returns, on the star lane of each present system, whether that
+// absent systems compute but never commit.  REGS: partner tables
+// in registers, for kernels with one or two waves a SIMD; WIDE: the LDS
+// stride and register file of the system-per-lane fused class.  Returns, on the star lane of each present system, whether that
 // system is still active.
 template <int N, bool ADV, bool WIDE, bool REGS>
 __device__ __forceinline__ bool bpl_run(const Bucket &B, const int first, const int count, const int *list,

@@ -731,11 +731,11 @@ __device__ __forceinline__ void large_store_rows(const Bucket &B, const LargeLan
 
 inline dim3 grid_for(int n, int block) { return dim3((unsigned)((n + block - 1) / block)); }
 
-// Launch geometry of a large-n bucket with k bodies per lane: grid, lanes,
+// Launch geometry of a large-n bucket, one body per lane: grid, lanes,
 // systems per workgroup.
-inline bool large_launch(const Bucket &B, int k, dim3 &grid, int &T, int &S)
+inline bool large_launch(const Bucket &B, dim3 &grid, int &T, int &S)
 {
-    large_shape(B.n, k, T, S);
+    large_shape(B.n, T, S);
     if (S < 1)
         return false;
     grid = dim3((unsigned)((B.count + S - 1) / S));

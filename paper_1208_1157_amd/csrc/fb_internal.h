@@ -258,11 +258,11 @@ hipError_t launch_plain_mvs(const Bucket &B, int waves_per_group, const StepPara
 hipError_t launch_mvs_bpl(const BucketSet &set, const StepParams &P, hipStream_t s);
 hipError_t launch_plain_mvs_large(const Bucket &B, const StepParams &P, hipStream_t s);
 hipError_t launch_count_active(const Bucket &B, int *count, hipStream_t s);
-// Workgroup shape of the large-n kernels (n > kMaxBodies) with k bodies per
-// lane: T lanes, a multiple of 64 up to 512 / k, holding S = floor(T / H)
-// systems of H = ceil(n / k) lanes each; the T that leaves the fewest lanes
-// idle.  S = 0 if the system does not fit.
-void large_shape(int n, int k, int &T, int &S);
+// Workgroup shape of the large-n kernels with one body per lane (n >
+// kMaxBodies; the Hermite steps choose theirs in fb_large.hip): T lanes, a
+// multiple of 64 up to 512, holding S = floor(T / n) systems; the T that
+// leaves the fewest lanes idle.  S = 0 if the system does not fit.
+void large_shape(int n, int &T, int &S);
 // Hermite steps of a bucket of more than kMaxBodies bodies (fb_large.hip).
 hipError_t launch_large(const Bucket &B, const StepParams &P, int num_cu, hipStream_t s);
 // FP64 FMA issue-ceiling probe: blocks x 256 lanes, iters x kFmaChains FMAs

@@ -496,8 +496,9 @@ __device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const in
 
 // Tile dispatch.  The body-per-lane class (SPLC false) keeps the fused
 // kernel at 256 VGPRs (2 waves per SIMD) and runs every tile body-per-lane,
-// partner loops unrolled (up to 10 bodies with adaptive steps / stop rules); the system-per-lane class gives the kernel the full register file (1
-// wave per SIMD) and runs system-per-lane tiles up to n = 10 (n = 8 with
+// partner loops unrolled (up to 10 bodies with adaptive steps / stop rules);
+// the system-per-lane class gives the kernel the full register file (1 wave
+// per SIMD) and runs system-per-lane tiles up to n = 10 (n = 8 with
 // adaptive steps / stop rules), body-per-lane beyond.
 // The body-per-lane class had rolled loops for every n and 3 waves per SIMD
 // (168 VGPRs), and a thinned population moved to the other class, one wave per
@@ -509,8 +510,10 @@ __device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const in
 // and 10.6 ms; 24 requests to a server (a few hundred wavefronts) 22.4 and
 // 13.9 ms of kernels.  13..16 bodies, fixed steps, 16000 and 65536 systems of 14:
 // three waves rolled 707 and 2457 us, two rolled 811 and 2555, two unrolled (the
-// partners in three parts) 550 and 2130.  11..16 with rules stay rolled: two waves take
-// 0.94 to 0.99 of three waves' time with adaptive steps.
+// partners in three parts) 550 and 2130.  11..16 with rules stay rolled: two
+// waves take 0.94 to 0.99 of three waves' time with adaptive steps, and 1.06 to
+// 1.11 in fixed steps with stop rules, where run_persistent leaves large buckets
+// to plain launches.
 template <bool ADV, bool SPLC>
 __device__ __forceinline__ bool run_tile(const Bucket &B, const Tile &T, const int *list,
                                          const StepParams &P, int &slot)
@@ -1444,21 +1447,18 @@ __global__ void k_restore(Bucket B, const long long *__restrict__ orig_off,
     default: return hipErrorInvalidValue;                                               \
     }
 
-void large_shape(int n, int k, int &T, int &S)
+void large_shape(int n, int &T, int &S)
 {
     T = 0;
     S = 0;
-    if (k < 1)
-        return;
-    const int H = (n + k - 1) / k;   // lanes per system
     long long best_used = -1, best_T = 1;
-    for (int t = 64; t <= kLargeMaxLanes / k; t += 64) {
-        const int s = t / H;
+    for (int t = 64; t <= kLargeMaxLanes; t += 64) {
+        const int s = t / n;
         if (s < 1)
             continue;
-        // more of the lanes in use (s H / t), compared exactly; ties keep the smaller t
-        if ((long long)s * H * best_T > best_used * t) {
-            best_used = (long long)s * H;
+        // more of the lanes in use (s n / t), compared exactly; ties keep the smaller t
+        if ((long long)s * n * best_T > best_used * t) {
+            best_used = (long long)s * n;
             best_T = t;
             T = t;
             S = s;
@@ -1472,7 +1472,7 @@ hipError_t launch_prepare_large(const Bucket &B, hipStream_t s)
         return hipSuccess;
     dim3 grid;
     int T, S;
-    if (!large_launch(B, 1, grid, T, S))
+    if (!large_launch(B, grid, T, S))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_prepare_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
     return hipGetLastError();
@@ -1485,7 +1485,7 @@ hipError_t launch_begin_adaptive(const Bucket &B, const RunStart &run, hipStream
     if (B.n > kMaxBodies) {
         dim3 grid;
         int T, S;
-        if (!large_launch(B, 1, grid, T, S))
+        if (!large_launch(B, grid, T, S))
             return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_begin_run_large, grid, dim3(T), large_lds_bytes(T), s, B, S, run);
         return hipGetLastError();
@@ -1654,7 +1654,7 @@ hipError_t launch_diag(const Bucket *b, int nb, double *energy, double *angmom, 
         }
         dim3 grid;
         int T, S;
-        if (!large_launch(B, 1, grid, T, S))
+        if (!large_launch(B, grid, T, S))
             return hipErrorInvalidValue;
         if (mvs_form)
             hipLaunchKernelGGL(k_diag_large<true>, grid, dim3(T), large_lds_bytes(T), s, B, S,
@@ -1691,7 +1691,7 @@ hipError_t launch_mvs_enter_large(const Bucket &B, hipStream_t s)
         return hipSuccess;
     dim3 grid;
     int T, S;
-    if (!large_launch(B, 1, grid, T, S))
+    if (!large_launch(B, grid, T, S))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_mvs_enter_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
     return hipGetLastError();
@@ -1704,7 +1704,7 @@ hipError_t launch_mvs_leave(const Bucket &B, hipStream_t s)
     if (B.n > kMaxMvsBodies) {
         dim3 grid;
         int T, S;
-        if (!large_launch(B, 1, grid, T, S))
+        if (!large_launch(B, grid, T, S))
             return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_mvs_leave_large, grid, dim3(T), large_lds_bytes(T), s, B, S);
         return hipGetLastError();
@@ -1721,7 +1721,7 @@ hipError_t launch_unpack_mvs_large(const Bucket &B, const StateOut &out, hipStre
         return hipSuccess;
     dim3 grid;
     int T, S;
-    if (!large_launch(B, 1, grid, T, S))
+    if (!large_launch(B, grid, T, S))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_unpack_mvs_large, grid, dim3(T), large_lds_bytes(T), s, B, S, out);
     return hipGetLastError();
@@ -1743,7 +1743,7 @@ hipError_t launch_log(const Bucket &B, const long long *orig_off, int kind, cons
     if (B.n > kMaxBodies) {
         dim3 grid;
         int T, S;
-        if (!large_launch(B, 1, grid, T, S))
+        if (!large_launch(B, grid, T, S))
             return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_log_large, grid, dim3(T), large_lds_bytes(T), s, B, S, orig_off,
                            kind, los[0], los[1], los[2], k, max_records, out);

@@ -403,7 +403,7 @@ __device__ __forceinline__ void mvs_bpl_momentum(BplLds &L, const int lane, cons
 }
 
 // Integrate one tile (floor(64/N) systems), one body per lane, for at most
-// P.quantum steps: the arithmetic of mvs_step in the same order.  Each
+// P.quantum steps: the arithmetic of mvs_spl_run in the same order.  Each
 // planet's lane drifts its own orbit, so the Kepler solver's latency is paid
 // once a step; positions (with masses) and velocities are exchanged through
 // the wavefront's LDS slice, one exchange for the accelerations and one for
@@ -624,7 +624,7 @@ __device__ __forceinline__ void large_mvs_momentum(const LargeView &V, const int
 }
 
 // Fixed-step MVS integration, one body per lane, for at most P.quantum steps
-// (the clock of the Hermite kernels; the steps of mvs_step, with the
+// (the clock of the Hermite kernels; the steps of mvs_spl_run, with the
 // outcomes of a system predicating its updates).  A step has five barriers:
 // one each for the momentum, whether any orbit is unbound and whether any
 // Kepler solution failed (the systems concerned are found only then), and
@@ -750,7 +750,7 @@ hipError_t launch_plain_mvs_large(const Bucket &B, const StepParams &P, hipStrea
         return hipSuccess;
     dim3 grid;
     int T, S;
-    if (!large_launch(B, 1, grid, T, S))
+    if (!large_launch(B, grid, T, S))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_plain_mvs_large, grid, dim3(T), large_lds_bytes(T), s, B, P, S);
     return hipGetLastError();

@@ -6,8 +6,9 @@ namespace {
 
 // The embedded pair of Cash & Karp (ACM TOMS 16, 1990) on y = (x, v),
 // y' = (v, a(x)): six stages, each one acceleration evaluation (Eq. 1,
-// planets in ascending order, the star last).  The step advances with the fifth-order weights; the error estimate is the
-// difference from the fourth-order weights.  Adaptive control: with X and V
+// planets in ascending order, the star last).  The step advances with the
+// fifth-order weights; the error estimate is the difference from the
+// fourth-order weights.  Adaptive control: with X and V
 // the largest |x_i| and |v_i| of the system at the step's start,
 // E = max_i max(|dx_i| / (eps X), |dv_i| / (eps V)); E <= 1 accepts and
 // proposes h min(5, max(0.2, 0.9 E^(-1/5))) (a step shortened onto t_end
@@ -499,7 +500,7 @@ void k_rkck_bpl(BucketSet set, StepParams P, double eps)
 // Runge-Kutta Cash-Karp for large systems (n > 16): one body per lane across
 // a workgroup
 // ---------------------------------------------------------------------------
-// The stages, weights and error control of k_plain_rkck in the large-n
+// The stages, weights and error control of k_rkck_bpl in the large-n
 // layout.  Each stage's positions go to one of two LDS copies in turn, so a
 // stage costs one workgroup barrier; a body's own term is an exact zero
 // through the r^2 floor, so every lane runs the same partner loop (planets in
@@ -684,7 +685,7 @@ hipError_t launch_rkck_large(const Bucket &B, const StepParams &P, double eps, h
         return hipSuccess;
     dim3 grid;
     int T, S;
-    if (!large_launch(B, 1, grid, T, S))
+    if (!large_launch(B, grid, T, S))
         return hipErrorInvalidValue;
     if (P.adaptive)
         hipLaunchKernelGGL(k_plain_rkck_large<true>, grid, dim3(T), large_lds_bytes(T), s, B, P, eps, S);

@@ -1,14 +1,16 @@
 // fb_solo.cpp -- stateless fixed-step Hermite integration of one homogeneous
 // batch of systems held in the caller's device arrays.
 //
-// The batch (n_sys systems of n bodies, body-major rows as everywhere in the
-// ABI) is packed into one structure-of-arrays bucket, given its set-up
-// evaluation (Algorithm 1's "prepare"), advanced by a plain launch of the
-// same kernels an ensemble uses (Eq. 3 predictor, Eq. 4 corrector twice per
-// step as in Algorithm 2), and unpacked back in place.  Nothing is read back
-// to the host and nothing outlives the call, so the call is pure stream
-// work.  The bucket lives either in a caller workspace or, for callers that
-// cannot allocate device memory, in a fixed per-device array of this file.
+// A small batch (n_sys systems of n bodies, body-major rows as everywhere in
+// the ABI) is one launch: its kernel loads the caller's rows, evaluates
+// (Algorithm 1's "prepare"), takes the steps (Eq. 3 predictor, Eq. 4 corrector
+// twice per step as in Algorithm 2) and stores the rows back.  A larger one is
+// laid out as one structure-of-arrays bucket with its set-up evaluation,
+// advanced by a plain launch of the same kernels an ensemble uses, and
+// unpacked back in place.  Nothing is read back to the host and nothing
+// outlives the call, so the call is pure stream work.  The bucket lives either
+// in a caller workspace or, for callers that cannot allocate device memory, in
+// a fixed per-device array of this file.
 #include "fewbody.h"
 #include "fb_internal.h"
 #include "fb_runtime_internal.h"
@@ -24,8 +26,8 @@ using namespace fb::rt;
 
 namespace {
 
-// Largest batch the allocation-free entry point takes: bucket, tables and
-// flag of, e.g., 131072 three-body or 38000 sixteen-body systems.
+// Largest batch the allocation-free entry point takes: the bucket of, e.g.,
+// 170000 three-body or 38000 sixteen-body systems.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
 constexpr int kMaxDevices = 64;
 
@@ -40,11 +42,11 @@ char *g_scratch_ptr[kMaxDevices];
 // Batches above this many systems are rejected before any size arithmetic.
 constexpr int32_t kMaxSoloSystems = 1 << 26;
 
-// Byte offsets of the batch's bucket, its body-offset table and its input
-// flag inside a workspace; plain arithmetic (no heap).
+// Byte offsets of the batch's bucket inside a workspace; plain arithmetic (no
+// heap).
 struct SoloLayout {
     BucketLayout b;
-    size_t orig_off, ints, total;
+    size_t total;
 };
 
 bool solo_layout(int32_t n_sys, int32_t n, SoloLayout &L)
@@ -73,8 +75,6 @@ bool solo_layout(int32_t n_sys, int32_t n, SoloLayout &L)
     bl.steps = take(8 * P);
     bl.status = take(4 * P);
     bl.orig = take(4 * P);
-    L.orig_off = take(8 * (P + 1));
-    L.ints = take(256);
     L.total = off;
     return true;
 }

@@ -17,8 +17,8 @@
 //   2               1.06 1.05  1.69 1.45  2.50 2.26  3.30 2.91  4.91 4.20
 //   4                                     4.46 4.15  5.90 5.42  8.75 7.72
 //   8                                                           15.8 14.6
-// 13..16 bodies, where two wavefronts on a SIMD hold a part of the partners at a
-// time: 60 steps of 16 bodies, 8192 systems (2 wavefronts a SIMD) 540 and 350
+// 13..16 bodies, of which (from 14 on) two wavefronts on a SIMD hold a third of
+// the partners at a time: 60 steps of 16 bodies, 8192 systems (2 wavefronts a SIMD) 540 and 350
 // us, 16000 730 and 645, 32000 1402 and 1240, 131072 4977 and 4574;
 // and with adaptive steps and the stop rules, 1 and 4 waves per SIMD: n = 8
 // 1.68x and 1.17x, n = 12 1.63x and 0.93x (its registers leave one wave per
