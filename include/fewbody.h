@@ -25,6 +25,13 @@
  * MVS and Runge-Kutta run them too; the autotuner leaves their launch shape
  * alone (it tunes the other buckets and the persistent launch around them);
  * the server rejects them with FB_E_INVAL.
+ * Results and launch shapes: a Hermite result of a system of up to
+ * FB_MAX_SMALL_BODIES bodies is the same to the bit whatever else the ensemble
+ * holds, and under every schedule, quantum and plan.  The large-n Hermite kernel shares
+ * a body's partners among lanes, in a layout chosen by how many systems of
+ * that n the ensemble holds, the device, and whether steps are adaptive or stop
+ * rules are set; the order of its sums, so the rounding, goes with the layout.
+ * The same ensemble on the same device with the same options repeats bitwise.
  * Flat body arrays are body-major: body b of system s is row off[s] + b with
  * off the exclusive prefix sum of n_body; pos/vel/acc/jerk rows hold x,y,z.
  * All floating point is IEEE binary64.
@@ -93,7 +100,10 @@ enum {
 enum {
     FB_SCHED_PLAIN = 0,       /* one launch per homogeneous body-count bucket  */
     FB_SCHED_PERSISTENT = 1   /* one fused persistent launch over all buckets,
-                                 tiles pulled longest-first from a queue        */
+                                 tiles pulled longest-first from a queue (large
+                                 n, and with stop rules in fixed steps large
+                                 buckets of 10..16 bodies, by launches of their
+                                 own beside it)                                 */
 };
 
 /* Integration options; NULL means all defaults.  Defaults: fixed step, no
@@ -118,9 +128,11 @@ typedef struct {
     int32_t steps_per_quantum;  /* persistent schedule: steps per launch
                                    (<=0: whole run in one launch); with
                                    compact and the automatic fused class,
-                                   once every surviving tile has a
-                                   wavefront of its own, the rest of the run
-                                   goes in one launch                           */
+                                   once every surviving tile has a SIMD of
+                                   its own, quanta are 16 times as long, and
+                                   once the slowest tiles have all the lanes
+                                   a body that they can get, the rest of the
+                                   run goes in one launch                       */
     int32_t compact;            /* persistent schedule: rebuild tiles from the
                                    still-active systems after every quantum     */
 } fb_opts;
@@ -170,7 +182,10 @@ fb_status fb_ensemble_create_device(int32_t n_sys, const int32_t *n_body,
  * FB_SYS_MAXSTEPS; NULL: FB_SYS_DONE) and steps since creation [n_sys]
  * (>= 0; NULL: 0).  With the values fb_get_state and fb_get_hermite_state
  * returned, later integration continues bitwise as the checkpointed
- * ensemble would have.  Validation and ownership as fb_ensemble_create;
+ * ensemble would have; for systems of more than FB_MAX_SMALL_BODIES bodies
+ * only if the ensemble holds as many systems of each such n as the
+ * checkpointed one did, on the same kind of device (otherwise to rounding:
+ * see above).  Validation and ownership as fb_ensemble_create;
  * FB_E_INVAL names the first bad value. */
 fb_status fb_ensemble_restore(int32_t n_sys, const int32_t *n_body,
                               const double *mass, const double *pos,
@@ -191,14 +206,17 @@ fb_status fb_integrate_steps(fb_ensemble *e, int64_t n_steps, double dt,
 
 /* Mixed-variable symplectic integration (Section 2.2.3) of every active
  * system by exactly n_steps fixed steps of dt (body 0 the central star;
- * one system per lane up to 8 bodies, one body per lane across a workgroup
- * for 9..FB_MAX_BODIES).  Each step is the paper's sequence of
+ * up to 8 bodies one system per lane where that fills the device; otherwise
+ * one body per lane of a wavefront up to FB_MAX_SMALL_BODIES bodies and one
+ * body per lane of a workgroup above).  Each step is the paper's sequence of
  * sub-steps: Cartesian drift dt/2, kick dt/2, Keplerian drift dt, kick dt/2,
  * Cartesian drift dt/2, in the democratic heliocentric splitting (Duncan,
  * Levison & Lee 1998): planets follow Kepler orbits about the star (mu =
  * m0) in heliocentric positions and barycentric velocities, kicks apply the
  * planet-planet forces, and the drift is the star's reflex motion.  Kepler's
- * equation is solved by Newton iteration per planet and step.  While the
+ * equation is solved per planet and step in universal form, by a series in
+ * the change of the eccentric anomaly or, beyond a radian, by Halley's
+ * iteration.  While the
  * ensemble holds MVS state its rows keep the MVS variables (and the last
  * kick's accelerations), so quanta and calls chain without conversion;
  * fb_get_state and fb_diagnostics convert on the way out,
@@ -375,7 +393,8 @@ fb_status fb_hermite_steps_device_noalloc(int32_t n_sys, int32_t n, const double
  * allows; FB_MAP_BODY_PER_LANE: 256 VGPRs, body-per-lane tiles only;
  * FB_MAP_AUTO: the former when every bucket allows it and its tiles give
  * every SIMD a wavefront), plus waves per workgroup and workgroups per CU
- * (1..32, 0 = default).  In the system-per-lane class a body count whose own
+ * (1..32, 0 = default; with FB_MAP_AUTO a launch whose tiles all run at once
+ * has as many wavefronts a CU, in workgroups of one).  In the system-per-lane class a body count whose own
  * plan is FB_MAP_BODY_PER_LANE runs body-per-lane tiles.  Plans are
  * process-wide; the autotuner sets them. */
 fb_status fb_set_plan(int32_t n, int32_t mapping, int32_t waves_per_group,

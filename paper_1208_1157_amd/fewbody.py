@@ -31,12 +31,12 @@ _lib = ctypes.CDLL(LIB_PATH)
 
 OK, E_INVAL, E_NOMEM, E_DEVICE, E_BUDGET, E_STATE, E_NOTFOUND = 0, -1, -2, -3, -4, -5, -6
 ACTIVE, DONE, ENCOUNTER, EJECTED, NONFINITE, STALLED_DT, MAXSTEPS, UNBOUND = range(8)
-MAX_MVS_BODIES = 8
+MAX_MVS_BODIES = 8       # MVS: most bodies of a system per lane
 STOP_ENCOUNTER, STOP_EJECT = 1, 2
 MAP_AUTO, MAP_SPL, MAP_BPL = 0, 1, 2
 SCHED_PLAIN, SCHED_PERSISTENT = 0, 1
 MAX_BODIES = 512         # bodies per system
-MAX_SMALL_BODIES = 16    # ... for every integrator and schedule (larger: fixed Hermite steps, plain schedule)
+MAX_SMALL_BODIES = 16    # ... for every integrator and schedule (larger: the large-n kernels, all but the server)
 
 
 class FbOpts(ctypes.Structure):
@@ -427,7 +427,7 @@ class Ensemble:
 
     def integrate_mvs(self, n_steps, dt, opts: Opts | None = None):
         """n_steps fixed steps of the mixed-variable symplectic integrator
-        (fb_integrate_mvs; systems of at most MAX_MVS_BODIES bodies)."""
+        (fb_integrate_mvs)."""
         o = (opts or Opts()).c()
         _check(_lib.fb_integrate_mvs(self._handle, int(n_steps), float(dt), ctypes.byref(o)))
 
