@@ -44,17 +44,12 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 METRIC = "FP64 Hermite system-steps/s at 131072×3-body; p50/p99 solve latency"
+# The headline kernel's source; its profile's key covers the headers it includes.
 KERNEL_SRC = os.path.join(ROOT, "paper_1208_1157_amd", "csrc", "fb_kernels.hip")
 # HBM bytes per launch of the integration kernel on this workload, from the
 # FETCH_SIZE / WRITE_SIZE counter passes (scaled by a 256 MiB copy kernel's
 # reading) recorded in profiles/, keyed by the kernel source they measured.
-MEASURED_TRAFFIC = {"f56593fdeadf867b": 92376093.0, "a3428dc18039eedc": 92445596.1,
-                    "1c9dff3d544099cf": 92417308.4, "234f298587126ea3": 92405022.4,
-                    "b0cf1370d8600140": 92417213.2, "d75718a170f1a208": 92400808.0,
-                    "2e972ba6903455f7": 92417165.5, "b18c3be0358ab8a1": 92417237.0,
-                    "1ed17940f99ee27b": 92404903.3, "0e3df7279f4c8f5d": 92412928.0,
-                    "51a920369b9cae68": 92407561.1, "ad207609a06017a7": 92422664.6,
-                    "426bec0504130fdf": 92406617.6}
+MEASURED_TRAFFIC = {"34a451ad46d0383b": 92410808.3}
 # Hardware counters of the same kernel on this workload from rocprofv3 runs
 # (profiles/), keyed the same way: FP64 flop per system-step from
 # SQ_INSTS_VALU_FLOPS_FP64 x 64 lanes; the fraction of SIMD cycles issuing
@@ -62,28 +57,8 @@ MEASURED_TRAFFIC = {"f56593fdeadf867b": 92376093.0, "a3428dc18039eedc": 92445596
 # shader clock those cycles implied on the profiled box.  They are records of
 # those runs, reported as such, not measurements of this run.
 PROFILED_COUNTERS = {
-    "1c9dff3d544099cf": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9671,
-                         "shader_clock_ghz": 2.018, "valu_insts_per_system_step": 388.01},
-    "234f298587126ea3": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9753,
-                         "shader_clock_ghz": 1.996, "valu_insts_per_system_step": 388.01},
-    "b0cf1370d8600140": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9729,
-                         "shader_clock_ghz": 1.977, "valu_insts_per_system_step": 388.01},
-    "d75718a170f1a208": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9685,
-                         "shader_clock_ghz": 1.999, "valu_insts_per_system_step": 388.01},
-    "2e972ba6903455f7": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9725,
-                         "shader_clock_ghz": 1.94, "valu_insts_per_system_step": 388.01},
-    "b18c3be0358ab8a1": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9708,
-                         "shader_clock_ghz": 2.025, "valu_insts_per_system_step": 388.01},
-    "1ed17940f99ee27b": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9677,
-                         "shader_clock_ghz": 1.939, "valu_insts_per_system_step": 388.01},
-    "0e3df7279f4c8f5d": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9626,
-                         "shader_clock_ghz": 2.114, "valu_insts_per_system_step": 388.0},
-    "51a920369b9cae68": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9692,
-                         "shader_clock_ghz": 2.066, "valu_insts_per_system_step": 388.0},
-    "ad207609a06017a7": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9556,
-                         "shader_clock_ghz": 2.057, "valu_insts_per_system_step": 388.0},
-    "426bec0504130fdf": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9680,
-                         "shader_clock_ghz": 2.092, "valu_insts_per_system_step": 388.0},
+    "34a451ad46d0383b": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9671,
+                         "shader_clock_ghz": 2.131, "valu_insts_per_system_step": 388.0},
 }
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X: 256 CUs x 2.4 GHz x 128 FP64 flop/clk/CU
 HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
@@ -104,9 +79,20 @@ PAPER_TABLE3_SECONDS = {
 
 
 def kernel_source_hash() -> str:
+    """Hash of the headline kernel's source file and of every header of its
+    folder that it includes, directly or through another."""
     import hashlib
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    import re
+    files, h = [KERNEL_SRC], hashlib.sha256()
+    for path in files:                       # grows as includes are found
+        with open(path, "rb") as f:
+            text = f.read()
+        h.update(text)
+        for name in re.findall(rb'^#include "([^"]+)"', text, re.M):
+            p = os.path.join(os.path.dirname(KERNEL_SRC), name.decode())
+            if os.path.exists(p) and p not in files:
+                files.append(p)
+    return h.hexdigest()[:16]
 
 
 def flops_per_system_step(n: int) -> float:
@@ -243,11 +229,12 @@ def lifetimes_extras(fb, gen, torch, log, orbits=100.0, quantum=2000):
     """Uneven lifetimes 65536 x (4..8): adaptive steps (eta 0.01) with the
     close-encounter and ejection rules, on a horizon of `orbits` inner orbits
     (100 by default, a bounded sample of the workload's 1e4, which takes about
-    23 s persistent and 83 s plain).  Plain: one launch per bucket, retired
+    15 s persistent and 50 s plain).  Plain: one launch per bucket, retired
     lanes idle until their wave's last system ends; persistent: quanta with
     in-kernel compaction of retired systems, the fused-kernel class chosen
-    automatically (body-per-lane; the tiles run to their ends once each has a
-    SIMD of its own); and, for comparison, the body-per-lane
+    automatically (body-per-lane; quanta 16 times as long once every tile has a
+    SIMD of its own, and the rest in one launch once the slowest tiles have all
+    the lanes a body that they can get); and, for comparison, the body-per-lane
     class throughout."""
     import numpy as np
     ens, p = gen.workload("lifetimes_65536x4-8")
