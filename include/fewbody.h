@@ -102,8 +102,8 @@ enum {
     FB_SCHED_PERSISTENT = 1   /* one fused persistent launch over all buckets,
                                  tiles pulled longest-first from a queue (large
                                  n, and with stop rules in fixed steps large
-                                 buckets of 10..16 bodies, by launches of their
-                                 own beside it)                                 */
+                                 buckets of 10..16 bodies beside smaller ones,
+                                 by launches of their own)                      */
 };
 
 /* Integration options; NULL means all defaults.  Defaults: fixed step, no
@@ -390,7 +390,8 @@ fb_status fb_hermite_steps_device_noalloc(int32_t n_sys, int32_t n, const double
  * the device a wavefront, and body-per-lane otherwise.  Entry n = 0 is the
  * fused persistent launch: its mapping selects the kernel class
  * (FB_MAP_SYSTEM_PER_LANE: full register file, system-per-lane tiles where n
- * allows; FB_MAP_BODY_PER_LANE: 256 VGPRs, body-per-lane tiles only;
+ * allows; FB_MAP_BODY_PER_LANE: body-per-lane tiles only, 256 VGPRs, or 168
+ * for fixed steps with stop rules of many systems of 9..16 bodies;
  * FB_MAP_AUTO: the former when every bucket allows it and its tiles give
  * every SIMD a wavefront), plus waves per workgroup and workgroups per CU
  * (1..32, 0 = default; with FB_MAP_AUTO a launch whose tiles all run at once

@@ -31,6 +31,7 @@ constexpr int kMaxSplPersistent = 0;   // the body-per-lane fused class runs no 
 constexpr int kMaxUnrolledAdv = 10;    // body per lane: 4 and more bodies always run unrolled, with
                                        // adaptive steps / stop rules 4..10
 constexpr int kMaxUnrolledStops = 8;   // ... with stop rules in fixed steps 4..8
+constexpr int kMinRolled = 9;          // fused class 2 (fixed steps with stop rules) runs 9..16 bodies
 constexpr int kMaxRkckSpl = 6;         // fixed Cash-Karp steps system per lane exist for n <= 6
 constexpr int kMaxMvsBodies = 8;       // MVS kernels (system per lane) exist for n <= 8
 
@@ -217,13 +218,14 @@ hipError_t launch_solo_quads(const SoloIO &io, int n, const StepParams &P, hipSt
 // Steps with G (2 or 4) lanes a body, kMinSplit bodies and more
 // (launch_plain with MAP_SPLIT2 and MAP_SPLIT4 comes here).
 hipError_t launch_split(const Bucket &B, int G, const StepParams &P, hipStream_t s);
-// spl_class: 0 = body-per-lane class fused kernel (256 VGPRs; system-per-
-// lane tiles for n <= kMaxSplPersistent), 1 = system-per-lane class (full
-// register file; system-per-lane tiles for n <= kMaxSplBodies, or
-// kMaxSplAdv with adaptive steps / stop rules).
+// cls: 0 = body-per-lane class fused kernel (256 VGPRs; system-per-lane tiles
+// for n <= kMaxSplPersistent), 1 = system-per-lane class (full register file;
+// system-per-lane tiles for n <= kMaxSplBodies, or kMaxSplAdv with adaptive
+// steps / stop rules), 2 = rolled body-per-lane tiles of kMinRolled bodies and
+// more with rules (168 VGPRs).
 hipError_t launch_persistent(const Bucket *d_buckets, const Tile *d_tiles,
                              const int *d_ntiles, int *d_head, const int *d_lists,
-                             const StepParams &P, int adv, int spl_class, int grid,
+                             const StepParams &P, int adv, int cls, int grid,
                              int waves_per_group, ActiveLists *compact,
                              hipStream_t s);
 hipError_t launch_build_tiles(const Bucket *d_buckets, int n_buckets,
@@ -275,12 +277,12 @@ hipError_t launch_rsqrt(const double *in, double *out, long long n, hipStream_t 
 hipError_t launch_restore(const Bucket &B, const long long *orig_off, const double *acc,
                           const double *jerk, const double *dtn, const long long *steps,
                           const int *status, hipStream_t s);
-size_t persistent_lds_bytes(int spl_class, int waves_per_group);
-int persistent_max_groups_per_cu(int adv, int spl_class, int waves_per_group);
+size_t persistent_lds_bytes(int cls, int waves_per_group);
+int persistent_max_groups_per_cu(int adv, int cls, int waves_per_group);
 // Largest n a persistent tile runs system-per-lane for, by kernel class.
-inline int persistent_spl_limit(int spl_class, int adv)
+inline int persistent_spl_limit(int cls, int adv)
 {
-    return spl_class ? (adv ? kMaxSplAdv : kMaxSplBodies) : kMaxSplPersistent;
+    return cls == 1 ? (adv ? kMaxSplAdv : kMaxSplBodies) : kMaxSplPersistent;
 }
 
 }  // namespace fb

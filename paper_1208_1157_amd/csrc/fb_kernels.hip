@@ -512,8 +512,8 @@ __device__ __noinline__ bool split_tile(const Bucket &B, const Tile &T, const in
 // three waves rolled 707 and 2457 us, two rolled 811 and 2555, two unrolled (the
 // partners in three parts) 550 and 2130.  11..16 with rules stay rolled: two
 // waves take 0.94 to 0.99 of three waves' time with adaptive steps, and 1.06 to
-// 1.11 in fixed steps with stop rules, where run_persistent leaves large buckets
-// to plain launches.
+// 1.11 in fixed steps with stop rules, which have a class of their own
+// (k_persistent_rolled).
 template <bool ADV, bool SPLC>
 __device__ __forceinline__ bool run_tile(const Bucket &B, const Tile &T, const int *list,
                                          const StepParams &P, int &slot)
@@ -578,7 +578,33 @@ __device__ __forceinline__ int place_tile(const int i, const int ntiles, const i
     return i < shared ? simds - shared + i : i < simds ? i - shared : ntiles - 1 - (i - simds);
 }
 
-template <bool ADV, bool COMPACT, bool SPLC>
+// Rolled tile of k_persistent_rolled.
+template <int N>
+__device__ __noinline__ bool rolled_tile(const Bucket &B, const Tile &T, const int *list,
+                                         const StepParams &P, int &slot)
+{
+    const StepParams Pr = uniform_params(P);
+    return bpl_run<N, true, false, false>(B, T.first, T.count, list, Pr, slot);
+}
+
+__device__ __forceinline__ bool run_rolled_tile(const Bucket &B, const Tile &T, const int *list,
+                                                const StepParams &P, int &slot)
+{
+    static_assert(kMinRolled == 9 && kMaxBodies == 16, "the body counts below");
+    switch (T.kind & 31) {
+    case 9: return rolled_tile<9>(B, T, list, P, slot);
+    case 10: return rolled_tile<10>(B, T, list, P, slot);
+    case 11: return rolled_tile<11>(B, T, list, P, slot);
+    case 12: return rolled_tile<12>(B, T, list, P, slot);
+    case 13: return rolled_tile<13>(B, T, list, P, slot);
+    case 14: return rolled_tile<14>(B, T, list, P, slot);
+    case 15: return rolled_tile<15>(B, T, list, P, slot);
+    case 16: return rolled_tile<16>(B, T, list, P, slot);
+    default: return false;
+    }
+}
+
+template <bool ADV, bool COMPACT, int CLS>
 __device__ __forceinline__ void persistent_body(const Bucket *__restrict__ buckets,
                                                 const Tile *__restrict__ tiles,
                                                 const int *__restrict__ ntiles_p,
@@ -612,7 +638,11 @@ __device__ __forceinline__ void persistent_body(const Bucket *__restrict__ bucke
         const Tile T = tiles[t];
         const Bucket B = buckets[T.bucket];
         int slot = 0;
-        const bool keep = run_tile<ADV, SPLC>(B, T, lists, P, slot);
+        bool keep;
+        if constexpr (CLS == 2)
+            keep = run_rolled_tile(B, T, lists, P, slot);
+        else
+            keep = run_tile<ADV, CLS == 1>(B, T, lists, P, slot);
         if (COMPACT)
             append_survivors(AL, T.bucket, keep, slot);
     }
@@ -624,7 +654,7 @@ void k_persistent(const Bucket *__restrict__ buckets, const Tile *__restrict__ t
                   const int *__restrict__ ntiles_p, int *__restrict__ head, const int *lists,
                   StepParams P, ActiveLists AL)
 {
-    persistent_body<ADV, COMPACT, false>(buckets, tiles, ntiles_p, head, lists, P, AL);
+    persistent_body<ADV, COMPACT, 0>(buckets, tiles, ntiles_p, head, lists, P, AL);
 }
 
 template <bool ADV, bool COMPACT>
@@ -635,7 +665,23 @@ __global__ __launch_bounds__(256) void k_persistent_spl(const Bucket *__restrict
                                                         const int *lists, StepParams P,
                                                         ActiveLists AL)
 {
-    persistent_body<ADV, COMPACT, true>(buckets, tiles, ntiles_p, head, lists, P, AL);
+    persistent_body<ADV, COMPACT, 1>(buckets, tiles, ntiles_p, head, lists, P, AL);
+}
+
+// Fixed steps with stop rules of kMinRolled bodies and more, where the tiles give
+// a SIMD more than two wavefronts: three, rolled (persistent_class), since two have
+// no room for the partners' state of 11 bodies and more beside that of the rules
+// and run rolled too.  60 steps, this class and the other, 40000 systems of 10..16 bodies 1742 and
+// 1945 us, compacted every 10 steps 1969 and 2282; 32000 of 10 846 and 1020; 16000 of
+// 16 1012 and 1157.  9 bodies alone stay with the other (16000 systems 460 and 381,
+// 70000 1445 and 1288), but not beside larger ones: 40000 of 9..16 1728 and 1841.
+template <bool COMPACT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_persistent_rolled(const Bucket *__restrict__ buckets, const Tile *__restrict__ tiles,
+                         const int *__restrict__ ntiles_p, int *__restrict__ head, const int *lists,
+                         StepParams P, ActiveLists AL)
+{
+    persistent_body<true, COMPACT, 2>(buckets, tiles, ntiles_p, head, lists, P, AL);
 }
 
 // Tiles for the next quantum from the survivor counts (one workgroup):
@@ -1566,19 +1612,21 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
     return hipGetLastError();
 }
 
-size_t persistent_lds_bytes(int spl_class, int waves_per_group)
+size_t persistent_lds_bytes(int cls, int waves_per_group)
 {
-    const size_t per_wave = spl_class ? kWideLdsStride : sizeof(BplLds);
+    const size_t per_wave = cls == 1 ? kWideLdsStride : sizeof(BplLds);
     return per_wave * waves_per_group;
 }
 
-int persistent_max_groups_per_cu(int adv, int spl_class, int waves_per_group)
+int persistent_max_groups_per_cu(int adv, int cls, int waves_per_group)
 {
     int blocks = 0;
     const int threads = 64 * waves_per_group;
-    const size_t lds = persistent_lds_bytes(spl_class, waves_per_group);
+    const size_t lds = persistent_lds_bytes(cls, waves_per_group);
     hipError_t e;
-    if (spl_class)
+    if (cls == 2)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_persistent_rolled<true>, threads, lds);
+    else if (cls == 1)
         e = adv ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_persistent_spl<true, true>,
                                                                threads, lds)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_persistent_spl<false, false>,
@@ -1593,17 +1641,21 @@ int persistent_max_groups_per_cu(int adv, int spl_class, int waves_per_group)
 
 hipError_t launch_persistent(const Bucket *d_buckets, const Tile *d_tiles, const int *d_ntiles,
                              int *d_head, const int *d_lists, const StepParams &P, int adv,
-                             int spl_class, int grid, int waves_per_group, ActiveLists *compact,
+                             int cls, int grid, int waves_per_group, ActiveLists *compact,
                              hipStream_t s)
 {
     const int W = waves_per_group < 1 ? 1 : (waves_per_group > 4 ? 4 : waves_per_group);
-    const size_t lds = persistent_lds_bytes(spl_class, W);
+    const size_t lds = persistent_lds_bytes(cls, W);
     ActiveLists AL = compact ? *compact : ActiveLists{nullptr, nullptr, nullptr, nullptr, nullptr};
     const dim3 g(grid), b(64 * W);
-#define FB_P(KERNEL, A, C)                                                               \
-    hipLaunchKernelGGL((KERNEL<A, C>), g, b, lds, s, d_buckets, d_tiles, d_ntiles, d_head, \
+#define FB_P(KERNEL, ...)                                                                \
+    hipLaunchKernelGGL((KERNEL<__VA_ARGS__>), g, b, lds, s, d_buckets, d_tiles, d_ntiles, d_head, \
                        d_lists, P, AL)
-    if (spl_class) {
+    if (cls == 2) {
+        if (!adv)
+            return hipErrorInvalidValue;
+        if (compact) FB_P(k_persistent_rolled, true); else FB_P(k_persistent_rolled, false);
+    } else if (cls == 1) {
         if (adv) {
             if (compact) FB_P(k_persistent_spl, true, true); else FB_P(k_persistent_spl, true, false);
         } else {

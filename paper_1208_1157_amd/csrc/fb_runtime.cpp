@@ -475,24 +475,26 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
     // Buckets are laid out in descending n: the large-n ones (n > kMaxBodies)
     // come first and run their own plain launches inside every quantum; the
     // fused launch's tile queue covers the others.  Fixed steps with stop rules
-    // of 10 and more bodies, uncompacted, join them where a bucket gives every
-    // SIMD two wavefronts: the plain launch runs three there, the fused one two
-    // (60 steps of 16000 systems of 10 bodies 519 and 593 us, of 16 1082 and
-    // 1190; of 65536 of 16 3651 and 3936).
-    auto own_launch = [&](const Bucket &B) {
-        return B.n > kMaxBodies || (o.stop_rules && !o.adaptive && !o.compact && p0.mapping != MAP_SPL &&
-                                    B.n >= 10 && B.count / (64 / B.n) >= 8 * e->num_cu);
-    };
+    // of 10 and more bodies, uncompacted and beside smaller ones, join them where
+    // a bucket gives every SIMD two wavefronts: the plain launch runs three there,
+    // the fused one two (60 steps of 16000 systems of 10 bodies 519 and 593 us, of
+    // 16 1082 and 1190; of 65536 of 16 3651 and 3936).
     int n_large = 0;
-    while (n_large < nbk && own_launch(e->buckets[n_large]))
+    while (n_large < nbk && e->buckets[n_large].n > kMaxBodies)
         ++n_large;
+    auto from = [&](int b) { return std::vector<Bucket>(e->buckets.begin() + b, e->buckets.end()); };
+    if (o.stop_rules && !o.adaptive && !o.compact &&
+        persistent_class(p0, from(n_large), false, true, e->num_cu) == 0)
+        while (n_large < nbk && e->buckets[n_large].n > kMinRolled &&
+               e->buckets[n_large].count / (64 / e->buckets[n_large].n) >= 8 * e->num_cu)
+            ++n_large;
     const int nb_small = nbk - n_large;
-    const std::vector<Bucket> small(e->buckets.begin() + n_large, e->buckets.end());
+    const std::vector<Bucket> small = from(n_large);
     const bool adv = o.adaptive || o.stop_rules;
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
     StepParams P = make_params(o, quantum);
     const bool compact = o.compact != 0;
-    int cls = persistent_class(p0, small, adv, e->num_cu);
+    int cls = persistent_class(p0, small, o.adaptive != 0, o.stop_rules != 0, e->num_cu);
     // Tiles that all run at once are placed one by one (place_tile), unless a
     // plan asks for a class and with it for its workgroups.
     long long tiles0 = 0;
@@ -707,7 +709,7 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
         // tiles run on to their ends in one launch.  65536 systems of 4..8
         // bodies, 10 orbits: 62.7 ms, running on at once 65.7; 16384, 3 orbits,
         // the same (with quanta as before until then 4% longer).
-        if (compact && cls == 0 && p0.mapping == 0 && !to_ends && bpl_waves <= 4LL * e->num_cu) {
+        if (compact && cls != 1 && p0.mapping == 0 && !to_ends && bpl_waves <= 4LL * e->num_cu) {
             hipError_t err = set_class(0);
             if (err != hipSuccess) {
                 result = hip_fail(err, "mapping switch");

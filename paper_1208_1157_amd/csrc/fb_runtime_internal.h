@@ -155,13 +155,26 @@ inline int plain_mapping(const Plan &p, const Bucket &B, bool adaptive, bool sto
 // adaptive steps or stop rules (auto) always the body-per-lane class: a
 // system-per-lane tile runs its 64 systems in lockstep, each to its own step
 // count, and measured 1.7x slower than body-per-lane tiles (about 10
-// systems each) on 65536 uneven-lifetime systems at full population.
+// systems each) on 65536 uneven-lifetime systems at full population.  Fixed
+// steps with stop rules of kMinRolled bodies and more take the rolled form of
+// that class (2) where their tiles give a SIMD more than two wavefronts and those
+// of 10 bodies and more are half of them or more (k_persistent_rolled).
 template <class BucketRange>
-int persistent_class(const Plan &p0, const BucketRange &buckets, bool adv, int num_cu)
+int persistent_class(const Plan &p0, const BucketRange &buckets, bool adaptive, bool stops, int num_cu)
 {
     if (p0.mapping == MAP_SPL)
         return 1;
-    if (p0.mapping == MAP_BPL || adv)
+    if (stops && !adaptive) {
+        long long tiles = 0, larger = 0;
+        bool rolled = true;
+        for (const Bucket &B : buckets) {
+            rolled = rolled && B.n >= kMinRolled;
+            tiles += B.count / (64 / B.n);
+            larger += B.n > kMinRolled ? B.count / (64 / B.n) : 0;
+        }
+        return rolled && tiles > 8LL * num_cu && 2 * larger >= tiles ? 2 : 0;
+    }
+    if (p0.mapping == MAP_BPL || adaptive)
         return 0;
     const int lim = persistent_spl_limit(1, 0);
     long long tiles = 0;
