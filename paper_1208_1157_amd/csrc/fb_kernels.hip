@@ -1595,19 +1595,19 @@ hipError_t launch_plain(const Bucket &B, int mapping, int waves_per_group, const
     const dim3 grid((unsigned)((tiles + W - 1) / W));
     const size_t lds = sizeof(BplLds) * W;
 #define FB_L(NN, ADV) case NN: hipLaunchKernelGGL((k_plain_bpl<NN, ADV>), grid, dim3(64 * W), lds, s, B, P); break
-    if (adv) {
-        static_assert(kMaxUnrolledStops == 8, "the body counts that launch_unrolled does not always serve");
-        switch (B.n) {
-            FB_L(2, true); FB_L(3, true); FB_L(9, true); FB_L(10, true); FB_L(11, true);
-            FB_L(12, true); FB_L(13, true); FB_L(14, true); FB_L(15, true); FB_L(16, true);
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        switch (B.n) {   // the body counts that launch_unrolled does not always serve
-            FB_L(2, false); FB_L(3, false);
-        default: return hipErrorInvalidValue;
-        }
+#define FB_LN(ADV)                                                                         \
+    switch (B.n) {                                                                         \
+        FB_L(2, ADV); FB_L(3, ADV); FB_L(4, ADV); FB_L(5, ADV); FB_L(6, ADV); FB_L(7, ADV); \
+        FB_L(8, ADV); FB_L(9, ADV); FB_L(10, ADV); FB_L(11, ADV); FB_L(12, ADV);           \
+        FB_L(13, ADV); FB_L(14, ADV); FB_L(15, ADV); FB_L(16, ADV);                        \
+    default: return hipErrorInvalidValue;                                                  \
     }
+    if (adv) {
+        FB_LN(true)
+    } else {
+        FB_LN(false)
+    }
+#undef FB_LN
 #undef FB_L
     return hipGetLastError();
 }

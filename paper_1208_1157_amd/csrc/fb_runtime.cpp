@@ -429,7 +429,9 @@ fb_status count_active(fb_ensemble *e, int &out)
 }
 
 // Plain schedule: one launch per bucket (one per quantum if quanta are set).
-fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound)
+// step_bound: the steps of every system that is not stopped by a failure, or
+// negative where systems are counted between quanta; most: no system takes more.
+fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound, long long most)
 {
     const int quantum = o.steps_per_quantum > 0 ? o.steps_per_quantum : INT_MAX;
     for (;;) {
@@ -441,13 +443,15 @@ fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound)
                 continue;
             }
             const Plan p = get_plan(B.n);
-            const int map = plain_mapping(p, B, P.adaptive != 0, P.stop_rules != 0, e->num_cu);
+            const int map = plain_mapping(p, B, P.adaptive != 0, P.stop_rules != 0, e->num_cu,
+                                          std::min<long long>(quantum, most));
             FB_HIP(launch_plain(B, map, p.waves_per_group, P, e->stream));
         }
         if (quantum == INT_MAX)
             return FB_OK;
         if (step_bound >= 0) {
             step_bound -= quantum;
+            most -= quantum;
             if (step_bound <= 0)
                 return FB_OK;
             continue;
@@ -466,7 +470,7 @@ fb_status run_plain(fb_ensemble *e, const fb_opts &o, long long step_bound)
 // each quantum are rebuilt on the device from the previous quantum's
 // survivors.  Quanta are captured once into a HIP graph (two quanta, so the
 // survivor lists alternate) and replayed.
-fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
+fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound, long long most)
 {
     const int nbk = (int)e->buckets.size();
     if (nbk == 0)
@@ -578,7 +582,8 @@ fb_status run_persistent(fb_ensemble *e, const fb_opts &o, long long step_bound)
                 err = launch_large(B, P, e->num_cu, s);
             } else {
                 const Plan p = get_plan(B.n);
-                err = launch_plain(B, plain_mapping(p, B, P.adaptive != 0, P.stop_rules != 0, e->num_cu),
+                err = launch_plain(B, plain_mapping(p, B, P.adaptive != 0, P.stop_rules != 0, e->num_cu,
+                                                    std::min<long long>(P.quantum, most)),
                                    p.waves_per_group, P, s);
             }
             if (err != hipSuccess)
@@ -850,7 +855,7 @@ fb_status run_mvs(fb_ensemble *e, const fb_opts &o, long long step_bound)
                 ProfScope ps(e->stream);
                 FB_HIP(launch_plain_mvs_large(B, P, e->stream));
             } else if (B.n <= kMaxMvsBodies &&
-                       plain_mapping(get_plan(B.n), B, false, false, e->num_cu) == MAP_SPL) {
+                       plain_mapping(get_plan(B.n), B, false, false, e->num_cu, INT_MAX) == MAP_SPL) {
                 ProfScope ps(e->stream);
                 FB_HIP(launch_plain_mvs(B, 1, P, e->stream));
             } else {
@@ -899,11 +904,11 @@ fb_status check_log(const fb_ensemble *e, const fb_log_spec *log, long long reco
     return FB_OK;
 }
 
-fb_status run(fb_ensemble *e, const fb_opts &o, long long step_bound)
+fb_status run(fb_ensemble *e, const fb_opts &o, long long step_bound, long long most = LLONG_MAX)
 {
     if (o.schedule == FB_SCHED_PERSISTENT)
-        return run_persistent(e, o, step_bound);
-    return run_plain(e, o, step_bound);
+        return run_persistent(e, o, step_bound, most);
+    return run_plain(e, o, step_bound, most);
 }
 
 }  // namespace
@@ -1136,7 +1141,7 @@ fb_status fb_integrate_steps(fb_ensemble *e, int64_t n_steps, double dt, const f
     if (st != FB_OK)
         return st;
     FB_HIP(begin_run(e, start_steps(n_steps, dt)));
-    return run(e, o, o.stop_rules ? -1 : n_steps);
+    return run(e, o, o.stop_rules ? -1 : n_steps, n_steps);
 }
 
 fb_status fb_integrate_mvs(fb_ensemble *e, int64_t n_steps, double dt, const fb_opts *po)
@@ -1231,7 +1236,7 @@ fb_status fb_integrate_steps_logged(fb_ensemble *e, int64_t n_steps, double dt, 
         fb_opts oq = o;
         oq.steps_per_quantum = log->every;
         for (long long done = 0; done < n_steps; done += log->every) {
-            st = run_plain(e, oq, log->every);
+            st = run_plain(e, oq, log->every, log->every);
             if (st != FB_OK)
                 return st;
             for (const Bucket &B : e->buckets)
@@ -1543,7 +1548,7 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
                 continue;
             struct Cand { int map, W; };
             std::vector<Cand> cands;
-            const int bpl = bpl_mapping(B, false, false, e->num_cu);
+            const int bpl = bpl_mapping(B, false, false, e->num_cu, steps);
             if (bpl != MAP_BPL)   // one wavefront a workgroup, whatever the plan
                 cands.push_back({bpl, get_plan(B.n).waves_per_group});
             for (int W : {1, 2, 4}) {
@@ -1596,7 +1601,7 @@ fb_status fb_autotune(fb_ensemble *e, int64_t steps, double dt, fb_tune_entry *o
             FB_HIP(restore());
             FB_HIP(begin_run(e, start_steps(steps, dt)));
             FB_HIP(hipEventRecord(ev0, e->stream));
-            st = run_persistent(e, po, steps);
+            st = run_persistent(e, po, steps, steps);
             if (st != FB_OK)
                 return st;
             FB_HIP(hipEventRecord(ev1, e->stream));

@@ -106,44 +106,74 @@ inline bool fused_split_done(const std::vector<FusedGroup> &groups)
     return !slow || slow->n < kMinSplit || slow->map == MAP_SPLIT4;
 }
 
-// Form of a body-per-lane launch over bucket B (n <= kMaxBodies): the
-// several-lanes-a-body ones (fb_split.h, measured there) while
+// Most steps of a launch of `count` n-body systems that is faster rolled than in
+// the form `map` (several lanes a body, or unrolled).  The rolled kernels keep three
+// wavefronts a SIMD and prepare nothing, so they load and store the systems in less
+// time; every step then costs more.  Per cent of the rolled time, launches of 1, 2,
+// 3, 4 and 6 steps, fixed:
+//   4 rolled wavefronts a SIMD, unrolled: n = 5 134 122 116 114 107, 6 128 118
+//     113 106 102, 8 136 120 111 110 105, 10 144 118 107 101 98, 16 124 107 100 100 92;
+//   0.45, two lanes a body, nine SIMDs of ten taken: 5 132 132 124 118 108, 8 137
+//     124 113 105 95, 16 126 108 95 86 76;
+//   0.9, unrolled: 5 121 112 106 100 92, 8 110 99 92 86 80, 16 114 96 87 79 71;
+//   0.1, four lanes a body: 5 97 100 95 90 83, 8 100 92 84 77 69, 16 87 71 62 56 49.
+inline int short_steps(int n, long long count, int map, int num_cu)
+{
+    const long long simds = 4LL * num_cu, tiles = split_tiles(n, count, MAP_BPL);
+    if (n < 4)
+        return 0;
+    if (tiles > simds)
+        return n <= 6 ? 6 : n <= 8 ? 4 : n <= 10 ? 3 : 2;
+    if (map == MAP_BPLU)
+        return n <= 10 && 4 * tiles > 3 * simds ? 2 : 2 * tiles > simds ? 1 : 0;
+    const long long split = split_tiles(n, count, map);
+    if (8 * split > 7 * simds)
+        return n <= 6 ? 5 : n <= 10 ? 3 : 2;
+    if (2 * split > simds)
+        return n <= 6 ? 3 : n <= 8 ? 2 : 1;
+    return n <= 6 && 8 * split > 3 * simds ? 2 : 0;
+}
+
+// Form of a body-per-lane launch of at most `steps` steps over bucket B (n <=
+// kMaxBodies): the several-lanes-a-body ones (fb_split.h, measured there) while
 // no SIMD gets more than one of their wavefronts, or the unrolled kernels
 // (fb_unrolled.hip, where both sides are measured) for 4..16
-// bodies (4..10 with adaptive steps or stop rules); for other body counts
-// while their wavefronts are no more than one per SIMD: 2 and 3 bodies (the quad
-// layout holds 16 systems a wavefront, the rolled one 32 and 21), and 11..16
-// with adaptive steps or stop rules (their registers leave one wave).  With stop
-// rules in fixed steps 9 and 10 bodies, which they leave one wave too, to two per
-// SIMD: 60 steps of 9 bodies, unrolled and rolled, 12000 systems 385 and 390 us,
-// 16000 478 and 455, 50000 1130 and 1022; of 10 16000 570 and 516, 50000 1568 and
+// bodies (4..10 with adaptive steps, 4..8 with stop rules in fixed steps); for
+// other body counts while their wavefronts are no more than one per SIMD: 2 and 3
+// bodies (the quad layout holds 16 systems a wavefront, the rolled one 32 and 21),
+// and the larger ones with rules (their registers leave one wave).  60 steps with
+// stop rules of 9 bodies, unrolled and rolled, 12000 systems 385 and 390 us, 16000
+// 478 and 455, 50000 1130 and 1022; of 10 16000 570 and 516, 50000 1568 and
 // 1378 (with adaptive steps, a longer chain to hide, one wave is faster there).
-inline int bpl_mapping(const Bucket &B, bool adaptive, bool stops, int num_cu)
+// Launches of a few steps are rolled (short_steps).
+inline int bpl_mapping(const Bucket &B, bool adaptive, bool stops, int num_cu, long long steps)
 {
     if (B.n > kMaxBodies)
         return MAP_BPL;
-    if (B.n >= kMinSplit)
-        for (int map : {MAP_SPLIT4, MAP_SPLIT2})
-            if (split_tiles(B.n, B.count, map) <= 4LL * num_cu)
-                return map;
     const int most = adaptive ? kMaxUnrolledAdv : stops ? kMaxUnrolledStops : kMaxBodies;
     const bool always = B.n >= 4 && B.n <= most;
-    const int waves_per_simd = !adaptive && stops && B.n > kMaxUnrolledStops && B.n <= kMaxUnrolledAdv ? 2 : 1;
-    return always || unrolled_tiles(B) <= 4LL * num_cu * waves_per_simd ? MAP_BPLU : MAP_BPL;
+    int form = always || unrolled_tiles(B) <= 4LL * num_cu ? MAP_BPLU : MAP_BPL;
+    if (B.n >= kMinSplit)
+        for (int map : {MAP_SPLIT2, MAP_SPLIT4})
+            if (split_tiles(B.n, B.count, map) <= 4LL * num_cu)
+                form = map;
+    return steps <= short_steps(B.n, B.count, form, num_cu) ? MAP_BPL : form;
 }
 
 // Lane mapping of a plain launch over bucket B: the plan's, or (auto)
 // system-per-lane when n allows it and the bucket's 64-system tiles give
 // every SIMD of the device a wavefront, else body-per-lane, whose n lanes
-// per system spread a small bucket over more of the device.
-inline int plain_mapping(const Plan &p, const Bucket &B, bool adaptive, bool stops, int num_cu)
+// per system spread a small bucket over more of the device.  `steps`: the most
+// steps the launch takes.
+inline int plain_mapping(const Plan &p, const Bucket &B, bool adaptive, bool stops, int num_cu,
+                         long long steps)
 {
     const int lim = adaptive || stops ? kMaxSplAdv : kMaxSplBodies;
     if (p.mapping == MAP_BPL || B.n > lim)
-        return bpl_mapping(B, adaptive, stops, num_cu);
+        return bpl_mapping(B, adaptive, stops, num_cu, steps);
     if (p.mapping == MAP_SPL)
         return MAP_SPL;
-    return (B.count + 63) / 64 >= 4LL * num_cu ? MAP_SPL : bpl_mapping(B, adaptive, stops, num_cu);
+    return (B.count + 63) / 64 >= 4LL * num_cu ? MAP_SPL : bpl_mapping(B, adaptive, stops, num_cu, steps);
 }
 
 // Fused persistent kernel class for a launch over buckets of these body

@@ -136,7 +136,7 @@ fb_status solo_run(char *base, const SoloLayout &L, const double *d_mass, double
     P.max_steps = LLONG_MAX;
     P.quantum = INT_MAX;
     P.simds = 0;
-    const int map = plain_mapping(p, B, false, false, num_cu > 0 ? num_cu : 256);
+    const int map = plain_mapping(p, B, false, false, num_cu > 0 ? num_cu : 256, INT_MAX);
     if (n_steps > 0 && solo_in_one(B.n, map)) {
         // A small batch: one launch, the bucket not used.  16 x 3 bodies, 10
         // steps: 18.6 us; 24.9 as three launches.
