@@ -196,12 +196,14 @@ __global__ __launch_bounds__(kBlock) void k_begin_clock(BucketSet set, RunStart 
         begin_run_clock(B, slot, B.status[slot], B.t[slot], run);
 }
 
-// ... of one bucket: without the set among the kernel's arguments (1.7 KB), and
-// with a workgroup a wavefront.  A call of one step, 20000 x 3 bodies, 9.1 us
-// through the set, 8.4 so; 4 x 6000 8.3 and 7.7.
-__global__ __launch_bounds__(64) void k_begin_clock_of(Bucket B, RunStart run)
+// ... of one bucket: without the set among the kernel's arguments (1.6 KB).  A call
+// of one step, 40000 x 3 bodies, 11.9 us through the set and 10.8 so.  Workgroups of
+// a wavefront would leave the SIMDs of a CU unevenly taken where the next launch
+// starts: 200 steps with stop rules of 8192 x 16 bodies 1671 us after this kernel,
+// 2324 after one with 64 lanes a workgroup.
+__global__ __launch_bounds__(kBlock) void k_begin_clock_of(Bucket B, RunStart run)
 {
-    const int slot = blockIdx.x * 64 + threadIdx.x;
+    const int slot = blockIdx.x * kBlock + threadIdx.x;
     if (slot < B.count)
         begin_run_clock(B, slot, B.status[slot], B.t[slot], run);
 }
@@ -505,7 +507,7 @@ hipError_t launch_begin_run(const Bucket *b, int nb, const RunStart &run, hipStr
     }
     if (nb == 1) {
         if (b->count > 0)
-            hipLaunchKernelGGL(k_begin_clock_of, dim3((unsigned)((b->count + 63) / 64)), dim3(64), 0, s, *b, run);
+            hipLaunchKernelGGL(k_begin_clock_of, dim3((unsigned)slot_blocks(*b)), dim3(kBlock), 0, s, *b, run);
         return hipGetLastError();
     }
     return for_sets(b, nb, any_n, slot_blocks, 1, [&](const BucketSet &set, dim3 grid) {
