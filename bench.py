@@ -49,7 +49,7 @@ KERNEL_SRC = os.path.join(ROOT, "paper_1208_1157_amd", "csrc", "fb_kernels.hip")
 # HBM bytes per launch of the integration kernel on this workload, from the
 # FETCH_SIZE / WRITE_SIZE counter passes (scaled by a 256 MiB copy kernel's
 # reading) recorded in profiles/, keyed by the kernel source they measured.
-MEASURED_TRAFFIC = {"34a451ad46d0383b": 92410808.3}
+MEASURED_TRAFFIC = {"a85d4ace579b9900": 92402522.1}
 # Hardware counters of the same kernel on this workload from rocprofv3 runs
 # (profiles/), keyed the same way: FP64 flop per system-step from
 # SQ_INSTS_VALU_FLOPS_FP64 x 64 lanes; the fraction of SIMD cycles issuing
@@ -57,8 +57,8 @@ MEASURED_TRAFFIC = {"34a451ad46d0383b": 92410808.3}
 # shader clock those cycles implied on the profiled box.  They are records of
 # those runs, reported as such, not measurements of this run.
 PROFILED_COUNTERS = {
-    "34a451ad46d0383b": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9671,
-                         "shader_clock_ghz": 2.131, "valu_insts_per_system_step": 388.0},
+    "a85d4ace579b9900": {"fp64_flops_per_system_step": 672.0, "valu_busy": 0.9678,
+                         "shader_clock_ghz": 2.173, "valu_insts_per_system_step": 388.0},
 }
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X: 256 CUs x 2.4 GHz x 128 FP64 flop/clk/CU
 HBM_PEAK_GBPS = 8000.0           # MI355X HBM3E
