@@ -591,9 +591,9 @@ LargeShape large_best(int n, int count, int num_cu, LargeRules r)
 // twentieth with stop rules alone: closer ones the estimate does not tell apart
 // (33 bodies, 1000 systems, adaptive, 303 and 343 us; 200 bodies, 4 systems, stop
 // rules, 1.20 and 1.26 ms).  With stop rules alone one lane a body is taken wherever
-// it is estimated best: 30 such sizes were 2 to 7% faster (80 bodies, 1000 systems,
-// 100 steps 3.1 and 3.4 ms; 400 bodies, 8 systems 3.6 and 3.7), 16 others of the
-// same distance with more lanes 3 to 10% slower.
+// it is estimated best: 30 sizes where it was closer were 2 to 7% faster (80 bodies,
+// 1000 systems, 62 steps 2.54 and 2.63 ms; 400 bodies, 8 systems, 10 steps 1.76
+// and 1.86), 16 others of the same distance with more lanes 3 to 10% slower.
 LargeShape large_layout(int n, int count, int num_cu, LargeRules r)
 {
     const LargeShape f = large_best(n, count, num_cu, r);
